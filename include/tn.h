@@ -116,8 +116,10 @@ void tn_destroy(tn_ctx *ctx);
 enum {
     TN_K_IDENTITY = 1,     /* C <- I                                        */
     TN_K_ROWOR = 2,        /* the level-by-level row-OR stream              */
-    TN_K_OUT_SIZES = 3,    /* row popcounts                                 */
-    TN_K_IN_SIZES = 4,     /* column popcounts                              */
+    TN_K_OUT_SIZES = 3,    /* row popcounts; asked for with the column ones:
+                              the start of both arrays                      */
+    TN_K_IN_SIZES = 4,     /* column popcounts; asked for with the row ones:
+                              the one pass that counts both                 */
     TN_K_BATCH = 5,        /* persistent multi-network row-OR               */
     TN_K_HASH = 6,         /* bucket map and bucket counts                  */
     TN_K_RECOMBINE = 7,    /* fusion of the hashed proxies                  */

@@ -727,16 +727,20 @@ tn_status component_sizes(tn_ctx *ctx, uint32_t n, const uint64_t *C, int64_t ld
     if (!out_sizes && !in_sizes) return TN_OK;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
-    if (out_sizes) {
-        tn::ProfScope ps(ctx, TN_K_OUT_SIZES);
-        hipError_t e = tn::launch_out_sizes(C, n, ld, out_sizes, ctx->stream, state, state_sw);
-        if (e != hipSuccess) return hip_fail(e, "out-size kernel launch");
+    hipError_t e = hipSuccess;
+    {
+        // both arrays from one pass over the matrix: their start is recorded
+        // as out-sizes and the pass as in-sizes (one of them alone: as it)
+        tn::ProfScope ps(ctx, out_sizes ? TN_K_OUT_SIZES : TN_K_IN_SIZES);
+        e = tn::launch_sizes_base(n, out_sizes, in_sizes, ctx->stream, state, state_sw);
+        if (e == hipSuccess && !(out_sizes && in_sizes))
+            e = tn::launch_sizes(C, n, ld, out_sizes, in_sizes, ctx->stream, state, state_sw);
     }
-    if (in_sizes) {
+    if (e == hipSuccess && out_sizes && in_sizes) {
         tn::ProfScope ps(ctx, TN_K_IN_SIZES);
-        hipError_t e = tn::launch_in_sizes(C, n, ld, in_sizes, ctx->stream, state, state_sw);
-        if (e != hipSuccess) return hip_fail(e, "in-size kernel launch");
+        e = tn::launch_sizes(C, n, ld, out_sizes, in_sizes, ctx->stream, state, state_sw);
     }
+    if (e != hipSuccess) return hip_fail(e, "size kernel launch");
     return TN_OK;
 }
 }  // namespace

@@ -1149,113 +1149,155 @@ __device__ __forceinline__ bool word_done(const uint32_t *persist, uint32_t psli
     return persist && persist[(size_t)(w / sw) * pslice] != 0u;
 }
 
-// out[u] = popcount of row u: one wavefront per row, lanes stride the words.
-// With a slice state (persist: pslice words per slice of sw words), a word
-// of a slice left all ones counts its valid columns without a read.
+// Component sizes.  k_sizes_base starts the two arrays, k_sizes adds the
+// counts of one pass over the matrix.
+//
+// With a slice state (persist: pslice words per slice of sw words) a word of
+// a slice left all ones counts without a read: its valid columns in every
+// out-size and n in its columns' in-sizes, both written here.
 __global__ void __launch_bounds__(256)
-k_out_sizes(const uint64_t *__restrict__ C, uint32_t n, int64_t ld, uint32_t nwords,
-            int32_t *__restrict__ out, const uint32_t *__restrict__ persist, uint32_t pslice,
-            uint32_t sw) {
+k_sizes_base(uint32_t n, uint32_t nwords, int32_t *__restrict__ out, int32_t *__restrict__ in,
+             const uint32_t *__restrict__ persist, uint32_t pslice, uint32_t sw) {
     const uint32_t lane = threadIdx.x & 63u;
-    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-    const uint32_t nwave = (gridDim.x * blockDim.x) >> 6;
-    // this lane's done words: their columns once, a row read for the rest
+    const uint32_t t = blockIdx.x * blockDim.x + threadIdx.x;
     int base = 0;
-    bool any_open = false;
-    for (uint32_t j = lane; j < nwords; j += 64) {
-        if (word_done(persist, pslice, sw, j))
-            base += (j + 1 < nwords || (n & 63u) == 0) ? 64 : (int)(n & 63u);
-        else
-            any_open = true;
-    }
-    if (__ballot(any_open) == 0) {
-        // every word of the row is done: the same count for every row,
-        // reduced once (a shuffle step is an LDS permute)
-        int total = base;
+    if (persist) {
+        for (uint32_t j = lane; j < nwords; j += 64)
+            if (word_done(persist, pslice, sw, j))
+                base += (j + 1 < nwords || (n & 63u) == 0) ? 64 : (int)(n & 63u);
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
-        for (uint32_t r = wave * 64 + lane; r < n; r += nwave * 64) out[r] = total;
-        return;
+        for (int off = 32; off > 0; off >>= 1) base += __shfl_xor(base, off, 64);
     }
-    for (uint32_t r = wave; r < n; r += nwave) {
-        const uint64_t *row = C + (size_t)r * (size_t)ld;
-        int c = base;
-        if (any_open) {
-            for (uint32_t j = lane; j < nwords; j += 64)
-                if (!word_done(persist, pslice, sw, j)) c += __popcll(row[j]);
-        }
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
-        if (lane == 0) out[r] = c;
+    for (uint32_t r = t; r < n; r += gridDim.x * blockDim.x) {
+        if (out) out[r] = base;
+        if (in) in[r] = word_done(persist, pslice, sw, r >> 6) ? (int32_t)n : 0;
     }
 }
 
-// in[w] = number of rows with bit w: each lane owns one word column over a
-// share of a chunk of rows and adds the words into 16 bit-planes (a
-// bit-sliced ripple counter, 64 column counters at once).  The four waves of
-// a workgroup take quarters of the chunk, add their 64 counts per lane into
-// LDS, and the workgroup adds each column's total to in[] once: one global
-// atomic per column and chunk of kInRowsPerChunk rows.
-constexpr uint32_t kInRowsPerChunk = 4096;  // per wave 1024 < 2^16: 16 planes suffice
-// With a slice state, a word column of a slice left all ones has n in
-// every column: the first chunk adds it, no chunk reads the column.
-__global__ void __launch_bounds__(256)
-k_in_sizes(const uint64_t *__restrict__ C, uint32_t n, int64_t ld, uint32_t nwords,
-           int32_t *__restrict__ in, const uint32_t *__restrict__ persist, uint32_t pslice,
-           uint32_t sw) {
-    __shared__ int32_t cnt[64 * 64];  // [bit][column word]: a wave's lanes on distinct banks
+// Sum and carry of three words: bit-wise full adders, one three-input
+// boolean instruction per half word each.
+__device__ __forceinline__ void full_add(uint64_t a, uint64_t b, uint64_t c, uint64_t &sum,
+                                         uint64_t &carry) {
+    const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b,
+                   bh = (uint32_t)(b >> 32), cl = (uint32_t)c, ch = (uint32_t)(c >> 32);
+    sum = (uint64_t)(uint32_t)__builtin_amdgcn_bitop3_b32(ah, bh, ch, 0x96) << 32 |
+          (uint32_t)__builtin_amdgcn_bitop3_b32(al, bl, cl, 0x96);
+    carry = (uint64_t)(uint32_t)__builtin_amdgcn_bitop3_b32(ah, bh, ch, 0xE8) << 32 |
+            (uint32_t)__builtin_amdgcn_bitop3_b32(al, bl, cl, 0xE8);
+}
+
+// Out-sizes (row popcounts) and in-sizes (column popcounts) of open words,
+// added to out and in, in one pass: memory-bound, so both come from the same
+// read.  A wavefront takes 64 >> lw rows at a time, 1 << lw lanes on
+// consecutive words of each (all 64 on one row where it has 64 words or
+// more), and 16 such steps per round, their loads all in flight.
+//  - Rows: the 16 popcounts of a lane are packed two to a register (a sum
+//    over 64 words is at most 4096) and summed over the row's lanes by a
+//    butterfly that halves the registers each of its first three steps.
+//  - Columns: 16 words enter a carry-save adder tree (15 full adders of two
+//    instructions per half word) and its carries eight more bit planes, 64
+//    column counters per lane; 6 instructions per word, where rippling each
+//    word through 16 planes took 64 and bound the kernel.
+// Workgroups add up in LDS, then with integer atomics, so the order does not
+// matter.  At n = 10^5 (1.25 GB) out- and in-sizes took 0.83 ms in two passes
+// and take 0.27 ms (4.9 TB/s; a large copy reaches 5.2); at n = 20,000 0.18
+// and 0.042 ms; at n = 1000 the column pass ran on a single workgroup (177 us
+// in all), this one takes 15 us.
+constexpr uint32_t kSizesWaves = 8;
+constexpr uint32_t kSizesSteps = 16;       // rows in flight per lane group
+constexpr uint32_t kSizesMaxSteps = 4080;  // per wavefront: 12 planes hold the counts
+template <bool OUT, bool IN>
+__global__ void __launch_bounds__(kSizesWaves * 64)
+k_sizes(const uint64_t *__restrict__ C, uint32_t n, int64_t ld, uint32_t nwords,
+        int32_t *__restrict__ out, int32_t *__restrict__ in, const uint32_t *__restrict__ persist,
+        uint32_t pslice, uint32_t sw, uint32_t lw, uint32_t rows_per_wave) {
+    __shared__ int32_t cnt[IN ? 64 * 64 : 1];  // [bit][column word]: a wave's lanes on distinct banks
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    for (uint32_t i = threadIdx.x; i < 64 * 64; i += blockDim.x) cnt[i] = 0;
-    __syncthreads();
-    const uint32_t j = blockIdx.x * 64 + lane;
-    const uint32_t share = kInRowsPerChunk / 4;
-    const uint32_t r0 = blockIdx.y * kInRowsPerChunk + wave * share;
-    const uint32_t r1 = min(n, r0 + share);
-    const bool done = j < nwords && word_done(persist, pslice, sw, j);
-    if (done && blockIdx.y == 0 && wave == 0) {
-        const uint32_t bits = (j + 1 < nwords || (n & 63u) == 0) ? 64u : (n & 63u);
-        for (uint32_t b = 0; b < bits; ++b) atomicAdd(&cnt[b * 64 + lane], (int32_t)n);
+    const uint32_t W = 1u << lw, sub = lane & (W - 1u), g = lane >> lw, GR = 64u >> lw;
+    const uint32_t j = blockIdx.x * W + sub;
+    const bool open = j < nwords && !word_done(persist, pslice, sw, j);
+    if (__ballot(open) == 0) return;  // the same words in every wave: the whole workgroup
+    if (IN) {
+        for (uint32_t i = threadIdx.x; i < 64 * 64; i += blockDim.x) cnt[i] = 0;
+        __syncthreads();
     }
-    if (j < nwords && r0 < r1 && !done) {
-        uint64_t c[16];
+    const uint64_t first = ((uint64_t)blockIdx.y * kSizesWaves + wave) * rows_per_wave;
+    const uint32_t r0 = (uint32_t)min((uint64_t)n, first);
+    const uint32_t r1 = (uint32_t)min((uint64_t)n, first + rows_per_wave);
+    const uint64_t *col = C + j;
+    uint64_t c[4] = {}, up[8] = {};
+    for (uint32_t base = r0; base < r1; base += kSizesSteps * GR) {
+        uint64_t x[kSizesSteps];
 #pragma unroll
-        for (int i = 0; i < 16; ++i) c[i] = 0;
-        const uint64_t *col = C + j;
-        uint32_t r = r0;
-        for (; r + 8 <= r1; r += 8) {
-            uint64_t x[8];
+        for (uint32_t q = 0; q < kSizesSteps; ++q) {
+            const uint32_t r = base + q * GR + g;
+            x[q] = (open && r < r1) ? col[(size_t)r * (size_t)ld] : 0ull;
+        }
+        if (OUT) {
+            uint32_t p[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = col[(size_t)(r + q) * (size_t)ld];
+            for (int i = 0; i < 8; ++i)
+                p[i] = (uint32_t)__popcll(x[2 * i]) | (uint32_t)__popcll(x[2 * i + 1]) << 16;
+            uint32_t mask = W >> 1, idx = 0;
 #pragma unroll
-            for (int q = 0; q < 8; ++q) {
-                uint64_t carry = x[q];
+            for (int half = 4; half > 0; half >>= 1) {
+                const bool hi = sub & mask;
+                idx |= hi ? (uint32_t)half : 0u;
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const uint64_t t = c[i] & carry;
-                    c[i] ^= carry;
-                    carry = t;
+                for (int i = 0; i < half; ++i) {
+                    const uint32_t send = hi ? p[i] : p[i + half];
+                    p[i] = (hi ? p[i + half] : p[i]) + (uint32_t)__shfl_xor((int)send, (int)mask, 64);
                 }
+                mask >>= 1;
+            }
+            for (; mask > 0; mask >>= 1) p[0] += (uint32_t)__shfl_xor((int)p[0], (int)mask, 64);
+            // W / 8 lanes hold the sums of rows 2 idx and 2 idx + 1
+            if ((sub & ((W >> 3) - 1u)) == 0) {
+                const uint32_t r = base + 2 * idx * GR + g;
+                if (r < r1) atomicAdd(out + r, (int32_t)(p[0] & 0xffffu));
+                if (r + GR < r1) atomicAdd(out + r + GR, (int32_t)(p[0] >> 16));
             }
         }
-        for (; r < r1; ++r) {
-            uint64_t carry = col[(size_t)r * (size_t)ld];
+        if (IN) {
+            uint64_t t2[8], t4[4], t8[2], carry;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const uint64_t t = c[i] & carry;
-                c[i] ^= carry;
+            for (int i = 0; i < 8; ++i) full_add(c[0], x[2 * i], x[2 * i + 1], c[0], t2[i]);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) full_add(c[1], t2[2 * i], t2[2 * i + 1], c[1], t4[i]);
+#pragma unroll
+            for (int i = 0; i < 2; ++i) full_add(c[2], t4[2 * i], t4[2 * i + 1], c[2], t8[i]);
+            full_add(c[3], t8[0], t8[1], c[3], carry);
+#pragma unroll
+            for (int i = 0; i < 8; ++i) {
+                const uint64_t t = up[i] & carry;
+                up[i] ^= carry;
                 carry = t;
             }
         }
-        for (uint32_t b = 0; b < 64; ++b) {
-            int32_t v = 0;
+    }
+    if (!IN) return;
+    if (open && r0 < r1) {
+        // the counters leave their planes: six planes where the wavefront's
+        // steps are at most 63
+        auto add = [&](auto planes) {
+            for (uint32_t b = 0; b < 64; ++b) {
+                int32_t v = 0;
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v |= (int32_t)((c[i] >> b) & 1ull) << i;
-            if (v) atomicAdd(&cnt[b * 64 + lane], v);
-        }
+                for (int i = 0; i < 4; ++i) v |= (int32_t)((c[i] >> b) & 1ull) << i;
+#pragma unroll
+                for (int i = 0; i < planes.value - 4; ++i)
+                    v |= (int32_t)((up[i] >> b) & 1ull) << (4 + i);
+                if (v) atomicAdd(&cnt[b * 64 + sub], v);
+            }
+        };
+        if (rows_per_wave / GR < 64)
+            add(std::integral_constant<int, 6>{});
+        else
+            add(std::integral_constant<int, 12>{});
     }
     __syncthreads();
-    for (uint32_t i = threadIdx.x; i < 64 * 64; i += blockDim.x) {
-        const uint32_t node = blockIdx.x * 64 * 64 + i;  // (column word) * 64 + bit
+    for (uint32_t i = threadIdx.x; i < 64 * W; i += blockDim.x) {
+        const uint32_t node = blockIdx.x * W * 64 + i;  // (column word) * 64 + bit
         const int32_t v = cnt[(i & 63u) * 64 + (i >> 6)];
         if (node < n && v) atomicAdd(in + node, v);
     }
@@ -1537,32 +1579,42 @@ uint32_t tail_slice_words(uint32_t n, uint32_t slice_words, int num_cus) {
     return sw;
 }
 
-hipError_t launch_out_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *out_sizes,
-                            hipStream_t st, const uint32_t *persist, uint32_t state_sw) {
-    const uint32_t nwords = (n + 63) / 64;
-    uint32_t blocks = (n + 3) / 4;
-    if (blocks > 16384u) blocks = 16384u;
-    // with a state every wave first reads the done words of its lanes: fewer
-    // waves, each taking more rows
-    if (persist && blocks > 2048u) blocks = 2048u;
-    const uint32_t pslice = persist ? (uint32_t)(2 * (((size_t)n + 31) / 32) + 2) : 0u;
-    hipLaunchKernelGGL(k_out_sizes, dim3(blocks), dim3(256), 0, st, C, n, ld, nwords, out_sizes,
-                       persist, pslice, state_sw ? state_sw : 1u);
+namespace {
+uint32_t state_slice_words(const uint32_t *persist, uint32_t n) {
+    return persist ? (uint32_t)(2 * (((size_t)n + 31) / 32) + 2) : 0u;
+}
+}  // namespace
+
+hipError_t launch_sizes_base(uint32_t n, int32_t *out_sizes, int32_t *in_sizes, hipStream_t st,
+                             const uint32_t *persist, uint32_t state_sw) {
+    // with a state every wave first reads the done words: fewer waves
+    const uint32_t blocks = std::min<uint32_t>((n + 255) / 256, persist ? 512u : 4096u);
+    hipLaunchKernelGGL(k_sizes_base, dim3(blocks), dim3(256), 0, st, n, (n + 63) / 64, out_sizes,
+                       in_sizes, persist, state_slice_words(persist, n), state_sw ? state_sw : 1u);
     return hipGetLastError();
 }
 
-hipError_t launch_in_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *in_sizes,
-                           hipStream_t st, const uint32_t *persist, uint32_t state_sw) {
+hipError_t launch_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *out_sizes,
+                        int32_t *in_sizes, hipStream_t st, const uint32_t *persist,
+                        uint32_t state_sw) {
     const uint32_t nwords = (n + 63) / 64;
-    uint32_t fb = (n + 255) / 256;
-    if (fb > 4096u) fb = 4096u;
-    hipLaunchKernelGGL(k_fill_i32, dim3(fb), dim3(256), 0, st, in_sizes, n, 0);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    dim3 grid((nwords + 63) / 64, (n + kInRowsPerChunk - 1) / kInRowsPerChunk);
-    const uint32_t pslice = persist ? (uint32_t)(2 * (((size_t)n + 31) / 32) + 2) : 0u;
-    hipLaunchKernelGGL(k_in_sizes, grid, dim3(256), 0, st, C, n, ld, nwords, in_sizes, persist,
-                       pslice, state_sw ? state_sw : 1u);
+    uint32_t lw = 3;  // 8 lanes at least: the butterfly's three halving steps
+    while (lw < 6 && (1u << lw) < nwords) ++lw;
+    const uint32_t xb = (nwords + (1u << lw) - 1) >> lw;
+    // about 1024 workgroups (four for each CU), whole rounds per wavefront;
+    // more rows per wavefront save column atomics, fewer leave CUs idle
+    const uint32_t unit = kSizesSteps * (64u >> lw);
+    const uint64_t want = (n + (uint64_t)(1024 + xb - 1) / xb * kSizesWaves - 1) /
+                          ((uint64_t)(1024 + xb - 1) / xb * kSizesWaves);
+    uint64_t rpw = (want + unit - 1) / unit * unit;
+    rpw = std::min<uint64_t>(rpw, (uint64_t)kSizesMaxSteps * (64u >> lw));
+    const uint32_t yb = (uint32_t)((n + kSizesWaves * rpw - 1) / (kSizesWaves * rpw));
+    auto k = out_sizes && in_sizes ? k_sizes<true, true>
+             : out_sizes           ? k_sizes<true, false>
+                                   : k_sizes<false, true>;
+    hipLaunchKernelGGL(k, dim3(xb, yb), dim3(kSizesWaves * 64), 0, st, C, n, ld, nwords, out_sizes,
+                       in_sizes, persist, state_slice_words(persist, n), state_sw ? state_sw : 1u,
+                       lw, (uint32_t)rpw);
     return hipGetLastError();
 }
 
