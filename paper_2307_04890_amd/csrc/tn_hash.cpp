@@ -18,6 +18,34 @@ namespace {
 constexpr uint64_t kP61 = (1ull << 61) - 1;
 constexpr size_t kLiftedBudget = (size_t)1 << 30;  // bytes of lifted tables per pass
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
+
+// Whether fusion by lists beats the tables, from the call's totals: the
+// microseconds of either as fitted on calls of n = 2*10^4 to 2*10^5 nodes and
+// H = 5 and 16 hashes (lists against tables, H = 16, K = 4096 unless said:
+// n = 2*10^5 with m/n = 0.2 and 0.15 events per node 1.01 against 5.79 and
+// 4.55 against 5.75 ms; n = 5*10^4, K = 1024 0.16 against 0.40; ER graphs of
+// n = 2*10^4 with m/n = 2 0.48 against 0.40 and n = 10^5 with 0.1 3.9 against
+// 1.8; H = 5, n = 6*10^4 with 0.3 1.2 against 0.36).  The tables cost their
+// building and staging (n H K) and n / 64 words of each hash per open node;
+// the lists' side is the setup per row and entry, the union nodes' entries
+// and bitmaps (few bits of LDS, so short reads of many nodes at a time, up
+// to 65,536 nodes; a hash table per node past that), and the random reads of
+// intersections.  Below 8192 nodes either takes about 0.1 ms, the tables
+// with fewer launches.
+bool fuse_by_lists(uint32_t n, uint32_t H, uint32_t K, const unsigned long long *stats,
+                   unsigned long long entries, unsigned long long nbitmaps, size_t room) {
+    using namespace tn;
+    // the lists take their lengths from the counts, and their room from the tables'
+    if (stats[kFuseNodeMix] != stats[kFuseCountMix]) return false;
+    if (entries * 4 + nbitmaps * ((n + 63) / 64) * 8 > room) return false;
+    const double N = n, rows = (double)H * K, open = (double)stats[kFuseOpen];
+    const double tables = 150 + 78e-9 * N * rows + 7.3e-9 * open * N * H;
+    const double lists = 120 + 8e-4 * rows + 8e-6 * (double)entries + 0.5e-6 * (double)nbitmaps * N +
+                         (n > 65536 ? 1.7e-6 : 8e-6) * (double)stats[kFuseEntries] +
+                         (n > 65536 ? 2.5e-3 * open : 0.0) +
+                         1.25e-8 * (double)stats[kFuseBits] * N + 1e-4 * (double)stats[kFuseInter];
+    return lists < tables;
+}
 }  // namespace
 
 extern "C" {
@@ -607,47 +635,70 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
     const size_t per_q = (size_t)H * K * 8;
     uint32_t qr = (uint32_t)std::max<size_t>(4, std::min<size_t>(nq, kLiftedBudget / per_q));
     qr = (qr + 3) / 4 * 4;
-    const size_t pt_bytes = align256((size_t)H * K * ldK * 8);
-    const size_t rs_bytes = align256((size_t)H * K * 4);
-    const size_t full_bytes = align256((size_t)H * K);
-    const size_t list_bytes = align256((size_t)n * 4 + 4);
-    const size_t bs_bytes = align256((size_t)H * ((K + 63) / 64) * 4);
-    const size_t lt_bytes = align256((size_t)qr * per_q);
-    tn_status st =
-        ensure_scratch(ctx, pt_bytes + rs_bytes + full_bytes + list_bytes + bs_bytes + lt_bytes);
+    const bool lists_fit = fuse_lists_fit(n, H, K);
+    // the totals first (8-byte entries), the lifted tables last: bitmaps and
+    // lists take their place in a call without tables
+    size_t need = 0;
+    auto part = [&](size_t bytes) {
+        const size_t at = need;
+        need += align256(bytes);
+        return at;
+    };
+    const size_t rows = (size_t)H * K, lt_bytes = (size_t)qr * per_q;
+    const size_t o_stats = part(kFuseStats * 8), o_pt = part(rows * ldK * 8), o_rs = part(rows * 4),
+                 o_full = part(rows), o_cls = part(n), o_open = part((size_t)n * 4),
+                 o_wide = part((size_t)n * 4), o_bs = part((size_t)H * ((K + 63) / 64) * 4),
+                 o_hist = part(lists_fit ? fuse_hist_words(H, K) * 4 : 0),
+                 o_start = part(lists_fit ? (rows + H) * 4 : 0),
+                 o_nodes = part(lists_fit ? (size_t)H * n * 4 : 0),
+                 o_rows = part(lists_fit ? rows * 8 : 0), o_brow = part(lists_fit ? rows * 4 : 0),
+                 o_lt = part(lt_bytes);
+    tn_status st = ensure_scratch(ctx, need);
     if (st != TN_OK) return st;
     unsigned char *base = (unsigned char *)ctx->scratch;
-    uint64_t *PT = (uint64_t *)base;
-    int32_t *rowsum = (int32_t *)(base + pt_bytes);
-    uint8_t *full = base + pt_bytes + rs_bytes;
-    uint32_t *list = (uint32_t *)(base + pt_bytes + rs_bytes + full_bytes);
-    uint32_t *nlist_dev = list + n;
-    int32_t *bsum = (int32_t *)(base + pt_bytes + rs_bytes + full_bytes + list_bytes);
-    uint64_t *Lt = (uint64_t *)(base + pt_bytes + rs_bytes + full_bytes + list_bytes + bs_bytes);
+    unsigned long long *stats = (unsigned long long *)(base + o_stats);
+    uint64_t *PT = (uint64_t *)(base + o_pt), *Lt = (uint64_t *)(base + o_lt);
+    int32_t *rowsum = (int32_t *)(base + o_rs), *bsum = (int32_t *)(base + o_bs);
+    uint8_t *full = base + o_full, *cls = base + o_cls;
+    uint32_t *open = (uint32_t *)(base + o_open), *wide = (uint32_t *)(base + o_wide);
     hipError_t e;
-    uint32_t nlist = 0;
+    unsigned long long host[kFuseStats] = {};
     {
         ProfScope ps(ctx, TN_K_AUX);
-        // one pass over the proxies: full rows, and the lifted row sums
-        e = launch_row_sums_full(H, K, ldK, P, count, bsum, lifted ? rowsum : nullptr, full,
-                                 ctx->stream);
-        if (e == hipSuccess && lifted)
-            e = launch_lifted_sizes(n, H, K, bucket, rowsum, lifted, ctx->stream);
+        e = launch_row_sums(H, K, ldK, P, count, bsum, rowsum, full, ctx->stream);
         if (e == hipSuccess)
-            e = launch_split_full(n, H, K, bucket, full, est, list, nlist_dev, ctx->stream);
+            e = launch_classify(n, H, K, bucket, count, rowsum, full, lifted, lists_fit, cls, est, open,
+                                wide, stats, ctx->stream);
     }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(&nlist, nlist_dev, sizeof(uint32_t), hipMemcpyDeviceToHost, ctx->stream);
+        e = hipMemcpyAsync(host, stats, sizeof(host), hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(e, "recombine set-up kernels");
-    // the transposed proxies feed the lifted tables only: none are needed
-    // when every node's proxy rows are full in every hash (est = n)
-    if (nlist > 0) {
+    const uint32_t nlist = (uint32_t)host[kFuseOpen];
+    if (nlist == 0) return TN_OK;  // est = n everywhere
+    if (lists_fit) {
+        unsigned long long entries = 0, nbitmaps = 0;
+        for (uint32_t j = 0; j < H; ++j) {
+            entries += host[kFuseRows + j];
+            nbitmaps += host[kFuseRows + 16 + j];
+        }
+        if (fuse_by_lists(n, H, K, host, entries, nbitmaps, lt_bytes)) {
+            ProfScope ps(ctx, TN_K_RECOMBINE);
+            const FuseScratch fs = {(uint32_t *)(base + o_hist), (uint32_t *)(base + o_start),
+                                    (uint32_t *)(base + o_nodes), (uint2 *)(base + o_rows),
+                                    (uint32_t *)(base + o_brow), Lt};
+            e = launch_fuse_lists(n, H, K, ldK, P, bucket, count, rowsum, cls, stats, fs,
+                                  (uint32_t)nbitmaps, wide, (uint32_t)host[kFuseWide], est,
+                                  ctx->stream);
+            return e == hipSuccess ? TN_OK : hip_fail(e, "list fusion launch");
+        }
+    }
+    {
         ProfScope ps(ctx, TN_K_AUX);
         e = launch_transpose_proxies(H, K, ldK, P, PT, ctx->stream);
         if (e != hipSuccess) return hip_fail(e, "proxy transpose launch");
     }
-    for (uint32_t q0 = 0; nlist > 0 && q0 < nq; q0 += qr) {
+    for (uint32_t q0 = 0; q0 < nq; q0 += qr) {
         const uint32_t cnt = std::min(qr, nq - q0);
         {
             ProfScope ps(ctx, TN_K_AUX);
@@ -656,7 +707,7 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
         if (e != hipSuccess) return hip_fail(e, "lifted-table kernel launch");
         {
             ProfScope ps(ctx, TN_K_RECOMBINE);
-            e = launch_recombine_est(n, H, K, bucket, Lt, q0, cnt, list, nlist, est, ctx->stream);
+            e = launch_recombine_est(n, H, K, bucket, Lt, q0, cnt, open, nlist, est, ctx->stream);
         }
         if (e != hipSuccess) return hip_fail(e, "recombine kernel launch");
     }

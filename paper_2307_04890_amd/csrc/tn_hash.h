@@ -9,23 +9,55 @@ hipError_t launch_hash_buckets(uint32_t n, uint32_t H, const uint64_t *coeffs, i
                                uint32_t *bucket, int32_t *count, hipStream_t st);
 hipError_t launch_transpose_proxies(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
                                     uint64_t *PT, hipStream_t st);
-// full[j K + r] = 1 iff proxy row r of P_j is full; with rowsum, also the
-// lifted row sums rowsum[j K + r] (bsum: scratch of H ceil(K/64) int32).
-hipError_t launch_row_sums_full(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
-                               const int32_t *count, int32_t *bsum, int32_t *rowsum, uint8_t *full,
-                               hipStream_t st);
-// lifted[j n + u] = rowsum[j K + h_j(u)].
-hipError_t launch_lifted_sizes(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
-                               const int32_t *rowsum, int32_t *lifted, hipStream_t st);
+// full[j K + r] = 1 iff row r of P_j is full, and rowsum[j K + r] = the nodes
+// that it lifts to: the sum of count[j] over the super-nodes set in it (bsum:
+// scratch of H ceil(K/64) int32).
+hipError_t launch_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
+                           const int32_t *count, int32_t *bsum, int32_t *rowsum, uint8_t *full,
+                           hipStream_t st);
 hipError_t launch_zero_i32(int32_t *p, size_t n, hipStream_t st);
 hipError_t launch_build_lifted(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *PT,
                                const uint32_t *bucket, uint32_t q0, uint32_t nq, uint64_t *Lt,
                                hipStream_t st);
-// est[u] = n for nodes whose proxy rows are full in every hash (full from
-// launch_row_sums_full); the others get est[u] = 0 and are listed in
-// list[0 .. *count).
-hipError_t launch_split_full(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
-                             const uint8_t *full, int32_t *est, uint32_t *list, uint32_t *count,
+// Fusion by lists (tn_hash.hip).  Totals of a call, uint64 on the device:
+enum : int {
+    kFuseOpen = 0,      // nodes some row of which is not full
+    kFuseWide = 1,      // ... the wide union nodes among them
+    kFuseEntries = 2,   // list entries and bitmaps that the union nodes read
+    kFuseBits = 3,
+    kFuseInter = 4,     // entries of the intersection nodes' shortest lists
+    kFuseNodeMix = 5,   // sums that agree where the counts are the buckets' own
+    kFuseCountMix = 6,
+    kFuseRows = 7,      // entries of each hash's lists, up to 16 hashes, and bitmaps
+    kFuseStats = 7 + 2 * 16
+};
+struct FuseScratch {
+    uint32_t *hist;        // fuse_hist_words
+    uint32_t *start;       // H (K + 1)
+    uint32_t *nodes;       // H n
+    uint2 *rows;           // H K
+    uint32_t *bitmap_row;  // H K
+    uint64_t *bitmaps;     // the sum of stats[kFuseRows + 16 ..], of ceil(n/64) words, then
+                           // the lists' entries (uint32, the sum of stats[kFuseRows ..])
+};
+// whether the lists' kernels take this size (8192 nodes and more, up to 16
+// hashes, LDS for K counters and n bits)
+bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K);
+size_t fuse_hist_words(uint32_t H, uint32_t K);
+// cls[u] (the node's kind), lifted[j n + u] = rowsum[j K + h_j(u)] (nullable),
+// est[u] = n where every row is full, else 0 and u in open[0 ..
+// stats[kFuseOpen]); the wide nodes in wide[0 .. stats[kFuseWide]); with
+// lists also the rows' totals.
+hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
+                           const int32_t *count, const int32_t *rowsum, const uint8_t *full,
+                           int32_t *lifted, bool lists, uint8_t *cls, int32_t *est,
+                           uint32_t *open, uint32_t *wide, unsigned long long *stats,
+                           hipStream_t st);
+// The estimates of union and intersection nodes.
+hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
+                             const uint32_t *bucket, const int32_t *count, const int32_t *rowsum,
+                             const uint8_t *cls, const unsigned long long *stats, FuseScratch s,
+                             uint32_t nbitmaps, const uint32_t *wide, uint32_t nwide, int32_t *est,
                              hipStream_t st);
 hipError_t launch_recombine_est(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
                                 const uint64_t *Lt, uint32_t q0, uint32_t nq, const uint32_t *list,

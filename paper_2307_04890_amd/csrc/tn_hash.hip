@@ -15,6 +15,8 @@
 #include <hip/hip_runtime.h>
 
 #include "tn_device.h"
+#include <algorithm>
+
 #include "tn_hash.h"
 
 namespace tn {
@@ -149,13 +151,13 @@ k_block_sums(uint32_t H, uint32_t K, const int32_t *__restrict__ count, int32_t 
 
 // One pass over every proxy row r of P_j, one wavefront per row, its lanes
 // on consecutive words: full[j][r] = 1 iff the row has all K bits set, and
-// (rowsum not NULL) rowsum[j][r] = sum of count[j][c] over the super-nodes
-// c set in the row.  A full word adds its block sum, an empty one nothing,
+// rowsum[j][r] = sum of count[j][c] over the super-nodes c set in the row.
+// A full word adds its block sum, an empty one nothing,
 // and each other word one count load per lane (lane l: super-node 64 wd + l).
 __global__ void __launch_bounds__(256)
-k_row_sums_full(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
-                const int32_t *__restrict__ count, const int32_t *__restrict__ bsum,
-                int32_t *__restrict__ rowsum, uint8_t *__restrict__ full) {
+k_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
+           const int32_t *__restrict__ count, const int32_t *__restrict__ bsum,
+           int32_t *__restrict__ rowsum, uint8_t *__restrict__ full) {
     const uint32_t lane = threadIdx.x & 63u;
     const size_t rows = (size_t)H * K;
     const uint32_t kw = (K + 63) / 64;
@@ -172,7 +174,6 @@ k_row_sums_full(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict_
             const uint64_t word = wd < kw ? Pr[wd] : 0ull;
             const bool fullw = wd < kw && word == (wd + 1 == kw ? last : ~0ull);
             all &= wd >= kw || fullw;
-            if (!rowsum) continue;
             if (fullw) acc += bsum[(size_t)j * kw + wd];
             // the other non-empty words, one at a time over the wavefront
             uint64_t partial = __ballot(wd < kw && word != 0ull && !fullw);
@@ -186,26 +187,13 @@ k_row_sums_full(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict_
                 if (c < K && ((wp >> lane) & 1ull)) acc += cj[c];
             }
         }
-        const bool row_full = __ballot(!all) == 0ull;
-        if (rowsum) {
 #pragma unroll
-            for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
-        }
+        for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
+        const bool row_full = __ballot(!all) == 0ull;
         if (lane == 0) {
-            if (rowsum) rowsum[row] = acc;
+            rowsum[row] = acc;
             full[row] = row_full ? 1 : 0;
         }
-    }
-}
-
-__global__ void __launch_bounds__(256)
-k_lifted_sizes(uint32_t n, uint32_t H, const uint32_t *__restrict__ bucket,
-               const int32_t *__restrict__ rowsum, uint32_t K, int32_t *__restrict__ lifted) {
-    const size_t total = (size_t)n * H;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < total;
-         i += (size_t)gridDim.x * blockDim.x) {
-        const uint32_t j = (uint32_t)(i / n);
-        lifted[i] = rowsum[(size_t)j * K + bucket[i]];
     }
 }
 
@@ -240,24 +228,6 @@ k_build_lifted(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *
             const uint64_t y = wave_transpose64(x[t]);
             const uint32_t r = (br0 + t) * 64 + lane;
             if (r < K) Lt[((size_t)qq * H + j) * K + r] = y;
-        }
-    }
-}
-
-// A node whose proxy row is full in every hash keeps every node: est = n.
-// Every other node is appended to `list` for the AND/popcount kernel.
-__global__ void __launch_bounds__(256)
-k_split_full(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
-             const uint8_t *__restrict__ full, int32_t *__restrict__ est,
-             uint32_t *__restrict__ list, uint32_t *__restrict__ count) {
-    for (uint32_t u = blockIdx.x * blockDim.x + threadIdx.x; u < n; u += gridDim.x * blockDim.x) {
-        bool all = true;
-        for (uint32_t j = 0; j < H && all; ++j) all = full[(size_t)j * K + bucket[(size_t)j * n + u]] != 0;
-        if (all) {
-            est[u] = (int32_t)n;
-        } else {
-            est[u] = 0;
-            list[atomicAdd(count, 1u)] = u;
         }
     }
 }
@@ -496,6 +466,671 @@ k_recombine_est2(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict_
         if (u[k] != 0xffffffffu && cnt[k]) atomicAdd(est + u[k], cnt[k]);
 }
 
+// ---- fusion by lists -------------------------------------------------------
+//
+// The tables above cost every node n / 64 words of each hash, whatever its
+// rows hold.  But a row that lifts to nearly all nodes, or to few, is a short
+// list: of the nodes it leaves out, or of those it keeps; any other row that
+// some node meets is a bitmap of n bits, built once for all its nodes.  A
+// node is then
+//  - done: every row is full, est = n, or lifts to all n nodes or one to
+//    none;
+//  - an intersection node where some row has a list of kept nodes: est = the
+//    nodes of the shortest one that every other row keeps too;
+//  - else a union node: est = n - |union of the nodes its rows leave out|, a
+//    small one where its lists fit a wavefront's table in LDS, else a wide
+//    one.
+// fuse_by_lists (tn_hash.cpp) says when this beats the tables: with 2*10^5
+// nodes and 4*10^4 events (H = 16, K = 4096), rows that leave out 39 nodes of
+// a hash on average, a call takes 1.01 ms against 5.79 ms.
+constexpr uint32_t kListPart = 64;        // lists of left-out nodes hold at most n / 64
+constexpr uint32_t kInterMax = 1u << 10;  // lists of kept nodes
+constexpr uint32_t kListSplit = 16;       // node ranges of a hash in the bucket sort
+constexpr uint32_t kHashSlots = 2048;     // a small node's table: 8 KB
+constexpr uint32_t kSmallBits = kHashSlots * 32;  // nodes that fit it as a bitmap
+constexpr uint32_t kSmallHashed = kHashSlots / 2, kSmallMarked = 4096;  // entries of a small node
+enum : uint8_t { kNodeDone = 0, kNodeSmall = 1, kNodeInter = 2, kNodeWide = 3 };
+// The lists a row can have (the two top bits of its descriptor's length).
+enum : uint32_t { kRowOut = 0, kRowKept = 1, kRowBits = 2 };
+
+// How a row that lifts to s of n nodes is held, and its list's entries (none:
+// a bitmap).
+__device__ __forceinline__ uint32_t row_list(uint32_t n, int32_t s, uint32_t &len) {
+    const uint32_t ones = (uint32_t)s, zeros = n - ones;
+    len = 0;
+    if (zeros <= n / kListPart) {
+        len = zeros;
+        return kRowOut;
+    }
+    if (ones <= kInterMax) {
+        len = ones;
+        return kRowKept;
+    }
+    return kRowBits;
+}
+
+// A 64-bit mix of (hash, super-node): the sums of it over the nodes' buckets
+// and over the counts agree when the counts are the buckets' own.
+__device__ __forceinline__ unsigned long long bucket_mix(uint32_t j, uint32_t r) {
+    unsigned long long z = ((unsigned long long)j << 32 | r) * 0x9e3779b97f4a7c15ull;
+    z ^= z >> 29;
+    return z * 0xbf58476d1ce4e5b9ull;
+}
+
+// Each node's kind (cls), its lifted sizes (lifted, nullable), est (n where
+// every row is full, else 0), the nodes some row of which is not full (open)
+// and the wide ones among them (wide); totals in stats.
+__global__ void __launch_bounds__(256)
+k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
+           const int32_t *__restrict__ rowsum, const uint8_t *__restrict__ full,
+           int32_t *__restrict__ lifted, uint8_t *__restrict__ cls, int32_t *__restrict__ est,
+           uint32_t *__restrict__ open, uint32_t *__restrict__ wide,
+           unsigned long long *__restrict__ stats) {
+    __shared__ uint32_t nopen, nwide, base[2];
+    __shared__ unsigned long long tot[4];
+    if (threadIdx.x < 4) tot[threadIdx.x] = 0;
+    unsigned long long entries = 0, bits = 0, inter = 0, sum = 0;
+    const uint32_t small = n <= kSmallBits ? kSmallMarked : kSmallHashed;
+    for (uint32_t t0 = blockIdx.x * blockDim.x; t0 < n; t0 += gridDim.x * blockDim.x) {
+        const uint32_t u = t0 + threadIdx.x;
+        if (threadIdx.x == 0) nopen = nwide = 0;
+        __syncthreads();
+        uint32_t slot = 0xffffffffu, wslot = 0xffffffffu;
+        if (u < n) {
+            uint64_t zsum = 0, out = 0;
+            bool all = true;
+            uint32_t smin = 0xffffffffu, nbits = 0;
+            for (uint32_t j0 = 0; j0 < H; j0 += 8) {
+                uint32_t b[8];
+                int32_t s[8];
+                uint8_t f[8];
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k)
+                    b[k] = j0 + k < H ? bucket[(size_t)(j0 + k) * n + u] : 0u;
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k)
+                    s[k] = j0 + k < H ? rowsum[(size_t)(j0 + k) * K + b[k]] : (int32_t)n;
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k)
+                    f[k] = j0 + k < H ? full[(size_t)(j0 + k) * K + b[k]] : (uint8_t)1;
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k) {
+                    if (lifted && j0 + k < H) lifted[(size_t)(j0 + k) * n + u] = s[k];
+                    if (j0 + k < H) sum += bucket_mix(j0 + k, b[k]);
+                    uint32_t len;
+                    const uint32_t kind = row_list(n, s[k], len);
+                    zsum += n - (uint32_t)s[k];
+                    all &= f[k] != 0;
+                    if (kind == kRowOut) out += len;
+                    if (kind == kRowKept) smin = min(smin, len);
+                    if (kind == kRowBits) ++nbits;
+                }
+            }
+            // an empty row keeps no node; rows without a left-out node make a
+            // small node of no entries
+            uint8_t c = kNodeDone;
+            if (!all && smin != 0) {
+                if (smin != 0xffffffffu) {
+                    c = kNodeInter;
+                    inter += smin;
+                } else {
+                    c = nbits == 0 && out <= small ? kNodeSmall : kNodeWide;
+                    entries += out;
+                    bits += nbits;
+                }
+            }
+            cls[u] = c;
+            est[u] = all ? (int32_t)n : 0;
+            if (!all) slot = atomicAdd(&nopen, 1u);
+            if (c == kNodeWide) wslot = atomicAdd(&nwide, 1u);
+        }
+        __syncthreads();
+        if (threadIdx.x == 0 && nopen) base[0] = (uint32_t)atomicAdd(stats + kFuseOpen, (unsigned long long)nopen);
+        if (threadIdx.x == 64 && nwide) base[1] = (uint32_t)atomicAdd(stats + kFuseWide, (unsigned long long)nwide);
+        __syncthreads();
+        if (slot != 0xffffffffu) open[base[0] + slot] = u;
+        if (wslot != 0xffffffffu) wide[base[1] + wslot] = u;
+        __syncthreads();
+    }
+    if (entries) atomicAdd(&tot[0], entries);
+    if (bits) atomicAdd(&tot[1], bits);
+    if (inter) atomicAdd(&tot[2], inter);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
+    if ((threadIdx.x & 63u) == 0) atomicAdd(&tot[3], sum);
+    __syncthreads();
+    if (threadIdx.x < 4 && tot[threadIdx.x])
+        atomicAdd(stats + kFuseEntries + threadIdx.x, tot[threadIdx.x]);
+}
+
+// The lists' entries and the bitmaps of a hash's rows that some node meets,
+// and the sum of bucket_mix over its counts, added to stats.  One workgroup
+// per hash.
+__global__ void __launch_bounds__(1024)
+k_list_totals(uint32_t n, uint32_t K, const int32_t *__restrict__ count,
+              const int32_t *__restrict__ rowsum, unsigned long long *__restrict__ stats) {
+    __shared__ unsigned long long tot[3];
+    if (stats[kFuseOpen] == 0) return;
+    const uint32_t j = blockIdx.x;
+    if (threadIdx.x < 3) tot[threadIdx.x] = 0;
+    unsigned long long v[3] = {};  // entries, bitmaps, mix
+    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) {
+        const int32_t c = count[(size_t)j * K + r];
+        v[2] += bucket_mix(j, r) * (unsigned long long)(uint32_t)c;
+        uint32_t len = 0;
+        if (c && row_list(n, rowsum[(size_t)j * K + r], len) == kRowBits) ++v[1];
+        v[0] += c ? len : 0u;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        if ((threadIdx.x & 63u) == 0) atomicAdd(&tot[k], v[k]);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) stats[kFuseRows + 16 * threadIdx.x + j] = tot[threadIdx.x];
+    if (threadIdx.x == 2) atomicAdd(stats + kFuseCountMix, tot[2]);
+}
+
+// The nodes of each hash sorted by bucket, in three kernels over (range of
+// nodes, hash): counts of each range in LDS, their exclusive sums, the
+// ranges' nodes at their places.
+__global__ void __launch_bounds__(512)
+k_bucket_hist(uint32_t n, uint32_t K, const uint32_t *__restrict__ bucket,
+              uint32_t *__restrict__ hist) {
+    extern __shared__ uint32_t cnt[];
+    const uint32_t j = blockIdx.y, per = (n + kListSplit - 1) / kListSplit;
+    const uint32_t w0 = min(n, blockIdx.x * per), w1 = min(n, w0 + per);
+    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) cnt[r] = 0;
+    __syncthreads();
+    for (uint32_t w = w0 + threadIdx.x; w < w1; w += blockDim.x) {
+        const uint32_t b = bucket[(size_t)j * n + w];
+        if (b < K) atomicAdd(cnt + b, 1u);
+    }
+    __syncthreads();
+    uint32_t *h = hist + ((size_t)j * kListSplit + blockIdx.x) * K;
+    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) h[r] = cnt[r];
+}
+
+// Exclusive sum of v over the workgroup's 1024 threads, its total in `total`.
+__device__ __forceinline__ uint32_t block_scan(uint32_t v, uint32_t *part, uint32_t &total) {
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    uint32_t x = v;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+        const uint32_t y = (uint32_t)__shfl_up((int)x, off, 64);
+        if ((int)lane >= off) x += y;
+    }
+    __syncthreads();
+    if (lane == 63) part[wave] = x;
+    __syncthreads();
+    uint32_t before = 0;
+    total = 0;
+    for (uint32_t k = 0; k < (blockDim.x >> 6); ++k) {
+        before += k < wave ? part[k] : 0u;
+        total += part[k];
+    }
+    return before + x - v;
+}
+
+// One workgroup per hash: the bucket starts and each range's places.
+__global__ void __launch_bounds__(1024)
+k_bucket_starts(uint32_t K, uint32_t *__restrict__ hist, uint32_t *__restrict__ start) {
+    __shared__ uint32_t part[16];
+    const uint32_t j = blockIdx.x;
+    uint32_t *h = hist + (size_t)j * kListSplit * K;
+    uint32_t carry = 0;
+    for (uint32_t r0 = 0; r0 < K; r0 += blockDim.x) {
+        const uint32_t r = r0 + threadIdx.x;
+        uint32_t c[kListSplit], tot = 0;
+#pragma unroll
+        for (uint32_t s = 0; s < kListSplit; ++s) c[s] = r < K ? h[(size_t)s * K + r] : 0u;
+#pragma unroll
+        for (uint32_t s = 0; s < kListSplit; ++s) tot += c[s];
+        uint32_t all;
+        uint32_t at = carry + block_scan(tot, part, all);
+        carry += all;
+        if (r < K) {
+            start[(size_t)j * (K + 1) + r] = at;
+#pragma unroll
+            for (uint32_t s = 0; s < kListSplit; ++s) {
+                h[(size_t)s * K + r] = at;
+                at += c[s];
+            }
+        }
+    }
+    if (threadIdx.x == 0) start[(size_t)j * (K + 1) + K] = carry;
+}
+
+__global__ void __launch_bounds__(512)
+k_bucket_nodes(uint32_t n, uint32_t K, const uint32_t *__restrict__ bucket,
+               const uint32_t *__restrict__ hist, uint32_t *__restrict__ nodes) {
+    extern __shared__ uint32_t cnt[];
+    const uint32_t j = blockIdx.y, per = (n + kListSplit - 1) / kListSplit;
+    const uint32_t w0 = min(n, blockIdx.x * per), w1 = min(n, w0 + per);
+    const uint32_t *h = hist + ((size_t)j * kListSplit + blockIdx.x) * K;
+    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) cnt[r] = h[r];
+    __syncthreads();
+    for (uint32_t w = w0 + threadIdx.x; w < w1; w += blockDim.x) {
+        const uint32_t b = bucket[(size_t)j * n + w];
+        if (b < K) nodes[(size_t)j * n + atomicAdd(cnt + b, 1u)] = w;
+    }
+}
+
+// rows[j K + r] = {first entry of the row's list, its length} or {its bitmap,
+// 0}, the length's two top bits its kind, and the row of each bitmap.  One
+// workgroup per hash, its entries and bitmaps after those of the hashes
+// before it.
+__global__ void __launch_bounds__(1024)
+k_list_starts(uint32_t n, uint32_t K, const int32_t *__restrict__ count,
+              const int32_t *__restrict__ rowsum, const unsigned long long *__restrict__ stats,
+              uint2 *__restrict__ rows, uint32_t *__restrict__ bitmap_row) {
+    __shared__ uint32_t part[16];
+    const uint32_t j = blockIdx.x;
+    uint32_t entries = 0, bitmaps = 0;
+    for (uint32_t i = 0; i < j; ++i) {
+        entries += (uint32_t)stats[kFuseRows + i];
+        bitmaps += (uint32_t)stats[kFuseRows + 16 + i];
+    }
+    for (uint32_t r0 = 0; r0 < K; r0 += blockDim.x) {
+        const uint32_t r = r0 + threadIdx.x;
+        uint32_t kind = kRowOut, len = 0, all;
+        if (r < K && count[(size_t)j * K + r]) kind = row_list(n, rowsum[(size_t)j * K + r], len);
+        const uint32_t e = entries + block_scan(len, part, all);
+        entries += all;
+        const uint32_t m = bitmaps + block_scan(kind == kRowBits ? 1u : 0u, part, all);
+        bitmaps += all;
+        if (r < K) rows[(size_t)j * K + r] = make_uint2(kind == kRowBits ? m : e, len | kind << 30);
+        if (kind == kRowBits) bitmap_row[m] = j * K + r;
+    }
+}
+
+// The bitmaps: bit w of a row's = the row leaves node w out.  A workgroup per
+// (bitmap, one of gridDim.y ranges of nodes), the row in LDS, the hash's
+// buckets in order, 64 verdicts a word.
+constexpr uint32_t kListMaxK = (uint32_t)(kRecombineLds / 4);  // K counters in LDS
+__global__ void __launch_bounds__(256)
+k_fill_bitmaps(uint32_t n, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
+               const uint32_t *__restrict__ bucket, const uint32_t *__restrict__ bitmap_row,
+               uint64_t *__restrict__ bitmaps) {
+    __shared__ uint32_t prow[kListMaxK / 32];
+    const size_t row = bitmap_row[blockIdx.x];
+    const uint32_t *Pr = (const uint32_t *)(P + row * ldK);  // row r of matrix j: j K + r rows on
+    for (uint32_t i = threadIdx.x; i < (K + 63) / 64 * 2; i += blockDim.x) prow[i] = Pr[i];
+    __syncthreads();
+    const uint32_t *bj = bucket + row / K * n;
+    uint64_t *out = bitmaps + (size_t)blockIdx.x * ((n + 63) / 64);
+    for (uint32_t w0 = blockIdx.y * 4 * blockDim.x + (threadIdx.x & ~63u); w0 < n;
+         w0 += gridDim.y * 4 * blockDim.x) {
+        uint32_t hb[4];
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t w = w0 + q * blockDim.x + (threadIdx.x & 63u);
+            hb[q] = w < n ? bj[w] : 0xffffffffu;
+        }
+#pragma unroll
+        for (uint32_t q = 0; q < 4; ++q) {
+            const uint32_t w = w0 + q * blockDim.x;
+            const bool left = hb[q] != 0xffffffffu && !((prow[hb[q] >> 5] >> (hb[q] & 31u)) & 1u);
+            const uint64_t m = __ballot(left);
+            if ((threadIdx.x & 63u) == 0 && w < n) out[w >> 6] = m;
+        }
+    }
+}
+
+// The rows' lists, one wavefront per row.  Of 64 words at a time (inverted
+// for a list of left-out nodes) the super-nodes go to LDS, then 64 of them at
+// a time to the lanes, each reading where its nodes are; with RUNS (16 nodes
+// and more on average) the wavefront copies one super-node's nodes at a time,
+// four in flight, else every lane copies its own.
+template <bool RUNS>
+__global__ void __launch_bounds__(64)
+k_fill_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
+             const uint32_t *__restrict__ start, const uint32_t *__restrict__ nodes,
+             const uint2 *__restrict__ rows, uint32_t *__restrict__ lists) {
+    __shared__ uint16_t ids[64 * 64];  // K <= kListMaxK < 2^16
+    const uint32_t lane = threadIdx.x;
+    const size_t row = blockIdx.x;
+    const uint2 d = rows[row];
+    const uint32_t len = d.y & 0x3fffffffu;
+    if (len == 0) return;
+    const bool kept = d.y >> 30 == kRowKept;
+    const uint32_t j = (uint32_t)(row / K), kw = (K + 63) / 64;
+    const uint64_t last = (K % 64) ? ((1ull << (K % 64)) - 1ull) : ~0ull;
+    const uint64_t *Pr = P + row * ldK;  // row r of matrix j: j K + r rows on
+    const uint32_t *sj = start + (size_t)j * (K + 1);
+    const uint32_t *nj = nodes + (size_t)j * n;
+    uint32_t *out = lists + d.x;
+    uint32_t at = 0;  // entries so far
+    // exclusive sum over the lanes; total from the last
+    auto scan = [&](uint32_t v, uint32_t &total) {
+        uint32_t x = v;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)x, off, 64);
+            if ((int)lane >= off) x += y;
+        }
+        total = (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+        return x - v;
+    };
+    for (uint32_t wd0 = 0; wd0 < kw && at < len; wd0 += 64) {
+        const uint32_t wd = wd0 + lane;
+        uint64_t x = 0;
+        if (wd < kw) {
+            x = kept ? Pr[wd] : ~Pr[wd];
+            if (wd + 1 == kw) x &= last;
+        }
+        uint32_t some;
+        uint32_t o = scan((uint32_t)__popcll(x), some);
+        __syncthreads();  // one wavefront: the last block's ids are read
+        for (; x; x &= x - 1ull) ids[o++] = (uint16_t)(wd * 64 + (uint32_t)__builtin_ctzll(x));
+        __syncthreads();
+        for (uint32_t i0 = 0; i0 < some; i0 += 64) {
+            uint32_t s0 = 0, k = 0;
+            if (i0 + lane < some) {
+                const uint32_t c = ids[i0 + lane];
+                s0 = sj[c];
+                k = sj[c + 1] - s0;
+            }
+            uint32_t total;
+            uint32_t to = at + scan(k, total);
+            // never past the row's own length
+            k = to < len ? min(k, len - to) : 0u;
+            at += total;
+            if (RUNS) {
+                const uint32_t m = min(64u, some - i0);
+                for (uint32_t q0 = 0; q0 < m; q0 += 4) {
+                    uint32_t v[4], longest = 0;
+#pragma unroll
+                    for (uint32_t q = 0; q < 4; ++q) {
+                        const uint32_t kk = q0 + q < m ? __builtin_amdgcn_readlane(k, q0 + q) : 0u;
+                        longest = max(longest, kk);
+                        v[q] = lane < kk ? nj[__builtin_amdgcn_readlane(s0, q0 + q) + lane] : 0u;
+                    }
+#pragma unroll
+                    for (uint32_t q = 0; q < 4; ++q) {
+                        const uint32_t kk = q0 + q < m ? __builtin_amdgcn_readlane(k, q0 + q) : 0u;
+                        if (lane < kk) out[__builtin_amdgcn_readlane(to, q0 + q) + lane] = v[q];
+                    }
+                    if (longest <= 64) continue;
+                    for (uint32_t q = 0; q < 4 && q0 + q < m; ++q) {
+                        const uint32_t kk = __builtin_amdgcn_readlane(k, q0 + q);
+                        const uint32_t from = __builtin_amdgcn_readlane(s0, q0 + q);
+                        const uint32_t dst = __builtin_amdgcn_readlane(to, q0 + q);
+                        for (uint32_t i = 64 + lane; i < kk; i += 64) out[dst + i] = nj[from + i];
+                    }
+                }
+            } else {
+                for (uint32_t i = 0; i < k; ++i) out[to + i] = nj[s0 + i];
+            }
+        }
+    }
+}
+
+// What a wavefront needs of a node's lists: lane j < H holds the descriptor
+// of its row in hash j.  The lists of left-out nodes are read in chunks of 64
+// entries; lane t gets where chunk t0 + t starts and how many it has.
+constexpr uint32_t kListHashes = 16;
+struct Chunks {
+    uint32_t offset, len, before, count;  // the lane's list, the chunks before it; all chunks
+    bool single;  // no list has more than 64 entries: chunk t is list t
+    __device__ __forceinline__ explicit Chunks(uint2 d) {
+        offset = d.x;
+        len = d.y >> 30 == kRowOut ? d.y : 0u;
+        single = __ballot(len > 64) == 0;
+        before = 0;
+        count = kListHashes;
+        if (single) return;
+        const uint32_t mine = (len + 63) / 64;
+        uint32_t upto = mine;
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)upto, off, 16);
+            if ((int)(threadIdx.x & 15u) >= off) upto += y;
+        }
+        before = upto - mine;
+        count = (uint32_t)__builtin_amdgcn_readlane((int)upto, 15);
+    }
+    __device__ __forceinline__ void at(uint32_t t0, uint32_t &from, uint32_t &entries) const {
+        const uint32_t t = t0 + (threadIdx.x & 63u);
+        from = offset;
+        entries = len;
+        if (single) return;
+        from = entries = 0;
+#pragma unroll
+        for (uint32_t j = 0; j < kListHashes; ++j) {
+            const uint32_t c0 = (uint32_t)__builtin_amdgcn_readlane((int)before, (int)j);
+            const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)len, (int)j);
+            const uint32_t o = (uint32_t)__builtin_amdgcn_readlane((int)offset, (int)j);
+            const uint32_t k = t - c0;  // chunk of this list
+            if (t >= c0 && 64 * k < l) {
+                from = o + 64 * k;
+                entries = min(64u, l - 64 * k);
+            }
+        }
+    }
+};
+
+// The estimates of small union nodes and of intersection nodes, one wavefront
+// (one workgroup) per node at a time.
+//  - Union: kBatch chunks of entries in flight; an entry is marked in a
+//    bitmap of n bits by an atomic OR whose old word tells a first mark, or,
+//    HASHED, where n bits are more than the 8 KB of a hash table, entered
+//    there by compare-and-swap (at most half full: kSmallHashed entries).
+//    Either is cleared whole, 16 bytes a lane.
+//  - Intersection: 64 nodes of the shortest list at a time against 4 hashes
+//    at a time, until none is left.
+// Bound by the latency of a node's chain of reads (buckets, rows, lists),
+// hidden by the wavefronts the tables leave room for (20 a CU), and by their
+// instructions: 147,000 nodes of 600 entries (n = 2*10^5) in 0.55 ms.
+constexpr uint32_t kBatch = 8;
+template <bool HASHED>
+__global__ void __launch_bounds__(64)
+k_fuse_small(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
+             const uint32_t *__restrict__ bucket, const uint8_t *__restrict__ cls,
+             const uint2 *__restrict__ rows, const uint32_t *__restrict__ lists,
+             int32_t *__restrict__ est) {
+    extern __shared__ __align__(16) uint32_t htab[];
+    const uint32_t lane = threadIdx.x;
+    const uint32_t none = HASHED ? 0xffffffffu : 0u;
+    const uint32_t words = HASHED ? kHashSlots : ((n + 127) / 128) * 4;
+    auto clear = [&] {
+        for (uint32_t i = 4 * lane; i < words; i += 256)
+            *(uint4 *)(htab + i) = make_uint4(none, none, none, none);
+    };
+    clear();
+    __syncthreads();  // one wavefront: orders its LDS accesses
+    auto buckets = [&](uint32_t u, uint32_t &b, uint32_t &c) {
+        c = u < n ? cls[u] : (uint32_t)kNodeDone;
+        b = u < n && lane < H ? bucket[(size_t)lane * n + u] : 0u;
+    };
+    uint32_t b, c;
+    buckets(blockIdx.x, b, c);
+    for (uint32_t u = blockIdx.x; u < n; u += gridDim.x) {
+        const uint32_t bu = b, cu = __builtin_amdgcn_readfirstlane(c);
+        uint2 d = make_uint2(0u, 0u);
+        if ((cu == kNodeSmall || cu == kNodeInter) && lane < H) d = rows[(size_t)lane * K + bu];
+        buckets(n - u > gridDim.x ? u + gridDim.x : n, b, c);
+        uint32_t mine = 0;
+        if (cu == kNodeSmall) {
+            const Chunks ch(d);
+            for (uint32_t t0 = 0; t0 < ch.count; t0 += 64) {
+                uint32_t from, entries;
+                ch.at(t0, from, entries);
+                const uint32_t some = min(64u, ch.count - t0);
+                for (uint32_t q0 = 0; q0 < some; q0 += kBatch) {
+                    uint32_t w[kBatch];
+#pragma unroll
+                    for (uint32_t q = 0; q < kBatch; ++q) {
+                        w[q] = 0xffffffffu;
+                        if (q0 + q < some) {
+                            const uint32_t o = __builtin_amdgcn_readlane(from, q0 + q);
+                            if (lane < (uint32_t)__builtin_amdgcn_readlane(entries, q0 + q))
+                                w[q] = lists[o + lane];
+                        }
+                    }
+                    if (HASHED) {
+#pragma unroll
+                        for (uint32_t h = 0; h < kBatch; h += 4) {
+                            uint32_t at[4];
+                            bool open[4];
+#pragma unroll
+                            for (uint32_t k = 0; k < 4; ++k) {
+                                at[k] = (w[h + k] * 2654435761u) >> 21;
+                                open[k] = w[h + k] < n;
+                            }
+                            while (__ballot(open[0] | open[1] | open[2] | open[3])) {
+                                uint32_t old[4];
+#pragma unroll
+                                for (uint32_t k = 0; k < 4; ++k)
+                                    if (open[k]) old[k] = atomicCAS(htab + at[k], none, w[h + k]);
+#pragma unroll
+                                for (uint32_t k = 0; k < 4; ++k)
+                                    if (open[k]) {
+                                        mine += old[k] == none ? 1u : 0u;
+                                        open[k] = old[k] != none && old[k] != w[h + k];
+                                        at[k] = (at[k] + 1) & (kHashSlots - 1);
+                                    }
+                            }
+                        }
+                    } else {
+#pragma unroll
+                        for (uint32_t q = 0; q < kBatch; ++q)
+                            if (w[q] < n) {
+                                const uint32_t bit = 1u << (w[q] & 31u);
+                                mine += (atomicOr(htab + (w[q] >> 5), bit) & bit) ? 0u : 1u;
+                            }
+                    }
+                }
+            }
+            __syncthreads();
+            clear();
+            __syncthreads();
+        } else if (cu == kNodeInter) {
+            // the shortest list of kept nodes
+            uint32_t key = d.y >> 30 == kRowKept ? (d.y & 0x3fffffffu) << 4 | lane : 0xffffffffu;
+#pragma unroll
+            for (int off = 8; off > 0; off >>= 1) key = min(key, (uint32_t)__shfl_xor(key, off, 16));
+            key = __builtin_amdgcn_readfirstlane(key);
+            const uint32_t js = key & 15u, len = key >> 4;
+            const uint32_t o = __builtin_amdgcn_readlane(d.x, js);
+            for (uint32_t i0 = 0; i0 < len; i0 += 64) {
+                const uint32_t w = i0 + lane < len ? lists[o + i0 + lane] : 0xffffffffu;
+                bool alive = w < n;
+                // the other hashes, from the one after js on
+                for (uint32_t k0 = 1; k0 < H; k0 += 4) {
+                    uint32_t hb[4];
+                    uint64_t x[4];
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) {
+                        const uint32_t j = (js + k0 + k) % H;
+                        hb[k] = alive && k0 + k < H ? bucket[(size_t)j * n + w] : 0u;
+                    }
+#pragma unroll
+                    for (uint32_t k = 0; k < 4; ++k) {
+                        const uint32_t j = (js + k0 + k) % H;
+                        const size_t r = (size_t)j * K + __builtin_amdgcn_readlane(bu, j);
+                        x[k] = alive && k0 + k < H ? P[r * ldK + (hb[k] >> 6)] >> (hb[k] & 63u) : 1ull;
+                    }
+                    alive = alive && (x[0] & x[1] & x[2] & x[3] & 1ull);
+                    if (__ballot(alive) == 0) break;
+                }
+                mine += alive ? 1u : 0u;
+            }
+        } else {
+            continue;
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+        if (lane == 0) est[u] = (int32_t)(cu == kNodeSmall ? n - mine : mine);
+    }
+}
+
+// The estimates of wide union nodes, one workgroup per node at a time: the
+// bitmaps of its rows are ORed into one in LDS, 16 bytes a thread, then its
+// lists marked there, the chunks dealt to the wavefronts, kBatch in flight
+// each.  Bound by the bitmaps' reads (n / 8 bytes each, from L2 where nodes
+// of a bucket share them) and the latency of the lists'; n bits of LDS limit
+// the nodes at work on a CU, so a workgroup has as many wavefronts as fill it
+// (launch_fuse_lists): 53,000 nodes of 1400 entries (n = 2*10^5) in 0.22 ms.
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__global__ void __launch_bounds__(1024)
+k_fuse_wide(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
+            const uint2 *__restrict__ rows, const uint32_t *__restrict__ lists,
+            const uint64_t *__restrict__ bitmaps, const uint32_t *__restrict__ list, uint32_t nlist,
+            int32_t *__restrict__ est) {
+    extern __shared__ __align__(16) uint32_t bm[];
+    __shared__ uint32_t sums[2];
+    const uint32_t tid = threadIdx.x, T = blockDim.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), waves = T >> 6;
+    const uint32_t nw = (n + 63) / 64;
+    uint64_t *bm64 = (uint64_t *)bm;
+    if (tid < 2) sums[tid] = 0;
+    uint32_t turn = 0;
+    __syncthreads();
+    for (uint32_t i = blockIdx.x; i < nlist; i += gridDim.x) {
+        const uint32_t u = list[i];
+        uint2 d = make_uint2(0u, 0u);
+        if (lane < H) d = rows[(size_t)lane * K + bucket[(size_t)lane * n + u]];
+        const uint32_t maps = (uint32_t)__ballot(d.y >> 30 == kRowBits);
+        uint32_t mine = 0;
+        for (uint32_t k0 = tid; k0 < nw; k0 += 4 * T) {
+            uint64_t x[4] = {};
+            for (uint32_t rest = maps; rest; rest &= rest - 1u) {
+                const uint64_t *m =
+                    bitmaps + (size_t)(uint32_t)__builtin_amdgcn_readlane(d.x, __builtin_ctz(rest)) * nw;
+                uint64_t y[4];
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) y[q] = k0 + q * T < nw ? m[k0 + q * T] : 0ull;
+#pragma unroll
+                for (uint32_t q = 0; q < 4; ++q) x[q] |= y[q];
+            }
+#pragma unroll
+            for (uint32_t q = 0; q < 4; ++q)
+                if (k0 + q * T < nw) {
+                    bm64[k0 + q * T] = x[q];
+                    mine += (uint32_t)__popcll(x[q]);
+                }
+        }
+        const Chunks ch(d);
+        __syncthreads();
+        for (uint32_t t0 = 0; t0 < ch.count; t0 += 64) {
+            uint32_t from, entries;
+            ch.at(t0, from, entries);
+            const uint32_t some = min(64u, ch.count - t0);
+            for (uint32_t q0 = wave; q0 < some; q0 += kBatch * waves) {
+                uint32_t w[kBatch];
+#pragma unroll
+                for (uint32_t q = 0; q < kBatch; ++q) {
+                    const uint32_t t = q0 + q * waves;
+                    w[q] = 0xffffffffu;
+                    if (t < some) {
+                        const uint32_t o = __builtin_amdgcn_readlane(from, t);
+                        if (lane < (uint32_t)__builtin_amdgcn_readlane(entries, t)) w[q] = lists[o + lane];
+                    }
+                }
+#pragma unroll
+                for (uint32_t q = 0; q < kBatch; ++q)
+                    if (w[q] < n) {
+                        const uint32_t bit = 1u << (w[q] & 31u);
+                        mine += (atomicOr(bm + (w[q] >> 5), bit) & bit) ? 0u : 1u;
+                    }
+            }
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+        // two sums in turn: the other one is cleared while this one is read
+        if (lane == 0) atomicAdd(&sums[turn], mine);
+        __syncthreads();  // and the bitmap may be written again
+        if (tid == 0) {
+            est[u] = (int32_t)(n - sums[turn]);
+            sums[turn ^ 1u] = 0;
+        }
+        turn ^= 1u;
+    }
+}
+
 uint32_t grid_for(size_t items, uint32_t per_block, uint32_t cap = 65536) {
     size_t g = (items + per_block - 1) / per_block;
     if (g < 1) g = 1;
@@ -530,25 +1165,101 @@ hipError_t launch_transpose_proxies(uint32_t H, uint32_t K, int64_t ldK, const u
     return hipGetLastError();
 }
 
-hipError_t launch_row_sums_full(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
-                               const int32_t *count, int32_t *bsum, int32_t *rowsum, uint8_t *full,
-                               hipStream_t st) {
+hipError_t launch_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
+                           const int32_t *count, int32_t *bsum, int32_t *rowsum, uint8_t *full,
+                           hipStream_t st) {
     const size_t kw = (K + 63) / 64;
-    if (rowsum) {
-        hipLaunchKernelGGL(k_block_sums, dim3(grid_for((size_t)H * kw * 64, 256)), dim3(256), 0, st,
-                           H, K, count, bsum);
-        hipError_t e = hipGetLastError();
-        if (e != hipSuccess) return e;
-    }
-    hipLaunchKernelGGL(k_row_sums_full, dim3(grid_for((size_t)H * K * 64, 256)), dim3(256), 0, st, H,
-                       K, ldK, P, count, bsum, rowsum, full);
+    hipLaunchKernelGGL(k_block_sums, dim3(grid_for((size_t)H * kw * 64, 256)), dim3(256), 0, st, H, K,
+                       count, bsum);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_row_sums, dim3(grid_for((size_t)H * K * 64, 256)), dim3(256), 0, st, H, K, ldK,
+                       P, count, bsum, rowsum, full);
     return hipGetLastError();
 }
 
-hipError_t launch_lifted_sizes(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
-                               const int32_t *rowsum, int32_t *lifted, hipStream_t st) {
-    hipLaunchKernelGGL(k_lifted_sizes, dim3(grid_for((size_t)n * H, 256)), dim3(256), 0, st, n, H,
-                       bucket, rowsum, K, lifted);
+static size_t fuse_wide_lds(uint32_t n) { return ((size_t)n + 63) / 64 * 8; }
+
+bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K) {
+    return n >= 8192 && H <= kListHashes && K <= kListMaxK && fuse_wide_lds(n) + 64 <= kRecombineLds;
+}
+
+size_t fuse_hist_words(uint32_t H, uint32_t K) { return (size_t)H * kListSplit * K; }
+
+hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
+                           const int32_t *count, const int32_t *rowsum, const uint8_t *full,
+                           int32_t *lifted, bool lists, uint8_t *cls, int32_t *est,
+                           uint32_t *open, uint32_t *wide, unsigned long long *stats,
+                           hipStream_t st) {
+    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, (int32_t *)stats,
+                       (size_t)2 * kFuseStats);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_classify, dim3(grid_for(n, 256, 512)), dim3(256), 0, st, n, H, K, bucket,
+                       rowsum, full, lifted, cls, est, open, wide, stats);
+    e = hipGetLastError();
+    if (e != hipSuccess || !lists) return e;
+    hipLaunchKernelGGL(k_list_totals, dim3(H), dim3(1024), 0, st, n, K, count, rowsum, stats);
+    return hipGetLastError();
+}
+
+hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
+                             const uint32_t *bucket, const int32_t *count, const int32_t *rowsum,
+                             const uint8_t *cls, const unsigned long long *stats, FuseScratch s,
+                             uint32_t nbitmaps, const uint32_t *wide, uint32_t nwide, int32_t *est,
+                             hipStream_t st) {
+    uint32_t *lists = (uint32_t *)(s.bitmaps + (size_t)nbitmaps * ((n + 63) / 64));
+    size_t lds = (size_t)K * 4;
+    for (const void *k : {(const void *)k_bucket_hist, (const void *)k_bucket_nodes}) {
+        hipError_t e = hipFuncSetAttribute(k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(k_bucket_hist, dim3(kListSplit, H), dim3(512), lds, st, n, K, bucket, s.hist);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bucket_starts, dim3(H), dim3(1024), 0, st, K, s.hist, s.start);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_bucket_nodes, dim3(kListSplit, H), dim3(512), lds, st, n, K, bucket, s.hist,
+                       s.nodes);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_list_starts, dim3(H), dim3(1024), 0, st, n, K, count, rowsum, stats, s.rows,
+                       s.bitmap_row);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    auto fill = n / K >= 16 ? k_fill_lists<true> : k_fill_lists<false>;
+    hipLaunchKernelGGL(fill, dim3(H * K), dim3(64), 0, st, n, H, K, ldK, P, s.start, s.nodes, s.rows,
+                       lists);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    const bool hashed = n > kSmallBits;
+    lds = hashed ? kHashSlots * 4 : ((size_t)n + 127) / 128 * 16;
+    const uint32_t per_cu = (uint32_t)std::min<size_t>(kRecombineLds / lds, 32);
+    auto small = hashed ? k_fuse_small<true> : k_fuse_small<false>;
+    hipLaunchKernelGGL(small, dim3(grid_for(n, 1, 256 * per_cu)), dim3(64), lds, st, n, H, K, ldK, P,
+                       bucket, cls, s.rows, lists, est);
+    e = hipGetLastError();
+    if (e != hipSuccess || nwide == 0) return e;
+    if (nbitmaps) {
+        const uint32_t splits = std::max(1u, std::min(n / 1024, 4096u / nbitmaps));
+        hipLaunchKernelGGL(k_fill_bitmaps, dim3(nbitmaps, splits), dim3(256), 0, st, n, K, ldK, P,
+                           bucket, s.bitmap_row, s.bitmaps);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    lds = fuse_wide_lds(n);
+    e = hipFuncSetAttribute((const void *)k_fuse_wide, hipFuncAttributeMaxDynamicSharedMemorySize,
+                            (int)lds);
+    if (e != hipSuccess) return e;
+    // as many bitmaps as a CU's LDS holds, at most 16, and about 24 wavefronts
+    // over them
+    const uint32_t fit = (uint32_t)std::min<size_t>(kRecombineLds / (lds + 64), 16);
+    uint32_t threads = 64;
+    while (threads < 1024 && fit * threads < 24 * 64) threads *= 2;
+    const uint32_t resident = std::min(fit, 2048u / threads);
+    hipLaunchKernelGGL(k_fuse_wide, dim3(grid_for(nwide, 1, 256 * resident)), dim3(threads), lds, st, n,
+                       H, K, bucket, s.rows, lists, s.bitmaps, wide, nwide, est);
     return hipGetLastError();
 }
 
@@ -574,17 +1285,6 @@ uint32_t recombine_group(uint32_t K) {
     size_t g = budget / ((size_t)K * 8);
     if (g > 4) g = 4;
     return (uint32_t)g;
-}
-
-hipError_t launch_split_full(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
-                             const uint8_t *full, int32_t *est, uint32_t *list, uint32_t *count,
-                             hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, (int32_t *)count, (size_t)1);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_split_full, dim3(grid_for(n, 256)), dim3(256), 0, st, n, H, K, bucket, full,
-                       est, list, count);
-    return hipGetLastError();
 }
 
 hipError_t launch_recombine_est(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
