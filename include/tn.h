@@ -325,10 +325,13 @@ void tn_online_destroy(tn_online *online);
  * library draws no random numbers).  M: DEVICE n x s uint8, row-major,
  * written entirely, starting on 16 bytes (rows move in 16-byte words).  est: DEVICE float64[n] or NULL.  log2s in [4, 16].
  * tn_hll_execute runs on a plan's schedule (asynchronous): on a TN_HLL
- * plan one launch per level (two for a level with compound items) spreads
- * the level's items over the whole device, one group of lanes per item and
- * row; on another plan the row-OR kernel's level loop runs with byte-wise
- * maximum, one workgroup per word column.  tn_hll_build plans (TN_HLL), runs
+ * plan one launch runs the whole stream, each workgroup's registers of every
+ * node in LDS, where n bytes of them fit (about 163,000 nodes) and few rounds
+ * of workgroups cover the 2^log2s registers; else one launch per level (two
+ * for a level with many compound items) spreads the level's items over the
+ * whole device, one group of lanes per item and row; on another plan the
+ * row-OR kernel's level loop runs with byte-wise maximum, one workgroup per
+ * word column.  tn_hll_build plans (TN_HLL), runs
  * and waits.  Errors: TN_E_ARG, plus those of tn_plan_create. */
 tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
                          const uint64_t *node_hash, uint8_t *M, double *est);

@@ -190,6 +190,22 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
         img.resize(flat_off + tn::flat_ops_bytes(hs), 0);
         tn::flat_ops_pack(hs, n, (uint32_t *)(img.data() + flat_off));
     }
+    // a TN_HLL plan whose register columns fit in LDS also keeps the ends of
+    // each level's gather sources and each source's gather within its level
+    const bool columns = hll && tn::hll_columns_fit(n, (uint32_t)hs.max_level_gathers);
+    const size_t src_off = (img.size() + 255) & ~(size_t)255;
+    const size_t slot_off = src_off + ((4 * ((size_t)hs.L + 1) + 255) & ~(size_t)255);
+    if (columns) {
+        img.resize(slot_off + 4 * std::max<size_t>(hs.gat_src.size(), 1), 0);
+        uint32_t *lvl_src = (uint32_t *)(img.data() + src_off);
+        uint32_t *slot = (uint32_t *)(img.data() + slot_off);
+        for (uint32_t l = 0; l < hs.L; ++l) {
+            for (uint32_t q = hs.lvl_gat[l]; q < hs.lvl_gat[l + 1]; ++q)
+                for (uint32_t k = hs.gat_ptr[q]; k < hs.gat_ptr[q + 1]; ++k)
+                    slot[k] = q - hs.lvl_gat[l];
+            lvl_src[l + 1] = hs.gat_ptr.empty() ? 0u : hs.gat_ptr[hs.lvl_gat[l + 1]];
+        }
+    }
     p->dev_bytes = img.size();
     hipError_t e = hipMalloc(&p->dev, p->dev_bytes);
     if (e != hipSuccess) {
@@ -206,6 +222,21 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     tn::fill_stats(hs, p->stats);
     if (hll) {
         p->gview = tn::schedule_view(hs, p->dev);
+        if (columns) {
+            const unsigned char *d = (const unsigned char *)p->dev;
+            p->columns = {hs.L,
+                          (uint32_t)(hs.pairs.size() / 2),
+                          (uint32_t)hs.gat_tgt.size(),
+                          (uint32_t)hs.gat_src.size(),
+                          p->gview.max_gat,
+                          p->gview.lvl_pair,
+                          p->gview.lvl_gat,
+                          (const uint32_t *)(d + src_off),
+                          p->gview.pairs,
+                          p->gview.gat_tgt,
+                          p->gview.gat_src,
+                          (const uint32_t *)(d + slot_off)};
+        }
         p->lvl_pair = std::move(hs.lvl_pair);
         p->lvl_gat = std::move(hs.lvl_gat);
     } else {
@@ -614,17 +645,21 @@ tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
     const uint32_t nwords = (1u << log2s) / 8;
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
-    // TN_HLL plans: one scratch row per gather of the widest level, then
-    // the saturation row G, the count of rows not yet G and 2^log2s uint32
-    // for the register maxima; others: per-workgroup sink words, then the
-    // compound scratch rows
+    // TN_HLL plans: the register columns where they fit in LDS (one launch),
+    // else one scratch row per gather of the widest level, then the saturation
+    // row G, the count of rows not yet G and 2^log2s uint32 for the register
+    // maxima; other plans: per-workgroup sink words, then the compound scratch
+    // rows
     const size_t gat_words = (size_t)std::max<uint32_t>(plan->gview.max_gat, 1) * nwords;
+    const bool columns = plan->hll && plan->columns.lvl_src &&
+                         tn::hll_columns_pay(n, plan->gview.max_gat, log2s);
     {
         const size_t words =
-            plan->hll ? gat_words + nwords + 1 + ((size_t)1 << log2s) / 2
-                      : (size_t)tn::rowmax_workgroups(nwords) * tn::kRoworSinkWords +
-                            (size_t)plan->scratch_rows *
-                                (size_t)tn::scratch_stride((uint32_t)nwords);
+            columns     ? tn::hll_columns_scratch(n, plan->gview.max_gat, log2s) / 8
+            : plan->hll ? gat_words + nwords + 1 + ((size_t)1 << log2s) / 2
+                        : (size_t)tn::rowmax_workgroups(nwords) * tn::kRoworSinkWords +
+                              (size_t)plan->scratch_rows *
+                                  (size_t)tn::scratch_stride((uint32_t)nwords);
         tn_status st = tn::ensure_scratch(ctx, sizeof(uint64_t) * words);
         if (st != TN_OK) return st;
     }
@@ -643,14 +678,19 @@ tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
     {
         tn::ProfScope ps(ctx, TN_K_AUX);
         e = tn::launch_fill_u32((uint32_t *)ctx->traffic, 4, 0u, ctx->stream);
-        if (e == hipSuccess) e = tn::launch_hll_init(n, log2s, node_hash, M, ctx->stream);
-        if (e == hipSuccess && sat)
+        if (e == hipSuccess && !columns)
+            e = tn::launch_hll_init(n, log2s, node_hash, M, ctx->stream);
+        if (e == hipSuccess && sat && !columns)
             e = tn::launch_hll_saturation_setup(n, log2s, node_hash, M, gmax, Grow, left,
                                                 ctx->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "HLL init launch");
     {
-        if (plan->hll) {
+        if (columns) {
+            tn::ProfScope ps(ctx, TN_K_ROWOR);
+            e = tn::launch_hll_columns(plan->columns, n, log2s, node_hash, sat, M,
+                                       (uint8_t *)ctx->scratch, ctx->stream);
+        } else if (plan->hll) {
             std::lock_guard<std::mutex> lk(plan->hll_mu);
             tn_status st = hll_graph(ctx, plan, nwords, M, Grow, left, sat);
             if (st != TN_OK) return st;

@@ -254,6 +254,257 @@ k_hll_gathers_write(uint64_t *__restrict__ M, uint32_t nwords, uint32_t G,
         hll_gather_write<LW>(M, nwords, lane, G, gat_tgt[g], scr + (size_t)g * nwords, Grow, left);
 }
 
+// The register stream of a TN_HLL plan on register columns: no merge ever
+// crosses from one register index to another, so a workgroup takes C
+// consecutive registers of every node (C bytes a row) and runs the whole
+// stream on them in LDS, a barrier per level instead of a launch.
+//
+// The waves specialise.  All but the last run the pairs, which come in
+// windows of one per thread, each window requested four windows before it is
+// used; within a window the threads of a level's pairs act, then the barrier
+// ends the level (a level that runs past its window goes on in the next one
+// without a barrier).  The last wave runs the gathers: a lane per source folds
+// it into its gather's slot by an LDS maximum, then a lane per target writes
+// it from its slot.  One wave's LDS accesses happen in order, so every source
+// of a level is read before a target is written, without a barrier (a level's
+// gathers touch other rows than its pairs).  The bounds of 64 levels sit in
+// the lanes of every wave.
+//
+// Saturation: a row holds at most g, the maximum over every node's own
+// registers, and one that holds g keeps it, so every 32 levels each thread
+// moves past the rows of its own that do, and the stream ends when all have.
+//
+// Bound by the latency of a level (LDS reads, writes, the barrier) and of the
+// windows: n = 10^5, m = 10^6, 256 registers (1724 levels, 579 pairs on
+// average) 1.25 ms, where one launch per level took 6.5 ms; of those 1.25 the
+// writes account for 0.37 and the windows' loads for 0.33.  Two or four pairs
+// a thread, or half the threads, are slower where levels are wide (1.25 to
+// 1.6 ms) and no faster where they are narrow.
+template <int C>
+struct ColT;
+template <>
+struct ColT<1> {
+    using T = uint8_t;
+};
+template <>
+struct ColT<4> {
+    using T = uint32_t;
+};
+
+template <int C>
+__device__ __forceinline__ uint32_t max_regs(uint32_t a, uint32_t b) {
+    if constexpr (C == 1) {
+        return max(a, b);
+    } else {  // as max_bytes7, on four bytes below 128
+        constexpr uint32_t H = 0x80808080u;
+        const uint32_t ge = ((a | H) - b) & H;
+        const uint32_t mask = (ge >> 7) * 0xFFu;
+        return (a & mask) | (b & ~mask);
+    }
+}
+
+// Waits for the wavefront's memory loads (vmcnt 0) here and now: a load that
+// only some levels make, were its wait left to its use, would have every
+// level wait there for the windows in flight.
+__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
+
+template <int C>
+__global__ void __launch_bounds__(1024)
+k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__ node_hash, bool sat,
+              uint32_t stride, uint8_t *__restrict__ out) {
+    using T = typename ColT<C>::T;
+    extern __shared__ __align__(16) uint8_t lds[];
+    T *col = (T *)lds;  // stride rows, and one for each idle lane
+    uint32_t *slot = (uint32_t *)(lds + (size_t)(stride + 64) * C);  // C of each gather
+    __shared__ uint32_t gmax[C];
+    __shared__ uint32_t open;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, threads = blockDim.x;
+    const uint32_t W = threads - 64;  // pairs of a window, one a thread
+    const uint32_t c0 = blockIdx.x * C;
+    if (tid < C) gmax[tid] = 0;
+    if (tid == 0) open = 0;
+    for (uint32_t i = tid; i < s.max_gat * C; i += threads) slot[i] = 0;
+    __syncthreads();
+    for (uint32_t u = tid; u < stride; u += threads) {
+        uint32_t v = 0;
+        if (u < n) {
+            const uint64_t x = node_hash[u];
+            const uint32_t j = (uint32_t)(x >> (64 - b)) - c0;
+            if (j < (uint32_t)C) {
+                const uint64_t tail = x & ((~0ull) >> b);
+                const uint32_t rho = tail ? (uint32_t)__clzll((long long)tail) - b + 1 : 64 - b + 1;
+                v = rho << (8 * j);
+                atomicMax(&gmax[j], rho);
+            }
+        }
+        col[u] = (T)v;
+    }
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(tid) >= W) {
+        // the gathers
+        uint32_t l0 = 0, eg, es, spos = 0, gpos = 0;
+        uint64_t some;  // which of the 64 levels have gathers
+        auto bounds = [&] {
+            const uint32_t l = min(l0 + lane, s.L);
+            eg = s.lvl_gat[min(l + 1, s.L)];
+            es = s.lvl_src[min(l + 1, s.L)];
+            some = __ballot(s.lvl_gat[l] != eg);
+        };
+        bounds();
+        uint32_t sbase = 0, send = 0, gbase = 0, gend = 0, sid = 0, sslot = 0, tgt = 0;
+        for (uint32_t l = 0; l < s.L;) {
+            l = __builtin_amdgcn_readfirstlane(l);
+            l0 = __builtin_amdgcn_readfirstlane(l0);
+            if ((some >> (l - l0)) & 1ull) {
+                const uint32_t sto = (uint32_t)__builtin_amdgcn_readlane((int)es, (int)(l - l0));
+                while (spos < sto) {
+                    if (spos >= send) {
+                        sbase = spos;
+                        send = spos + 64;
+                        const uint32_t i = min(sbase + lane, s.sources - 1);
+                        sid = s.gat_src[i];
+                        sslot = s.src_slot[i];
+                    }
+                    const uint32_t to = min(sto, send);
+                    if (sbase + lane >= spos && sbase + lane < to) {
+                        const uint32_t x = col[sid];
+#pragma unroll
+                        for (int k = 0; k < C; ++k)
+                            atomicMax(&slot[sslot * C + k], (x >> (8 * k)) & 0xffu);
+                    }
+                    spos = to;
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                const uint32_t gto = (uint32_t)__builtin_amdgcn_readlane((int)eg, (int)(l - l0));
+                const uint32_t g0 = gpos;
+                while (gpos < gto) {
+                    if (gpos >= gend) {
+                        gbase = gpos;
+                        gend = gpos + 64;
+                        tgt = s.gat_tgt[min(gbase + lane, s.gathers - 1)];
+                    }
+                    const uint32_t to = min(gto, gend);
+                    if (gbase + lane >= gpos && gbase + lane < to) {
+                        uint32_t *v = slot + (gbase + lane - g0) * C;
+                        uint32_t x = 0;
+#pragma unroll
+                        for (int k = 0; k < C; ++k) {
+                            x |= v[k] << (8 * k);
+                            v[k] = 0;
+                        }
+                        col[tgt] = (T)x;
+                    }
+                    gpos = to;
+                }
+            }
+            __syncthreads();
+            ++l;
+            if (sat && (l & 31u) == 1 && l > 1 && __builtin_amdgcn_readfirstlane(open) == 0) l = s.L;
+            if (l - l0 >= 64 && l < s.L) {
+                l0 = l;
+                bounds();
+            }
+        }
+    } else {
+        // the pairs
+        uint32_t l0 = 0, ep;
+        auto bounds = [&] {
+            ep = s.lvl_pair[min(l0 + lane + 1, s.L)];
+            wait_loads();
+        };
+        bounds();
+        // the load of a window is unconditional, so that the wait before its
+        // use counts the windows after it (past the last pair nothing is used)
+        const uint2 *pair = s.pairs ? s.pair : (const uint2 *)s.lvl_pair;
+        const uint32_t last = s.pairs ? s.pairs - 1 : 0u;
+        auto load = [&](uint32_t base) { return pair[min(base + tid, last)]; };
+        uint2 w0 = load(0), w1 = load(W), w2 = load(2 * W), w3 = load(3 * W);
+        const uint32_t first = __builtin_amdgcn_readfirstlane(tid);  // the wave's
+        const uint32_t idle = stride + lane;  // a row of its own for a lane without a pair
+        uint32_t g = 0;
+#pragma unroll
+        for (int k = 0; k < C; ++k) g |= gmax[k] << (8 * k);
+        uint32_t l = 0, pos = 0, full = tid;
+        // the levels' pairs in one window; true at the stream's end
+        auto window = [&](uint2 it, uint32_t base) -> bool {
+            const uint32_t v = it.y & kNodeMask, vw = it.y & kDirBit ? idle : v;
+            for (;;) {
+                // kept in scalar registers (every lane's are the same)
+                l = __builtin_amdgcn_readfirstlane(l);
+                l0 = __builtin_amdgcn_readfirstlane(l0);
+                pos = __builtin_amdgcn_readfirstlane(pos);
+                if (l >= s.L) return true;
+                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)ep, (int)(l - l0));
+                const uint32_t hi = min(end, base + W);
+                if (base + first < hi && base + first + 64 > pos) {  // the wave has some
+                    const bool in = base + tid - pos < hi - pos;
+                    const uint32_t r = max_regs<C>(col[in ? it.x : idle], col[in ? v : idle]);
+                    col[in ? it.x : idle] = (T)r;
+                    col[in ? vw : idle] = (T)r;
+                }
+                pos = hi;
+                if (end > base + W) return false;
+                __syncthreads();
+                ++l;
+                if (sat && l > 1 && (l & 31u) < 3u) {
+                    // after levels 32 k: look; 32 k + 1: all have; 32 k + 2: reset
+                    if ((l & 31u) == 0) {
+                        while (full < n && (uint32_t)col[full] == g) full += W;
+                        if (full < n) open = 1;
+                    } else if ((l & 31u) == 1) {
+                        if (__builtin_amdgcn_readfirstlane(open) == 0) l = s.L;
+                    } else if (tid == 0) {
+                        open = 0;
+                    }
+                }
+                if (l - l0 >= 64 && l < s.L) {
+                    l0 = l;
+                    bounds();
+                }
+            }
+        };
+        for (uint32_t base = 0;; base += 4 * W) {
+            if (window(w0, base)) break;
+            w0 = load(base + 4 * W);
+            if (window(w1, base + W)) break;
+            w1 = load(base + 5 * W);
+            if (window(w2, base + 2 * W)) break;
+            w2 = load(base + 6 * W);
+            if (window(w3, base + 3 * W)) break;
+            w3 = load(base + 7 * W);
+        }
+    }
+    __syncthreads();
+    if constexpr (C == 4) {
+        // straight into the register rows
+        uint32_t *M = (uint32_t *)out + blockIdx.x;
+        const size_t row = (size_t)gridDim.x;
+        for (uint32_t u = tid; u < n; u += threads) M[u * row] = col[u];
+    } else {
+        uint4 *o = (uint4 *)(out + (size_t)blockIdx.x * stride);
+        for (uint32_t i = tid; i < stride / 16; i += threads) o[i] = ((const uint4 *)lds)[i];
+    }
+}
+
+// M[u][c] = cols[c][u]: n rows of ncol bytes (a multiple of 16) from columns
+// `stride` bytes apart (a multiple of 16); tiles of 64 x 64 bytes in LDS.
+__global__ void __launch_bounds__(256)
+k_hll_rows(uint32_t n, uint32_t ncol, uint32_t stride, const uint8_t *__restrict__ cols,
+           uint8_t *__restrict__ M) {
+    __shared__ __align__(16) uint8_t tile[64][80];
+    const uint32_t u0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
+    const uint32_t a = threadIdx.x >> 2, q = (threadIdx.x & 3u) * 16;
+    if (c0 + a < ncol && u0 + q < stride) {
+        const uint4 v = *(const uint4 *)(cols + (size_t)(c0 + a) * stride + u0 + q);
+        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int k = 0; k < 16; ++k) tile[q + k][a] = (uint8_t)(w[k >> 2] >> (8 * (k & 3)));
+    }
+    __syncthreads();
+    if (u0 + a < n && c0 + q < ncol)
+        *(uint4 *)(M + (size_t)(u0 + a) * ncol + c0 + q) = *(const uint4 *)&tile[a][q];
+}
+
 // gmax[j] = the largest register j over every node's own registers.
 __global__ void __launch_bounds__(256)
 k_hll_gmax(uint32_t n, uint32_t b, const uint64_t *__restrict__ node_hash,
@@ -362,6 +613,76 @@ hipError_t launch_hll_saturation_setup(uint32_t n, uint32_t log2s, const uint64_
     if (cb > 16384u) cb = 16384u;
     hipLaunchKernelGGL(k_hll_count_left, dim3(cb), dim3(256), 0, st, n, nwords,
                        (const uint64_t *)M, Grow, left);
+    return hipGetLastError();
+}
+
+namespace {
+constexpr size_t kColLds = 160 * 1024 - 64;  // LDS of a workgroup, the statics aside
+size_t column_lds(uint32_t n, uint32_t max_gat, int C) {
+    return ((size_t)((n + 15u) & ~15u) + 64) * C + (size_t)max_gat * C * 4;
+}
+int column_bytes(uint32_t n, uint32_t max_gat) {
+    return column_lds(n, max_gat, 4) <= kColLds ? 4 : column_lds(n, max_gat, 1) <= kColLds ? 1 : 0;
+}
+}  // namespace
+
+bool hll_columns_fit(uint32_t n, uint32_t max_gat) { return column_bytes(n, max_gat) > 0; }
+
+// Threads of a workgroup, and how many rounds of resident workgroups the
+// columns take: the most threads (wide levels) that need no more rounds than
+// fewer would (small networks with many registers leave room for several
+// workgroups on a CU).
+static void column_launch(uint32_t n, uint32_t max_gat, uint32_t log2s, uint32_t &threads,
+                          uint32_t &rounds) {
+    const int C = column_bytes(n, max_gat);
+    const uint32_t groups = (1u << log2s) / C;
+    threads = 0;
+    for (uint32_t t = 1024; t >= 256; t /= 2) {
+        const uint32_t resident =
+            256 * (uint32_t)std::min<size_t>(kColLds / column_lds(n, max_gat, C), 2048 / t);
+        const uint32_t r = (groups + resident - 1) / resident;
+        if (threads == 0 || r < rounds) {
+            rounds = r;
+            threads = t;
+        }
+    }
+}
+
+// Every round runs the whole stream again, while a launch per level takes
+// longer rows at once: at n = 10^5, m = 10^6 1, 4 and 8 rounds (2^8, 2^10 and
+// 2^11 registers) took 1.37, 5.1 and 10.2 ms against 6.7, 7.7 and 9.4 ms; at
+// n = 3*10^4 (four registers a workgroup) 4 rounds (2^12) 4.0 against 11.4 ms.
+bool hll_columns_pay(uint32_t n, uint32_t max_gat, uint32_t log2s) {
+    if (!hll_columns_fit(n, max_gat)) return false;
+    uint32_t threads, rounds;
+    column_launch(n, max_gat, log2s, threads, rounds);
+    return rounds <= 4;
+}
+
+size_t hll_columns_scratch(uint32_t n, uint32_t max_gat, uint32_t log2s) {
+    return column_bytes(n, max_gat) == 1 ? (size_t)((n + 15u) & ~15u) << log2s : 0;
+}
+
+hipError_t launch_hll_columns(const HllColumns &s, uint32_t n, uint32_t log2s,
+                              const uint64_t *node_hash, bool sat, uint8_t *M, uint8_t *scratch,
+                              hipStream_t st) {
+    const int C = column_bytes(n, s.max_gat);
+    if (C == 0) return hipErrorInvalidValue;
+    const uint32_t ncol = 1u << log2s, stride = (n + 15u) & ~15u;
+    const size_t lds = column_lds(n, s.max_gat, C);
+    auto k = C == 4 ? k_hll_columns<4> : k_hll_columns<1>;
+    hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
+                                       (int)lds);
+    if (e != hipSuccess) return e;
+    uint32_t threads, rounds;
+    column_launch(n, s.max_gat, log2s, threads, rounds);
+    const uint32_t groups = ncol / C;
+    hipLaunchKernelGGL(k, dim3(groups), dim3(threads), lds, st, s, n, log2s, node_hash, sat,
+                       stride, C == 4 ? M : scratch);
+    e = hipGetLastError();
+    if (e != hipSuccess || C == 4) return e;
+    hipLaunchKernelGGL(k_hll_rows, dim3((n + 63) / 64, (ncol + 63) / 64), dim3(256), 0, st, n, ncol,
+                       stride, scratch, M);
     return hipGetLastError();
 }
 

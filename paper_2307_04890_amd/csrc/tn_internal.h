@@ -95,6 +95,16 @@ struct DevSchedule {
     const uint32_t *gat_src;
 };
 
+// The time-step schedule as k_hll_columns reads it: DevSchedule's arrays, the
+// ends of each level's gather sources, and of each source the index of its
+// gather within the level.
+struct HllColumns {
+    uint32_t L, pairs, gathers, sources, max_gat;
+    const uint32_t *lvl_pair, *lvl_gat, *lvl_src;
+    const uint2 *pair;
+    const uint32_t *gat_tgt, *gat_src, *src_slot;
+};
+
 // Device view of a binary-op schedule: level l owns ops [lvl[l], lvl[l+1]).
 struct DevOps {
     uint32_t L;
@@ -205,6 +215,7 @@ struct tn_plan {
     // the device, its level boundaries on the host, instead of the ops
     bool hll = false;
     tn::DevSchedule gview{};
+    tn::HllColumns columns{};  // for networks whose register columns fit in LDS
     std::vector<uint32_t> lvl_pair, lvl_gat;
     // ... and their level launches captured in a HIP graph, for the register
     // rows, scratch and row width they were captured with (replaced when one
@@ -399,6 +410,17 @@ hipError_t launch_hll_levels(const DevSchedule &s, const uint32_t *lvl_pair,
 hipError_t launch_hll_saturation_setup(uint32_t n, uint32_t log2s, const uint64_t *node_hash,
                                        const uint8_t *M, unsigned int *gmax, uint64_t *Grow,
                                        unsigned int *left, hipStream_t st);
+// The register stream of a TN_HLL plan in one launch, each workgroup's
+// registers of every node in LDS (and one that brings them into rows): from
+// the node hashes to M, with `sat` ending where every row is saturated.
+// hll_columns_fit: whether n rows (and the widest level's gathers) fit;
+// hll_columns_pay: whether this beats a launch per level.
+bool hll_columns_fit(uint32_t n, uint32_t max_gat);
+bool hll_columns_pay(uint32_t n, uint32_t max_gat, uint32_t log2s);
+size_t hll_columns_scratch(uint32_t n, uint32_t max_gat, uint32_t log2s);
+hipError_t launch_hll_columns(const HllColumns &s, uint32_t n, uint32_t log2s,
+                              const uint64_t *node_hash, bool sat, uint8_t *M, uint8_t *scratch,
+                              hipStream_t st);
 // Levels per captured graph of a TN_HLL plan; between graphs the host reads
 // *left and stops once it is 0.
 constexpr uint32_t kHllSegmentLevels = 256;

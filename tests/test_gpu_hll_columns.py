@@ -1,0 +1,68 @@
+"""The two register streams of a TN_HLL plan (register columns in LDS, one
+launch per level) against the row-OR kernel's register stream of an ops plan,
+on networks at the bounds of the columns: one and four registers a workgroup,
+several workgroups a CU, several rounds, levels wider than a window, levels
+of gathers only, saturation inside a run of levels."""
+import numpy as np
+import pytest
+
+import tn_inputs as T
+
+pytestmark = pytest.mark.gpu
+torch = pytest.importorskip("torch")
+
+import paper_2307_04890_amd as tn  # noqa: E402
+
+
+def _both(n, ev, b, flags, saturation=True):
+    h = T.hll_node_hashes(n, seed=n + b)
+    ctx = tn.get_context()
+    ref = tn.Plan(n, *ev, flags)
+    want, we = ref.hll(h, b)
+    p = tn.Plan(n, *ev, flags | tn.HLL)
+    try:
+        ctx.saturation(saturation)
+        for _ in range(2):  # a second pass starts from the hashes again
+            M, est = p.hll(h, b)
+            assert torch.equal(M, want)
+            assert torch.equal(est, we)
+    finally:
+        ctx.saturation(True)
+        ref.close()
+        p.close()
+
+
+# 40,000 nodes: the last sizes with four registers a workgroup are below,
+# 160,000 the last with one; a launch per level past four rounds of
+# workgroups (2^11 registers at one a workgroup) and past 163,000 nodes
+@pytest.mark.parametrize("n,b", [(37, 4), (1000, 12), (5000, 8), (30_000, 12), (40_650, 5), (41_000, 5),
+                                 (50_000, 10), (50_000, 11), (163_000, 4), (170_000, 4)])
+@pytest.mark.parametrize("flags", [0, tn.DIRECTED | tn.FORWARD])
+def test_columns_and_levels_match_the_ops_stream(n, b, flags):
+    _both(n, T.activity_driven(n, 4 * n, max(1, n // 3), seed=n), b, flags)
+
+
+@pytest.mark.parametrize("saturation", [True, False])
+@pytest.mark.parametrize("n,m,steps", [(300, 30_000, 15_000), (2000, 60_000, 30_000), (44_000, 1_500_000, 200_000)])
+def test_streams_that_saturate(n, m, steps, saturation):
+    _both(n, T.uniform_pairs(n, m, steps, seed=m), 6, 0, saturation)
+
+
+@pytest.mark.parametrize("flags", [0, tn.FORWARD, tn.TIES_SEQUENTIAL])
+def test_levels_of_gathers(flags):
+    # stars: levels with many gathers and sources, some with no pair
+    for n, steps, k in [(200, 500, 30), (5000, 300, 200), (45_000, 100, 1500)]:
+        _both(n, T.star_steps(n, steps, k, seed=n), 5, flags)
+    # one time step of everything: levels wider than a window
+    _both(3000, T.uniform_pairs(3000, 9000, 1, seed=3), 7, flags)
+    _both(60_000, T.uniform_pairs(60_000, 30_000, 1, seed=4), 4, flags)
+
+
+def test_networks_without_pairs():
+    _both(100, (np.zeros(0, np.uint32), np.zeros(0, np.uint32), np.zeros(0, np.int64)), 5, 0)
+    # every step a path of three nodes: gathers only
+    t = np.repeat(np.arange(50, dtype=np.int64), 2)
+    mid = np.arange(50, dtype=np.uint32) * 3 + 1
+    src = np.stack([mid - 1, mid], 1).ravel()
+    dst = np.stack([mid, mid + 1], 1).ravel()
+    _both(151, (src, dst, t), 6, 0)
