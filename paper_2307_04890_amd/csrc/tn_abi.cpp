@@ -681,7 +681,7 @@ tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
         if (e == hipSuccess && !columns)
             e = tn::launch_hll_init(n, log2s, node_hash, M, ctx->stream);
         if (e == hipSuccess && sat && !columns)
-            e = tn::launch_hll_saturation_setup(n, log2s, node_hash, M, gmax, Grow, left,
+            e = tn::launch_hll_saturation_setup(n, log2s, node_hash, gmax, Grow, left,
                                                 ctx->stream);
     }
     if (e != hipSuccess) return hip_fail(e, "HLL init launch");

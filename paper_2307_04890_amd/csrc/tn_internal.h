@@ -408,8 +408,8 @@ hipError_t launch_hll_levels(const DevSchedule &s, const uint32_t *lvl_pair,
                              uint64_t *M, uint64_t *scratch, const uint64_t *Grow,
                              unsigned int *left, hipStream_t st);
 hipError_t launch_hll_saturation_setup(uint32_t n, uint32_t log2s, const uint64_t *node_hash,
-                                       const uint8_t *M, unsigned int *gmax, uint64_t *Grow,
-                                       unsigned int *left, hipStream_t st);
+                                       unsigned int *gmax, uint64_t *Grow, unsigned int *left,
+                                       hipStream_t st);
 // The register stream of a TN_HLL plan in one launch, each workgroup's
 // registers of every node in LDS (and one that brings them into rows): from
 // the node hashes to M, with `sat` ending where every row is saturated.

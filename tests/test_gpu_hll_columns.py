@@ -66,3 +66,20 @@ def test_networks_without_pairs():
     src = np.stack([mid - 1, mid], 1).ravel()
     dst = np.stack([mid, mid + 1], 1).ravel()
     _both(151, (src, dst, t), 6, 0)
+
+
+@pytest.mark.parametrize("n,b", [(1, 11), (2, 16), (200, 14), (170_000, 4)])
+def test_rows_that_start_saturated(n, b):
+    # a launch per level counts the rows not yet saturated: with one register
+    # between all nodes some are from the start
+    ev = T.activity_driven(max(n, 2), 5 * n, n, seed=n) if n > 2 else (
+        np.zeros(1, np.uint32), np.full(1, n - 1, np.uint32), np.zeros(1, np.int64))
+    top = np.uint64(3) << np.uint64(64 - b)
+    h = (T.hll_node_hashes(n, seed=b) >> np.uint64(b)) | top  # every node in register 3
+    for hashes in (h, np.full(n, h[0])):
+        ref, p = tn.Plan(n, *ev), tn.Plan(n, *ev, tn.HLL)
+        want, we = ref.hll(hashes, b)
+        M, est = p.hll(hashes, b)
+        assert torch.equal(M, want) and torch.equal(est, we)
+        ref.close()
+        p.close()
