@@ -194,15 +194,6 @@ tn_status wave_image_pack(const std::vector<HostSchedule> &hs, uint32_t K, WaveI
     return TN_OK;
 }
 
-// Device side of the upload: one buffer, grown as needed, kept across chunks.
-struct WaveBuf {
-    void *dev = nullptr;
-    size_t cap = 0;
-    ~WaveBuf() {
-        if (dev) (void)hipFree(dev);
-    }
-};
-
 // One chunk of small proxies: uploads the packed image, runs the H op
 // schedules on one wavefront per word column of each proxy (slice state per
 // column in state, col_words per proxy), reads the done count into
@@ -210,7 +201,7 @@ struct WaveBuf {
 tn_status run_wave_chunk(tn_ctx *ctx, const std::vector<HostSchedule> &hs, WaveImage &img,
                          uint32_t K, const std::vector<uint64_t *> &Cs, int64_t ldK,
                          uint32_t *state, size_t col_words, unsigned int *done_dev,
-                         unsigned int *done_host, int64_t &levels, WaveBuf &buf) {
+                         unsigned int *done_host, int64_t &levels, StreamSlot &buf) {
     const uint32_t H = (uint32_t)hs.size();
     uint32_t max_scr = 0;
     int64_t ops = 0, lv = 0;
@@ -221,18 +212,18 @@ tn_status run_wave_chunk(tn_ctx *ctx, const std::vector<HostSchedule> &hs, WaveI
     }
     levels += lv;
     hipError_t e = hipSuccess;
-    if (img.bytes > buf.cap) {
+    if (img.bytes > buf.dev_bytes) {
         // the previous chunk's copy and launch are complete (it was waited for)
-        const size_t cap = std::max(img.bytes, buf.cap + buf.cap / 2);
+        const size_t cap = std::max(img.bytes, buf.dev_bytes + buf.dev_bytes / 2);
         if (buf.dev) (void)hipFree(buf.dev);
         buf.dev = nullptr;
-        buf.cap = 0;
+        buf.dev_bytes = 0;
         e = hipMalloc(&buf.dev, cap);
         if (e != hipSuccess) {
             buf.dev = nullptr;
             return fail(TN_E_NOMEM, "proxy schedule allocation failed");
         }
-        buf.cap = cap;
+        buf.dev_bytes = cap;
     }
     unsigned char *dev = (unsigned char *)buf.dev;
     for (uint32_t j = 0; j < H; ++j) {
@@ -351,15 +342,22 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
     std::vector<uint32_t> lw;
     std::vector<uint32_t *> pst(H, nullptr);
     uint32_t *state = nullptr;
-    WaveBuf wbuf;
+    StreamBuffers *buf = nullptr;
     unsigned int *done_host = nullptr;
     unsigned int *done_dev = nullptr;
     uint64_t tiles = 0;
     int64_t launched = 0, run_events = 0, levels = 0;
     bool all_done = false;
-    e = hipHostMalloc((void **)&done_host, sizeof(unsigned int), 0);
-    if (e != hipSuccess) return hip_fail(e, "pinned counter");
-    *done_host = 0;
+    // the slice state's room (wavefront columns; tiles make their own) and the
+    // done counter
+    st = stream_buffers_take(ctx, wave ? (size_t)H * kw * wave_col + 1 : 0, &buf);
+    if (st != TN_OK) return st;
+    done_host = buf->ring[0].done_host;
+    e = hipEventRecord(buf->init_ev, ctx->stream);
+    if (e != hipSuccess) {
+        stream_buffers_give(ctx, buf);
+        return hip_fail(e, "stream set-up");
+    }
     // Chunk 0 is planned here on every host thread: its latency comes first,
     // and proxies of few super-nodes often saturate within it.  Only if they
     // do not, later chunks are planned by background threads, one proxy of
@@ -384,7 +382,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
     std::mutex mu;
     std::condition_variable cv;
     std::atomic<size_t> next{H};  // background tasks: proxy j of chunk c is task c * H + j
-    bool stop = false;    // under mu: no more chunks are wanted
+    std::atomic<bool> stop{false};  // set under mu: no more chunks are wanted
     size_t consumed = 0;  // under mu: chunks launched
     bool pin_images = false;  // set below, before the first chunk is planned
     auto plan_chunk = [&](size_t c, unsigned threads) {
@@ -429,7 +427,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
         std::string err;
         const tn_status ps = plan_events(K, mc, src ? src + a : nullptr, dst ? dst + a : nullptr,
                                          t ? t + a : nullptr, flags, h, err, maps[j], n,
-                                         wave ? kFormOps : kFormGather);
+                                         wave ? kFormOps : kFormGather, &stop);
         bool last;
         {
             std::lock_guard<std::mutex> lk(mu);
@@ -440,7 +438,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
             }
             last = --plans[c].left == 0;
         }
-        if (!last) return;
+        if (!last || stop) return;
         // every other task of chunk c has finished: its schedules are ours
         WaveImage img;
         tn_status ws = TN_OK;
@@ -504,12 +502,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
                 // per-column slice state of every proxy, the done counter;
                 // the proxies start as the identity
                 const size_t words = (size_t)H * kw * wave_col;
-                e = hipMalloc((void **)&state, sizeof(uint32_t) * (words + 1));
-                if (e != hipSuccess) {
-                    state = nullptr;
-                    st = fail(TN_E_NOMEM, "slice state allocation failed");
-                    break;
-                }
+                state = buf->persist;
                 done_dev = state + words;
                 tiles = (uint64_t)H * kw;
                 e = launch_fill_u32(state, words + 1, 0u, ctx->stream);
@@ -521,7 +514,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
                 }
             }
             st = run_wave_chunk(ctx, plans[c].hs, plans[c].img, K, Cs, ldK, state, wave_col * kw,
-                                done_dev, done_host, levels, wbuf);
+                                done_dev, done_host, levels, buf->ring[0]);
             plans[c].hs.clear();
             if (st != TN_OK) break;
             ++launched;
@@ -606,8 +599,8 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
     cv.notify_all();
     for (auto &th : pool) th.join();
     (void)hipStreamSynchronize(ctx->stream);
-    if (state) (void)hipFree(state);
-    (void)hipHostFree(done_host);
+    if (state && !wave) (void)hipFree(state);
+    stream_buffers_give(ctx, buf);
     if (stats) {
         stats->chunks = (int64_t)bounds.size();
         stats->chunks_run = launched;

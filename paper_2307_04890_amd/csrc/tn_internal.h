@@ -3,6 +3,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <mutex>
 #include <string>
@@ -119,11 +120,13 @@ struct DevOps {
 // nodes of a hashed network.
 // `forms` selects the gather form (pairs + gathers, for the batched kernel),
 // the binary-op form (for the global kernel), or both.
+// `stop` (nullable): planning is given up once it is set, and `out` is then
+// not to be used.
 tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
                       const uint32_t *dst, const int64_t *t, uint32_t flags,
                       HostSchedule &out, std::string &err,
                       const uint32_t *map = nullptr, uint32_t n_src = 0,
-                      int forms = kFormGather);
+                      int forms = kFormGather, const std::atomic<bool> *stop = nullptr);
 
 // Size in bytes of the device image of a schedule and its packing.
 size_t schedule_device_bytes(const HostSchedule &s);
@@ -152,6 +155,32 @@ struct DeviceGuard {
     }
 };
 
+// Buffers of one stream of chunks (tn_stream.cpp, tn_hash.cpp): a ring of
+// launch slots (schedule buffer, pinned staging copy, done-counter snapshot,
+// and the event that marks the slot's last launch complete) and the slices'
+// saturation state.  A context keeps one set between calls, since pinning
+// and device allocations cost a call several milliseconds: a stream takes it
+// (or makes one of its own while another holds it) and gives it back once its
+// launches are complete.
+struct StreamSlot {
+    void *dev = nullptr;
+    size_t dev_bytes = 0;
+    void *pinned = nullptr;
+    size_t pinned_bytes = 0;
+    unsigned int *done_host = nullptr;
+    hipEvent_t ev = nullptr;
+    bool used = false;
+};
+struct StreamBuffers {
+    static constexpr int kRing = 4;
+    // what a context keeps at most; a larger set is freed
+    static constexpr size_t kKeepDevice = (size_t)256 << 20, kKeepPinned = (size_t)64 << 20;
+    StreamSlot ring[kRing];
+    hipEvent_t init_ev = nullptr;  // the last stream's set-up
+    uint32_t *persist = nullptr;
+    size_t persist_words = 0;
+};
+
 }  // namespace tn
 
 struct tn_ctx {
@@ -178,6 +207,7 @@ struct tn_ctx {
     hipEvent_t ring_ev[kRingSlots] = {};
     bool ring_busy[kRingSlots] = {};
     int ring_next = 0;
+    tn::StreamBuffers *stream_kept = nullptr;
     bool saturation = true;
     int num_cus = 0;
     // kernel timing (tn_profile_enable)
@@ -426,6 +456,12 @@ hipError_t launch_hll_columns(const HllColumns &s, uint32_t n, uint32_t log2s,
 constexpr uint32_t kHllSegmentLevels = 256;
 hipError_t launch_hll_estimate(uint32_t n, uint32_t log2s, const uint8_t *M, double *est,
                                hipStream_t st);
+// Stream buffers with room for persist_words of slice state, every slot free
+// and its done count 0, or an error; given back (kept, or freed) once the
+// context's stream and every slot's last launch are complete.
+tn_status stream_buffers_take(tn_ctx *ctx, size_t persist_words, StreamBuffers **out);
+void stream_buffers_give(tn_ctx *ctx, StreamBuffers *b);
+void stream_buffers_free(StreamBuffers *b);
 // streamed one-shot build (tn_stream.cpp)
 tn_status build_streamed(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src,
                          const uint32_t *dst, const int64_t *t, uint32_t flags, uint64_t *C,

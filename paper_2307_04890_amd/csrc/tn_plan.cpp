@@ -407,7 +407,7 @@ void finish_ops(Planner &p, HostSchedule &out) {
 tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
                       const uint32_t *dst, const int64_t *t, uint32_t flags,
                       HostSchedule &out, std::string &err, const uint32_t *map,
-                      uint32_t n_src, int forms) {
+                      uint32_t n_src, int forms, const std::atomic<bool> *stop) {
     auto t0 = std::chrono::steady_clock::now();
     if (n == 0) { err = "n must be > 0"; return TN_E_ARG; }
     if (m < 0) { err = "m must be >= 0"; return TN_E_ARG; }
@@ -442,10 +442,19 @@ tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
     // first, and (u, v) brings u's row into v's, i.e. the reverse-time rule
     // applied to (v, u).
     const bool forward = flags & TN_FORWARD;
+    uint32_t steps = 0;
+    auto stopped = [&] {
+        return stop && (++steps & 255u) == 0 && stop->load(std::memory_order_relaxed);
+    };
+    bool given_up = false;
     auto walk = [&](Planner &pl) {
         if (forward) {
             int64_t a = 0;
             while (a < m) {
+                if (stopped()) {
+                    given_up = true;
+                    return;
+                }
                 int64_t b = a + 1;
                 if (!seq)
                     while (b < m && t[b] == t[a]) ++b;
@@ -456,6 +465,10 @@ tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
         }
         int64_t b = m;
         while (b > 0) {
+            if (stopped()) {
+                given_up = true;
+                return;
+            }
             int64_t a = b - 1;
             if (!seq)
                 while (a > 0 && t[a - 1] == t[b - 1]) --a;
@@ -468,6 +481,7 @@ tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
         po.ops.reserve((size_t)m + (size_t)m / 4);
         po.olev.reserve((size_t)m + (size_t)m / 4);
         walk(po);
+        if (given_up) return TN_OK;
         finish_ops(po, out);
         out.op_pairs = po.n_pairs;
         out.op_directed = po.n_dir;
@@ -490,6 +504,7 @@ tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
     p.pv.reserve((size_t)m);
     p.plev.reserve((size_t)m);
     walk(p);
+    if (given_up) return TN_OK;
     // counting sort by level
     const uint32_t L = p.L;
     out.L = L;

@@ -46,21 +46,6 @@ struct Chunk {
     bool ready = false;
 };
 
-// One device slot of the launch ring: a schedule buffer, its pinned staging
-// copy, the done-counter snapshot taken after the launch that used it, and
-// the event that marks that launch complete.
-struct Slot {
-    void *dev = nullptr;
-    size_t dev_bytes = 0;
-    void *pinned = nullptr;
-    size_t pinned_bytes = 0;
-    unsigned int *done_host = nullptr;
-    hipEvent_t ev = nullptr;
-    bool used = false;
-};
-
-constexpr int kRing = 4;
-
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
@@ -71,9 +56,9 @@ struct StreamState {
     uint64_t *C = nullptr;
     int64_t ld = 0;
     uint32_t sw = 0, slices = 0;
-    uint32_t *persist = nullptr;  // per-slice state, then the done counter
+    StreamBuffers *buf = nullptr;
+    uint32_t *persist = nullptr;  // buf's: per-slice state, then the done counter
     unsigned int *done_count = nullptr;
-    Slot ring[kRing];
     int64_t launches = 0;  // launches so far (ring position)
     // zero phase: while every launch so far ran all its levels in it, the
     // persisted non-zero-row bits are exact and the next chunk may go on
@@ -157,18 +142,80 @@ void default_chunks(int64_t m, int64_t &chunk, int64_t &first, int shrink) {
     }
 }
 
-namespace {
-
-void state_release(tn_ctx *ctx, StreamState &s) {
-    (void)hipStreamSynchronize(ctx->stream);
-    for (Slot &r : s.ring) {
+void stream_buffers_free(StreamBuffers *b) {
+    if (!b) return;
+    for (StreamSlot &r : b->ring) {
         if (r.dev) (void)hipFree(r.dev);
         if (r.pinned) (void)hipHostFree(r.pinned);
         if (r.done_host) (void)hipHostFree(r.done_host);
         if (r.ev) (void)hipEventDestroy(r.ev);
-        r = Slot();
     }
-    if (s.persist) (void)hipFree(s.persist);
+    if (b->init_ev) (void)hipEventDestroy(b->init_ev);
+    if (b->persist) (void)hipFree(b->persist);
+    delete b;
+}
+
+tn_status stream_buffers_take(tn_ctx *ctx, size_t persist_words, StreamBuffers **out) {
+    StreamBuffers *b = ctx->stream_kept;
+    ctx->stream_kept = nullptr;
+    *out = nullptr;
+    hipError_t e = hipSuccess;
+    if (!b) {
+        b = new (std::nothrow) StreamBuffers();
+        if (!b) return fail(TN_E_NOMEM, "stream buffers allocation failed");
+        e = hipEventCreateWithFlags(&b->init_ev, hipEventDisableTiming);
+        for (StreamSlot &r : b->ring) {
+            if (e == hipSuccess) e = hipEventCreateWithFlags(&r.ev, hipEventDisableTiming);
+            if (e == hipSuccess) e = hipHostMalloc((void **)&r.done_host, sizeof(unsigned int), 0);
+        }
+        if (e != hipSuccess) {
+            stream_buffers_free(b);
+            return hip_fail(e, "launch ring set-up");
+        }
+    }
+    if (persist_words > b->persist_words) {
+        if (b->persist) (void)hipFree(b->persist);
+        b->persist = nullptr;
+        b->persist_words = 0;
+        e = hipMalloc((void **)&b->persist, sizeof(uint32_t) * persist_words);
+        if (e != hipSuccess) {
+            b->persist = nullptr;
+            stream_buffers_free(b);
+            return fail(TN_E_NOMEM, "slice state allocation failed");
+        }
+        b->persist_words = persist_words;
+    }
+    for (StreamSlot &r : b->ring) {
+        r.used = false;
+        *r.done_host = 0;
+    }
+    *out = b;
+    return TN_OK;
+}
+
+void stream_buffers_give(tn_ctx *ctx, StreamBuffers *b) {
+    if (!b) return;
+    // every launch that used them, on whatever stream it was enqueued
+    hipError_t e = hipStreamSynchronize(ctx->stream);
+    if (e == hipSuccess) e = hipEventSynchronize(b->init_ev);
+    size_t dev = sizeof(uint32_t) * b->persist_words, pinned = 0;
+    for (StreamSlot &r : b->ring) {
+        if (e == hipSuccess && r.used) e = hipEventSynchronize(r.ev);
+        dev += r.dev_bytes;
+        pinned += r.pinned_bytes;
+    }
+    if (e != hipSuccess || ctx->stream_kept || dev > StreamBuffers::kKeepDevice ||
+        pinned > StreamBuffers::kKeepPinned)
+        stream_buffers_free(b);
+    else
+        ctx->stream_kept = b;
+}
+
+namespace {
+
+void state_release(tn_ctx *ctx, StreamState &s) {
+    stream_buffers_give(ctx, s.buf);
+    s.buf = nullptr;
     s.persist = nullptr;
 }
 
@@ -190,26 +237,16 @@ tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, ui
         }
     }
     const size_t pwords = rowor_persist_words(n, s.sw);
-    e = hipMalloc((void **)&s.persist, sizeof(uint32_t) * (pwords + 1));
-    if (e != hipSuccess) {
-        s.persist = nullptr;
-        return fail(TN_E_NOMEM, "slice state allocation failed");
-    }
+    const tn_status st = stream_buffers_take(ctx, pwords + 1, &s.buf);
+    if (st != TN_OK) return st;
+    s.persist = s.buf->persist;
     s.done_count = s.persist + pwords;
-    for (Slot &r : s.ring) {
-        e = hipEventCreateWithFlags(&r.ev, hipEventDisableTiming);
-        if (e == hipSuccess) e = hipHostMalloc((void **)&r.done_host, sizeof(unsigned int), 0);
-        if (e != hipSuccess) {
-            state_release(ctx, s);
-            return hip_fail(e, "launch ring set-up");
-        }
-        *r.done_host = 0;
-    }
     e = launch_fill_u32(s.persist, pwords + 1, 0u, ctx->stream);
     if (e == hipSuccess) {
         ProfScope ps(ctx, TN_K_IDENTITY);
         e = launch_identity(C, n, ld, ctx->traffic, ctx->stream);
     }
+    if (e == hipSuccess) e = hipEventRecord(s.buf->init_ev, ctx->stream);
     if (e != hipSuccess) {
         state_release(ctx, s);
         return hip_fail(e, "identity kernel launch");
@@ -253,7 +290,7 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
     std::vector<void *> old_dev, old_pinned;
     // a completed launch may already report every slice full
     auto poll = [&]() {
-        for (Slot &r : s.ring)
+        for (StreamSlot &r : s.buf->ring)
             if (r.used && hipEventQuery(r.ev) == hipSuccess && *r.done_host == s.slices)
                 s.all_done = true;
     };
@@ -279,8 +316,8 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
             Chunk &ch = *chunks[c];
             if (!stop.load()) {
                 ch.st = plan_events(s.n, ch.b - ch.a, src + ch.a, dst + ch.a, t + ch.a, s.flags,
-                                    ch.hs, ch.err, nullptr, 0, kFormOps);
-                if (ch.st == TN_OK) {
+                                    ch.hs, ch.err, nullptr, 0, kFormOps, &stop);
+                if (ch.st == TN_OK && !stop.load()) {
                     // a chunk of short levels on the wavefront kernel takes
                     // the flat form (no level starts in the kernel's loop)
                     const int64_t nops = (int64_t)ch.hs.ops.size() / 4;
@@ -321,7 +358,7 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
         }
         poll();
         if (s.all_done) break;
-        Slot &r = s.ring[s.launches % kRing];
+        StreamSlot &r = s.buf->ring[s.launches % StreamBuffers::kRing];
         if (r.used) {
             e = hipEventSynchronize(r.ev);
             if (e != hipSuccess) {
@@ -497,7 +534,7 @@ tn_status build_streamed(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     }
     if (st == TN_OK && stats) {
         // launches that completed after the last poll may have saturated it
-        for (const Slot &r : s.ring)
+        for (const StreamSlot &r : s.buf->ring)
             if (r.used && *r.done_host == s.slices) stats->saturated = 1;
         stats->seconds =
             std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
