@@ -184,8 +184,7 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     else tn::ops_pack(hs, img);
     // a small network with short levels also keeps its ops in the flat form
     const int64_t nops = (int64_t)(hs.ops.size() / 4);
-    const bool flat = !hll && tn::rowor_wave_pays(n, hs.scratch_rows, nops, hs.Lops) &&
-                      !tn::rowor_wave_wide(nops, hs.Lops);
+    const bool flat = !hll && tn::rowor_wave_pays(n, hs.scratch_rows, nops, hs.Lops);
     const size_t flat_off = (img.size() + 255) & ~(size_t)255;
     if (flat) {
         img.resize(flat_off + tn::flat_ops_bytes(hs), 0);
@@ -420,6 +419,18 @@ tn_status plan_fwd(tn_ctx *ctx, const tn_plan *plan, uint32_t l0, uint32_t l1, v
 }
 }  // namespace
 
+namespace {
+// The context's traffic counters, made on first use.
+tn_status ensure_traffic(tn_ctx *ctx) {
+    if (ctx->traffic) return TN_OK;
+    if (hipMalloc((void **)&ctx->traffic, 2 * sizeof(unsigned long long)) != hipSuccess) {
+        ctx->traffic = nullptr;
+        return fail(TN_E_NOMEM, "traffic counter allocation failed");
+    }
+    return TN_OK;
+}
+}  // namespace
+
 tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld,
                           uint32_t slice_words) {
     if (!ctx || !plan) return fail(TN_E_ARG, "ctx or plan is NULL");
@@ -429,16 +440,31 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
     if (ld < nwords) return fail(TN_E_ARG, "ld must be >= ceil(n/64)");
     if (plan->device != ctx->device) return fail(TN_E_ARG, "plan lives on another device");
     if (plan->hll) return fail(TN_E_ARG, "a TN_HLL plan runs only tn_hll_execute");
-    // a small network with the slice width left to the library runs on one
-    // wavefront per word column, its column in LDS
-    const bool wave = slice_words == 0 && tn::default_slice_words(n, ld) == 1 &&
-                      tn::rowor_wave_pays(n, plan->scratch_rows, plan->stats.ops,
-                                          plan->stats.op_levels);
+    // a network whose word columns fit in LDS, with the slice width left to
+    // the library, runs on one workgroup per column, or where levels are short
+    // on one wavefront
+    const bool column = slice_words == 0 &&
+                        tn::rowor_column_pays(n, plan->scratch_rows, plan->stats.ops,
+                                              plan->stats.op_levels, ctx->saturation);
+    const bool wave = slice_words == 0 && plan->flat;
     if (slice_words == 0) slice_words = tn::default_slice_words(n, ld);
     if (slice_words > 64 || (slice_words & (slice_words - 1)))
         return fail(TN_E_ARG, "slice_words must be a power of two <= 64");
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
+    if (column) {
+        ctx->state = nullptr;
+        ctx->state_sw = 0;
+        tn_status st = ensure_traffic(ctx);
+        if (st != TN_OK) return st;
+        // the identity is part of the launch
+        { tn::ProfScope ps(ctx, TN_K_IDENTITY); }
+        tn::ProfScope ps(ctx, TN_K_ROWOR);
+        hipError_t e = tn::launch_rowor_column(plan->view, n, C, ld, plan->scratch_rows,
+                                               ctx->traffic, ctx->saturation, true, nullptr, nullptr,
+                                               ctx->stream);
+        return e == hipSuccess ? TN_OK : hip_fail(e, "row-OR kernel launch");
+    }
     // per-workgroup sink words (for the widest grid of the launches below,
     // so that every launch finds the compound scratch rows at one place),
     // then those rows, then (for a zero phase) the slice state the launches
@@ -461,12 +487,9 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
     ctx->state = nullptr;
     ctx->state_sw = 0;
     hipError_t e;
-    if (!ctx->traffic) {
-        e = hipMalloc((void **)&ctx->traffic, 2 * sizeof(unsigned long long));
-        if (e != hipSuccess) {
-            ctx->traffic = nullptr;
-            return fail(TN_E_NOMEM, "traffic counter allocation failed");
-        }
+    {
+        tn_status st = ensure_traffic(ctx);
+        if (st != TN_OK) return st;
     }
     {
         tn::ProfScope ps(ctx, TN_K_IDENTITY);
@@ -527,13 +550,10 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
                 ctx->state = persist;
                 ctx->state_sw = tail_sw;
             }
-        } else if (wave && plan->flat)
+        } else if (wave)
             e = tn::launch_rowor_wave_flat1(plan->flat, plan->view.nops, n, C, ld,
                                             plan->scratch_rows, ctx->traffic, ctx->saturation,
                                             ctx->stream);
-        else if (wave)
-            e = tn::launch_rowor_wave(plan->view, n, C, ld, plan->scratch_rows, ctx->traffic,
-                                      ctx->saturation, nullptr, nullptr, ctx->stream);
         else {
             e = tn::launch_rowor_global(plan->view, n, C, ld, slice_words,
                                         (uint64_t *)ctx->scratch, sinks, plan->scratch_rows,
@@ -669,12 +689,9 @@ tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
     unsigned int *gmax = (unsigned int *)(Grow + nwords + 1);
     const bool sat = plan->hll && ctx->saturation;
     hipError_t e;
-    if (!ctx->traffic) {
-        e = hipMalloc((void **)&ctx->traffic, 2 * sizeof(unsigned long long));
-        if (e != hipSuccess) {
-            ctx->traffic = nullptr;
-            return fail(TN_E_NOMEM, "traffic counter allocation failed");
-        }
+    {
+        tn_status st = ensure_traffic(ctx);
+        if (st != TN_OK) return st;
     }
     {
         tn::ProfScope ps(ctx, TN_K_AUX);

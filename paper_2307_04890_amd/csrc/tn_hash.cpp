@@ -119,7 +119,7 @@ struct WaveImage {
     size_t cap = 0;
     size_t bytes = 0;
     bool pinned = false;
-    bool flat = false;  // the flat schedule format (k_rowor_wave_flat)
+    bool flat = false;  // the flat schedule format (k_rowor_wave_flat), else for k_rowor_columns
     std::vector<size_t> off;
     WaveImage() = default;
     WaveImage(const WaveImage &) = delete;
@@ -150,14 +150,16 @@ struct WaveImage {
 // rows as LDS byte offsets of a column of K real rows then the scratch rows,
 // and a level-end bit, so that the kernel needs no level starts.
 tn_status wave_image_pack(const std::vector<HostSchedule> &hs, uint32_t K, WaveImage &w,
-                          bool pinned) {
+                          bool pinned, bool saturation) {
     const uint32_t H = (uint32_t)hs.size();
     int64_t ops = 0, lv = 0;
+    uint32_t max_scr = 0;
     for (uint32_t j = 0; j < H; ++j) {
         ops += (int64_t)hs[j].ops.size() / 4;
         lv += hs[j].Lops;
+        max_scr = std::max(max_scr, hs[j].scratch_rows);
     }
-    w.flat = !rowor_wave_wide(ops, lv);
+    w.flat = !rowor_column_pays(K, max_scr, ops, lv, saturation);
     w.off.assign(H + 1, 0);
     for (uint32_t j = 0; j < H; ++j) {
         const size_t bytes = w.flat ? flat_ops_bytes(hs[j]) : ops_device_bytes(hs[j]);
@@ -242,13 +244,12 @@ tn_status run_wave_chunk(tn_ctx *ctx, const std::vector<HostSchedule> &hs, WaveI
     e = hipMemcpyAsync(dev, img.pin, img.bytes, hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess) {
         ProfScope ps(ctx, TN_K_BATCH);
-        if (img.flat)
+        if (!img.flat)
+            e = launch_rowor_columns((const WaveNet *)(dev + img.off[H]), H, K, max_scr,
+                                     ctx->saturation, done_dev, ctx->stream);
+        else
             e = launch_rowor_wave_flat((const WaveNet *)(dev + img.off[H]), H, K, max_scr,
                                        ctx->saturation, done_dev, nullptr, ctx->stream);
-        else
-            e = launch_rowor_wave_multi((const WaveNet *)(dev + img.off[H]), H, K, max_scr,
-                                        rowor_wave_wide(ops, lv), nullptr, ctx->saturation,
-                                        done_dev, ctx->stream);
     }
     if (e == hipSuccess)
         e = hipMemcpyAsync(done_host, done_dev, sizeof(unsigned int), hipMemcpyDeviceToHost,
@@ -406,7 +407,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
                 }
             }
             // chunk 0 is uploaded once and its latency comes first: never pinned
-            ws = wave_image_pack(hs, K, img, pin_images && c > 0);
+            ws = wave_image_pack(hs, K, img, pin_images && c > 0, ctx->saturation);
         }
         {
             std::lock_guard<std::mutex> lk(mu);
@@ -450,7 +451,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
                     spare.pop_back();
                 }
             }
-            ws = wave_image_pack(plans[c].hs, K, img, pin_images);
+            ws = wave_image_pack(plans[c].hs, K, img, pin_images, ctx->saturation);
         }
         {
             std::lock_guard<std::mutex> lk(mu);

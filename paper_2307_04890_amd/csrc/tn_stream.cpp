@@ -40,6 +40,7 @@ struct Chunk {
     int64_t a = 0, b = 0;  // events [a, b)
     HostSchedule hs;
     std::vector<unsigned char> image;
+    bool column = false;  // runs on one workgroup per word column
     bool flat = false;  // the flat form, then room for one WaveNet (k_rowor_wave_flat)
     std::string err;
     tn_status st = TN_OK;
@@ -226,7 +227,9 @@ tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, ui
     s.flags = flags;
     s.C = C;
     s.ld = ld;
-    s.sw = default_slice_words(n, ld);
+    // one-word slices where chunks may run on whole word columns in LDS
+    s.sw = ctx->saturation && rowor_column_fits(n, kOpsScratchRows) ? 1u
+                                                                    : default_slice_words(n, ld);
     s.slices = rowor_workgroups(n, s.sw);
     hipError_t e;
     if (!ctx->traffic) {
@@ -321,9 +324,11 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
                     // a chunk of short levels on the wavefront kernel takes
                     // the flat form (no level starts in the kernel's loop)
                     const int64_t nops = (int64_t)ch.hs.ops.size() / 4;
-                    ch.flat = s.sw == 1 && rowor_wave_pays(s.n, ch.hs.scratch_rows, nops,
-                                                           ch.hs.Lops) &&
-                              !rowor_wave_wide(nops, ch.hs.Lops);
+                    ch.column = s.sw == 1 &&
+                                rowor_column_pays(s.n, ch.hs.scratch_rows, nops, ch.hs.Lops,
+                                                  ctx->saturation);
+                    ch.flat = s.sw == 1 &&
+                              rowor_wave_pays(s.n, ch.hs.scratch_rows, nops, ch.hs.Lops);
                     if (ch.flat) {
                         ch.image.assign(align256(flat_ops_bytes(ch.hs)) + sizeof(WaveNet), 0);
                         flat_ops_pack(ch.hs, s.n, reinterpret_cast<uint32_t *>(ch.image.data()));
@@ -422,19 +427,17 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
                 if (zl < ch.hs.Lops) s.zero_open = false;
                 s.zero_ops += (int64_t)ch.hs.ops.size() / 4;
             }
-            if (ch.flat)
+            if (ch.column)
+                // the slice state goes on only when saturated columns may stop
+                e = launch_rowor_column(ops_view(ch.hs, r.dev), s.n, s.C, s.ld,
+                                        ch.hs.scratch_rows, ctx->traffic, ctx->saturation, false,
+                                        ctx->saturation ? s.persist : nullptr, s.done_count,
+                                        ctx->stream);
+            else if (ch.flat)
                 e = launch_rowor_wave_flat(
                     reinterpret_cast<const WaveNet *>((unsigned char *)r.dev + net_off), 1, s.n,
                     ch.hs.scratch_rows, ctx->saturation, s.done_count, ctx->traffic,
                     ctx->stream);
-            else if (s.sw == 1 && rowor_wave_pays(s.n, ch.hs.scratch_rows,
-                                                  (int64_t)ch.hs.ops.size() / 4, ch.hs.Lops))
-                // a small network: one wavefront per word column; the slice
-                // state goes on only when saturated slices may stop
-                e = launch_rowor_wave(ops_view(ch.hs, r.dev), s.n, s.C, s.ld,
-                                      ch.hs.scratch_rows, ctx->traffic, ctx->saturation,
-                                      ctx->saturation ? s.persist : nullptr, s.done_count,
-                                      ctx->stream);
             else
                 e = launch_rowor_global(ops_view(ch.hs, r.dev), s.n, s.C, s.ld, s.sw,
                                         (uint64_t *)ctx->scratch, s.slices, ch.hs.scratch_rows,

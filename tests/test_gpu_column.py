@@ -1,0 +1,124 @@
+"""GPU parity of the row-OR stream on one workgroup per word column: networks
+whose columns fit in LDS, at the edges of the sizes and level widths where it
+is taken, against the slices of the matrix in memory (an explicit slice width
+selects them) and the oracle's words."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import tn_inputs as T
+from gpu_util import host
+
+pytestmark = pytest.mark.gpu
+
+tn = pytest.importorskip("paper_2307_04890_amd")
+
+WIDE = 80  # ops a level on average above which small networks take it
+
+
+def case(kind, n, per_node, seed):
+    m = int(n * per_node)
+    if kind == "uniform":
+        return T.uniform_pairs(n, m, max(2, m // n), seed=seed)
+    if kind == "random":
+        return T.random_tiny(n, m, max(2, m // 300), seed=seed, allow_self=True)
+    if kind == "stars":
+        return T.star_steps(n, m // 25, 90, seed=seed)
+    return T.activity_driven(n, m, max(2, m // 5), seed=seed)
+
+
+# sizes about a word column, the wavefront's LDS (7,167 rows beside 1,024 of
+# scratch), its 16-bit row ids, and the workgroup's LDS (~19,300 rows)
+SIZES = [(63, "random", 60), (64, "random", 60), (65, "uniform", 40), (513, "uniform", 30),
+         (1025, "uniform", 12), (3000, "random", 20), (7167, "activity", 6), (7168, "activity", 6),
+         (8193, "uniform", 5), (10_000, "random", 12), (10_001, "stars", 1), (16_385, "uniform", 4),
+         (19_200, "activity", 3), (19_456, "uniform", 4), (20_600, "uniform", 3)]
+
+
+@pytest.mark.parametrize("flags", [0, tn.DIRECTED | tn.FORWARD, tn.TIES_SEQUENTIAL])
+@pytest.mark.parametrize("n,kind,per_node", SIZES)
+def test_word_columns_in_lds_match_slices_in_memory(n, kind, per_node, flags):
+    s, d, t = case(kind, n, per_node, 9100 + n)
+    nw = oracle.words(n)
+    p = tn.Plan(n, s, d, t, flags)
+    want = p.execute(slice_words=1).clone()
+    # row padding of more than the matrix itself, left dirty by an earlier use
+    C = torch.full((n, 2 * nw + 3), -1, dtype=torch.int64, device="cuda")
+    ctx = tn.get_context()
+    try:
+        for sat in (True, False, True):
+            ctx.saturation(sat)
+            p.execute(C=C)
+            assert (host(C) == host(want)).all(), sat
+            S, _ = tn.build_component_matrix_streamed(n, s, d, t, flags,
+                                                      chunk_events=max(1, len(s) // 5))
+            assert (host(S) == host(want)).all(), sat
+    finally:
+        ctx.saturation(True)
+        p.close()
+    ref = oracle.forward_matrix if flags & tn.FORWARD else oracle.reverse_matrix
+    for w0 in (0, nw - 1):
+        got = ref(n, s, d, t, directed=bool(flags & tn.DIRECTED),
+                  sequential=bool(flags & tn.TIES_SEQUENTIAL), w0=w0, nw=1)
+        assert (host(want)[:, w0:w0 + 1] == got).all(), w0
+
+
+@pytest.mark.parametrize("n", [1000, 9000])
+def test_full_columns_stop_and_are_counted(n):
+    # every row fills up long before the earliest events: plans give the full
+    # matrix, a stream ends early, and a plan's traffic is one pass over it
+    s, d, t = T.uniform_pairs(n, 40 * n, 40, seed=9200)
+    st = tn.host_schedule(n, s, d, t)["stats"]
+    assert st["ops"] > WIDE * st["op_levels"]
+    nw = oracle.words(n)
+    p = tn.Plan(n, s, d, t)
+    C = p.execute()
+    assert tn.get_context().last_traffic() == (n * nw, n * nw)
+    p.close()
+    full = np.full((n, nw), ~np.uint64(0))
+    if n % 64:
+        full[:, -1] = np.uint64((1 << (n % 64)) - 1)
+    assert (host(C) == full).all()
+    S, st = tn.build_component_matrix_streamed(n, s, d, t, chunk_events=2 * n)
+    assert (host(S) == full).all()
+    assert st["saturated"] == 1 and st["chunks_run"] < st["chunks"]
+
+
+@pytest.mark.parametrize("K", [65, 1000, 4096])
+@pytest.mark.parametrize("sat", [True, False])
+def test_hashed_proxies_of_wide_and_narrow_levels(K, sat):
+    # proxies of wide levels (one workgroup per column) and of narrow ones (a
+    # wavefront) by chunk size, against the batch of the mapped networks
+    n, H = 12_000, 3
+    s, d, t = T.uniform_pairs(n, 60_000, 60, seed=9300)
+    A = T.hash_coefficients(H, seed=9301)
+    ctx = tn.get_context()
+    try:
+        ctx.saturation(sat)
+        # chunks of one time step have narrow levels, of many steps wide ones
+        outs = [tn.hash_build_proxies(n, s, d, t, A, K, chunk_events=c) for c in (0, 300, 20_000)]
+    finally:
+        ctx.saturation(True)
+    bucket = outs[0][0].cpu().numpy()
+    for h in range(H):
+        want = oracle.reverse_matrix(K, bucket[h][s], bucket[h][d], t)
+        for o in outs:
+            assert (host(o[2][h]) == want).all(), h
+
+
+def test_streams_of_one_context_keep_their_matrices():
+    # two contexts on streams of their own, each with its own size
+    rng = np.random.default_rng(9400)
+    made = []
+    for n in (900, 8200):
+        s, d, t = T.uniform_pairs(n, 12 * n, 12, seed=int(rng.integers(1 << 30)))
+        st = torch.cuda.Stream()
+        with torch.cuda.stream(st):
+            p = tn.Plan(n, s, d, t)
+            C = p.execute()
+            made.append((n, s, d, t, p, C, st))
+    torch.cuda.synchronize()
+    for n, s, d, t, p, C, st in made:
+        assert torch.equal(C, p.execute(slice_words=2)), n
+        p.close()
