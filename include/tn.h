@@ -346,8 +346,8 @@ tn_status tn_hll_build(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src,
  * (Sec. 3.4: rows only gain bits); its columns then count in every row's
  * out-size and have in-size n without a read of the matrix, so a saturated
  * network's sizes cost no second pass over C.  Other slices, and executions
- * that keep no state (saturation off, small networks on one wavefront per
- * word column), are counted from C.  Arguments and errors as
+ * that keep no state (saturation off, networks whose word columns fit
+ * in LDS), are counted from C.  Arguments and errors as
  * tn_plan_execute and tn_component_sizes; out_sizes, in_sizes: DEVICE
  * int32[n], either may be NULL. */
 tn_status tn_plan_execute_sizes(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld,
@@ -432,7 +432,7 @@ tn_status tn_hash_compress(tn_ctx *ctx, uint32_t n, int64_t m,
  * is a sixteenth of the others: proxies of few super-nodes saturate within
  * few events); each chunk's H mapped sub-streams are
  * planned on host threads and applied in one launch that resumes from the
- * proxies (K <= 4096: one wavefront per word column of every proxy, the
+ * proxies (K <= 4096: one workgroup per word column of every proxy, the
  * column in LDS; larger K: batched tiles).  Once every column or tile of
  * every proxy is all ones the earlier chunks are skipped.  The proxies
  * equal those of tn_hash_compress + tn_batch_execute.  stats (HOST, may be

@@ -8,7 +8,7 @@
 
 #include "tn_internal.h"
 #include "tn_mlp.h"
-#include "tn_wave.h"
+#include "tn_column.h"
 
 namespace {
 thread_local std::string g_err;
@@ -171,7 +171,7 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     std::string err;
     const bool hll = flags & TN_HLL;
     tn_status st = tn::plan_events(n, m, src, dst, t, flags & ~(uint32_t)TN_HLL, hs, err, nullptr,
-                                   0, hll ? tn::kFormGather : tn::kFormOps);
+                                   0, hll ? tn::kFormGather : tn::kFormOps | tn::kFormColumn);
     if (st != TN_OK) return fail(st, err);
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
@@ -181,15 +181,9 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     p->hll = hll;
     std::vector<unsigned char> img;
     if (hll) tn::schedule_pack(hs, img);
-    else tn::ops_pack(hs, img);
-    // a small network with short levels also keeps its ops in the flat form
-    const int64_t nops = (int64_t)(hs.ops.size() / 4);
-    const bool flat = !hll && tn::rowor_wave_pays(n, hs.scratch_rows, nops, hs.Lops);
-    const size_t flat_off = (img.size() + 255) & ~(size_t)255;
-    if (flat) {
-        img.resize(flat_off + tn::flat_ops_bytes(hs), 0);
-        tn::flat_ops_pack(hs, n, (uint32_t *)(img.data() + flat_off));
-    }
+    // a network whose word columns fit in LDS also keeps its ops in that form
+    const bool column = !hll && hs.in_columns;
+    const size_t column_off = hll ? 0 : tn::ops_device_bytes(hs);
     // a TN_HLL plan whose register columns fit in LDS also keeps the ends of
     // each level's gather sources and each source's gather within its level
     const bool columns = hll && tn::hll_columns_fit(n, (uint32_t)hs.max_level_gathers);
@@ -206,13 +200,25 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
             lvl_src[l + 1] = hs.gat_ptr.empty() ? 0u : hs.gat_ptr[hs.lvl_gat[l + 1]];
         }
     }
-    p->dev_bytes = img.size();
+    p->dev_bytes = hll ? img.size() : column_off + 4 * hs.column.size();
     hipError_t e = hipMalloc(&p->dev, p->dev_bytes);
     if (e != hipSuccess) {
         delete p;
         return fail(TN_E_NOMEM, "device schedule allocation failed");
     }
-    e = hipMemcpyAsync(p->dev, img.data(), img.size(), hipMemcpyHostToDevice, ctx->stream);
+    auto put = [&](size_t off, const void *from, size_t bytes) {
+        if (bytes && e == hipSuccess)
+            e = hipMemcpyAsync((unsigned char *)p->dev + off, from, bytes, hipMemcpyHostToDevice,
+                               ctx->stream);
+    };
+    if (hll) {
+        put(0, img.data(), img.size());
+    } else {
+        const tn::DevOps at = tn::ops_view(hs, nullptr);  // offsets
+        put((size_t)at.lvl, hs.lvl_op.data(), 4 * hs.lvl_op.size());
+        put((size_t)at.ops, hs.ops.data(), 4 * hs.ops.size());
+        put(column_off, hs.column.data(), 4 * hs.column.size());
+    }
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
         (void)hipFree(p->dev);
@@ -241,7 +247,12 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
         p->lvl_gat = std::move(hs.lvl_gat);
     } else {
         p->view = tn::ops_view(hs, p->dev);
-        if (flat) p->flat = (const uint32_t *)((unsigned char *)p->dev + flat_off);
+        if (column) {
+            p->column = (const uint2 *)((unsigned char *)p->dev + column_off);
+            p->column_blocks = tn::column_net(hs).blocks;
+            p->column_levels = hs.Lops;
+            p->scratch_used = hs.scratch_used;
+        }
         p->scratch_rows = hs.scratch_rows;
         p->zero_levels = tn::zero_phase_levels(hs, n);
         {
@@ -441,12 +452,8 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
     if (plan->device != ctx->device) return fail(TN_E_ARG, "plan lives on another device");
     if (plan->hll) return fail(TN_E_ARG, "a TN_HLL plan runs only tn_hll_execute");
     // a network whose word columns fit in LDS, with the slice width left to
-    // the library, runs on one workgroup per column, or where levels are short
-    // on one wavefront
-    const bool column = slice_words == 0 &&
-                        tn::rowor_column_pays(n, plan->scratch_rows, plan->stats.ops,
-                                              plan->stats.op_levels, ctx->saturation);
-    const bool wave = slice_words == 0 && plan->flat;
+    // the library, runs on one workgroup per column
+    const bool column = slice_words == 0 && plan->column;
     if (slice_words == 0) slice_words = tn::default_slice_words(n, ld);
     if (slice_words > 64 || (slice_words & (slice_words - 1)))
         return fail(TN_E_ARG, "slice_words must be a power of two <= 64");
@@ -460,9 +467,9 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
         // the identity is part of the launch
         { tn::ProfScope ps(ctx, TN_K_IDENTITY); }
         tn::ProfScope ps(ctx, TN_K_ROWOR);
-        hipError_t e = tn::launch_rowor_column(plan->view, n, C, ld, plan->scratch_rows,
-                                               ctx->traffic, ctx->saturation, true, nullptr, nullptr,
-                                               ctx->stream);
+        hipError_t e = tn::launch_rowor_column(
+            {plan->column, plan->column_blocks, plan->column_levels, C, ld, nullptr}, n,
+            plan->scratch_used, ctx->traffic, ctx->saturation, true, nullptr, ctx->stream);
         return e == hipSuccess ? TN_OK : hip_fail(e, "row-OR kernel launch");
     }
     // per-workgroup sink words (for the widest grid of the launches below,
@@ -474,7 +481,7 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
     const size_t sink_rows_words =
         (size_t)sinks * tn::kRoworSinkWords +
         (size_t)plan->scratch_rows * (size_t)tn::scratch_stride((uint32_t)nwords);
-    const bool zero_phase = !wave && ctx->saturation && plan->zero_levels > 0;
+    const bool zero_phase = ctx->saturation && plan->zero_levels > 0;
     const size_t pwords = zero_phase ? tn::rowor_persist_words(n, tail_sw) + 1 : 0;
     const size_t owords = zero_phase ? sinks : 0;
     {
@@ -500,7 +507,7 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
     if (e != hipSuccess) return hip_fail(e, "identity kernel launch");
     // the plain recurrence (saturation off, or no room for its bitmap) runs
     // on the forwarded schedule where the slice width allows
-    const bool fwd = !wave && (!ctx->saturation || !tn::rowor_saturates(n, plan->scratch_rows)) &&
+    const bool fwd = (!ctx->saturation || !tn::rowor_saturates(n, plan->scratch_rows)) &&
                      tn::rowor_fwd_supported(n, slice_words) && plan->stats.ops > 0;
     if (fwd) {
         tn_status st = plan_fwd(ctx, plan, 0, plan->stats.op_levels, &plan->fwd_dev,
@@ -550,11 +557,7 @@ tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t
                 ctx->state = persist;
                 ctx->state_sw = tail_sw;
             }
-        } else if (wave)
-            e = tn::launch_rowor_wave_flat1(plan->flat, plan->view.nops, n, C, ld,
-                                            plan->scratch_rows, ctx->traffic, ctx->saturation,
-                                            ctx->stream);
-        else {
+        } else {
             e = tn::launch_rowor_global(plan->view, n, C, ld, slice_words,
                                         (uint64_t *)ctx->scratch, sinks, plan->scratch_rows,
                                         ctx->traffic, ctx->saturation, persist,

@@ -1,0 +1,53 @@
+// The row-OR stream of networks whose word columns fit in LDS (Sec. 3.1
+// Algorithm 1 in reverse time, Sec. 3.4), and of many such networks in one
+// launch (the hashed proxies, Sec. 4.3).
+#pragma once
+
+#include "tn_internal.h"
+
+namespace tn {
+
+// The column form of an op schedule: ops in level order as {a | b << 16,
+// d1 | d2 << 16}, their rows in the column (the real rows, then the scratch
+// rows in use; d2 = d1 where there is no second target), in blocks of 64.
+// kColumnFlag is set in the first word of the last op of each level, and in the
+// second word of op i < 32 of a block where bit i of the level of the block's
+// first op is.  Ops that pad the last block act on the row past the scratch rows.
+constexpr uint32_t kColumnRow = 0x7fffu;
+constexpr uint32_t kColumnFlag = 0x80000000u;
+// One network of a launch (persist nullable: the layout of
+// launch_rowor_global's with one-word slices).
+struct ColumnNet {
+    const uint2 *ops;  // device
+    uint32_t blocks, levels;
+    uint64_t *C;
+    int64_t ld;
+    uint32_t *persist;
+};
+// Whether n real rows, scratch_rows in use and the padding's row fit.
+inline bool rowor_column_fits(uint32_t n, uint32_t scratch_rows) {
+    return (uint64_t)n + scratch_rows < kColumnRows;
+}
+// The column form of s (s.column not empty, or no ops): blocks and levels set.
+inline ColumnNet column_net(const HostSchedule &s) {
+    ColumnNet net{};
+    net.blocks = (uint32_t)(s.column.size() / 128);
+    net.levels = s.Lops;
+    return net;
+}
+// One network.  It loads and stores C once, keeps persist when given, and
+// counts those loads and stores in traffic (nullable); with saturation a
+// column stops once every real row of it is all ones.  fresh: C starts as the
+// identity, written here with its row padding, and the traffic counters are
+// set, not added to.  scratch_rows: those in use.
+hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratch_rows,
+                               unsigned long long *traffic, bool saturation, bool fresh,
+                               unsigned int *done_count, hipStream_t st);
+// Many networks of n nodes (nets: DEVICE array), scratch rows in use up to
+// max_scratch_rows in every one; blocks, levels: theirs together.  fresh: every
+// matrix starts as the identity.
+hipError_t launch_rowor_columns(const ColumnNet *nets, uint32_t count, uint32_t n,
+                                uint32_t max_scratch_rows, int64_t blocks, int64_t levels,
+                                bool saturation, bool fresh, unsigned int *done_count, hipStream_t st);
+
+}  // namespace tn

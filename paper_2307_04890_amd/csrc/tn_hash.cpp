@@ -12,7 +12,7 @@
 
 #include "tn_batch.h"
 #include "tn_hash.h"
-#include "tn_wave.h"
+#include "tn_column.h"
 
 namespace {
 constexpr uint64_t kP61 = (1ull << 61) - 1;
@@ -103,40 +103,40 @@ tn_status tn_hash_compress(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *s
 
 namespace tn {
 namespace {
-// Proxies of at most this many super-nodes run on one wavefront per column
-// (timed on ER networks with Poisson events, K = 2100 to 3900: 1.4x to 2.2x
-// faster than batched tiles; proxies that fill up within the first chunk
-// lose the tiles' early stop there, a fraction of a millisecond).
-constexpr uint32_t kWaveProxyK = 4096;
+// Proxies of at most this many super-nodes run on word columns in LDS, the
+// H of them in one launch, larger ones as batched tiles (streamed builds, ms, on
+// tiles and on columns: 16 proxies of 8192, random events, 27.9 and 67.3; 4 of
+// 10^4, uniform events, 6.8 and 8.8, their op schedules taking the host longer).
+constexpr uint32_t kColumnProxyK = 4096;
 
 // Host image of one chunk of small proxies: the H op schedules at 256-byte
-// aligned offsets off[j], then room for the H WaveNet records at off[H].
+// aligned offsets off[j], then room for the H ColumnNet records at off[H].
 // Images are packed by the planner threads and recycled from chunk to
 // chunk.  A long stream keeps them in pinned memory, so that an upload is
 // one DMA; with few chunks the pinning would cost more than it saves.
-struct WaveImage {
+struct ColumnImage {
     unsigned char *pin = nullptr;
     size_t cap = 0;
     size_t bytes = 0;
     bool pinned = false;
-    bool flat = false;  // the flat schedule format (k_rowor_wave_flat), else for k_rowor_columns
     std::vector<size_t> off;
-    WaveImage() = default;
-    WaveImage(const WaveImage &) = delete;
-    WaveImage &operator=(const WaveImage &) = delete;
-    WaveImage(WaveImage &&o) noexcept { swap(o); }
-    WaveImage &operator=(WaveImage &&o) noexcept {
+    std::vector<ColumnNet> nets;
+    ColumnImage() = default;
+    ColumnImage(const ColumnImage &) = delete;
+    ColumnImage &operator=(const ColumnImage &) = delete;
+    ColumnImage(ColumnImage &&o) noexcept { swap(o); }
+    ColumnImage &operator=(ColumnImage &&o) noexcept {
         swap(o);
         return *this;
     }
-    ~WaveImage() { release(); }
-    void swap(WaveImage &o) noexcept {
+    ~ColumnImage() { release(); }
+    void swap(ColumnImage &o) noexcept {
         std::swap(pin, o.pin);
         std::swap(cap, o.cap);
         std::swap(bytes, o.bytes);
         std::swap(pinned, o.pinned);
-        std::swap(flat, o.flat);
         off.swap(o.off);
+        nets.swap(o.nets);
     }
     void release() {
         if (pin && pinned) (void)hipHostFree(pin);
@@ -146,26 +146,14 @@ struct WaveImage {
     }
 };
 
-// Short levels (at most 80 ops on average) take the flat format: each op's
-// rows as LDS byte offsets of a column of K real rows then the scratch rows,
-// and a level-end bit, so that the kernel needs no level starts.
-tn_status wave_image_pack(const std::vector<HostSchedule> &hs, uint32_t K, WaveImage &w,
-                          bool pinned, bool saturation) {
+// The H schedules in the column form.
+tn_status column_image_pack(const std::vector<HostSchedule> &hs, ColumnImage &w, bool pinned) {
     const uint32_t H = (uint32_t)hs.size();
-    int64_t ops = 0, lv = 0;
-    uint32_t max_scr = 0;
-    for (uint32_t j = 0; j < H; ++j) {
-        ops += (int64_t)hs[j].ops.size() / 4;
-        lv += hs[j].Lops;
-        max_scr = std::max(max_scr, hs[j].scratch_rows);
-    }
-    w.flat = !rowor_column_pays(K, max_scr, ops, lv, saturation);
     w.off.assign(H + 1, 0);
-    for (uint32_t j = 0; j < H; ++j) {
-        const size_t bytes = w.flat ? flat_ops_bytes(hs[j]) : ops_device_bytes(hs[j]);
-        w.off[j + 1] = w.off[j] + ((bytes + 255) & ~(size_t)255);
-    }
-    w.bytes = w.off[H] + sizeof(WaveNet) * H;
+    for (uint32_t j = 0; j < H; ++j)
+        w.off[j + 1] = w.off[j] + ((std::max<size_t>(4 * hs[j].column.size(), 4) + 255) & ~(size_t)255);
+    w.bytes = w.off[H] + sizeof(ColumnNet) * H;
+    w.nets.resize(H);
     if (w.bytes > w.cap || w.pinned != pinned) {
         const size_t cap = std::max(w.bytes, w.cap + w.cap / 2);
         w.release();
@@ -182,35 +170,28 @@ tn_status wave_image_pack(const std::vector<HostSchedule> &hs, uint32_t K, WaveI
         w.cap = cap;
     }
     for (uint32_t j = 0; j < H; ++j) {
-        const HostSchedule &s = hs[j];
-        unsigned char *b = w.pin + w.off[j];
-        if (!w.flat) {
-            std::memcpy(b, s.lvl_op.data(), 4 * s.lvl_op.size());
-            if (!s.ops.empty())
-                std::memcpy(b + ((4 * s.lvl_op.size() + 255) & ~(size_t)255), s.ops.data(),
-                            4 * s.ops.size());
-            continue;
-        }
-        flat_ops_pack(s, K, reinterpret_cast<uint32_t *>(b));
+        w.nets[j] = column_net(hs[j]);
+        if (!hs[j].column.empty())
+            std::memcpy(w.pin + w.off[j], hs[j].column.data(), 4 * hs[j].column.size());
     }
     return TN_OK;
 }
 
 // One chunk of small proxies: uploads the packed image, runs the H op
-// schedules on one wavefront per word column of each proxy (slice state per
-// column in state, col_words per proxy), reads the done count into
-// *done_host and waits.
-tn_status run_wave_chunk(tn_ctx *ctx, const std::vector<HostSchedule> &hs, WaveImage &img,
+// schedules on one workgroup per word column of each proxy (slice state per
+// column in state, col_words per proxy; fresh: the proxies start as the
+// identity), reads the done count into *done_host and waits.
+tn_status run_column_chunk(tn_ctx *ctx, const std::vector<HostSchedule> &hs, ColumnImage &img,
                          uint32_t K, const std::vector<uint64_t *> &Cs, int64_t ldK,
                          uint32_t *state, size_t col_words, unsigned int *done_dev,
-                         unsigned int *done_host, int64_t &levels, StreamSlot &buf) {
+                         unsigned int *done_host, int64_t &levels, StreamSlot &buf, bool fresh) {
     const uint32_t H = (uint32_t)hs.size();
-    uint32_t max_scr = 0;
-    int64_t ops = 0, lv = 0;
+    uint32_t scratch = 0;
+    int64_t blocks = 0, lv = 0;
     for (uint32_t j = 0; j < H; ++j) {
-        max_scr = std::max(max_scr, hs[j].scratch_rows);
+        scratch = std::max(scratch, hs[j].scratch_used);
+        blocks += img.nets[j].blocks;
         lv += hs[j].Lops;
-        ops += (int64_t)hs[j].ops.size() / 4;
     }
     levels += lv;
     hipError_t e = hipSuccess;
@@ -229,27 +210,18 @@ tn_status run_wave_chunk(tn_ctx *ctx, const std::vector<HostSchedule> &hs, WaveI
     }
     unsigned char *dev = (unsigned char *)buf.dev;
     for (uint32_t j = 0; j < H; ++j) {
-        WaveNet net;
-        if (img.flat) {
-            net.s = DevOps{hs[j].Lops, (uint32_t)(hs[j].ops.size() / 4), nullptr,
-                           reinterpret_cast<const uint4 *>(dev + img.off[j])};
-        } else {
-            net.s = ops_view(hs[j], dev + img.off[j]);
-        }
+        ColumnNet &net = img.nets[j];
+        net.ops = reinterpret_cast<const uint2 *>(dev + img.off[j]);
         net.C = Cs[j];
         net.ld = ldK;
         net.persist = ctx->saturation ? state + (size_t)j * col_words : nullptr;
-        std::memcpy(img.pin + img.off[H] + sizeof(WaveNet) * j, &net, sizeof(WaveNet));
+        std::memcpy(img.pin + img.off[H] + sizeof(ColumnNet) * j, &net, sizeof(ColumnNet));
     }
     e = hipMemcpyAsync(dev, img.pin, img.bytes, hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess) {
         ProfScope ps(ctx, TN_K_BATCH);
-        if (!img.flat)
-            e = launch_rowor_columns((const WaveNet *)(dev + img.off[H]), H, K, max_scr,
-                                     ctx->saturation, done_dev, ctx->stream);
-        else
-            e = launch_rowor_wave_flat((const WaveNet *)(dev + img.off[H]), H, K, max_scr,
-                                       ctx->saturation, done_dev, nullptr, ctx->stream);
+        e = launch_rowor_columns((const ColumnNet *)(dev + img.off[H]), H, K, scratch, blocks, lv,
+                                 ctx->saturation, fresh, done_dev, ctx->stream);
     }
     if (e == hipSuccess)
         e = hipMemcpyAsync(done_host, done_dev, sizeof(unsigned int), hipMemcpyDeviceToHost,
@@ -330,16 +302,14 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
         maps[j] = hb + (size_t)j * n;
         Cs[j] = P + (size_t)j * K * ldK;
     }
-    // Small proxies (K <= kWaveProxyK) run as op schedules on one wavefront
-    // per word column with the column in LDS (levels cost a few LDS round
-    // trips there, against a barrier and schedule loads in the batched
-    // kernel); larger ones as batched tiles.  One stream keeps one kind, as
-    // the two keep different slice states, so the wavefront path is taken
-    // only when every chunk's schedule fits it: the op planner never needs
-    // more than max(default, K - 1) scratch rows for K nodes.
-    const bool wave = K <= kWaveProxyK && rowor_wave_fits(K, std::max(kOpsScratchRows, K - 1));
+    // Small proxies (K <= kColumnProxyK) run as op schedules on word columns in
+    // LDS, larger ones as batched tiles.  One stream keeps one kind, as the two
+    // keep different slice states, so columns are taken only when every chunk's
+    // schedule fits: the op planner never needs more than max(default, K - 1)
+    // scratch rows for K nodes.
+    const bool columns = K <= kColumnProxyK && rowor_column_fits(K, std::max(kOpsScratchRows, K - 1));
     const uint32_t kw = (K + 63) / 64;
-    const size_t wave_col = 2 * (size_t)((K + 31) / 32) + 2;  // slice state words per column
+    const size_t column_words = 2 * (size_t)((K + 31) / 32) + 2;  // slice state words per column
     std::vector<uint32_t> lw;
     std::vector<uint32_t *> pst(H, nullptr);
     uint32_t *state = nullptr;
@@ -349,9 +319,9 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
     uint64_t tiles = 0;
     int64_t launched = 0, run_events = 0, levels = 0;
     bool all_done = false;
-    // the slice state's room (wavefront columns; tiles make their own) and the
+    // the slice state's room (word columns; tiles make their own) and the
     // done counter
-    st = stream_buffers_take(ctx, wave ? (size_t)H * kw * wave_col + 1 : 0, &buf);
+    st = stream_buffers_take(ctx, columns ? (size_t)H * kw * column_words + 1 : 0, &buf);
     if (st != TN_OK) return st;
     done_host = buf->ring[0].done_host;
     e = hipEventRecord(buf->init_ev, ctx->stream);
@@ -368,13 +338,13 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
     const size_t nch = bounds.size();
     struct Planned {
         std::vector<HostSchedule> hs;
-        WaveImage img;  // small proxies: the packed schedules
+        ColumnImage img;  // small proxies: the packed schedules
         tn_status st = TN_OK;
         std::string err;
         uint32_t left = 0;  // under mu: proxies of the chunk still being planned
         bool ready = false;
     };
-    std::vector<WaveImage> spare;  // under mu: images of launched chunks
+    std::vector<ColumnImage> spare;  // under mu: images of launched chunks
     std::vector<Planned> plans(nch);
     for (size_t c = 1; c < nch; ++c) {
         plans[c].hs.assign(H, HostSchedule());
@@ -395,10 +365,10 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
         std::string err;
         const tn_status ps = plan_batch((int32_t)H, ns.data(), ms.data(), ss.data(), ds.data(),
                                         ts.data(), flags, hs, err, maps.data(), n, threads,
-                                        wave ? kFormOps : kFormGather);
-        WaveImage img;
+                                        columns ? kFormColumn : kFormGather);
+        ColumnImage img;
         tn_status ws = TN_OK;
-        if (wave && ps == TN_OK) {
+        if (columns && ps == TN_OK) {
             {
                 std::lock_guard<std::mutex> lk(mu);
                 if (!spare.empty()) {
@@ -407,7 +377,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
                 }
             }
             // chunk 0 is uploaded once and its latency comes first: never pinned
-            ws = wave_image_pack(hs, K, img, pin_images && c > 0, ctx->saturation);
+            ws = column_image_pack(hs, img, pin_images && c > 0);
         }
         {
             std::lock_guard<std::mutex> lk(mu);
@@ -428,7 +398,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
         std::string err;
         const tn_status ps = plan_events(K, mc, src ? src + a : nullptr, dst ? dst + a : nullptr,
                                          t ? t + a : nullptr, flags, h, err, maps[j], n,
-                                         wave ? kFormOps : kFormGather, &stop);
+                                         columns ? kFormColumn : kFormGather, &stop);
         bool last;
         {
             std::lock_guard<std::mutex> lk(mu);
@@ -441,9 +411,9 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
         }
         if (!last || stop) return;
         // every other task of chunk c has finished: its schedules are ours
-        WaveImage img;
+        ColumnImage img;
         tn_status ws = TN_OK;
-        if (wave && plans[c].st == TN_OK) {
+        if (columns && plans[c].st == TN_OK) {
             {
                 std::lock_guard<std::mutex> lk(mu);
                 if (!spare.empty()) {
@@ -451,7 +421,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
                     spare.pop_back();
                 }
             }
-            ws = wave_image_pack(plans[c].hs, K, img, pin_images, ctx->saturation);
+            ws = column_image_pack(plans[c].hs, img, pin_images);
         }
         {
             std::lock_guard<std::mutex> lk(mu);
@@ -498,24 +468,21 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
             st = fail(plans[c].st, plans[c].err);
             break;
         }
-        if (wave) {
+        if (columns) {
             if (c == 0) {
-                // per-column slice state of every proxy, the done counter;
-                // the proxies start as the identity
-                const size_t words = (size_t)H * kw * wave_col;
+                // per-column slice state of every proxy, the done counter
+                const size_t words = (size_t)H * kw * column_words;
                 state = buf->persist;
                 done_dev = state + words;
                 tiles = (uint64_t)H * kw;
                 e = launch_fill_u32(state, words + 1, 0u, ctx->stream);
-                for (uint32_t j = 0; j < H && e == hipSuccess; ++j)
-                    e = launch_identity(Cs[j], K, ldK, nullptr, ctx->stream);
                 if (e != hipSuccess) {
                     st = hip_fail(e, "proxy initialisation");
                     break;
                 }
             }
-            st = run_wave_chunk(ctx, plans[c].hs, plans[c].img, K, Cs, ldK, state, wave_col * kw,
-                                done_dev, done_host, levels, buf->ring[0]);
+            st = run_column_chunk(ctx, plans[c].hs, plans[c].img, K, Cs, ldK, state, column_words * kw,
+                                done_dev, done_host, levels, buf->ring[0], c == 0);
             plans[c].hs.clear();
             if (st != TN_OK) break;
             ++launched;
@@ -600,7 +567,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
     cv.notify_all();
     for (auto &th : pool) th.join();
     (void)hipStreamSynchronize(ctx->stream);
-    if (state && !wave) (void)hipFree(state);
+    if (state && !columns) (void)hipFree(state);
     stream_buffers_give(ctx, buf);
     if (stats) {
         stats->chunks = (int64_t)bounds.size();
@@ -608,7 +575,7 @@ tn_status tn_hash_build_proxies(tn_ctx *ctx, uint32_t n, int64_t m, const uint32
         stats->events_run = run_events;
         stats->levels_run = levels;
         stats->saturated = all_done ? 1 : 0;
-        stats->slice_words = wave ? 1 : (lw.empty() ? 0 : (int32_t)(1u << lw[0]));
+        stats->slice_words = columns ? 1 : (lw.empty() ? 0 : (int32_t)(1u << lw[0]));
         stats->seconds = std::chrono::duration<double>(std::chrono::steady_clock::now() - t0).count();
     }
     return st;

@@ -26,7 +26,16 @@ constexpr uint32_t kScratchBit = 0x80000000u;
 constexpr uint32_t kNoRow = 0xffffffffu;
 constexpr uint32_t kOpsLevelCap = 1024;
 constexpr uint32_t kOpsScratchRows = 1024;
-enum : int { kFormGather = 1, kFormOps = 2 };
+// Rows of a word column in LDS (tn_column.hip): 160 KB less the kernel's own.
+constexpr uint32_t kColumnRows = 160 * 1024 / 8 - 8;
+// Scratch rows that ops cycle through: fewer where only so many fit beside n
+// rows in LDS (n = 20,000, activity-driven events: 471 give the same levels).
+constexpr uint32_t ops_scratch_rows(uint32_t n) {
+    return n + kOpsScratchRows >= kColumnRows && n + 64 < kColumnRows ? kColumnRows - 1 - n
+                                                                     : kOpsScratchRows;
+}
+// kFormColumn: the column form (tn_column.h) where the rows fit, else kFormOps
+enum : int { kFormGather = 1, kFormOps = 2, kFormColumn = 4 };
 
 // A single network's schedule on the host.  Items are sorted by level;
 // level l owns pairs [lvl_pair[l], lvl_pair[l+1]) and gathers
@@ -51,8 +60,11 @@ struct HostSchedule {
     uint32_t Lops = 0;
     uint32_t op_levels_unsplit = 0;
     uint32_t scratch_rows = 0;
+    uint32_t scratch_used = 0;     // scratch rows [0, scratch_used) occur in ops
     std::vector<uint32_t> lvl_op;  // Lops + 1
     std::vector<uint32_t> ops;     // 4 * nops
+    bool in_columns = false;       // made in the column form (kFormColumn and the rows fit)
+    std::vector<uint32_t> column;  // 2 * nops, padded to blocks of 64 ops
     int64_t op_pairs = 0, op_directed = 0, op_targets = 0, op_sources = 0, op_compound = 0;
     int64_t max_level_items = 0;
     int64_t max_level_gathers = 0;
@@ -225,9 +237,10 @@ struct tn_plan {
     void *dev = nullptr;
     size_t dev_bytes = 0;
     tn::DevOps view{};
-    // the same ops in the flat form, for small networks whose levels are
-    // short (one wavefront per word column; null otherwise)
-    const uint32_t *flat = nullptr;
+    // the same ops in the column form, where word columns fit in LDS (null
+    // otherwise)
+    const uint2 *column = nullptr;
+    uint32_t column_blocks = 0, column_levels = 0, scratch_used = 0;
     uint32_t scratch_rows = 0;
     uint32_t zero_levels = 0;  // levels of the zero phase (tn::zero_phase_levels)
     // the op schedule on the host, and its forwarded form on the device,

@@ -20,6 +20,7 @@
 #include <cstring>
 
 #include "tn_internal.h"
+#include "tn_column.h"
 
 namespace tn {
 
@@ -34,7 +35,7 @@ struct Planner {
 
     // ops form: last level that wrote / read each row and scratch row
     std::vector<uint32_t> lw, lr, slw, slr;
-    uint32_t S = 0, next_scratch = 0;
+    uint32_t S = 0, next_scratch = 0, scratch_used = 0;
     struct Op {
         uint32_t a, b, d1, d2;
     };
@@ -65,7 +66,7 @@ struct Planner {
         if (ops) {
             lw.assign(n_, 0);
             lr.assign(n_, 0);
-            grow_scratch(kOpsScratchRows);
+            grow_scratch(ops_scratch_rows(n_));
         } else {
             last.assign(n_, 0);
         }
@@ -309,6 +310,7 @@ struct Planner {
             for (uint32_t q = b0; q < b1 && !has; ++q) has = nbr[q] != x;
             if (!has) continue;  // no incoming information: row unchanged
             const bool own = in_place && ++seen == targets;
+            if (!own) scratch_used = std::min(S, scratch_used + 1);
             const uint32_t tsc = own ? x : ((next_scratch++ % S) | kScratchBit);
             uint32_t acc = x;
             int64_t k = 0;
@@ -364,7 +366,7 @@ namespace {
 
 // Binary-op form: levels of at most kOpsLevelCap ops (a wider level is split
 // into consecutive levels; its ops are independent, so any split is exact).
-void finish_ops(Planner &p, HostSchedule &out) {
+void finish_ops(Planner &p, HostSchedule &out, int forms) {
     const uint32_t L = p.L;
     const size_t P = p.ops.size();
     std::vector<uint32_t> cnt((size_t)L + 1, 0);
@@ -375,15 +377,29 @@ void finish_ops(Planner &p, HostSchedule &out) {
     const uint32_t Lf = base[L + 1];
     out.Lops = Lf;
     out.lvl_op.assign((size_t)Lf + 1, 0);
-    out.ops.resize(4 * P);
+    // op i of the planner goes to place q: the ops, the column form
+    const bool column = (forms & kFormColumn) && rowor_column_fits(out.n, p.scratch_used);
+    const bool ops = (forms & kFormOps) || !column;
+    out.in_columns = column;
+    if (ops) out.ops.resize(4 * P);
+    const size_t padded = (P + 63) & ~(size_t)63;
+    if (column) out.column.resize(2 * padded);
+    const uint32_t to_row = out.n - kScratchBit;  // a scratch id's row is id + to_row
+    auto place = [&](size_t i, size_t q) {
+        const Planner::Op &o = p.ops[i];
+        if (ops) std::memcpy(&out.ops[4 * q], &o, sizeof(o));
+        if (column) {
+            auto row = [&](uint32_t id) { return id + (id >> 31) * to_row; };
+            const uint32_t d1 = row(o.d1), d2 = o.d2 == kNoRow ? d1 : row(o.d2);
+            out.column[2 * q] = row(o.a) | row(o.b) << 16;
+            out.column[2 * q + 1] = d1 | d2 << 16;
+        }
+    };
     if (Lf == L) {
         // no level is split (the usual case): one counting-sort pass
         for (uint32_t l = 0; l < L; ++l) out.lvl_op[l + 1] = out.lvl_op[l] + cnt[l + 1];
         std::vector<uint32_t> pos(out.lvl_op.begin(), out.lvl_op.end() - 1);
-        for (size_t i = 0; i < P; ++i) {
-            const size_t q = pos[p.olev[i] - 1]++;
-            std::memcpy(&out.ops[4 * q], &p.ops[i], sizeof(Planner::Op));
-        }
+        for (size_t i = 0; i < P; ++i) place(i, pos[p.olev[i] - 1]++);
     } else {
         std::vector<uint32_t> fcnt(Lf, 0), rank((size_t)L + 1, 0), flev(P);
         for (size_t i = 0; i < P; ++i) {
@@ -393,12 +409,21 @@ void finish_ops(Planner &p, HostSchedule &out) {
         }
         for (uint32_t l = 0; l < Lf; ++l) out.lvl_op[l + 1] = out.lvl_op[l] + fcnt[l];
         std::vector<uint32_t> pos(out.lvl_op.begin(), out.lvl_op.end() - 1);
-        for (size_t i = 0; i < P; ++i) {
-            const size_t q = pos[flev[i]]++;
-            std::memcpy(&out.ops[4 * q], &p.ops[i], sizeof(Planner::Op));
+        for (size_t i = 0; i < P; ++i) place(i, pos[flev[i]]++);
+    }
+    if (column && P) {
+        const uint32_t idle = out.n + p.scratch_used;
+        for (size_t q = P; q < padded; ++q) out.column[2 * q] = out.column[2 * q + 1] = idle | idle << 16;
+        // the levels' ends, and each block's first level (every level has ops)
+        for (uint32_t l = 0, k = 0; l < Lf; ++l) {
+            out.column[2 * ((size_t)out.lvl_op[l + 1] - 1)] |= kColumnFlag;
+            for (; 64 * (size_t)k < out.lvl_op[l + 1]; ++k)
+                for (uint32_t i = 0; l >> i; ++i)
+                    out.column[2 * (64 * (size_t)k + i) + 1] |= (l >> i & 1) * kColumnFlag;
         }
     }
     out.scratch_rows = p.S;
+    out.scratch_used = p.scratch_used;
     out.op_levels_unsplit = L;
 }
 
@@ -476,13 +501,13 @@ tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
             b = a;
         }
     };
-    if (forms & kFormOps) {
+    if (forms & (kFormOps | kFormColumn)) {
         Planner po(n, directed, true);
         po.ops.reserve((size_t)m + (size_t)m / 4);
         po.olev.reserve((size_t)m + (size_t)m / 4);
         walk(po);
         if (given_up) return TN_OK;
-        finish_ops(po, out);
+        finish_ops(po, out, forms);
         out.op_pairs = po.n_pairs;
         out.op_directed = po.n_dir;
         out.op_targets = po.n_targets;

@@ -30,7 +30,7 @@
 #include <thread>
 
 #include "tn_internal.h"
-#include "tn_wave.h"
+#include "tn_column.h"
 
 namespace tn {
 
@@ -40,8 +40,7 @@ struct Chunk {
     int64_t a = 0, b = 0;  // events [a, b)
     HostSchedule hs;
     std::vector<unsigned char> image;
-    bool column = false;  // runs on one workgroup per word column
-    bool flat = false;  // the flat form, then room for one WaveNet (k_rowor_wave_flat)
+    bool column = false;  // hs in the column form, no image
     std::string err;
     tn_status st = TN_OK;
     bool ready = false;
@@ -227,9 +226,8 @@ tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, ui
     s.flags = flags;
     s.C = C;
     s.ld = ld;
-    // one-word slices where chunks may run on whole word columns in LDS
-    s.sw = ctx->saturation && rowor_column_fits(n, kOpsScratchRows) ? 1u
-                                                                    : default_slice_words(n, ld);
+    // one-word slices where chunks run on whole word columns in LDS
+    s.sw = rowor_column_fits(n, ops_scratch_rows(n)) ? 1u : default_slice_words(n, ld);
     s.slices = rowor_workgroups(n, s.sw);
     hipError_t e;
     if (!ctx->traffic) {
@@ -289,7 +287,8 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
     int64_t max_events = 0;
     for (const auto &c : chunks) max_events = std::max(max_events, c->b - c->a);
     const size_t reserve_ops = (size_t)max_events + (size_t)max_events / 4 + 4;
-    const size_t image_guess = align256(4 * (reserve_ops + 1)) + align256(16 * reserve_ops);
+    const size_t image_guess = s.sw == 1 ? align256(8 * reserve_ops)
+                                         : align256(4 * (reserve_ops + 1)) + align256(16 * reserve_ops);
     std::vector<void *> old_dev, old_pinned;
     // a completed launch may already report every slice full
     auto poll = [&]() {
@@ -319,22 +318,11 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
             Chunk &ch = *chunks[c];
             if (!stop.load()) {
                 ch.st = plan_events(s.n, ch.b - ch.a, src + ch.a, dst + ch.a, t + ch.a, s.flags,
-                                    ch.hs, ch.err, nullptr, 0, kFormOps, &stop);
+                                    ch.hs, ch.err, nullptr, 0,
+                                    s.sw == 1 ? kFormColumn : kFormOps, &stop);
                 if (ch.st == TN_OK && !stop.load()) {
-                    // a chunk of short levels on the wavefront kernel takes
-                    // the flat form (no level starts in the kernel's loop)
-                    const int64_t nops = (int64_t)ch.hs.ops.size() / 4;
-                    ch.column = s.sw == 1 &&
-                                rowor_column_pays(s.n, ch.hs.scratch_rows, nops, ch.hs.Lops,
-                                                  ctx->saturation);
-                    ch.flat = s.sw == 1 &&
-                              rowor_wave_pays(s.n, ch.hs.scratch_rows, nops, ch.hs.Lops);
-                    if (ch.flat) {
-                        ch.image.assign(align256(flat_ops_bytes(ch.hs)) + sizeof(WaveNet), 0);
-                        flat_ops_pack(ch.hs, s.n, reinterpret_cast<uint32_t *>(ch.image.data()));
-                    } else {
-                        ops_pack(ch.hs, ch.image);
-                    }
+                    ch.column = ch.hs.in_columns;
+                    if (!ch.column) ops_pack(ch.hs, ch.image);
                 }
             }
             {
@@ -375,7 +363,7 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
                 break;
             }
         }
-        const size_t bytes = ch.image.size();
+        const size_t bytes = ch.column ? 4 * ch.hs.column.size() : ch.image.size();
         if (bytes > r.dev_bytes) {
             const size_t cap = std::max(std::max(bytes, image_guess), r.dev_bytes + r.dev_bytes / 2);
             if (r.dev) old_dev.push_back(r.dev);
@@ -402,42 +390,28 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
             }
             r.pinned_bytes = cap;
         }
-        std::memcpy(r.pinned, ch.image.data(), bytes);
-        const size_t net_off = bytes - sizeof(WaveNet);  // flat: where the WaveNet goes
-        if (ch.flat) {
-            WaveNet net;
-            net.s = DevOps{ch.hs.Lops, (uint32_t)(ch.hs.ops.size() / 4), nullptr,
-                           reinterpret_cast<const uint4 *>(r.dev)};
-            net.C = s.C;
-            net.ld = s.ld;
-            net.persist = ctx->saturation ? s.persist : nullptr;
-            std::memcpy((unsigned char *)r.pinned + net_off, &net, sizeof(WaveNet));
-        }
+        if (bytes) std::memcpy(r.pinned, ch.column ? (const void *)ch.hs.column.data() : ch.image.data(), bytes);
         const size_t need = sizeof(uint64_t) * ((size_t)s.slices * kRoworSinkWords +
                                                 (size_t)ch.hs.scratch_rows *
                                                     (size_t)scratch_stride((uint32_t)nwords));
-        st = ensure_scratch(ctx, need);
+        if (!ch.column) st = ensure_scratch(ctx, need);
         if (st != TN_OK) break;
-        e = hipMemcpyAsync(r.dev, r.pinned, bytes, hipMemcpyHostToDevice, ctx->stream);
+        if (bytes) e = hipMemcpyAsync(r.dev, r.pinned, bytes, hipMemcpyHostToDevice, ctx->stream);
         if (e == hipSuccess) {
             ProfScope ps(ctx, TN_K_ROWOR);
             uint32_t zl = 0;
             if (s.zero_open) {
                 zl = zero_phase_levels(ch.hs, (int64_t)s.n - s.zero_ops);
                 if (zl < ch.hs.Lops) s.zero_open = false;
-                s.zero_ops += (int64_t)ch.hs.ops.size() / 4;
+                s.zero_ops += ch.hs.lvl_op.back();
             }
             if (ch.column)
                 // the slice state goes on only when saturated columns may stop
-                e = launch_rowor_column(ops_view(ch.hs, r.dev), s.n, s.C, s.ld,
-                                        ch.hs.scratch_rows, ctx->traffic, ctx->saturation, false,
-                                        ctx->saturation ? s.persist : nullptr, s.done_count,
-                                        ctx->stream);
-            else if (ch.flat)
-                e = launch_rowor_wave_flat(
-                    reinterpret_cast<const WaveNet *>((unsigned char *)r.dev + net_off), 1, s.n,
-                    ch.hs.scratch_rows, ctx->saturation, s.done_count, ctx->traffic,
-                    ctx->stream);
+                e = launch_rowor_column({reinterpret_cast<const uint2 *>(r.dev),
+                                         column_net(ch.hs).blocks, ch.hs.Lops, s.C, s.ld,
+                                         ctx->saturation ? s.persist : nullptr},
+                                        s.n, ch.hs.scratch_used, ctx->traffic, ctx->saturation,
+                                        false, s.done_count, ctx->stream);
             else
                 e = launch_rowor_global(ops_view(ch.hs, r.dev), s.n, s.C, s.ld, s.sw,
                                         (uint64_t *)ctx->scratch, s.slices, ch.hs.scratch_rows,

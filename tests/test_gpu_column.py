@@ -14,9 +14,6 @@ pytestmark = pytest.mark.gpu
 
 tn = pytest.importorskip("paper_2307_04890_amd")
 
-WIDE = 80  # ops a level on average above which small networks take it
-
-
 def case(kind, n, per_node, seed):
     m = int(n * per_node)
     if kind == "uniform":
@@ -28,12 +25,13 @@ def case(kind, n, per_node, seed):
     return T.activity_driven(n, m, max(2, m // 5), seed=seed)
 
 
-# sizes about a word column, the wavefront's LDS (7,167 rows beside 1,024 of
-# scratch), its 16-bit row ids, and the workgroup's LDS (~19,300 rows)
+# sizes about a word column, level widths about the thread counts, and the LDS
+# (20,472 rows: 1,024 of scratch to 19,447 nodes, fewer to 20,407)
 SIZES = [(63, "random", 60), (64, "random", 60), (65, "uniform", 40), (513, "uniform", 30),
          (1025, "uniform", 12), (3000, "random", 20), (7167, "activity", 6), (7168, "activity", 6),
          (8193, "uniform", 5), (10_000, "random", 12), (10_001, "stars", 1), (16_385, "uniform", 4),
-         (19_200, "activity", 3), (19_456, "uniform", 4), (20_600, "uniform", 3)]
+         (19_447, "activity", 3), (19_448, "uniform", 4), (20_407, "activity", 3),
+         (20_408, "activity", 3)]
 
 
 @pytest.mark.parametrize("flags", [0, tn.DIRECTED | tn.FORWARD, tn.TIES_SEQUENTIAL])
@@ -69,8 +67,6 @@ def test_full_columns_stop_and_are_counted(n):
     # every row fills up long before the earliest events: plans give the full
     # matrix, a stream ends early, and a plan's traffic is one pass over it
     s, d, t = T.uniform_pairs(n, 40 * n, 40, seed=9200)
-    st = tn.host_schedule(n, s, d, t)["stats"]
-    assert st["ops"] > WIDE * st["op_levels"]
     nw = oracle.words(n)
     p = tn.Plan(n, s, d, t)
     C = p.execute()
@@ -88,8 +84,8 @@ def test_full_columns_stop_and_are_counted(n):
 @pytest.mark.parametrize("K", [65, 1000, 4096])
 @pytest.mark.parametrize("sat", [True, False])
 def test_hashed_proxies_of_wide_and_narrow_levels(K, sat):
-    # proxies of wide levels (one workgroup per column) and of narrow ones (a
-    # wavefront) by chunk size, against the batch of the mapped networks
+    # proxies of narrow and of wide levels by chunk size, against the mapped
+    # networks' matrices
     n, H = 12_000, 3
     s, d, t = T.uniform_pairs(n, 60_000, 60, seed=9300)
     A = T.hash_coefficients(H, seed=9301)
