@@ -360,7 +360,7 @@ tn_status tn_plan_execute_sizes(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, i
 tn_status tn_component_sizes(tn_ctx *ctx, uint32_t n, const uint64_t *C,
                              int64_t ld, int32_t *out_sizes, int32_t *in_sizes);
 
-/* ---- many networks in one persistent launch ---------------------------- */
+/* ---- many networks in one graph launch --------------------------------- */
 
 /* Plans B networks (host threads) and uploads their schedules.  Arrays of B
  * entries: n[b], m[b], and HOST pointers src[b], dst[b], t[b] as in
@@ -370,11 +370,13 @@ tn_status tn_batch_create(tn_ctx *ctx, int32_t B, const uint32_t *n,
                           const uint32_t *const *dst, const int64_t *const *t,
                           uint32_t flags, tn_batch **out);
 
-/* Builds all B component matrices in one persistent launch: workgroups take
- * (network, column slice) tiles from a device work queue, largest first,
- * keep the slice in LDS when it fits, and write it back to C[b].  The first
- * call tunes the tile shape on the device and captures the launch in a HIP
- * graph; later calls with the same C / ld replay it.  C: HOST array of B
+/* Builds all B component matrices in one graph launch.  Networks whose word
+ * columns fit in LDS (n and the scratch rows in use under 20,472) run one
+ * workgroup per column; of larger ones, workgroups of a persistent kernel
+ * take (network, column slice) tiles from a device work queue, largest first.
+ * The first call tunes the tile shape on the device, where there are tiles,
+ * and captures the launches in a HIP graph; later calls with the same C / ld
+ * replay it.  C: HOST array of B
  * DEVICE pointers, ld: HOST array of B leading dimensions. */
 tn_status tn_batch_execute(tn_ctx *ctx, tn_batch *batch, uint64_t *const *C,
                            const int64_t *ld);
@@ -388,7 +390,8 @@ tn_status tn_batch_get_stats(const tn_batch *batch, tn_plan_stats *stats,
  * executed): shape[0] threads per workgroup, [1] dynamic LDS bytes per
  * workgroup, [2] workgroups resident per compute unit, [3] grid size,
  * [4] slice halvings below the widest slice that fits, [5] slice width of
- * global-memory tiles in words.  shape: HOST int64[6].  Errors: TN_E_ARG. */
+ * global-memory tiles in words; of word columns (those that take the most LDS
+ * for [0] to [2], all for [3], [4] is 0) where no network runs as tiles.  shape: HOST int64[6].  Errors: TN_E_ARG. */
 tn_status tn_batch_get_shape(const tn_batch *batch, int64_t *shape);
 
 void tn_batch_destroy(tn_batch *batch);

@@ -354,7 +354,7 @@ def host_schedule(n: int, src, dst, t, flags: int = 0, fwd_level_cap: int = 0) -
 
 
 class Batch:
-    """Schedules of many networks built in one persistent launch (tn_batch_create).
+    """Schedules of many networks built in one graph launch (tn_batch_create).
 
     ``nets`` is a sequence of (n, src, dst, t).  The first execute() tunes the
     tile shape on the device and captures the launch in a HIP graph."""

@@ -288,7 +288,7 @@ void fill_stats(const HostSchedule &hs, tn_plan_stats &s) {
         for (size_t l = 0; l + 1 < hs.lvl_op.size(); ++l)
             widest = std::max<int64_t>(widest, hs.lvl_op[l + 1] - hs.lvl_op[l]);
         s.max_level_items = widest;
-        s.device_bytes = (int64_t)ops_device_bytes(hs);
+        s.device_bytes = (int64_t)(hs.ops.empty() ? 4 * hs.column.size() : ops_device_bytes(hs));
     } else {
         s.levels = hs.L;
         s.pairs = (int64_t)hs.pairs.size() / 2;
@@ -301,7 +301,7 @@ void fill_stats(const HostSchedule &hs, tn_plan_stats &s) {
         s.device_bytes = (int64_t)schedule_device_bytes(hs);
     }
     s.host_seconds = hs.host_seconds;
-    s.ops = (int64_t)hs.ops.size() / 4;
+    s.ops = hs.lvl_op.empty() ? 0 : (int64_t)hs.lvl_op.back();
     s.op_levels = hs.Lops;
     s.scratch_rows = hs.scratch_rows;
 }

@@ -1,5 +1,5 @@
-// Host side of batched builds: parallel planning, tile shapes, per-XCD work
-// queues, the on-device autotuner and HIP graph capture.
+// Host side of batched builds: parallel planning, word columns, tile shapes,
+// per-XCD work queues, the on-device autotuner and HIP graph capture.
 #include <algorithm>
 #include <atomic>
 #include <chrono>
@@ -8,6 +8,7 @@
 #include <thread>
 
 #include "tn_batch.h"
+#include "tn_column.h"
 
 namespace tn {
 // Launch shape of a batch: slice halvings, threads per workgroup, LDS bytes
@@ -56,8 +57,23 @@ struct tn_batch {
     std::vector<uint2> h_tiles;
     uint32_t h_qptr[9] = {0};
     int64_t lds_tiles = 0;
-    // graph of the current shape
+    // networks on word columns in LDS (lw, mode and views are the others'):
+    // their columns in groups by the LDS they take, each group one launch
+    struct ColumnGroup {
+        uint32_t first = 0, count = 0, rows = 0, threads = 0;
+    };
+    std::vector<tn::ColumnTileNet> h_cols;  // by network; n = 0: tiles
+    std::vector<uint32_t> col_rows;
+    std::vector<ColumnGroup> groups;
+    uint32_t col_tiles = 0;
+    tn::ColumnTileNet *d_cols = nullptr;
+    uint2 *d_col_tiles = nullptr;
+    bool all_columns() const { return h_tiles.empty(); }
+    // graph of the current shape: the groups and the tiles on streams of their
+    // own, joined by events
     hipStream_t cap_stream = nullptr;
+    std::vector<hipStream_t> group_streams;
+    std::vector<hipEvent_t> group_events;
     hipGraphExec_t exec = nullptr;
     bool tuned = false;
     std::vector<uint64_t *> last_C;
@@ -104,6 +120,44 @@ void free_meta(tn_batch *b) {
     b->meta_bytes = 0;
 }
 
+// The column networks' tiles, those that take most first (a barrier per level and
+// 64 ops a turn of a wavefront), grouped by how many of them fit on a compute
+// unit: a group's launch reserves the LDS of its largest.  Threads by group, as
+// wavefronts fill a unit's slots: 48 uneven networks, 500 to 20,000 nodes, 1881
+// us so, with 256 for all 2044, 512 1886, 1024 1985; 100 of 200 to 2,000 417,
+// 415, 417, 502.
+void group_columns(tn_batch *b, std::vector<uint2> &tiles) {
+    struct T {
+        double cost;
+        uint32_t net, fit;
+    };
+    std::vector<T> nets;
+    for (int32_t i = 0; i < b->B; ++i) {
+        if (!b->h_cols[i].n) continue;
+        const uint32_t fit = std::min<uint32_t>(8, kColumnRows / (b->col_rows[i] + 1));
+        const tn_plan_stats &st = b->stats[i];
+        nets.push_back({150.0 * (double)st.op_levels + 0.3 * (double)st.ops, (uint32_t)i,
+                        fit >= 8 ? 8u : fit >= 4 ? 4u : fit});
+    }
+    std::stable_sort(nets.begin(), nets.end(), [](const T &x, const T &y) {
+        return x.fit != y.fit ? x.fit < y.fit : x.cost > y.cost;
+    });
+    tiles.clear();
+    b->groups.clear();
+    uint32_t fit = 0;
+    for (const T &t : nets) {
+        if (t.fit != fit) {
+            fit = t.fit;
+            b->groups.push_back({(uint32_t)tiles.size(), 0, 0, fit == 1 ? 1024u : fit <= 3 ? 512u : 256u});
+        }
+        tn_batch::ColumnGroup &g = b->groups.back();
+        g.rows = std::max(g.rows, b->col_rows[t.net]);
+        for (uint32_t w = 0; w < b->nwords[t.net]; ++w) tiles.push_back(make_uint2(t.net, w));
+        g.count = (uint32_t)tiles.size() - g.first;
+    }
+    b->col_tiles = (uint32_t)tiles.size();
+}
+
 // Chooses tile shapes for `policy` (0: widest slice that fits, k: k halvings
 // for more, smaller tiles), builds the LPT-ordered per-XCD queues and
 // uploads the descriptors.
@@ -127,7 +181,10 @@ tn_status apply_shape(tn_ctx *ctx, tn_batch *b, const BatchShape &shape) {
     };
     std::vector<T> tiles;
     b->lds_tiles = 0;
+    std::vector<uint2> col_tiles;
+    group_columns(b, col_tiles);
     for (int32_t i = 0; i < B; ++i) {
+        if (b->h_cols[i].n) continue;
         const uint32_t nw = b->nwords[i];
         const size_t bm = sat_bitmap_bytes(b->n[i]);
         // the bitmap must fit beside the LDS tile, or alone for a global tile
@@ -193,6 +250,8 @@ tn_status apply_shape(tn_ctx *ctx, tn_batch *b, const BatchShape &shape) {
     const size_t o_qptr = off; off = align256(off + sizeof(uint32_t) * 9);
     const size_t o_cnt = off; off = align256(off + sizeof(uint32_t) * 8);
     const size_t o_scr = off; off = align256(off + sizeof(uint64_t) * std::max<size_t>(gscr_words, 1));
+    const size_t o_cols = off; off = align256(off + sizeof(ColumnTileNet) * B);
+    const size_t o_ctiles = off; off = align256(off + sizeof(uint2) * std::max<size_t>(col_tiles.size(), 1));
     e = hipMalloc(&b->dev_meta, off);
     if (e != hipSuccess) {
         b->dev_meta = nullptr;
@@ -205,6 +264,8 @@ tn_status apply_shape(tn_ctx *ctx, tn_batch *b, const BatchShape &shape) {
     b->d_qptr = (uint32_t *)(base + o_qptr);
     b->d_counters = (uint32_t *)(base + o_cnt);
     b->d_gscratch = (uint64_t *)(base + o_scr);
+    b->d_cols = (ColumnTileNet *)(base + o_cols);
+    b->d_col_tiles = (uint2 *)(base + o_ctiles);
     b->h_nets.assign(B, NetDesc{});
     for (int32_t i = 0; i < B; ++i) {
         NetDesc &nd = b->h_nets[i];
@@ -223,6 +284,9 @@ tn_status apply_shape(tn_ctx *ctx, tn_batch *b, const BatchShape &shape) {
     e = hipMemcpy(b->d_tiles, b->h_tiles.data(), sizeof(uint2) * ntiles, hipMemcpyHostToDevice);
     if (e == hipSuccess)
         e = hipMemcpy(b->d_qptr, b->h_qptr, sizeof(uint32_t) * 9, hipMemcpyHostToDevice);
+    if (e == hipSuccess && !col_tiles.empty())
+        e = hipMemcpy(b->d_col_tiles, col_tiles.data(), sizeof(uint2) * col_tiles.size(),
+                      hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "batch metadata upload");
     b->last_C.clear();
     b->last_ld.clear();
@@ -240,11 +304,16 @@ tn_status bind_outputs(tn_ctx *ctx, tn_batch *b, uint64_t *const *C, const int64
         NetDesc &nd = b->h_nets[i];
         nd.C = C[i];
         nd.ld = ld[i];
+        b->h_cols[i].net.C = C[i];
+        b->h_cols[i].net.ld = ld[i];
         nd.pair = nd.lw >= 1 && (nd.mode == kTileLds ||
                                  (ld[i] % 2 == 0 && ((uintptr_t)C[i] & 15u) == 0));
     }
     hipError_t e = hipMemcpy(b->d_nets, b->h_nets.data(), sizeof(NetDesc) * b->B,
                              hipMemcpyHostToDevice);
+    if (e == hipSuccess)
+        e = hipMemcpy(b->d_cols, b->h_cols.data(), sizeof(ColumnTileNet) * b->B,
+                      hipMemcpyHostToDevice);
     if (e != hipSuccess) return hip_fail(e, "batch descriptor upload");
     b->last_C.assign(C, C + b->B);
     b->last_ld.assign(ld, ld + b->B);
@@ -254,6 +323,39 @@ tn_status bind_outputs(tn_ctx *ctx, tn_batch *b, uint64_t *const *C, const int64
 hipError_t launch_direct(tn_batch *b, hipStream_t st) {
     return launch_batch(b->d_nets, b->d_tiles, b->d_qptr, b->d_counters, b->grid, b->shape.threads,
                         b->dyn_lds, b->done_count, st);
+}
+
+// Launches everything on st, the groups and the tiles side by side on streams
+// of the batch's own (st is being captured).
+hipError_t launch_forked(tn_batch *b, hipStream_t st) {
+    const size_t parts = b->groups.size() + (b->all_columns() ? 0 : 1);
+    hipError_t e = hipSuccess;
+    while (e == hipSuccess && b->group_events.size() < std::max<size_t>(parts, 1)) {
+        hipEvent_t ev;
+        e = hipEventCreateWithFlags(&ev, hipEventDisableTiming);
+        if (e == hipSuccess) b->group_events.push_back(ev);
+    }
+    while (e == hipSuccess && b->group_streams.size() + 1 < parts) {
+        hipStream_t s;
+        e = hipStreamCreateWithFlags(&s, hipStreamNonBlocking);
+        if (e == hipSuccess) b->group_streams.push_back(s);
+    }
+    if (e == hipSuccess && parts > 1) e = hipEventRecord(b->group_events[0], st);
+    for (size_t k = 0; e == hipSuccess && k < parts; ++k) {
+        hipStream_t s = k == 0 ? st : b->group_streams[k - 1];
+        if (k) e = hipStreamWaitEvent(s, b->group_events[0], 0);
+        if (e != hipSuccess) break;
+        if (k == b->groups.size()) {
+            e = launch_direct(b, s);
+        } else {
+            const tn_batch::ColumnGroup &g = b->groups[k];
+            e = launch_rowor_column_tiles(b->d_cols, b->d_col_tiles + g.first, g.count, g.rows,
+                                          g.threads, b->sat, s);
+        }
+        if (k && e == hipSuccess) e = hipEventRecord(b->group_events[k], s);
+        if (k && e == hipSuccess) e = hipStreamWaitEvent(st, b->group_events[k], 0);
+    }
+    return e;
 }
 
 tn_status capture_graph(tn_batch *b) {
@@ -266,7 +368,7 @@ tn_status capture_graph(tn_batch *b) {
     hipGraph_t g = nullptr;
     e = hipStreamBeginCapture(b->cap_stream, hipStreamCaptureModeThreadLocal);
     if (e != hipSuccess) return hip_fail(e, "hipStreamBeginCapture");
-    hipError_t le = launch_direct(b, b->cap_stream);
+    hipError_t le = launch_forked(b, b->cap_stream);
     e = hipStreamEndCapture(b->cap_stream, &g);
     if (le != hipSuccess) {
         if (g) (void)hipGraphDestroy(g);
@@ -364,8 +466,18 @@ tn_status plan_batch(int32_t B, const uint32_t *n, const int64_t *m, const uint3
         for (;;) {
             const int32_t i = next.fetch_add(1);
             if (i >= B) return;
+            // the column form where it fits (batches on word columns and on
+            // LDS tiles of several words a row, us: 48 networks of 500 to
+            // 20,000 nodes 1881 and 6972, 100 of 200 to 2,000 417 and 2809, 16
+            // of 3,000 to 9,000 498 and 3732)
+            const bool column = forms == kFormColumn && rowor_column_fits(n[i], 64);
             sts[i] = plan_events(n[i], m[i], src[i], dst[i], t[i], flags, hs[i], errs[i],
-                                 maps ? maps[i] : nullptr, n_src, forms);
+                                 maps ? maps[i] : nullptr, n_src, column ? kFormColumn : kFormGather);
+            if (column && sts[i] == TN_OK && !hs[i].in_columns) {
+                hs[i] = HostSchedule();
+                sts[i] = plan_events(n[i], m[i], src[i], dst[i], t[i], flags, hs[i], errs[i],
+                                     maps ? maps[i] : nullptr, n_src, kFormGather);
+            }
         }
     };
     std::vector<std::thread> pool;
@@ -388,7 +500,7 @@ tn_status batch_create(tn_ctx *ctx, int32_t B, const uint32_t *n, const int64_t 
     *out = nullptr;
     std::vector<HostSchedule> hs;
     std::string err;
-    tn_status st = plan_batch(B, n, m, src, dst, t, flags, hs, err, maps, n_src, 0, kFormGather);
+    tn_status st = plan_batch(B, n, m, src, dst, t, flags, hs, err, maps, n_src, 0, kFormColumn);
     if (st != TN_OK) return fail(st, err);
     return batch_from_plans(ctx, B, n, flags, hs, out, stream);
 }
@@ -410,7 +522,8 @@ tn_status batch_from_plans(tn_ctx *ctx, int32_t B, const uint32_t *n, uint32_t f
     size_t total = 0;
     for (int32_t i = 0; i < B; ++i) {
         offs[i] = total;
-        total += align256(schedule_device_bytes(hs[i]));
+        total += align256(hs[i].in_columns ? std::max<size_t>(4 * hs[i].column.size(), 4)
+                                           : schedule_device_bytes(hs[i]));
     }
     hipError_t e = hipMalloc(&b->dev_sched, total);
     if (e != hipSuccess) {
@@ -422,6 +535,8 @@ tn_status batch_from_plans(tn_ctx *ctx, int32_t B, const uint32_t *n, uint32_t f
     // next slots); the alignment gaps between arrays are cleared first
     std::vector<SchedPiece> pieces;
     b->stats.resize(B);
+    b->h_cols.assign(B, ColumnTileNet{});
+    b->col_rows.assign(B, 0);
     e = hipMemsetAsync(b->dev_sched, 0, total, ctx->stream);
     if (e != hipSuccess) {
         (void)hipFree(b->dev_sched);
@@ -429,7 +544,11 @@ tn_status batch_from_plans(tn_ctx *ctx, int32_t B, const uint32_t *n, uint32_t f
         return hip_fail(e, "batch schedule clear");
     }
     for (int32_t i = 0; i < B; ++i) {
-        schedule_pieces(hs[i], pieces);
+        if (hs[i].in_columns)
+            pieces.assign(hs[i].column.empty() ? 0 : 1,
+                          SchedPiece{0, hs[i].column.data(), 4 * hs[i].column.size()});
+        else
+            schedule_pieces(hs[i], pieces);
         tn_status us = TN_OK;
         for (const SchedPiece &pc : pieces) {
             us = ring_upload(ctx, (unsigned char *)b->dev_sched + offs[i] + pc.off, pc.src, pc.bytes);
@@ -441,7 +560,14 @@ tn_status batch_from_plans(tn_ctx *ctx, int32_t B, const uint32_t *n, uint32_t f
             delete b;
             return us;
         }
-        b->views.push_back(schedule_view(hs[i], (unsigned char *)b->dev_sched + offs[i]));
+        if (hs[i].in_columns) {
+            b->h_cols[i] = {column_net(hs[i]), n[i], (n[i] + 63) / 64};
+            b->h_cols[i].net.ops = (const uint2 *)((unsigned char *)b->dev_sched + offs[i]);
+            b->col_rows[i] = n[i] + hs[i].scratch_used;
+            b->views.push_back(DevSchedule{});
+        } else {
+            b->views.push_back(schedule_view(hs[i], (unsigned char *)b->dev_sched + offs[i]));
+        }
         fill_stats(hs[i], b->stats[i]);
         b->n.push_back(n[i]);
         b->nwords.push_back((n[i] + 63) / 64);
@@ -457,6 +583,7 @@ tn_status batch_from_plans(tn_ctx *ctx, int32_t B, const uint32_t *n, uint32_t f
         if (stream->persist) b->persist.assign(stream->persist, stream->persist + B);
     }
     tn_status st = apply_shape(ctx, b, BatchShape{});
+    if (b->all_columns()) b->tuned = true;  // no tile to tune
     if (st != TN_OK) {
         free_meta(b);
         (void)hipFree(b->dev_sched);
@@ -522,6 +649,8 @@ void batch_destroy(tn_batch *b) {
     (void)hipDeviceSynchronize();
     free_meta(b);
     if (b->cap_stream) (void)hipStreamDestroy(b->cap_stream);
+    for (hipStream_t s : b->group_streams) (void)hipStreamDestroy(s);
+    for (hipEvent_t ev : b->group_events) (void)hipEventDestroy(ev);
     if (b->dev_sched) (void)hipFree(b->dev_sched);
     delete b;
 }
@@ -545,13 +674,23 @@ tn_status tn_batch_get_stats(const tn_batch *b, tn_plan_stats *stats, int64_t *t
     if (!b) return tn::fail(TN_E_ARG, "batch is NULL");
     if (stats)
         for (int32_t i = 0; i < b->B; ++i) stats[i] = b->stats[i];
-    if (tiles) *tiles = (int64_t)b->h_tiles.size();
-    if (lds_tiles) *lds_tiles = b->lds_tiles;
+    if (tiles) *tiles = (int64_t)b->h_tiles.size() + b->col_tiles;
+    if (lds_tiles) *lds_tiles = b->lds_tiles + b->col_tiles;
     return TN_OK;
 }
 
 tn_status tn_batch_get_shape(const tn_batch *batch, int64_t *shape) {
     if (!batch || !shape) return tn::fail(TN_E_ARG, "batch or shape is NULL");
+    if (batch->all_columns()) {
+        const tn_batch::ColumnGroup &g = batch->groups[0];
+        shape[0] = g.threads;
+        shape[1] = 8 * ((int64_t)g.rows + 1);
+        shape[2] = tn::kColumnRows / (g.rows + 1);
+        shape[3] = batch->col_tiles;
+        shape[4] = 0;
+        shape[5] = batch->shape.gwidth;
+        return TN_OK;
+    }
     shape[0] = batch->shape.threads;
     shape[1] = (int64_t)batch->dyn_lds;
     shape[2] = batch->per_cu;

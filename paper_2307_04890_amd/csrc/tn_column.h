@@ -50,4 +50,15 @@ hipError_t launch_rowor_columns(const ColumnNet *nets, uint32_t count, uint32_t 
                                 uint32_t max_scratch_rows, int64_t blocks, int64_t levels,
                                 bool saturation, bool fresh, unsigned int *done_count, hipStream_t st);
 
+// Word columns of networks of any sizes: workgroup b runs column tiles[b].y of
+// nets[tiles[b].x] (DEVICE arrays) from the identity; rows: the most that n
+// real and the scratch rows in use of one of them take.
+struct ColumnTileNet {
+    ColumnNet net;
+    uint32_t n, nwords;
+};
+hipError_t launch_rowor_column_tiles(const ColumnTileNet *nets, const uint2 *tiles, uint32_t count,
+                                     uint32_t rows, uint32_t threads, bool saturation,
+                                     hipStream_t st);
+
 }  // namespace tn

@@ -206,6 +206,15 @@ k_rowor_columns(const ColumnNet *__restrict__ nets, uint32_t n, uint32_t nwords,
     rowor_column<FRESH>(nets[b / nwords], b % nwords, n, nwords, sat, done_count);
 }
 
+// Columns of networks of any sizes (a batch): workgroup b runs tiles[b].
+__global__ void __launch_bounds__(1024)
+k_rowor_column_tiles(const ColumnTileNet *__restrict__ nets, const uint2 *__restrict__ tiles,
+                     bool sat) {
+    const uint2 tile = tiles[blockIdx.x];
+    const ColumnTileNet &t = nets[tile.x];
+    rowor_column<true>(t.net, tile.y, t.n, t.nwords, sat, nullptr);
+}
+
 size_t column_lds(uint32_t n, uint32_t scratch_rows) { return ((size_t)n + scratch_rows + 1) * 8; }
 
 // Threads of a workgroup, from the ops of a level on average: enough
@@ -249,6 +258,20 @@ hipError_t launch_rowor_columns(const ColumnNet *nets, uint32_t count, uint32_t 
     const uint32_t nwords = (n + 63) / 64;
     hipLaunchKernelGGL(k, dim3(count * nwords), dim3(threads), lds, st, nets, n, nwords, saturation,
                        done_count);
+    return hipGetLastError();
+}
+
+hipError_t launch_rowor_column_tiles(const ColumnTileNet *nets, const uint2 *tiles, uint32_t count,
+                                     uint32_t rows, uint32_t threads, bool saturation,
+                                     hipStream_t st) {
+    if (count == 0) return hipSuccess;
+    if (!rowor_column_fits(rows, 0)) return hipErrorInvalidValue;
+    const size_t lds = column_lds(rows, 0);
+    hipError_t e = hipFuncSetAttribute((const void *)k_rowor_column_tiles,
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_rowor_column_tiles, dim3(count), dim3(threads), lds, st, nets, tiles,
+                       saturation);
     return hipGetLastError();
 }
 

@@ -118,3 +118,40 @@ def test_streams_of_one_context_keep_their_matrices():
     for n, s, d, t, p, C, st in made:
         assert torch.equal(C, p.execute(slice_words=2)), n
         p.close()
+
+
+# rows about eight, four, three, two and one column to a compute unit, past the
+# last that fits, a lone node, no events
+BATCH = [(1, 0), (64, 500), (700, 0), (2558, 9000), (2559, 9000), (5117, 9000), (5118, 9000),
+         (6823, 9000), (6824, 9000), (10_235, 9000), (10_236, 30_000), (20_407, 30_000),
+         (20_480, 9000)]
+
+
+@pytest.mark.parametrize("flags", [0, tn.DIRECTED | tn.FORWARD, tn.TIES_SEQUENTIAL])
+@pytest.mark.parametrize("last", [len(BATCH), len(BATCH) - 1, 3])
+def test_batches_of_word_columns_match_single_plans(last, flags):
+    nets = []
+    for k, (n, m) in enumerate(BATCH[:last]):
+        ev = T.uniform_pairs(n, m, max(2, m // 40), seed=9500 + k) if n > 1 and m else \
+            (np.zeros(0, np.uint32), np.zeros(0, np.uint32), np.zeros(0, np.int64))
+        nets.append((n, *ev))
+    want = []
+    for net in nets:
+        p = tn.Plan(*net, flags)
+        want.append(p.execute(slice_words=1).clone())
+        p.close()
+    b = tn.Batch(nets, flags=flags)
+    ctx = tn.get_context()
+    try:
+        for sat in (True, False, True):
+            ctx.saturation(sat)
+            for lead in (0, 3):  # a second set of outputs, with row padding left dirty
+                Cs = [torch.full((n, oracle.words(n) + lead), -1, dtype=torch.int64, device="cuda")
+                      for n, *_ in nets]
+                for _ in range(2):  # captured, then replayed
+                    b.execute(Cs)
+                    for k, (C, w) in enumerate(zip(Cs, want)):
+                        assert (host(C) == host(w)).all(), (BATCH[k], sat, lead)
+    finally:
+        ctx.saturation(True)
+        b.close()
