@@ -179,20 +179,22 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     if (!p) return fail(TN_E_NOMEM, "plan allocation failed");
     p->device = ctx->device;
     p->hll = hll;
-    std::vector<unsigned char> img;
-    if (hll) tn::schedule_pack(hs, img);
     // a network whose word columns fit in LDS also keeps its ops in that form
     const bool column = !hll && hs.in_columns;
-    const size_t column_off = hll ? 0 : tn::ops_device_bytes(hs);
-    // a TN_HLL plan whose register columns fit in LDS also keeps the ends of
-    // each level's gather sources and each source's gather within its level
+    const size_t column_off = tn::ops_device_bytes(hs);
+    // a TN_HLL plan whose register columns fit in LDS also keeps its pairs in
+    // blocks, the ends of each level's gather sources and each source's gather
+    // within its level
     const bool columns = hll && tn::hll_columns_fit(n, (uint32_t)hs.max_level_gathers);
-    const size_t src_off = (img.size() + 255) & ~(size_t)255;
+    const size_t src_off = hll ? tn::schedule_device_bytes(hs) : 0;
     const size_t slot_off = src_off + ((4 * ((size_t)hs.L + 1) + 255) & ~(size_t)255);
+    const size_t pair_off =
+        (slot_off + 4 * std::max<size_t>(hs.gat_src.size(), 1) + 255) & ~(size_t)255;
+    std::vector<uint32_t> lvl_src, slot, pairs;
     if (columns) {
-        img.resize(slot_off + 4 * std::max<size_t>(hs.gat_src.size(), 1), 0);
-        uint32_t *lvl_src = (uint32_t *)(img.data() + src_off);
-        uint32_t *slot = (uint32_t *)(img.data() + slot_off);
+        tn::hll_column_pairs(hs, tn::hll_columns_stride(n), pairs);
+        lvl_src.assign((size_t)hs.L + 1, 0);
+        slot.resize(hs.gat_src.size());
         for (uint32_t l = 0; l < hs.L; ++l) {
             for (uint32_t q = hs.lvl_gat[l]; q < hs.lvl_gat[l + 1]; ++q)
                 for (uint32_t k = hs.gat_ptr[q]; k < hs.gat_ptr[q + 1]; ++k)
@@ -200,7 +202,9 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
             lvl_src[l + 1] = hs.gat_ptr.empty() ? 0u : hs.gat_ptr[hs.lvl_gat[l + 1]];
         }
     }
-    p->dev_bytes = hll ? img.size() : column_off + 4 * hs.column.size();
+    p->dev_bytes = columns ? pair_off + 4 * pairs.size()
+                   : hll   ? src_off
+                           : column_off + 4 * hs.column.size();
     hipError_t e = hipMalloc(&p->dev, p->dev_bytes);
     if (e != hipSuccess) {
         delete p;
@@ -212,7 +216,12 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
                                ctx->stream);
     };
     if (hll) {
-        put(0, img.data(), img.size());
+        std::vector<tn::SchedPiece> pieces;
+        tn::schedule_pieces(hs, pieces);
+        for (const tn::SchedPiece &pc : pieces) put(pc.off, pc.src, pc.bytes);
+        put(src_off, lvl_src.data(), 4 * lvl_src.size());
+        put(slot_off, slot.data(), 4 * slot.size());
+        put(pair_off, pairs.data(), 4 * pairs.size());
     } else {
         const tn::DevOps at = tn::ops_view(hs, nullptr);  // offsets
         put((size_t)at.lvl, hs.lvl_op.data(), 4 * hs.lvl_op.size());
@@ -231,14 +240,13 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
         if (columns) {
             const unsigned char *d = (const unsigned char *)p->dev;
             p->columns = {hs.L,
-                          (uint32_t)(hs.pairs.size() / 2),
+                          (uint32_t)(pairs.size() / 128),
                           (uint32_t)hs.gat_tgt.size(),
                           (uint32_t)hs.gat_src.size(),
                           p->gview.max_gat,
-                          p->gview.lvl_pair,
+                          (const uint2 *)(d + pair_off),
                           p->gview.lvl_gat,
                           (const uint32_t *)(d + src_off),
-                          p->gview.pairs,
                           p->gview.gat_tgt,
                           p->gview.gat_src,
                           (const uint32_t *)(d + slot_off)};
@@ -676,7 +684,8 @@ tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
     // rows
     const size_t gat_words = (size_t)std::max<uint32_t>(plan->gview.max_gat, 1) * nwords;
     const bool columns = plan->hll && plan->columns.lvl_src &&
-                         tn::hll_columns_pay(n, plan->gview.max_gat, log2s);
+                         tn::hll_columns_pay(n, plan->gview.max_gat, log2s, plan->stats.levels,
+                                             plan->stats.pairs);
     {
         const size_t words =
             columns     ? tn::hll_columns_scratch(n, plan->gview.max_gat, log2s) / 8

@@ -8,32 +8,23 @@
 
 #include "tn_device.h"
 #include "tn_column.h"
+#include "tn_levels.h"
 
 namespace tn {
 
 namespace {
 
-constexpr uint32_t kDepth = 8;  // blocks a wavefront has requested ahead
-
 // Word column w of one network (n real rows, then the scratch rows and the
-// row of padding ops, in LDS).  Block j of 64 ops is a turn of wavefront
-// j % (W / 64); the ops of one level within it act together, then a barrier
-// ends the level.  A block names its first level, so a wavefront needs no level
-// starts and only counts barriers until then.  While the rows of a block's
-// first level are read, the wavefront unpacks its next block and requests
-// another.
+// row of padding ops, in LDS).
 //
-// With sat the column stops once every real row is all ones (rows only gain
-// bits): every 32 levels each wavefront moves past the rows of its own that are.
+// With sat the column stops once every real row is all ones: rows only gain
+// bits.
 //
 // FRESH: the column starts as the identity's and the row padding is written
 // too, so that no launch has to write the matrix before.
 //
 // Bound by the latency of a level (LDS reads, writes, the barrier; 144 ns) where
 // levels are narrow, by LDS bank conflicts where they are wide (700 ops: 340 ns).
-// The whole loop is uniform within a wavefront, the ops of a level apart: a
-// divergent check cost 15 to 25 %, unpacking after the writes 15 %, 4 blocks
-// ahead 25 %, one wavefront for all ops the same as two on 9 ops a level.
 // Events, nodes, ops a level: activity-driven, 500, 9: 125 us (250 on a
 // wavefront with an LDS ring of 16-byte ops), 10^4, 55: 275 (3270 on slices of C
 // in memory); random, 16,000, 699: 391 (6140 so); uniform, 1,000, 119: 16.  16
@@ -56,100 +47,15 @@ rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool
     for (uint32_t r = tid; r < n; r += W)
         rows[r] = FRESH ? ((r >> 6) == w ? 1ull << (r & 63u) : 0ull) : C[(size_t)r * ld + w];
     if (net.blocks) {
-        const uint32_t turn = W / 64, L = net.levels;
-        // the load of a block is unconditional, so that the wait before its
-        // use counts the blocks after it (past the last block none is used)
-        auto load = [&](uint32_t j) {
-            return net.ops[64 * (size_t)min(j, net.blocks - 1) + lane];
-        };
-        const uint32_t j0 = __builtin_amdgcn_readfirstlane(tid >> 6);  // the wavefront
-        uint32_t j = j0;
-        uint2 win[kDepth];
-#pragma unroll
-        for (uint32_t k = 0; k < kDepth; ++k) win[k] = load(j + k * turn);
-        __syncthreads();
-        uint32_t l = 0, full = 64 * j0, blocks = net.blocks;
-        uint64_t rest = 0;                // lanes of the block whose ops are still to act
-        uint32_t look = sat ? 32u : ~0u;  // the next level with a part of the check
-        // ends the level; the column's end leaves no blocks and no lanes
-        auto advance = [&] {
-            __syncthreads();
-            ++l;
-            if (__builtin_expect(l != look, 1)) return;
-            bool stop = false;
-            if ((l & 31u) == 0) {  // after levels 32 k: look
-                while (full < n && __all(full + lane >= n || rows[full + lane] == fullw)) full += W;
-                if (full < n) open = 1;
-                ++look;
-            } else if ((l & 31u) == 1) {  // 32 k + 1: all are
-                stop = __builtin_amdgcn_readfirstlane(open) == 0;
-                ++look;
-            } else {  // 32 k + 2: reset
-                if (j0 == 0) open = 0;
-                look += 30;
-            }
-            if (stop) {
-                l = L;
-                blocks = 0;
-                rest = 0;
-            }
-        };
-        struct Ops {
-            uint32_t a, b, d1, d2;  // rows of the lane's op
-            uint64_t ends;          // lanes that end a level
-            uint32_t l0;            // level of the block's first op
-        };
-        auto unpack = [](const uint2 &o) {
-            return Ops{o.x & kColumnRow,
-                       (o.x >> 16) & kColumnRow,
-                       o.y & kColumnRow,
-                       (o.y >> 16) & kColumnRow,
-                       __ballot((int32_t)o.x < 0),
-                       (uint32_t)__ballot((int32_t)o.y < 0)};
-        };
-        Ops cur = unpack(win[0]);
-        uint64_t ra, rb;  // the rows read
-        auto act = [&] {
-            // the lanes up to the next end
-            const uint64_t in = (cur.ends ^ (cur.ends - 1)) & rest;
-            const uint64_t r = ra | rb;
-            asm volatile("" : : "v"(r));
-            if (__builtin_amdgcn_inverse_ballot_w64(in)) {
-                rows[cur.d1] = r;
-                rows[cur.d2] = r;
-            }
-            rest ^= in;
-            asm volatile("" : "+s"(rest));
-        };
-        for (;; j += kDepth * turn) {
-            bool more = true;
-#pragma unroll
-            for (uint32_t k = 0; k < kDepth; ++k) {
-                if (j + k * turn >= blocks) {
-                    more = false;
-                    break;
-                }
-                rest = ~0ull;
-                while (l < cur.l0) advance();
-                ra = rows[cur.a];
-                rb = rows[cur.b];
-                // the next block's ops, while the rows are read
-                const Ops nxt = unpack(win[(k + 1) % kDepth]);
-                win[k] = load(j + (k + kDepth) * turn);
-                asm volatile("" : : "v"(nxt.a), "v"(nxt.b), "v"(nxt.d1), "v"(nxt.d2), "s"(nxt.ends), "s"(nxt.l0));
-                act();
-                while (rest) {
-                    cur.ends &= cur.ends - 1;
-                    advance();
-                    ra = rows[cur.a];
-                    rb = rows[cur.b];
-                    act();
-                }
-                cur = nxt;
-            }
-            if (!more) break;
-        }
-        while (l < L) advance();  // the other wavefronts' levels
+        run_levels<uint64_t>(
+            rows, net.ops, net.blocks, net.levels, W / 64, n, sat, &open,
+            [](const uint2 &o) {
+                return LevelOps{o.x & kColumnRow, (o.x >> 16) & kColumnRow, o.y & kColumnRow,
+                                (o.y >> 16) & kColumnRow, __ballot((int32_t)o.x < 0),
+                                (uint32_t)__ballot((int32_t)o.y < 0)};
+            },
+            [](uint64_t x, uint64_t y) { return x | y; },
+            [=](uint64_t v) { return v == fullw; });
     }
     __syncthreads();
     for (uint32_t r = tid; r < n; r += W) C[(size_t)r * ld + w] = rows[r];

@@ -11,6 +11,7 @@
 
 #include "tn_device.h"
 #include "tn_internal.h"
+#include "tn_levels.h"
 
 namespace tn {
 
@@ -259,27 +260,22 @@ k_hll_gathers_write(uint64_t *__restrict__ M, uint32_t nwords, uint32_t G,
 // consecutive registers of every node (C bytes a row) and runs the whole
 // stream on them in LDS, a barrier per level instead of a launch.
 //
-// The waves specialise.  All but the last run the pairs, which come in
-// windows of one per thread, each window requested four windows before it is
-// used; within a window the threads of a level's pairs act, then the barrier
-// ends the level (a level that runs past its window goes on in the next one
-// without a barrier).  The last wave runs the gathers: a lane per source folds
-// it into its gather's slot by an LDS maximum, then a lane per target writes
-// it from its slot.  One wave's LDS accesses happen in order, so every source
-// of a level is read before a target is written, without a barrier (a level's
-// gathers touch other rows than its pairs).  The bounds of 64 levels sit in
-// the lanes of every wave.
+// The waves specialise.  All but the last run the pairs (run_levels).  The last
+// runs the gathers: a lane per source folds it into its gather's slot by an LDS
+// maximum, then a lane per target writes it from its slot.  One wave's LDS
+// accesses happen in order, so every source of a level is read before a target
+// is written, without a barrier (a level's gathers touch other rows than its
+// pairs).  The bounds of 64 levels sit in the wave's lanes, the next 64 sources
+// and targets are requested one window ahead.
 //
 // Saturation: a row holds at most g, the maximum over every node's own
-// registers, and one that holds g keeps it, so every 32 levels each thread
-// moves past the rows of its own that do, and the stream ends when all have.
+// registers, and one that holds g keeps it, so the
+// stream ends when all do.
 //
-// Bound by the latency of a level (LDS reads, writes, the barrier) and of the
-// windows: n = 10^5, m = 10^6, 256 registers (1724 levels, 579 pairs on
-// average) 1.25 ms, where one launch per level took 6.5 ms; of those 1.25 the
-// writes account for 0.37 and the windows' loads for 0.33.  Two or four pairs
-// a thread, or half the threads, are slower where levels are wide (1.25 to
-// 1.6 ms) and no faster where they are narrow.
+// Bound by the latency of a level (LDS reads, writes, the barrier), by bank
+// conflicts where levels are wide: n = 10^5, m = 10^6, 256
+// registers (1724 levels, 579 pairs on average) 0.70 ms, where a loop over level
+// starts and windows of pairs took 1.25 and a launch per level 6.5.
 template <int C>
 struct ColT;
 template <>
@@ -302,11 +298,6 @@ __device__ __forceinline__ uint32_t max_regs(uint32_t a, uint32_t b) {
         return (a & mask) | (b & ~mask);
     }
 }
-
-// Waits for the wavefront's memory loads (vmcnt 0) here and now: a load that
-// only some levels make, were its wait left to its use, would have every
-// level wait there for the windows in flight.
-__device__ __forceinline__ void wait_loads() { __builtin_amdgcn_s_waitcnt(0x0F70); }
 
 template <int C>
 __global__ void __launch_bounds__(1024)
@@ -340,7 +331,9 @@ k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__
         col[u] = (T)v;
     }
     __syncthreads();
-    if (__builtin_amdgcn_readfirstlane(tid) >= W) {
+    if (s.L == 0) {
+        // no merge
+    } else if (__builtin_amdgcn_readfirstlane(tid) >= W) {
         // the gathers
         uint32_t l0 = 0, eg, es, spos = 0, gpos = 0;
         uint64_t some;  // which of the 64 levels have gathers
@@ -351,7 +344,20 @@ k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__
             some = __ballot(s.lvl_gat[l] != eg);
         };
         bounds();
+        // a window of sources, of targets: [base, base + 64), and the next
         uint32_t sbase = 0, send = 0, gbase = 0, gend = 0, sid = 0, sslot = 0, tgt = 0;
+        uint32_t nsid = 0, nslot = 0, ntgt = 0;
+        auto sources = [&](uint32_t at) {
+            const uint32_t i = min(at + lane, s.sources - 1);
+            nsid = s.gat_src[i];
+            nslot = s.src_slot[i];
+        };
+        auto targets = [&](uint32_t at) { ntgt = s.gat_tgt[min(at + lane, s.gathers - 1)]; };
+        if (s.gathers) {
+            sources(0);
+            targets(0);
+        }
+        __syncthreads();
         for (uint32_t l = 0; l < s.L;) {
             l = __builtin_amdgcn_readfirstlane(l);
             l0 = __builtin_amdgcn_readfirstlane(l0);
@@ -361,9 +367,9 @@ k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__
                     if (spos >= send) {
                         sbase = spos;
                         send = spos + 64;
-                        const uint32_t i = min(sbase + lane, s.sources - 1);
-                        sid = s.gat_src[i];
-                        sslot = s.src_slot[i];
+                        sid = nsid;
+                        sslot = nslot;
+                        sources(send);
                     }
                     const uint32_t to = min(sto, send);
                     if (sbase + lane >= spos && sbase + lane < to) {
@@ -381,7 +387,8 @@ k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__
                     if (gpos >= gend) {
                         gbase = gpos;
                         gend = gpos + 64;
-                        tgt = s.gat_tgt[min(gbase + lane, s.gathers - 1)];
+                        tgt = ntgt;
+                        targets(gend);
                     }
                     const uint32_t to = min(gto, gend);
                     if (gbase + lane >= gpos && gbase + lane < to) {
@@ -407,72 +414,19 @@ k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__
         }
     } else {
         // the pairs
-        uint32_t l0 = 0, ep;
-        auto bounds = [&] {
-            ep = s.lvl_pair[min(l0 + lane + 1, s.L)];
-            wait_loads();
-        };
-        bounds();
-        // the load of a window is unconditional, so that the wait before its
-        // use counts the windows after it (past the last pair nothing is used)
-        const uint2 *pair = s.pairs ? s.pair : (const uint2 *)s.lvl_pair;
-        const uint32_t last = s.pairs ? s.pairs - 1 : 0u;
-        auto load = [&](uint32_t base) { return pair[min(base + tid, last)]; };
-        uint2 w0 = load(0), w1 = load(W), w2 = load(2 * W), w3 = load(3 * W);
-        const uint32_t first = __builtin_amdgcn_readfirstlane(tid);  // the wave's
-        const uint32_t idle = stride + lane;  // a row of its own for a lane without a pair
+        const uint32_t idle = stride + lane;  // the second target of a one-way pair
         uint32_t g = 0;
 #pragma unroll
         for (int k = 0; k < C; ++k) g |= gmax[k] << (8 * k);
-        uint32_t l = 0, pos = 0, full = tid;
-        // the levels' pairs in one window; true at the stream's end
-        auto window = [&](uint2 it, uint32_t base) -> bool {
-            const uint32_t v = it.y & kNodeMask, vw = it.y & kDirBit ? idle : v;
-            for (;;) {
-                // kept in scalar registers (every lane's are the same)
-                l = __builtin_amdgcn_readfirstlane(l);
-                l0 = __builtin_amdgcn_readfirstlane(l0);
-                pos = __builtin_amdgcn_readfirstlane(pos);
-                if (l >= s.L) return true;
-                const uint32_t end = (uint32_t)__builtin_amdgcn_readlane((int)ep, (int)(l - l0));
-                const uint32_t hi = min(end, base + W);
-                if (base + first < hi && base + first + 64 > pos) {  // the wave has some
-                    const bool in = base + tid - pos < hi - pos;
-                    const uint32_t r = max_regs<C>(col[in ? it.x : idle], col[in ? v : idle]);
-                    col[in ? it.x : idle] = (T)r;
-                    col[in ? vw : idle] = (T)r;
-                }
-                pos = hi;
-                if (end > base + W) return false;
-                __syncthreads();
-                ++l;
-                if (sat && l > 1 && (l & 31u) < 3u) {
-                    // after levels 32 k: look; 32 k + 1: all have; 32 k + 2: reset
-                    if ((l & 31u) == 0) {
-                        while (full < n && (uint32_t)col[full] == g) full += W;
-                        if (full < n) open = 1;
-                    } else if ((l & 31u) == 1) {
-                        if (__builtin_amdgcn_readfirstlane(open) == 0) l = s.L;
-                    } else if (tid == 0) {
-                        open = 0;
-                    }
-                }
-                if (l - l0 >= 64 && l < s.L) {
-                    l0 = l;
-                    bounds();
-                }
-            }
-        };
-        for (uint32_t base = 0;; base += 4 * W) {
-            if (window(w0, base)) break;
-            w0 = load(base + 4 * W);
-            if (window(w1, base + W)) break;
-            w1 = load(base + 5 * W);
-            if (window(w2, base + 2 * W)) break;
-            w2 = load(base + 6 * W);
-            if (window(w3, base + 3 * W)) break;
-            w3 = load(base + 7 * W);
-        }
+        run_levels<uint32_t>(
+            col, s.pair, s.blocks, s.L, W / 64, n, sat, &open,
+            [=](const uint2 &o) {
+                const uint32_t u = o.x & kHllNode, v = o.y & kNodeMask;
+                return LevelOps{u, v, u, o.y & kDirBit ? idle : v, __ballot((int32_t)o.x < 0),
+                                (uint32_t)__ballot(o.x & kHllLevel)};
+            },
+            [](uint32_t x, uint32_t y) { return max_regs<C>(x, y); },
+            [=](uint32_t v) { return v == g; });
     }
     __syncthreads();
     if constexpr (C == 4) {
@@ -633,7 +587,7 @@ hipError_t launch_hll_saturation_setup(uint32_t n, uint32_t log2s, const uint64_
 namespace {
 constexpr size_t kColLds = 160 * 1024 - 64;  // LDS of a workgroup, the statics aside
 size_t column_lds(uint32_t n, uint32_t max_gat, int C) {
-    return ((size_t)((n + 15u) & ~15u) + 64) * C + (size_t)max_gat * C * 4;
+    return ((size_t)hll_columns_stride(n) + 64) * C + (size_t)max_gat * C * 4;
 }
 int column_bytes(uint32_t n, uint32_t max_gat) {
     return column_lds(n, max_gat, 4) <= kColLds ? 4 : column_lds(n, max_gat, 1) <= kColLds ? 1 : 0;
@@ -662,19 +616,23 @@ static void column_launch(uint32_t n, uint32_t max_gat, uint32_t log2s, uint32_t
     }
 }
 
-// Every round runs the whole stream again, while a launch per level takes
-// longer rows at once: at n = 10^5, m = 10^6 1, 4 and 8 rounds (2^8, 2^10 and
-// 2^11 registers) took 1.37, 5.1 and 10.2 ms against 6.7, 7.7 and 9.4 ms; at
-// n = 3*10^4 (four registers a workgroup) 4 rounds (2^12) 4.0 against 11.4 ms.
-bool hll_columns_pay(uint32_t n, uint32_t max_gat, uint32_t log2s) {
+// Every round runs the whole stream again: 0.24 us a level, 0.28 ns a pair, 0.4
+// ns a row.  A launch per level takes all registers at once: 3.3 us a level and
+// each pair's four rows at 3.5 TB/s.  Measured (us, columns and levels): 10^5
+// nodes, 1724 levels, 10^6 pairs, 2^8, 2^10, 2^11 registers (1, 4, 8 rounds)
+// 800, 2818, 5589 and 6017, 7008, 8707; 1.5 * 10^5 nodes, 51 levels, 7.5 * 10^5
+// pairs, 2^8, 2^10, 2^11 378, 1186, 2286 and 497, 839, 1706; 3 * 10^4 nodes
+// (four registers a workgroup), 1775 levels, 2^12 2713 and 11018.
+bool hll_columns_pay(uint32_t n, uint32_t max_gat, uint32_t log2s, int64_t levels, int64_t pairs) {
     if (!hll_columns_fit(n, max_gat)) return false;
     uint32_t threads, rounds;
     column_launch(n, max_gat, log2s, threads, rounds);
-    return rounds <= 4;
+    return rounds * (0.24 * (double)levels + 0.28e-3 * (double)pairs + 0.4e-3 * n) <=
+           3.3 * (double)levels + 1.14e-6 * (double)pairs * (double)(1u << log2s);
 }
 
 size_t hll_columns_scratch(uint32_t n, uint32_t max_gat, uint32_t log2s) {
-    return column_bytes(n, max_gat) == 1 ? (size_t)((n + 15u) & ~15u) << log2s : 0;
+    return column_bytes(n, max_gat) == 1 ? (size_t)hll_columns_stride(n) << log2s : 0;
 }
 
 hipError_t launch_hll_columns(const HllColumns &s, uint32_t n, uint32_t log2s,
@@ -682,7 +640,7 @@ hipError_t launch_hll_columns(const HllColumns &s, uint32_t n, uint32_t log2s,
                               hipStream_t st) {
     const int C = column_bytes(n, s.max_gat);
     if (C == 0) return hipErrorInvalidValue;
-    const uint32_t ncol = 1u << log2s, stride = (n + 15u) & ~15u;
+    const uint32_t ncol = 1u << log2s, stride = hll_columns_stride(n);
     const size_t lds = column_lds(n, s.max_gat, C);
     auto k = C == 4 ? k_hll_columns<4> : k_hll_columns<1>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,

@@ -108,15 +108,21 @@ struct DevSchedule {
     const uint32_t *gat_src;
 };
 
-// The time-step schedule as k_hll_columns reads it: DevSchedule's arrays, the
-// ends of each level's gather sources, and of each source the index of its
-// gather within the level.
+// The time-step schedule as k_hll_columns reads it: the pairs in level order as
+// {u, v | kDirBit}, in blocks of 64, with kHllEnd set in u of the last of each
+// level and kHllLevel in u of pair i < 32 of a block where bit i of the level of
+// the block's first pair is (a level without pairs has one of two idle rows, as
+// the last block's padding has); of the gathers DevSchedule's arrays, the ends
+// of each level's sources, and of each source the index of its gather within
+// the level.
+constexpr uint32_t kHllEnd = 0x80000000u, kHllLevel = 0x40000000u, kHllNode = 0x3fffffffu;
 struct HllColumns {
-    uint32_t L, pairs, gathers, sources, max_gat;
-    const uint32_t *lvl_pair, *lvl_gat, *lvl_src;
+    uint32_t L, blocks, gathers, sources, max_gat;
     const uint2 *pair;
-    const uint32_t *gat_tgt, *gat_src, *src_slot;
+    const uint32_t *lvl_gat, *lvl_src, *gat_tgt, *gat_src, *src_slot;
 };
+// The pairs of s in that form (2 uint32 each); stride: the first idle row.
+void hll_column_pairs(const HostSchedule &s, uint32_t stride, std::vector<uint32_t> &out);
 
 // Device view of a binary-op schedule: level l owns ops [lvl[l], lvl[l+1]).
 struct DevOps {
@@ -142,7 +148,6 @@ tn_status plan_events(uint32_t n, int64_t m, const uint32_t *src,
 
 // Size in bytes of the device image of a schedule and its packing.
 size_t schedule_device_bytes(const HostSchedule &s);
-void schedule_pack(const HostSchedule &s, std::vector<unsigned char> &image);
 DevSchedule schedule_view(const HostSchedule &s, const void *dev_base);
 size_t ops_device_bytes(const HostSchedule &s);
 void ops_pack(const HostSchedule &s, std::vector<unsigned char> &image);
@@ -304,7 +309,7 @@ struct ProfScope {
 // freed as soon as the call returns.
 tn_status ring_upload(tn_ctx *ctx, void *dst, const void *src, size_t bytes);
 void ring_free(tn_ctx *ctx);
-// The arrays of a schedule's device image (schedule_pack): offset in the
+// The arrays of a schedule's device image (schedule_view): offset in the
 // image, host data, bytes.
 struct SchedPiece {
     size_t off;
@@ -458,8 +463,10 @@ hipError_t launch_hll_saturation_setup(uint32_t n, uint32_t log2s, const uint64_
 // the node hashes to M, with `sat` ending where every row is saturated.
 // hll_columns_fit: whether n rows (and the widest level's gathers) fit;
 // hll_columns_pay: whether this beats a launch per level.
+// rows of a register column, a multiple of 16
+inline uint32_t hll_columns_stride(uint32_t n) { return (n + 15u) & ~15u; }
 bool hll_columns_fit(uint32_t n, uint32_t max_gat);
-bool hll_columns_pay(uint32_t n, uint32_t max_gat, uint32_t log2s);
+bool hll_columns_pay(uint32_t n, uint32_t max_gat, uint32_t log2s, int64_t levels, int64_t pairs);
 size_t hll_columns_scratch(uint32_t n, uint32_t max_gat, uint32_t log2s);
 hipError_t launch_hll_columns(const HllColumns &s, uint32_t n, uint32_t log2s,
                               const uint64_t *node_hash, bool sat, uint8_t *M, uint8_t *scratch,

@@ -619,6 +619,29 @@ void schedule_pieces(const HostSchedule &s, std::vector<SchedPiece> &out) {
     put(o.gat_src, s.gat_src);
 }
 
+void hll_column_pairs(const HostSchedule &s, uint32_t stride, std::vector<uint32_t> &out) {
+    size_t count = 0;
+    for (uint32_t l = 0; l < s.L; ++l)
+        count += std::max<uint32_t>(1, s.lvl_pair[l + 1] - s.lvl_pair[l]);
+    out.resize(2 * ((count + 63) & ~(size_t)63));
+    const uint32_t idle[2] = {stride, stride | kDirBit};
+    std::vector<uint32_t> first;  // level of each block's first pair
+    size_t q = 0;
+    for (uint32_t l = 0; l < s.L; ++l) {
+        const uint32_t np = s.lvl_pair[l + 1] - s.lvl_pair[l];
+        if (np) std::memcpy(&out[2 * q], &s.pairs[2 * (size_t)s.lvl_pair[l]], 8 * (size_t)np);
+        else std::memcpy(&out[2 * q], idle, 8);
+        q += std::max<uint32_t>(1, np);
+        if (l + 1 < s.L) out[2 * (q - 1)] |= kHllEnd;
+        else
+            for (; q & 63; ++q) std::memcpy(&out[2 * q], idle, 8);
+        while (64 * first.size() < q) first.push_back(l);
+    }
+    for (size_t k = 0; k < first.size(); ++k)
+        for (uint32_t i = 0; first[k] >> i; ++i)
+            if (first[k] >> i & 1) out[2 * (64 * k + i)] |= kHllLevel;
+}
+
 size_t ops_device_bytes(const HostSchedule &s) {
     return align256(4 * s.lvl_op.size()) + align256(4 * std::max<size_t>(s.ops.size(), 4));
 }
@@ -638,20 +661,6 @@ DevOps ops_view(const HostSchedule &s, const void *dev_base) {
     d.lvl = (const uint32_t *)b;
     d.ops = (const uint4 *)(b + align256(4 * s.lvl_op.size()));
     return d;
-}
-
-void schedule_pack(const HostSchedule &s, std::vector<unsigned char> &img) {
-    Layout o = layout_of(s);
-    img.assign(o.total, 0);
-    auto put = [&](size_t off, const std::vector<uint32_t> &v) {
-        if (!v.empty()) std::memcpy(img.data() + off, v.data(), 4 * v.size());
-    };
-    put(o.lvl_pair, s.lvl_pair);
-    put(o.lvl_gat, s.lvl_gat);
-    put(o.pairs, s.pairs);
-    put(o.gat_tgt, s.gat_tgt);
-    put(o.gat_ptr, s.gat_ptr);
-    put(o.gat_src, s.gat_src);
 }
 
 DevSchedule schedule_view(const HostSchedule &s, const void *dev_base) {

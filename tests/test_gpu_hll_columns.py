@@ -53,7 +53,7 @@ def test_levels_of_gathers(flags):
     # stars: levels with many gathers and sources, some with no pair
     for n, steps, k in [(200, 500, 30), (5000, 300, 200), (45_000, 100, 1500)]:
         _both(n, T.star_steps(n, steps, k, seed=n), 5, flags)
-    # one time step of everything: levels wider than a window
+    # one time step of everything: levels wider than a turn of every wavefront
     _both(3000, T.uniform_pairs(3000, 9000, 1, seed=3), 7, flags)
     _both(60_000, T.uniform_pairs(60_000, 30_000, 1, seed=4), 4, flags)
 
@@ -83,3 +83,14 @@ def test_rows_that_start_saturated(n, b):
         assert torch.equal(M, want) and torch.equal(est, we)
         ref.close()
         p.close()
+
+
+@pytest.mark.parametrize("flags", [0, tn.DIRECTED])
+@pytest.mark.parametrize("m", [0, 1, 63, 64, 65, 959, 960, 961, 20_000])
+def test_blocks_of_pairs(m, flags):
+    # no pair, the last block's padding, blocks about the wavefronts' first
+    # turns: one wide level, then levels of one pair each
+    u = np.arange(0, 2 * m, 2, dtype=np.uint32)
+    _both(2 * m + 2, (u, u + 1, np.zeros(m, np.int64)), 5, flags)
+    k = np.arange(m, dtype=np.uint32)
+    _both(m + 1, (k, k + 1, k.astype(np.int64)), 5, flags)
