@@ -119,7 +119,9 @@ enum {
     TN_K_OUT_SIZES = 3,    /* row popcounts; asked for with the column ones:
                               the start of both arrays                      */
     TN_K_IN_SIZES = 4,     /* column popcounts; asked for with the row ones:
-                              the one pass that counts both                 */
+                              the one pass that counts both (part of
+                              TN_K_ROWOR where tn_plan_execute_sizes runs on
+                              word columns)                                 */
     TN_K_BATCH = 5,        /* persistent multi-network row-OR               */
     TN_K_HASH = 6,         /* bucket map and bucket counts                  */
     TN_K_RECOMBINE = 7,    /* fusion of the hashed proxies                  */

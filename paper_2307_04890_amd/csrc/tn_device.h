@@ -57,4 +57,16 @@ __device__ __forceinline__ uint64_t max_bytes7(uint64_t x, uint64_t y) {
     return (x & mask) | (y & ~mask);
 }
 
+// Sum and carry of three words: bit-wise full adders, one three-input
+// boolean instruction per half word each.
+__device__ __forceinline__ void full_add(uint64_t a, uint64_t b, uint64_t c, uint64_t &sum,
+                                         uint64_t &carry) {
+    const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b,
+                   bh = (uint32_t)(b >> 32), cl = (uint32_t)c, ch = (uint32_t)(c >> 32);
+    sum = (uint64_t)(uint32_t)__builtin_amdgcn_bitop3_b32(ah, bh, ch, 0x96) << 32 |
+          (uint32_t)__builtin_amdgcn_bitop3_b32(al, bl, cl, 0x96);
+    carry = (uint64_t)(uint32_t)__builtin_amdgcn_bitop3_b32(ah, bh, ch, 0xE8) << 32 |
+            (uint32_t)__builtin_amdgcn_bitop3_b32(al, bl, cl, 0xE8);
+}
+
 }  // namespace tn

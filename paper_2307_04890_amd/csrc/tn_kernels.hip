@@ -1174,18 +1174,6 @@ k_sizes_base(uint32_t n, uint32_t nwords, int32_t *__restrict__ out, int32_t *__
     }
 }
 
-// Sum and carry of three words: bit-wise full adders, one three-input
-// boolean instruction per half word each.
-__device__ __forceinline__ void full_add(uint64_t a, uint64_t b, uint64_t c, uint64_t &sum,
-                                         uint64_t &carry) {
-    const uint32_t al = (uint32_t)a, ah = (uint32_t)(a >> 32), bl = (uint32_t)b,
-                   bh = (uint32_t)(b >> 32), cl = (uint32_t)c, ch = (uint32_t)(c >> 32);
-    sum = (uint64_t)(uint32_t)__builtin_amdgcn_bitop3_b32(ah, bh, ch, 0x96) << 32 |
-          (uint32_t)__builtin_amdgcn_bitop3_b32(al, bl, cl, 0x96);
-    carry = (uint64_t)(uint32_t)__builtin_amdgcn_bitop3_b32(ah, bh, ch, 0xE8) << 32 |
-            (uint32_t)__builtin_amdgcn_bitop3_b32(al, bl, cl, 0xE8);
-}
-
 // Out-sizes (row popcounts) and in-sizes (column popcounts) of open words,
 // added to out and in, in one pass: memory-bound, so both come from the same
 // read.  A wavefront takes 64 >> lw rows at a time, 1 << lw lanes on

@@ -27,7 +27,7 @@ def case(kind, n, per_node, seed):
 
 # sizes about a word column, level widths about the thread counts, and the LDS
 # (20,472 rows: 1,024 of scratch to 19,447 nodes, fewer to 20,407)
-SIZES = [(63, "random", 60), (64, "random", 60), (65, "uniform", 40), (513, "uniform", 30),
+SIZES = [(2, "random", 5), (63, "random", 60), (64, "random", 60), (65, "uniform", 40), (513, "uniform", 30),
          (1025, "uniform", 12), (3000, "random", 20), (7167, "activity", 6), (7168, "activity", 6),
          (8193, "uniform", 5), (10_000, "random", 12), (10_001, "stars", 1), (16_385, "uniform", 4),
          (19_447, "activity", 3), (19_448, "uniform", 4), (20_407, "activity", 3),
@@ -41,6 +41,7 @@ def test_word_columns_in_lds_match_slices_in_memory(n, kind, per_node, flags):
     nw = oracle.words(n)
     p = tn.Plan(n, s, d, t, flags)
     want = p.execute(slice_words=1).clone()
+    wout, winn = tn.component_sizes(want, n)
     # row padding of more than the matrix itself, left dirty by an earlier use
     C = torch.full((n, 2 * nw + 3), -1, dtype=torch.int64, device="cuda")
     ctx = tn.get_context()
@@ -49,6 +50,10 @@ def test_word_columns_in_lds_match_slices_in_memory(n, kind, per_node, flags):
             ctx.saturation(sat)
             p.execute(C=C)
             assert (host(C) == host(want)).all(), sat
+            # the sizes that come with the columns
+            E, out, inn = p.execute_sizes(C)
+            assert (host(E) == host(want)).all(), sat
+            assert torch.equal(out, wout) and torch.equal(inn, winn), sat
             S, _ = tn.build_component_matrix_streamed(n, s, d, t, flags,
                                                       chunk_events=max(1, len(s) // 5))
             assert (host(S) == host(want)).all(), sat
