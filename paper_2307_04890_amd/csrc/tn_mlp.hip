@@ -47,9 +47,21 @@ __device__ __forceinline__ f4 load4(const float *__restrict__ p, bool wide) {
 
 __device__ __forceinline__ bool on16(const void *p) { return ((uintptr_t)p & 15u) == 0; }
 
-__device__ __forceinline__ f4 relu4(f4 v) {
+// max(v, 0), and 0 for NaN, as fmaxf: the median with 0 and infinity, one
+// instruction where fmaxf first quiets a NaN in one of its own.  (top() hides
+// the infinity from the compiler, which would make it fmaxf again.)
+__device__ __forceinline__ float top() {
+    float v = __builtin_inff();
+    asm volatile("" : "+v"(v));
+    return v;
+}
+__device__ __forceinline__ float relu(float v, float inf) {
+    return __builtin_amdgcn_fmed3f(v, 0.f, inf);
+}
+
+__device__ __forceinline__ f4 relu4(f4 v, float inf) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) v[i] = fmaxf(v[i], 0.f);
+    for (int i = 0; i < 4; ++i) v[i] = relu(v[i], inf);
     return v;
 }
 
@@ -61,10 +73,13 @@ __device__ __forceinline__ f4 relu4(f4 v) {
 // r of sample l % 16: exactly a B operand whose k runs over t and r, so the
 // second layer reads them where they are, with W2 loaded in the same order.
 // No LDS and no exchange but the output's sum over the four lane groups.
-// Bound by the matrix cores (80 instructions of 32 cycles per tile): at
-// N = 10^6 110 us (94 TFLOP/s) against 302 us (34 TFLOP/s) with one sample per
-// lane on the vector units, the weights broadcast from LDS.
-template <bool PREDICT>
+// Bound by the matrix cores (80 instructions of 32 cycles per tile, 67 us at
+// N = 10^6; 83 % of the time that wavefronts run): 101 us (103 TFLOP/s), 112 us
+// with rows that were only requested once the tile before was done and two
+// instructions a ReLU, 302 us (34 TFLOP/s) with one sample per lane on the
+// vector units, the weights broadcast from LDS.  Outputs a tile late, under the
+// next one's products, or rows two tiles ahead, took the same 101 us.
+template <bool PREDICT, bool WIDE, bool BOUND>
 __global__ void __launch_bounds__(256)
 k_mlp_outputs(const float *__restrict__ params, const float *__restrict__ x, int64_t N,
               uint32_t n_nodes, const int32_t *__restrict__ est, float *__restrict__ out) {
@@ -72,7 +87,7 @@ k_mlp_outputs(const float *__restrict__ params, const float *__restrict__ x, int
     const int64_t tiles = (N + 15) / 16;
     const int64_t step = (int64_t)gridDim.x * (blockDim.x >> 6);
     int64_t tile = (int64_t)blockIdx.x * (blockDim.x >> 6) + (threadIdx.x >> 6);
-    const bool pwide = on16(params), xwide = on16(x);
+    const bool pwide = on16(params);
     f4 w1[4], w2[4][4], b1[4], b2[4], w3[4];
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
@@ -84,24 +99,40 @@ k_mlp_outputs(const float *__restrict__ params, const float *__restrict__ x, int
         for (int k = 0; k < 4; ++k)
             w2[t][k] = load4(params + oW2 + (16 * t + col) * kH + 16 * k + 4 * g, pwide);
     }
-    const float b3 = params[oB3];
-    auto fetch = [&](int64_t tl) {
-        const int64_t s = tl * 16 + col;
-        return tl < tiles && s < N ? load4(x + s * kIn + 4 * g, xwide) : f4{};
+    const float b3 = params[oB3], inf = top();
+    // a tile's rows, and what bounds its estimates (the last sample's past the
+    // last one); unconditional, so that they stay in flight for a whole tile
+    struct Rows {
+        f4 x;
+        int32_t most;
     };
-    f4 xi = fetch(tile);
+    auto fetch = [&](int64_t tl) {
+        const int64_t s = min(tl * 16 + col, N - 1);
+        const float *p = x + s * kIn + 4 * g;
+        Rows r;
+        if constexpr (WIDE) {
+            r.x = *(const f4 *)p;
+        } else {
+#pragma unroll
+            for (int q = 0; q < 4; ++q) r.x[q] = p[q];
+        }
+        r.most = PREDICT && BOUND ? est[s] : 0;
+        return r;
+    };
+    Rows now = fetch(tile);
     for (; tile < tiles; tile += step) {
-        const f4 xn = fetch(tile + step);  // the next tile's rows, in flight
+        const Rows next = fetch(tile + step);
+        __builtin_amdgcn_sched_barrier(0);  // requested before this tile, not after it
         f4 h[4], z[4];
 #pragma unroll
         for (int t = 0; t < 4; ++t) h[t] = b1[t];
 #pragma unroll
         for (int k = 0; k < 4; ++k)
 #pragma unroll
-            for (int t = 0; t < 4; ++t) h[t] = mfma4(w1[t][k], xi[k], h[t]);
+            for (int t = 0; t < 4; ++t) h[t] = mfma4(w1[t][k], now.x[k], h[t]);
 #pragma unroll
         for (int t = 0; t < 4; ++t) {
-            h[t] = relu4(h[t]);
+            h[t] = relu4(h[t], inf);
             z[t] = b2[t];
         }
 #pragma unroll
@@ -114,20 +145,20 @@ k_mlp_outputs(const float *__restrict__ params, const float *__restrict__ x, int
 #pragma unroll
         for (int t = 0; t < 4; ++t)
 #pragma unroll
-            for (int r = 0; r < 4; ++r) y = fmaf(w3[t][r], fmaxf(z[t][r], 0.f), y);
+            for (int r = 0; r < 4; ++r) y = fmaf(w3[t][r], relu(z[t][r], inf), y);
         y += __shfl_xor(y, 16, 64);
         y += __shfl_xor(y, 32, 64);
         y += b3;
         const int64_t s = tile * 16 + col;
         if (g == 0 && s < N) {
             if (PREDICT) {
-                const float hi = est ? (float)est[s] : (float)n_nodes;
+                const float hi = BOUND ? (float)now.most : (float)n_nodes;
                 out[s] = fminf(fmaxf((float)n_nodes * expf(y), 1.f), hi);
             } else {
                 out[s] = y;
             }
         }
-        xi = xn;
+        now = next;
     }
 }
 
@@ -161,7 +192,7 @@ k_mlp_backward(const float *__restrict__ params, const float *__restrict__ x,
     const f4 w1 = load4(params + oW1 + (16 * w + col) * kIn + 4 * g, pwide);
     const f4 b1 = load4(params + oB1 + u0, pwide), b2 = load4(params + oB2 + u0, pwide);
     const f4 w3 = load4(params + oW3 + u0, pwide);
-    const float b3 = params[oB3];
+    const float b3 = params[oB3], inf = top();
     f4 w2[4], w2t[4];  // rows, and columns, of W2: k runs over 16 g + 4 q + r
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
@@ -192,7 +223,7 @@ k_mlp_backward(const float *__restrict__ params, const float *__restrict__ x,
         }
 #pragma unroll
         for (int a = 0; a < 2; ++a) {
-            h1[a] = relu4(h1[a]);
+            h1[a] = relu4(h1[a], inf);
             *(f4 *)&sh1[16 * a + col][u0] = h1[a];
         }
         __syncthreads();
@@ -413,7 +444,9 @@ uint32_t output_blocks(int64_t N) { return (uint32_t)std::min<int64_t>((N + 63) 
 hipError_t launch_mlp_forward(const float *params, const float *x, int64_t N, float *yhat,
                               hipStream_t st) {
     if (N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_outputs<false>, dim3(output_blocks(N)), dim3(256), 0, st, params, x, N,
+    auto k = ((uintptr_t)x & 15u) == 0 ? k_mlp_outputs<false, true, false>
+                                       : k_mlp_outputs<false, false, false>;
+    hipLaunchKernelGGL(k, dim3(output_blocks(N)), dim3(256), 0, st, params, x, N,
                        0u, (const int32_t *)nullptr, yhat);
     return hipGetLastError();
 }
@@ -421,7 +454,10 @@ hipError_t launch_mlp_forward(const float *params, const float *x, int64_t N, fl
 hipError_t launch_mlp_predict(const float *params, const float *x, int64_t N, uint32_t n_nodes,
                               const int32_t *est, float *sizes, hipStream_t st) {
     if (N <= 0) return hipSuccess;
-    hipLaunchKernelGGL(k_mlp_outputs<true>, dim3(output_blocks(N)), dim3(256), 0, st, params, x, N,
+    const bool wide = ((uintptr_t)x & 15u) == 0;
+    auto k = wide ? (est ? k_mlp_outputs<true, true, true> : k_mlp_outputs<true, true, false>)
+                  : (est ? k_mlp_outputs<true, false, true> : k_mlp_outputs<true, false, false>);
+    hipLaunchKernelGGL(k, dim3(output_blocks(N)), dim3(256), 0, st, params, x, N,
                        n_nodes, est, sizes);
     return hipGetLastError();
 }

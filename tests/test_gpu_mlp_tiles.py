@@ -128,3 +128,34 @@ def test_features_against_float64(n, aligned):
     want = np.log(lifted.T.astype(np.float64) / n)
     # the ratio's two roundings enter the logarithm as they are; it adds its own
     assert (np.abs(x.view(n, 16).cpu().numpy() - want) <= 3 * U + 4 * U * np.abs(want)).all()
+
+
+@pytest.mark.parametrize("N", [1, 15, 16, 17, 33, 9000])
+def test_rows_off_16_bytes_bounds_and_nan(N):
+    # rows that start off 16 bytes take single loads: the same bits; a NaN unit
+    # counts as 0 (its layer's other units as they are), and no output passes
+    # its node's bound
+    p, x = _data(N, seed=71)[:2]
+    x[N // 2, 3] = np.nan
+    n = 5000
+    P = torch.from_numpy(p).cuda()
+    est = torch.arange(1, N + 1, dtype=torch.int32, device="cuda")
+    got = []
+    for lead in (0, 1):
+        buf = torch.zeros(16 * N + lead, dtype=torch.float32, device="cuda")
+        X = buf[lead:].view(N, 16)
+        X.copy_(torch.from_numpy(x))
+        got.append((tn.mlp_forward(P, X), tn.mlp_predict(P, X, n), tn.mlp_predict(P, X, n, est=est)))
+    for a, b in zip(*got):
+        assert torch.equal(a, b)
+    y, free, bound = (a.cpu().numpy().reshape(-1) for a in got[0])
+    w1, b1, w2, b2, w3, b3 = (a.astype(np.float64) for a in _layers(p))
+    h1 = np.fmax(x.astype(np.float64) @ w1.T + b1, 0)
+    want = (np.fmax(h1 @ w2.T + b2, 0) @ w3.T + b3)[:, 0]
+    clean = np.where(np.isnan(x), 0, x)
+    tol = DEPTH * U * _forward(p, clean, absolute=True)[0]
+    assert (np.abs(y - want) <= tol).all()
+    # (without bounds the outputs stop at n)
+    e = est.cpu().numpy()
+    assert np.where(free < n, bound == np.minimum(free, e),
+                    (bound >= np.minimum(n, e)) & (bound <= e)).all()
