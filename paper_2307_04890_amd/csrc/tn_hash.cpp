@@ -20,29 +20,30 @@ constexpr size_t kLiftedBudget = (size_t)1 << 30;  // bytes of lifted tables per
 inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Whether fusion by lists beats the tables, from the call's totals: the
-// microseconds of either as fitted on calls of n = 2*10^4 to 2*10^5 nodes and
-// H = 5 and 16 hashes (lists against tables, H = 16, K = 4096 unless said:
-// n = 2*10^5 with m/n = 0.2 and 0.15 events per node 1.01 against 5.79 and
-// 4.55 against 5.75 ms; n = 5*10^4, K = 1024 0.16 against 0.40; ER graphs of
-// n = 2*10^4 with m/n = 2 0.48 against 0.40 and n = 10^5 with 0.1 3.9 against
-// 1.8; H = 5, n = 6*10^4 with 0.3 1.2 against 0.36).  The tables cost their
-// building and staging (n H K) and n / 64 words of each hash per open node;
-// the lists' side is the setup per row and entry, the union nodes' entries
-// and bitmaps (few bits of LDS, so short reads of many nodes at a time, up
-// to 65,536 nodes; a hash table per node past that), and the random reads of
-// intersections.  Below 8192 nodes either takes about 0.1 ms, the tables
-// with fewer launches.
+// microseconds of either as fitted on calls of n = 10^4 to 3*10^5 nodes and H = 5
+// to 16 hashes (lists against tables, H = 16, K = 4096 and activity-driven
+// events unless said: n = 2*10^5 with m/n = 0.2 and 0.15 events per node 0.66
+// against 5.80 and 4.59 against 5.73 ms; n = 6*10^4, K = 2048, 0.33 0.21 against
+// 0.59, K = 4096 3.97 against 0.96; n = 10^5, 0.3 2.07 against 1.79, H = 5, 0.4
+// 0.30 against 0.63; n = 10^4, H = 8, K = 512, 0.4 0.142 against 0.105).  The
+// tables cost their building and staging (n H K) and n / 64 words of each hash
+// per open node; the lists' side is the setup per row and entry, the union
+// nodes' entries and bitmaps (more where a node takes a hash table, past
+// kMarkBits nodes), and the random reads of intersections.  Below 8192 nodes
+// either takes about 0.1 ms, the tables with fewer launches.
 bool fuse_by_lists(uint32_t n, uint32_t H, uint32_t K, const unsigned long long *stats,
                    unsigned long long entries, unsigned long long nbitmaps, size_t room) {
     using namespace tn;
     // the lists take their lengths from the counts, and their room from the tables'
     if (stats[kFuseNodeMix] != stats[kFuseCountMix]) return false;
-    if (entries * 4 + nbitmaps * ((n + 63) / 64) * 8 > room) return false;
+    // (64 entries more: the last list's chunk is read whole)
+    if ((entries + 64) * 4 + nbitmaps * ((n + 63) / 64) * 8 > room) return false;
     const double N = n, rows = (double)H * K, open = (double)stats[kFuseOpen];
-    const double tables = 150 + 78e-9 * N * rows + 7.3e-9 * open * N * H;
-    const double lists = 120 + 8e-4 * rows + 8e-6 * (double)entries + 0.5e-6 * (double)nbitmaps * N +
-                         (n > 65536 ? 1.7e-6 : 8e-6) * (double)stats[kFuseEntries] +
-                         (n > 65536 ? 2.5e-3 * open : 0.0) +
+    const bool marked = n <= kMarkBits;
+    const double tables = 105 + 78e-9 * N * rows + 7.3e-9 * open * N * H;
+    const double lists = 100 + 8e-4 * rows + 8e-6 * (double)entries + 0.5e-6 * (double)nbitmaps * N +
+                         (marked ? 1.3e-6 : 1.7e-6) * (double)stats[kFuseEntries] +
+                         (marked ? 0.9e-3 : 2.5e-3) * open +
                          1.25e-8 * (double)stats[kFuseBits] * N + 1e-4 * (double)stats[kFuseInter];
     return lists < tables;
 }
@@ -649,8 +650,7 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
                                     (uint32_t *)(base + o_nodes), (uint2 *)(base + o_rows),
                                     (uint32_t *)(base + o_brow), Lt};
             e = launch_fuse_lists(n, H, K, ldK, P, bucket, count, rowsum, cls, stats, fs,
-                                  (uint32_t)nbitmaps, wide, (uint32_t)host[kFuseWide], est,
-                                  ctx->stream);
+                                  (uint32_t)nbitmaps, wide, host, est, ctx->stream);
             return e == hipSuccess ? TN_OK : hip_fail(e, "list fusion launch");
         }
     }

@@ -5,6 +5,9 @@
 
 namespace tn {
 
+// Nodes whose bitmap leaves room for four on a CU (k_fuse_marked).
+constexpr uint32_t kMarkBits = 327680;
+
 hipError_t launch_hash_buckets(uint32_t n, uint32_t H, const uint64_t *coeffs, int order, uint32_t K,
                                uint32_t *bucket, int32_t *count, hipStream_t st);
 hipError_t launch_transpose_proxies(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
@@ -28,8 +31,9 @@ enum : int {
     kFuseInter = 4,     // entries of the intersection nodes' shortest lists
     kFuseNodeMix = 5,   // sums that agree where the counts are the buckets' own
     kFuseCountMix = 6,
-    kFuseRows = 7,      // entries of each hash's lists, up to 16 hashes, and bitmaps
-    kFuseStats = 7 + 2 * 16
+    kFuseSmall = 7,     // the small union nodes
+    kFuseRows = 8,      // entries of each hash's lists, up to 16 hashes, and bitmaps
+    kFuseStats = 8 + 2 * 16
 };
 struct FuseScratch {
     uint32_t *hist;        // fuse_hist_words
@@ -46,19 +50,20 @@ bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K);
 size_t fuse_hist_words(uint32_t H, uint32_t K);
 // cls[u] (the node's kind), lifted[j n + u] = rowsum[j K + h_j(u)] (nullable),
 // est[u] = n where every row is full, else 0 and u in open[0 ..
-// stats[kFuseOpen]); the wide nodes in wide[0 .. stats[kFuseWide]); with
-// lists also the rows' totals.
+// stats[kFuseOpen]); the wide nodes in wide[0 .. stats[kFuseWide]), the small
+// ones in the last stats[kFuseSmall] of wide's n; with lists also the rows'
+// totals.
 hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
                            const int32_t *count, const int32_t *rowsum, const uint8_t *full,
                            int32_t *lifted, bool lists, uint8_t *cls, int32_t *est,
                            uint32_t *open, uint32_t *wide, unsigned long long *stats,
                            hipStream_t st);
-// The estimates of union and intersection nodes.
+// The estimates of union and intersection nodes (stats_host: stats' values).
 hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
                              const uint32_t *bucket, const int32_t *count, const int32_t *rowsum,
                              const uint8_t *cls, const unsigned long long *stats, FuseScratch s,
-                             uint32_t nbitmaps, const uint32_t *wide, uint32_t nwide, int32_t *est,
-                             hipStream_t st);
+                             uint32_t nbitmaps, const uint32_t *wide,
+                             const unsigned long long *stats_host, int32_t *est, hipStream_t st);
 hipError_t launch_recombine_est(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
                                 const uint64_t *Lt, uint32_t q0, uint32_t nq, const uint32_t *list,
                                 uint32_t nlist, int32_t *est, hipStream_t st);

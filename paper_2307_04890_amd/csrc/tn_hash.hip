@@ -487,8 +487,7 @@ constexpr uint32_t kListPart = 64;        // lists of left-out nodes hold at mos
 constexpr uint32_t kInterMax = 1u << 10;  // lists of kept nodes
 constexpr uint32_t kListSplit = 16;       // node ranges of a hash in the bucket sort
 constexpr uint32_t kHashSlots = 2048;     // a small node's table: 8 KB
-constexpr uint32_t kSmallBits = kHashSlots * 32;  // nodes that fit it as a bitmap
-constexpr uint32_t kSmallHashed = kHashSlots / 2, kSmallMarked = 4096;  // entries of a small node
+constexpr uint32_t kSmallHashed = kHashSlots / 2, kSmallMarked = 2560;  // entries of a small node
 enum : uint8_t { kNodeDone = 0, kNodeSmall = 1, kNodeInter = 2, kNodeWide = 3 };
 // The lists a row can have (the two top bits of its descriptor's length).
 enum : uint32_t { kRowOut = 0, kRowKept = 1, kRowBits = 2 };
@@ -519,23 +518,24 @@ __device__ __forceinline__ unsigned long long bucket_mix(uint32_t j, uint32_t r)
 
 // Each node's kind (cls), its lifted sizes (lifted, nullable), est (n where
 // every row is full, else 0), the nodes some row of which is not full (open)
-// and the wide ones among them (wide); totals in stats.
+// and of them the wide ones (wide, from its start) and the small ones (wide,
+// from its end); totals in stats.
 __global__ void __launch_bounds__(256)
 k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
            const int32_t *__restrict__ rowsum, const uint8_t *__restrict__ full,
            int32_t *__restrict__ lifted, uint8_t *__restrict__ cls, int32_t *__restrict__ est,
            uint32_t *__restrict__ open, uint32_t *__restrict__ wide,
            unsigned long long *__restrict__ stats) {
-    __shared__ uint32_t nopen, nwide, base[2];
+    __shared__ uint32_t nopen, nwide, nsmall, base[3];
     __shared__ unsigned long long tot[4];
     if (threadIdx.x < 4) tot[threadIdx.x] = 0;
     unsigned long long entries = 0, bits = 0, inter = 0, sum = 0;
-    const uint32_t small = n <= kSmallBits ? kSmallMarked : kSmallHashed;
+    const uint32_t small = n <= kMarkBits ? kSmallMarked : kSmallHashed;
     for (uint32_t t0 = blockIdx.x * blockDim.x; t0 < n; t0 += gridDim.x * blockDim.x) {
         const uint32_t u = t0 + threadIdx.x;
-        if (threadIdx.x == 0) nopen = nwide = 0;
+        if (threadIdx.x == 0) nopen = nwide = nsmall = 0;
         __syncthreads();
-        uint32_t slot = 0xffffffffu, wslot = 0xffffffffu;
+        uint32_t slot = 0xffffffffu, wslot = 0xffffffffu, sslot = 0xffffffffu;
         if (u < n) {
             uint64_t zsum = 0, out = 0;
             bool all = true;
@@ -583,13 +583,16 @@ k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ buck
             est[u] = all ? (int32_t)n : 0;
             if (!all) slot = atomicAdd(&nopen, 1u);
             if (c == kNodeWide) wslot = atomicAdd(&nwide, 1u);
+            if (c == kNodeSmall) sslot = atomicAdd(&nsmall, 1u);
         }
         __syncthreads();
         if (threadIdx.x == 0 && nopen) base[0] = (uint32_t)atomicAdd(stats + kFuseOpen, (unsigned long long)nopen);
         if (threadIdx.x == 64 && nwide) base[1] = (uint32_t)atomicAdd(stats + kFuseWide, (unsigned long long)nwide);
+        if (threadIdx.x == 128 && nsmall) base[2] = (uint32_t)atomicAdd(stats + kFuseSmall, (unsigned long long)nsmall);
         __syncthreads();
         if (slot != 0xffffffffu) open[base[0] + slot] = u;
         if (wslot != 0xffffffffu) wide[base[1] + wslot] = u;
+        if (sslot != 0xffffffffu) wide[n - 1 - (base[2] + sslot)] = u;
         __syncthreads();
     }
     if (entries) atomicAdd(&tot[0], entries);
@@ -912,29 +915,211 @@ struct Chunks {
     }
 };
 
-// The estimates of small union nodes and of intersection nodes, one wavefront
-// (one workgroup) per node at a time.
-//  - Union: kBatch chunks of entries in flight; an entry is marked in a
-//    bitmap of n bits by an atomic OR whose old word tells a first mark, or,
-//    HASHED, where n bits are more than the 8 KB of a hash table, entered
-//    there by compare-and-swap (at most half full: kSmallHashed entries).
-//    Either is cleared whole, 16 bytes a lane.
-//  - Intersection: 64 nodes of the shortest list at a time against 4 hashes
-//    at a time, until none is left.
-// Bound by the latency of a node's chain of reads (buckets, rows, lists),
-// hidden by the wavefronts the tables leave room for (20 a CU), and by their
-// instructions: 147,000 nodes of 600 entries (n = 2*10^5) in 0.55 ms.
+// The estimates of intersection nodes, a wavefront (a workgroup) each: 64 nodes
+// of the shortest list at a time against 4 hashes at a time, until none is left.
+// Bound by the latency of a node's chain of reads, hidden by 32 wavefronts a CU.
 constexpr uint32_t kBatch = 8;
-template <bool HASHED>
 __global__ void __launch_bounds__(64)
-k_fuse_small(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
+k_fuse_inter(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
+             const uint32_t *__restrict__ bucket, const uint8_t *__restrict__ cls,
+             const uint2 *__restrict__ rows, const uint32_t *__restrict__ lists,
+             int32_t *__restrict__ est) {
+    const uint32_t lane = threadIdx.x;
+    // 64 classes at a time
+    for (uint32_t u0 = blockIdx.x * 64; u0 < n; u0 += gridDim.x * 64) {
+        uint64_t some = __ballot(u0 + lane < n && cls[u0 + lane] == kNodeInter);
+        for (; some; some &= some - 1) {
+            const uint32_t u = u0 + __builtin_ctzll(some);
+            const uint32_t bu = lane < H ? bucket[(size_t)lane * n + u] : 0u;
+            uint2 d = make_uint2(0u, 0u);
+            if (lane < H) d = rows[(size_t)lane * K + bu];
+            uint32_t mine = 0;
+        // the shortest list of kept nodes
+        uint32_t key = d.y >> 30 == kRowKept ? (d.y & 0x3fffffffu) << 4 | lane : 0xffffffffu;
+#pragma unroll
+        for (int off = 8; off > 0; off >>= 1) key = min(key, (uint32_t)__shfl_xor(key, off, 16));
+        key = __builtin_amdgcn_readfirstlane(key);
+        const uint32_t js = key & 15u, len = key >> 4;
+        const uint32_t o = __builtin_amdgcn_readlane(d.x, js);
+        for (uint32_t i0 = 0; i0 < len; i0 += 64) {
+            const uint32_t w = i0 + lane < len ? lists[o + i0 + lane] : 0xffffffffu;
+            bool alive = w < n;
+            // the other hashes, from the one after js on
+            for (uint32_t k0 = 1; k0 < H; k0 += 4) {
+                uint32_t hb[4];
+                uint64_t x[4];
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t j = (js + k0 + k) % H;
+                    hb[k] = alive && k0 + k < H ? bucket[(size_t)j * n + w] : 0u;
+                }
+#pragma unroll
+                for (uint32_t k = 0; k < 4; ++k) {
+                    const uint32_t j = (js + k0 + k) % H;
+                    const size_t r = (size_t)j * K + __builtin_amdgcn_readlane(bu, j);
+                    x[k] = alive && k0 + k < H ? P[r * ldK + (hb[k] >> 6)] >> (hb[k] & 63u) : 1ull;
+                }
+                alive = alive && (x[0] & x[1] & x[2] & x[3] & 1ull);
+                if (__ballot(alive) == 0) break;
+            }
+            mine += alive ? 1u : 0u;
+        }
+#pragma unroll
+            for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
+            if (lane == 0) est[u] = (int32_t)mine;
+        }
+    }
+}
+
+// The estimates of small union nodes, one wavefront (one workgroup) per node at
+// a time, where a bitmap of n bits leaves room for a few wavefronts on a CU
+// (n <= kMarkBits): an entry is marked by an atomic OR whose old word tells a
+// node met before.
+//
+// A node passes five stages, one a turn, every load of which is unconditional
+// and has a whole turn to arrive: its number; its buckets; its rows' descriptors;
+// the map of its lists' chunks of 64 entries (chunk t in lane t) and the loads of
+// the first kMarkSlots; the marks.  A lane past a chunk's end (entries of other
+// lists, or past the last list) marks no bit.  Four nodes are in hand, so the
+// turns are written out by fours, each node staying in its registers.
+//
+// Bound by vector instructions (300 a node; 1143 with a hash table of 8 KB by
+// compare-and-swap, whatever the wavefronts) and the latency that 6 wavefronts a
+// CU (n = 2*10^5) leave.  185,000 nodes of 160 to 2560 entries and the 15,000 wider
+// ones take 0.39 ms there; with the table (to 1024 entries) and the wide nodes'
+// workgroups for the rest it was 0.75.  24 slots 0.34 where 16 take 0.32.
+constexpr uint32_t kMarkSlots = 16;
+struct MarkNode {
+    uint32_t u, b;       // the node; the lane's bucket
+    uint2 d;             // the lane's row
+    uint32_t from, len;  // chunk `lane`
+    uint32_t count;      // chunks
+};
+__global__ void __launch_bounds__(64)
+k_fuse_marked(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
+              const uint32_t *__restrict__ small, uint32_t nsmall, const uint2 *__restrict__ rows,
+              const uint32_t *__restrict__ lists, int32_t *__restrict__ est) {
+    extern __shared__ __align__(16) uint32_t htab[];
+    const uint32_t lane = threadIdx.x, G = gridDim.x, words = ((n + 127) / 128) * 4;
+    auto clear = [&] {
+        for (uint32_t i = 4 * lane; i < words; i += 256)
+            *(uint4 *)(htab + i) = make_uint4(0u, 0u, 0u, 0u);
+    };
+    clear();
+    const uint32_t hash = lane < H ? lane : 0u;
+    const uint32_t *const mine = bucket + (size_t)hash * n;
+    const uint2 *const desc = rows + (size_t)hash * K;
+    // (past the list's end the last node again, of no chunk then)
+    auto number = [&](uint32_t i) { return small[min(i, nsmall - 1)]; };
+    auto buckets = [&](uint32_t u, MarkNode &x) {
+        x.u = u;
+        x.b = mine[u];
+    };
+    auto descriptors = [&](MarkNode &x) { x.d = desc[x.b]; };
+    // chunk t of the node's lists goes to lane t
+    auto chunks = [&](uint32_t i, MarkNode &x) {
+        const uint32_t l = i < nsmall && lane < H && x.d.y >> 30 == kRowOut ? x.d.y : 0u;
+        const uint32_t parts = (l + 63) / 64;
+        uint32_t upto = parts;
+#pragma unroll
+        for (int off = 1; off < 16; off <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)upto, off, 16);
+            if ((int)(lane & 15u) >= off) upto += y;
+        }
+        x.count = (uint32_t)__builtin_amdgcn_readlane((int)upto, 15);
+        const uint32_t first = upto - parts;
+        x.from = x.len = 0;
+        for (uint32_t k = 0; __ballot(k < parts); ++k) {
+            // a lane without a chunk k pushes nothing, to the last lane (there
+            // are fewer chunks than lanes)
+            const bool has = k < parts;
+            const int to = (int)(has ? 4 * (first + k) : 4 * 63u);
+            x.from += (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(has ? x.d.x + 64 * k : 0u));
+            x.len += (uint32_t)__builtin_amdgcn_ds_permute(to, (int)(has ? min(64u, l - 64 * k) : 0u));
+        }
+    };
+    auto entry = [&](const MarkNode &x, uint32_t t) {
+        return (lists + (uint32_t)__builtin_amdgcn_readlane((int)x.from, (int)t))[lane];
+    };
+    // the marks of 8 chunks from t on, and the words marked; adds the entries
+    // and those met before
+    auto mark = [&](const MarkNode &x, uint32_t t, const uint32_t *w, uint32_t *at, uint32_t &all,
+                    uint32_t &again) {
+        uint32_t bit[8], old[8];
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) {
+            const uint32_t l = (uint32_t)__builtin_amdgcn_readlane((int)x.len, (int)(t + k));
+            const uint32_t v = min(w[k], n - 1);
+            all += l;
+            at[k] = v >> 5;
+            bit[k] = lane < l ? 1u << (v & 31u) : 0u;
+            old[k] = atomicOr(htab + at[k], bit[k]);
+        }
+#pragma unroll
+        for (uint32_t k = 0; k < 8; ++k) again += (uint32_t)__popcll(__ballot(old[k] & bit[k]));
+    };
+    uint32_t ahead;  // the node of the turn after `last`
+    auto turn = [&](uint32_t i, MarkNode &now, MarkNode &next, MarkNode &third, MarkNode &last,
+                    uint32_t *w, uint32_t *wn) {
+        chunks(i + G, next);
+#pragma unroll
+        for (uint32_t t = 0; t < kMarkSlots; ++t) wn[t] = entry(next, t);
+        descriptors(third);
+        buckets(ahead, last);
+        ahead = number(i + 4 * G);
+        uint32_t at[kMarkSlots], all = 0, again = 0;
+#pragma unroll
+        for (uint32_t t = 0; t < kMarkSlots; t += 8) mark(now, t, w + t, at + t, all, again);
+        if (now.count > kMarkSlots) {
+            for (uint32_t t = kMarkSlots; t < now.count; t += 8) {
+                uint32_t x[8], words[8];
+#pragma unroll
+                for (uint32_t k = 0; k < 8; ++k) x[k] = entry(now, t + k);
+                mark(now, t, x, words, all, again);
+            }
+            clear();
+        } else {
+#pragma unroll
+            for (uint32_t t = 0; t < kMarkSlots; ++t) htab[at[t]] = 0u;
+        }
+        if (lane == 0) est[now.u] = (int32_t)(n - (all - again));
+    };
+    MarkNode a, b, c, d;
+    uint32_t w0[kMarkSlots], w1[kMarkSlots];
+    uint32_t i = blockIdx.x;
+    buckets(number(i), a);
+    buckets(number(i + G), b);
+    descriptors(a);
+    buckets(number(i + 2 * G), c);
+    descriptors(b);
+    ahead = number(i + 3 * G);
+    chunks(i, a);
+#pragma unroll
+    for (uint32_t t = 0; t < kMarkSlots; ++t) w0[t] = entry(a, t);
+    for (;;) {
+        turn(i, a, b, c, d, w0, w1);
+        if ((i += G) >= nsmall) break;
+        turn(i, b, c, d, a, w1, w0);
+        if ((i += G) >= nsmall) break;
+        turn(i, c, d, a, b, w0, w1);
+        if ((i += G) >= nsmall) break;
+        turn(i, d, a, b, c, w1, w0);
+        if ((i += G) >= nsmall) break;
+    }
+}
+
+// The same where n bits are too many: entries go into a hash table of 8 KB by
+// compare-and-swap (at most half full: kSmallHashed entries), kBatch chunks in
+// flight, 20 wavefronts a CU.  147,000 nodes of 600 entries took 0.53 ms here
+// (n = 2*10^5; 0.21 by marks).
+__global__ void __launch_bounds__(64)
+k_fuse_hashed(uint32_t n, uint32_t H, uint32_t K,
              const uint32_t *__restrict__ bucket, const uint8_t *__restrict__ cls,
              const uint2 *__restrict__ rows, const uint32_t *__restrict__ lists,
              int32_t *__restrict__ est) {
     extern __shared__ __align__(16) uint32_t htab[];
     const uint32_t lane = threadIdx.x;
-    const uint32_t none = HASHED ? 0xffffffffu : 0u;
-    const uint32_t words = HASHED ? kHashSlots : ((n + 127) / 128) * 4;
+    const uint32_t none = 0xffffffffu, words = kHashSlots;
     auto clear = [&] {
         for (uint32_t i = 4 * lane; i < words; i += 256)
             *(uint4 *)(htab + i) = make_uint4(none, none, none, none);
@@ -950,7 +1135,7 @@ k_fuse_small(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__
     for (uint32_t u = blockIdx.x; u < n; u += gridDim.x) {
         const uint32_t bu = b, cu = __builtin_amdgcn_readfirstlane(c);
         uint2 d = make_uint2(0u, 0u);
-        if ((cu == kNodeSmall || cu == kNodeInter) && lane < H) d = rows[(size_t)lane * K + bu];
+        if (cu == kNodeSmall && lane < H) d = rows[(size_t)lane * K + bu];
         buckets(n - u > gridDim.x ? u + gridDim.x : n, b, c);
         uint32_t mine = 0;
         if (cu == kNodeSmall) {
@@ -970,80 +1155,40 @@ k_fuse_small(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__
                                 w[q] = lists[o + lane];
                         }
                     }
-                    if (HASHED) {
 #pragma unroll
-                        for (uint32_t h = 0; h < kBatch; h += 4) {
-                            uint32_t at[4];
-                            bool open[4];
+                    for (uint32_t h = 0; h < kBatch; h += 4) {
+                        uint32_t at[4];
+                        bool open[4];
 #pragma unroll
-                            for (uint32_t k = 0; k < 4; ++k) {
-                                at[k] = (w[h + k] * 2654435761u) >> 21;
-                                open[k] = w[h + k] < n;
-                            }
-                            while (__ballot(open[0] | open[1] | open[2] | open[3])) {
-                                uint32_t old[4];
-#pragma unroll
-                                for (uint32_t k = 0; k < 4; ++k)
-                                    if (open[k]) old[k] = atomicCAS(htab + at[k], none, w[h + k]);
-#pragma unroll
-                                for (uint32_t k = 0; k < 4; ++k)
-                                    if (open[k]) {
-                                        mine += old[k] == none ? 1u : 0u;
-                                        open[k] = old[k] != none && old[k] != w[h + k];
-                                        at[k] = (at[k] + 1) & (kHashSlots - 1);
-                                    }
-                            }
+                        for (uint32_t k = 0; k < 4; ++k) {
+                            at[k] = (w[h + k] * 2654435761u) >> 21;
+                            open[k] = w[h + k] < n;
                         }
-                    } else {
+                        while (__ballot(open[0] | open[1] | open[2] | open[3])) {
+                            uint32_t old[4];
 #pragma unroll
-                        for (uint32_t q = 0; q < kBatch; ++q)
-                            if (w[q] < n) {
-                                const uint32_t bit = 1u << (w[q] & 31u);
-                                mine += (atomicOr(htab + (w[q] >> 5), bit) & bit) ? 0u : 1u;
-                            }
+                            for (uint32_t k = 0; k < 4; ++k)
+                                if (open[k]) old[k] = atomicCAS(htab + at[k], none, w[h + k]);
+#pragma unroll
+                            for (uint32_t k = 0; k < 4; ++k)
+                                if (open[k]) {
+                                    mine += old[k] == none ? 1u : 0u;
+                                    open[k] = old[k] != none && old[k] != w[h + k];
+                                    at[k] = (at[k] + 1) & (kHashSlots - 1);
+                                }
+                        }
                     }
                 }
             }
             __syncthreads();
             clear();
             __syncthreads();
-        } else if (cu == kNodeInter) {
-            // the shortest list of kept nodes
-            uint32_t key = d.y >> 30 == kRowKept ? (d.y & 0x3fffffffu) << 4 | lane : 0xffffffffu;
-#pragma unroll
-            for (int off = 8; off > 0; off >>= 1) key = min(key, (uint32_t)__shfl_xor(key, off, 16));
-            key = __builtin_amdgcn_readfirstlane(key);
-            const uint32_t js = key & 15u, len = key >> 4;
-            const uint32_t o = __builtin_amdgcn_readlane(d.x, js);
-            for (uint32_t i0 = 0; i0 < len; i0 += 64) {
-                const uint32_t w = i0 + lane < len ? lists[o + i0 + lane] : 0xffffffffu;
-                bool alive = w < n;
-                // the other hashes, from the one after js on
-                for (uint32_t k0 = 1; k0 < H; k0 += 4) {
-                    uint32_t hb[4];
-                    uint64_t x[4];
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) {
-                        const uint32_t j = (js + k0 + k) % H;
-                        hb[k] = alive && k0 + k < H ? bucket[(size_t)j * n + w] : 0u;
-                    }
-#pragma unroll
-                    for (uint32_t k = 0; k < 4; ++k) {
-                        const uint32_t j = (js + k0 + k) % H;
-                        const size_t r = (size_t)j * K + __builtin_amdgcn_readlane(bu, j);
-                        x[k] = alive && k0 + k < H ? P[r * ldK + (hb[k] >> 6)] >> (hb[k] & 63u) : 1ull;
-                    }
-                    alive = alive && (x[0] & x[1] & x[2] & x[3] & 1ull);
-                    if (__ballot(alive) == 0) break;
-                }
-                mine += alive ? 1u : 0u;
-            }
         } else {
             continue;
         }
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) mine += __shfl_xor(mine, off, 64);
-        if (lane == 0) est[u] = (int32_t)(cu == kNodeSmall ? n - mine : mine);
+        if (lane == 0) est[u] = (int32_t)(n - mine);
     }
 }
 
@@ -1206,8 +1351,8 @@ hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *b
 hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
                              const uint32_t *bucket, const int32_t *count, const int32_t *rowsum,
                              const uint8_t *cls, const unsigned long long *stats, FuseScratch s,
-                             uint32_t nbitmaps, const uint32_t *wide, uint32_t nwide, int32_t *est,
-                             hipStream_t st) {
+                             uint32_t nbitmaps, const uint32_t *wide,
+                             const unsigned long long *stats_host, int32_t *est, hipStream_t st) {
     uint32_t *lists = (uint32_t *)(s.bitmaps + (size_t)nbitmaps * ((n + 63) / 64));
     size_t lds = (size_t)K * 4;
     for (const void *k : {(const void *)k_bucket_hist, (const void *)k_bucket_nodes}) {
@@ -1233,12 +1378,24 @@ hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, co
                        lists);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    const bool hashed = n > kSmallBits;
-    lds = hashed ? kHashSlots * 4 : ((size_t)n + 127) / 128 * 16;
-    const uint32_t per_cu = (uint32_t)std::min<size_t>(kRecombineLds / lds, 32);
-    auto small = hashed ? k_fuse_small<true> : k_fuse_small<false>;
-    hipLaunchKernelGGL(small, dim3(grid_for(n, 1, 256 * per_cu)), dim3(64), lds, st, n, H, K, ldK, P,
-                       bucket, cls, s.rows, lists, est);
+    if (stats_host[kFuseInter]) {
+        hipLaunchKernelGGL(k_fuse_inter, dim3(grid_for(n, 64, 256 * 32)), dim3(64), 0, st, n, H, K, ldK,
+                           P, bucket, cls, s.rows, lists, est);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    const uint32_t nsmall = (uint32_t)stats_host[kFuseSmall], nwide = (uint32_t)stats_host[kFuseWide];
+    if (nsmall && n <= kMarkBits) {
+        lds = ((size_t)n + 127) / 128 * 16;
+        const uint32_t per_cu = (uint32_t)std::min<size_t>(kRecombineLds / lds, 20);
+        hipLaunchKernelGGL(k_fuse_marked, dim3(grid_for(nsmall, 1, 256 * per_cu)), dim3(64), lds, st, n,
+                           H, K, bucket, wide + n - nsmall, nsmall, s.rows, lists, est);
+    } else if (nsmall) {
+        lds = kHashSlots * 4;
+        const uint32_t per_cu = (uint32_t)std::min<size_t>(kRecombineLds / lds, 32);
+        hipLaunchKernelGGL(k_fuse_hashed, dim3(grid_for(n, 1, 256 * per_cu)), dim3(64), lds, st, n, H, K,
+                           bucket, cls, s.rows, lists, est);
+    }
     e = hipGetLastError();
     if (e != hipSuccess || nwide == 0) return e;
     if (nbitmaps) {

@@ -128,3 +128,26 @@ def test_rows_at_the_bounds_of_the_lists():
     P = np.packbits(bits, axis=2, bitorder="little").view(np.uint64)
     est = _check(n, bucket, count, P, us=np.arange(64))
     assert est[:8].tolist() == [n - 128, n - 129, 1024, 1025, n - 1, 1, 0, n]
+
+
+# about the last n whose nodes mark a bitmap of n bits, below it the last few
+# sizes of a bitmap in 16-byte steps; lists of none, one to several chunks of 64
+# entries, nodes of up to 16 chunks, more, and past 2560 entries
+@pytest.mark.parametrize("n,K,H,density", [
+    (8192, 300, 16, [0.995, 1.0]), (8193, 300, 16, [0.97, 1.0]), (12_289, 192, 3, [0.994]),
+    (65_537, 1024, 9, [0.9992, 1.0]), (65_600, 512, 16, [0.994, 0.999]),
+    (327_680, 1024, 4, [0.998]), (327_680, 1024, 4, [0.9997, 1.0]), (327_681, 1024, 4, [0.9997]),
+])
+def test_marked_and_hashed_nodes(n, K, H, density):
+    bucket, count, P = _proxies(n, H, K, density, seed=n + K)
+    us = np.concatenate([np.random.default_rng(n).integers(0, n, 250), [0, n - 1]])
+    _check(n, bucket, count, P, us=us)
+
+
+def test_lists_of_whole_chunks():
+    # every bucket holds 64 nodes, so a list ends where a chunk does
+    n, H, K = 16_384, 8, 256
+    _, _, P = _proxies(n, H, K, [0.98, 1.0], seed=11)
+    bucket = np.stack([np.random.default_rng(j).permutation(n) % K for j in range(H)]).astype(np.uint32)
+    count = np.full((H, K), 64, np.int32)
+    _check(n, bucket, count, P, us=np.arange(0, n, 37))
