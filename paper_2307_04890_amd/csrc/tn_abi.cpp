@@ -190,8 +190,9 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     const size_t slot_off = src_off + ((4 * ((size_t)hs.L + 1) + 255) & ~(size_t)255);
     const size_t pair_off =
         (slot_off + 4 * std::max<size_t>(hs.gat_src.size(), 1) + 255) & ~(size_t)255;
-    std::vector<uint32_t> lvl_src, slot, pairs;
+    std::vector<uint32_t> lvl_src, slot, pairs, quad, lvl_quad;
     if (columns) {
+        tn::hll_column_quads(hs, quad, lvl_quad);
         tn::hll_column_pairs(hs, tn::hll_columns_stride(n), pairs);
         lvl_src.assign((size_t)hs.L + 1, 0);
         slot.resize(hs.gat_src.size());
@@ -202,7 +203,9 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
             lvl_src[l + 1] = hs.gat_ptr.empty() ? 0u : hs.gat_ptr[hs.lvl_gat[l + 1]];
         }
     }
-    p->dev_bytes = columns ? pair_off + 4 * pairs.size()
+    const size_t quad_off = (pair_off + 4 * pairs.size() + 255) & ~(size_t)255;
+    const size_t lq_off = quad_off + 4 * quad.size();
+    p->dev_bytes = columns ? lq_off + 4 * lvl_quad.size()
                    : hll   ? src_off
                            : column_off + 4 * hs.column.size();
     hipError_t e = hipMalloc(&p->dev, p->dev_bytes);
@@ -222,6 +225,8 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
         put(src_off, lvl_src.data(), 4 * lvl_src.size());
         put(slot_off, slot.data(), 4 * slot.size());
         put(pair_off, pairs.data(), 4 * pairs.size());
+        put(quad_off, quad.data(), 4 * quad.size());
+        put(lq_off, lvl_quad.data(), 4 * lvl_quad.size());
     } else {
         const tn::DevOps at = tn::ops_view(hs, nullptr);  // offsets
         put((size_t)at.lvl, hs.lvl_op.data(), 4 * hs.lvl_op.size());
@@ -241,10 +246,13 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
             const unsigned char *d = (const unsigned char *)p->dev;
             p->columns = {hs.L,
                           (uint32_t)(pairs.size() / 128),
+                          (uint32_t)(quad.size() / 4),
                           (uint32_t)hs.gat_tgt.size(),
                           (uint32_t)hs.gat_src.size(),
                           p->gview.max_gat,
                           (const uint2 *)(d + pair_off),
+                          (const uint4 *)(d + quad_off),
+                          (const uint32_t *)(d + lq_off),
                           p->gview.lvl_gat,
                           (const uint32_t *)(d + src_off),
                           p->gview.gat_tgt,

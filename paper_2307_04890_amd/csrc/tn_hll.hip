@@ -265,8 +265,9 @@ k_hll_gathers_write(uint64_t *__restrict__ M, uint32_t nwords, uint32_t G,
 // maximum, then a lane per target writes it from its slot.  One wave's LDS
 // accesses happen in order, so every source of a level is read before a target
 // is written, without a barrier (a level's gathers touch other rows than its
-// pairs).  The bounds of 64 levels sit in the wave's lanes, the next 64 sources
-// and targets are requested one window ahead.
+// pairs).  Levels of small gathers (at most four sources, 64 gathers) skip the
+// slots: a lane per gather reads its sources and writes its target, from a block
+// of 64 requested one ahead.  The gathers of 64 levels sit in the wave's lanes.
 //
 // Saturation: a row holds at most g, the maximum over every node's own
 // registers, and one that holds g keeps it, so the
@@ -274,8 +275,9 @@ k_hll_gathers_write(uint64_t *__restrict__ M, uint32_t nwords, uint32_t G,
 //
 // Bound by the latency of a level (LDS reads, writes, the barrier), by bank
 // conflicts where levels are wide: n = 10^5, m = 10^6, 256
-// registers (1724 levels, 579 pairs on average) 0.70 ms, where a loop over level
-// starts and windows of pairs took 1.25 and a launch per level 6.5.
+// registers (1724 levels, 579 pairs on average) 0.64 ms, 0.70 with every gather
+// through its slot, 1.25 with a loop over level starts and windows of pairs, 6.5
+// with a launch per level.
 template <int C>
 struct ColT;
 template <>
@@ -335,73 +337,75 @@ k_hll_columns(HllColumns s, uint32_t n, uint32_t b, const uint64_t *__restrict__
         // no merge
     } else if (__builtin_amdgcn_readfirstlane(tid) >= W) {
         // the gathers
-        uint32_t l0 = 0, eg, es, spos = 0, gpos = 0;
+        uint32_t l0 = 0, lq;
         uint64_t some;  // which of the 64 levels have gathers
         auto bounds = [&] {
-            const uint32_t l = min(l0 + lane, s.L);
-            eg = s.lvl_gat[min(l + 1, s.L)];
-            es = s.lvl_src[min(l + 1, s.L)];
-            some = __ballot(s.lvl_gat[l] != eg);
+            lq = l0 + lane < s.L ? s.lvl_quad[l0 + lane] : 0u;
+            some = __ballot(lq != 0);
         };
         bounds();
-        // a window of sources, of targets: [base, base + 64), and the next
-        uint32_t sbase = 0, send = 0, gbase = 0, gend = 0, sid = 0, sslot = 0, tgt = 0;
-        uint32_t nsid = 0, nslot = 0, ntgt = 0;
-        auto sources = [&](uint32_t at) {
-            const uint32_t i = min(at + lane, s.sources - 1);
-            nsid = s.gat_src[i];
-            nslot = s.src_slot[i];
-        };
-        auto targets = [&](uint32_t at) { ntgt = s.gat_tgt[min(at + lane, s.gathers - 1)]; };
-        if (s.gathers) {
-            sources(0);
-            targets(0);
-        }
+        // a block of 64 quads, and the next
+        const uint32_t last = s.quads ? s.quads - 1 : 0u;
+        const uint4 *quads = s.quads ? s.quad : (const uint4 *)s.pair;
+        auto fetch = [&](uint32_t k) { return quads[min(64 * k + lane, last)]; };
+        uint4 now = fetch(0), next = fetch(1);
+        uint32_t block = 0;
         __syncthreads();
         for (uint32_t l = 0; l < s.L;) {
             l = __builtin_amdgcn_readfirstlane(l);
             l0 = __builtin_amdgcn_readfirstlane(l0);
             if ((some >> (l - l0)) & 1ull) {
-                const uint32_t sto = (uint32_t)__builtin_amdgcn_readlane((int)es, (int)(l - l0));
-                while (spos < sto) {
-                    if (spos >= send) {
-                        sbase = spos;
-                        send = spos + 64;
-                        sid = nsid;
-                        sslot = nslot;
-                        sources(send);
+                const uint32_t q = (uint32_t)__builtin_amdgcn_readlane((int)lq, (int)(l - l0));
+                const uint32_t first = q >> 8, count = q & 0xffu;
+                if (count != kHllBig) {
+                    if (first >> 6 != block) {  // the next one: blocks come in order
+                        block = first >> 6;
+                        now = next;
+                        next = fetch(block + 1);
                     }
-                    const uint32_t to = min(sto, send);
-                    if (sbase + lane >= spos && sbase + lane < to) {
-                        const uint32_t x = col[sid];
+                    if (lane - (first & 63u) < count) {
+                        const uint32_t w = col[now.x & kHllSource], x = col[now.y & kHllSource];
+                        const uint32_t y = col[now.z & kHllSource], z = col[now.w & kHllSource];
+                        col[now.x >> 18 | now.y >> 18 << 14] =
+                            (T)max_regs<C>(max_regs<C>(w, x), max_regs<C>(y, z));
+                    }
+                } else {
+                    const uint32_t g0 = s.lvl_gat[l], g1 = s.lvl_gat[l + 1];
+                    const uint32_t s0 = s.lvl_src[l], s1 = s.lvl_src[l + 1];
+                    // four rounds of sources, of targets in flight
+                    for (uint32_t i = s0 + lane; i < s1; i += 256) {
+                        uint32_t from[4], at[4];
 #pragma unroll
-                        for (int k = 0; k < C; ++k)
-                            atomicMax(&slot[sslot * C + k], (x >> (8 * k)) & 0xffu);
-                    }
-                    spos = to;
-                }
-                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-                const uint32_t gto = (uint32_t)__builtin_amdgcn_readlane((int)eg, (int)(l - l0));
-                const uint32_t g0 = gpos;
-                while (gpos < gto) {
-                    if (gpos >= gend) {
-                        gbase = gpos;
-                        gend = gpos + 64;
-                        tgt = ntgt;
-                        targets(gend);
-                    }
-                    const uint32_t to = min(gto, gend);
-                    if (gbase + lane >= gpos && gbase + lane < to) {
-                        uint32_t *v = slot + (gbase + lane - g0) * C;
-                        uint32_t x = 0;
-#pragma unroll
-                        for (int k = 0; k < C; ++k) {
-                            x |= v[k] << (8 * k);
-                            v[k] = 0;
+                        for (uint32_t r = 0; r < 4; ++r) {
+                            from[r] = s.gat_src[min(i + 64 * r, s1 - 1)];
+                            at[r] = s.src_slot[min(i + 64 * r, s1 - 1)];
                         }
-                        col[tgt] = (T)x;
+#pragma unroll
+                        for (uint32_t r = 0; r < 4; ++r) {
+                            const uint32_t x = col[from[r]];
+#pragma unroll
+                            for (int k = 0; k < C; ++k)
+                                atomicMax(&slot[at[r] * C + k], (x >> (8 * k)) & 0xffu);
+                        }
                     }
-                    gpos = to;
+                    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                    for (uint32_t i = g0 + lane; i < g1; i += 256) {
+                        uint32_t to[4];
+#pragma unroll
+                        for (uint32_t r = 0; r < 4; ++r) to[r] = s.gat_tgt[min(i + 64 * r, g1 - 1)];
+#pragma unroll
+                        for (uint32_t r = 0; r < 4; ++r) {
+                            if (i + 64 * r >= g1) continue;
+                            uint32_t *v = slot + (i + 64 * r - g0) * C;
+                            uint32_t x = 0;
+#pragma unroll
+                            for (int k = 0; k < C; ++k) {
+                                x |= v[k] << (8 * k);
+                                v[k] = 0;
+                            }
+                            col[to[r]] = (T)x;
+                        }
+                    }
                 }
             }
             __syncthreads();

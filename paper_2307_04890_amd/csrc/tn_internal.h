@@ -112,17 +112,26 @@ struct DevSchedule {
 // {u, v | kDirBit}, in blocks of 64, with kHllEnd set in u of the last of each
 // level and kHllLevel in u of pair i < 32 of a block where bit i of the level of
 // the block's first pair is (a level without pairs has one of two idle rows, as
-// the last block's padding has); of the gathers DevSchedule's arrays, the ends
-// of each level's sources, and of each source the index of its gather within
-// the level.
+// the last block's padding has).  Of the gathers:
+//  - levels of at most 64 gathers of at most four sources each: quads, in level
+//    order and in blocks of 64 that no level straddles (lvl_quad: the level's
+//    first quad and how many, 0 for other levels): the sources (18 bits, one
+//    repeated for fewer) and, in the upper bits of the first two words, the target;
+//  - the others (kHllBig in lvl_quad): DevSchedule's arrays, the ends of each
+//    level's sources, and of each source the index of its gather in the level.
 constexpr uint32_t kHllEnd = 0x80000000u, kHllLevel = 0x40000000u, kHllNode = 0x3fffffffu;
+constexpr uint32_t kHllBig = 0x80u, kHllSource = 0x3ffffu;
 struct HllColumns {
-    uint32_t L, blocks, gathers, sources, max_gat;
+    uint32_t L, blocks, quads, gathers, sources, max_gat;
     const uint2 *pair;
+    const uint4 *quad;
+    const uint32_t *lvl_quad;  // first << 8 | count, or kHllBig
     const uint32_t *lvl_gat, *lvl_src, *gat_tgt, *gat_src, *src_slot;
 };
 // The pairs of s in that form (2 uint32 each); stride: the first idle row.
 void hll_column_pairs(const HostSchedule &s, uint32_t stride, std::vector<uint32_t> &out);
+void hll_column_quads(const HostSchedule &s, std::vector<uint32_t> &quad,
+                      std::vector<uint32_t> &lvl_quad);
 
 // Device view of a binary-op schedule: level l owns ops [lvl[l], lvl[l+1]).
 struct DevOps {

@@ -642,6 +642,34 @@ void hll_column_pairs(const HostSchedule &s, uint32_t stride, std::vector<uint32
             if (first[k] >> i & 1) out[2 * (64 * k + i)] |= kHllLevel;
 }
 
+void hll_column_quads(const HostSchedule &s, std::vector<uint32_t> &quad,
+                      std::vector<uint32_t> &lvl_quad) {
+    lvl_quad.assign(s.L, 0);
+    quad.clear();
+    uint32_t at = 0;
+    for (uint32_t l = 0; l < s.L; ++l) {
+        const uint32_t g0 = s.lvl_gat[l], g1 = s.lvl_gat[l + 1], ng = g1 - g0;
+        if (ng == 0) continue;
+        bool big = ng > 64;
+        for (uint32_t q = g0; q < g1 && !big; ++q) big = s.gat_ptr[q + 1] - s.gat_ptr[q] > 4;
+        if (!big && at % 64 + ng > 64) at = (at + 63) & ~63u;
+        if (big || at >= 1u << 24) {
+            lvl_quad[l] = kHllBig;
+            continue;
+        }
+        lvl_quad[l] = at << 8 | ng;
+        quad.resize(4 * ((size_t)at + ng), 0);
+        for (uint32_t q = g0; q < g1; ++q, ++at) {
+            uint32_t *w = &quad[4 * (size_t)at];
+            const uint32_t p = s.gat_ptr[q], k = s.gat_ptr[q + 1] - p;
+            for (uint32_t i = 0; i < 4; ++i) w[i] = s.gat_src[p + std::min(i, k - 1)];
+            w[0] |= s.gat_tgt[q] << 18;
+            w[1] |= s.gat_tgt[q] >> 14 << 18;
+        }
+    }
+    quad.resize((quad.size() + 255) & ~(size_t)255, 0);
+}
+
 size_t ops_device_bytes(const HostSchedule &s) {
     return align256(4 * s.lvl_op.size()) + align256(4 * std::max<size_t>(s.ops.size(), 4));
 }

@@ -94,3 +94,24 @@ def test_blocks_of_pairs(m, flags):
     _both(2 * m + 2, (u, u + 1, np.zeros(m, np.int64)), 5, flags)
     k = np.arange(m, dtype=np.uint32)
     _both(m + 1, (k, k + 1, k.astype(np.int64)), 5, flags)
+
+
+@pytest.mark.parametrize("flags", [0, tn.DIRECTED | tn.FORWARD])
+@pytest.mark.parametrize("n", [700, 45_000])
+@pytest.mark.parametrize("leaves,stars", [(2, 1), (2, 21), (2, 22), (3, 16), (3, 17), (4, 3), (63, 1)])
+def test_levels_of_small_gathers(leaves, stars, n, flags):
+    # stars of 3 to 64 nodes, side by side in a step: centres of 3, 4, 5 and 64
+    # sources, levels of up to 64 gathers and of more, blocks of 64 that end
+    # within a step and between steps, pairs beside them
+    g = np.random.default_rng(n + leaves + stars)
+    src, dst, t = [], [], []
+    for step in range(200):
+        at = g.permutation(n)[:stars * (leaves + 1) + 2]
+        for c in range(stars if step % 7 else 1):
+            star = at[c * (leaves + 1):(c + 1) * (leaves + 1)]
+            src += [star[0]] * leaves
+            dst += list(star[1:])
+        src.append(at[-2])
+        dst.append(at[-1])
+        t += [step] * (len(src) - len(t))
+    _both(n, (np.asarray(src, np.uint32), np.asarray(dst, np.uint32), np.asarray(t, np.int64)), 6, flags)
