@@ -29,8 +29,10 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // tables cost their building and staging (n H K) and n / 64 words of each hash
 // per open node; the lists' side is the setup per row and entry, the union
 // nodes' entries and bitmaps (more where a node takes a hash table, past
-// kMarkBits nodes), and the random reads of intersections.  Below 8192 nodes
-// either takes about 0.1 ms, the tables with fewer launches.
+// kMarkBits nodes), and the random reads of intersections.  Below
+// kListMinN nodes the lists gain little (n = 10^4, H = 16, K = 512 0.106 against
+// 0.116 ms) or lose (n = 2*10^4, 0.43 against 0.33), and their totals cost each
+// call 10 us.
 bool fuse_by_lists(uint32_t n, uint32_t H, uint32_t K, const unsigned long long *stats,
                    unsigned long long entries, unsigned long long nbitmaps, size_t room) {
     using namespace tn;
@@ -607,7 +609,7 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
         return at;
     };
     const size_t rows = (size_t)H * K, lt_bytes = (size_t)qr * per_q;
-    const size_t o_stats = part(kFuseStats * 8), o_pt = part(rows * ldK * 8), o_rs = part(rows * 4),
+    const size_t o_stats = part(kFuseWords * 8), o_pt = part(rows * ldK * 8), o_rs = part(rows * 4),
                  o_full = part(rows), o_cls = part(n), o_open = part((size_t)n * 4),
                  o_wide = part((size_t)n * 4), o_bs = part((size_t)H * ((K + 63) / 64) * 4),
                  o_hist = part(lists_fit ? fuse_hist_words(H, K) * 4 : 0),
@@ -624,7 +626,7 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
     uint8_t *full = base + o_full, *cls = base + o_cls;
     uint32_t *open = (uint32_t *)(base + o_open), *wide = (uint32_t *)(base + o_wide);
     hipError_t e;
-    unsigned long long host[kFuseStats] = {};
+    unsigned long long host[kFuseWords] = {};
     {
         ProfScope ps(ctx, TN_K_AUX);
         e = launch_row_sums(H, K, ldK, P, count, bsum, rowsum, full, ctx->stream);
@@ -633,9 +635,12 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
                                 wide, stats, ctx->stream);
     }
     if (e == hipSuccess)
-        e = hipMemcpyAsync(host, stats, sizeof(host), hipMemcpyDeviceToHost, ctx->stream);
+        e = hipMemcpyAsync(host, stats, lists_fit ? sizeof(host) : sizeof(host[0]),
+                           hipMemcpyDeviceToHost, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) return hip_fail(e, "recombine set-up kernels");
+    for (int k = 0; k < kFuseParts; ++k)
+        for (int t = 0; t < 5; ++t) host[kFuseEntries + t] += host[kFuseStats + 8 * k + t];
     const uint32_t nlist = (uint32_t)host[kFuseOpen];
     if (nlist == 0) return TN_OK;  // est = n everywhere
     if (lists_fit) {

@@ -33,7 +33,12 @@ enum : int {
     kFuseCountMix = 6,
     kFuseSmall = 7,     // the small union nodes
     kFuseRows = 8,      // entries of each hash's lists, up to 16 hashes, and bitmaps
-    kFuseStats = 8 + 2 * 16
+    kFuseStats = 8 + 2 * 16,
+    // parts of kFuseEntries .. kFuseInter, kFuseNodeMix and kFuseCountMix, which
+    // the host adds up: kFuseParts of 64 bytes after the rest (hundreds of
+    // workgroups' atomics on one word took as long as the kernel's work)
+    kFuseParts = 32,
+    kFuseWords = kFuseStats + 8 * kFuseParts
 };
 struct FuseScratch {
     uint32_t *hist;        // fuse_hist_words

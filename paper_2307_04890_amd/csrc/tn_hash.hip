@@ -486,6 +486,7 @@ k_recombine_est2(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict_
 constexpr uint32_t kListPart = 64;        // lists of left-out nodes hold at most n / 64
 constexpr uint32_t kInterMax = 1u << 10;  // lists of kept nodes
 constexpr uint32_t kListSplit = 16;       // node ranges of a hash in the bucket sort
+constexpr uint32_t kListMinN = 24576;
 constexpr uint32_t kHashSlots = 2048;     // a small node's table: 8 KB
 constexpr uint32_t kSmallHashed = kHashSlots / 2, kSmallMarked = 2560;  // entries of a small node
 enum : uint8_t { kNodeDone = 0, kNodeSmall = 1, kNodeInter = 2, kNodeWide = 3 };
@@ -519,48 +520,49 @@ __device__ __forceinline__ unsigned long long bucket_mix(uint32_t j, uint32_t r)
 // Each node's kind (cls), its lifted sizes (lifted, nullable), est (n where
 // every row is full, else 0), the nodes some row of which is not full (open)
 // and of them the wide ones (wide, from its start) and the small ones (wide,
-// from its end); totals in stats.
+// from its end); totals in stats.  Without LISTS only what the tables need: the
+// lifted sizes, est and the open nodes.
+template <bool LISTS, uint32_t B>  // B hashes at a time
 __global__ void __launch_bounds__(256)
 k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
            const int32_t *__restrict__ rowsum, const uint8_t *__restrict__ full,
            int32_t *__restrict__ lifted, uint8_t *__restrict__ cls, int32_t *__restrict__ est,
            uint32_t *__restrict__ open, uint32_t *__restrict__ wide,
            unsigned long long *__restrict__ stats) {
-    __shared__ uint32_t nopen, nwide, nsmall, base[3];
-    __shared__ unsigned long long tot[4];
-    if (threadIdx.x < 4) tot[threadIdx.x] = 0;
-    unsigned long long entries = 0, bits = 0, inter = 0, sum = 0;
+    __shared__ uint32_t part[4][3], base[3];  // open, wide and small nodes
+    __shared__ unsigned long long tot[3];
+    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
+    if (threadIdx.x < 3) tot[threadIdx.x] = 0;
+    unsigned long long entries = 0, bits = 0, inter = 0;
     const uint32_t small = n <= kMarkBits ? kSmallMarked : kSmallHashed;
     for (uint32_t t0 = blockIdx.x * blockDim.x; t0 < n; t0 += gridDim.x * blockDim.x) {
         const uint32_t u = t0 + threadIdx.x;
-        if (threadIdx.x == 0) nopen = nwide = nsmall = 0;
-        __syncthreads();
-        uint32_t slot = 0xffffffffu, wslot = 0xffffffffu, sslot = 0xffffffffu;
+        bool all = true;
+        uint8_t c = kNodeDone;
         if (u < n) {
-            uint64_t zsum = 0, out = 0;
-            bool all = true;
+            uint64_t out = 0;
             uint32_t smin = 0xffffffffu, nbits = 0;
-            for (uint32_t j0 = 0; j0 < H; j0 += 8) {
-                uint32_t b[8];
-                int32_t s[8];
-                uint8_t f[8];
+            for (uint32_t j0 = 0; j0 < H; j0 += B) {
+                // past the last hash its loads again: none depends on a branch, so
+                // that all are in flight
+                uint32_t b[B];
+                int32_t s[B];
+                uint8_t f[B];
 #pragma unroll
-                for (uint32_t k = 0; k < 8; ++k)
-                    b[k] = j0 + k < H ? bucket[(size_t)(j0 + k) * n + u] : 0u;
+                for (uint32_t k = 0; k < B; ++k)
+                    b[k] = bucket[(size_t)min(j0 + k, H - 1) * n + u];
 #pragma unroll
-                for (uint32_t k = 0; k < 8; ++k)
-                    s[k] = j0 + k < H ? rowsum[(size_t)(j0 + k) * K + b[k]] : (int32_t)n;
+                for (uint32_t k = 0; k < B; ++k) s[k] = rowsum[(size_t)min(j0 + k, H - 1) * K + b[k]];
 #pragma unroll
-                for (uint32_t k = 0; k < 8; ++k)
-                    f[k] = j0 + k < H ? full[(size_t)(j0 + k) * K + b[k]] : (uint8_t)1;
+                for (uint32_t k = 0; k < B; ++k) f[k] = full[(size_t)min(j0 + k, H - 1) * K + b[k]];
 #pragma unroll
-                for (uint32_t k = 0; k < 8; ++k) {
-                    if (lifted && j0 + k < H) lifted[(size_t)(j0 + k) * n + u] = s[k];
-                    if (j0 + k < H) sum += bucket_mix(j0 + k, b[k]);
+                for (uint32_t k = 0; k < B; ++k) {
+                    if (j0 + k >= H) continue;
+                    if (lifted) lifted[(size_t)(j0 + k) * n + u] = s[k];
+                    all &= f[k] != 0;
+                    if (!LISTS) continue;
                     uint32_t len;
                     const uint32_t kind = row_list(n, s[k], len);
-                    zsum += n - (uint32_t)s[k];
-                    all &= f[k] != 0;
                     if (kind == kRowOut) out += len;
                     if (kind == kRowKept) smin = min(smin, len);
                     if (kind == kRowBits) ++nbits;
@@ -568,8 +570,7 @@ k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ buck
             }
             // an empty row keeps no node; rows without a left-out node make a
             // small node of no entries
-            uint8_t c = kNodeDone;
-            if (!all && smin != 0) {
+            if (LISTS && !all && smin != 0) {
                 if (smin != 0xffffffffu) {
                     c = kNodeInter;
                     inter += smin;
@@ -579,61 +580,92 @@ k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ buck
                     bits += nbits;
                 }
             }
-            cls[u] = c;
+            if (LISTS) cls[u] = c;
             est[u] = all ? (int32_t)n : 0;
-            if (!all) slot = atomicAdd(&nopen, 1u);
-            if (c == kNodeWide) wslot = atomicAdd(&nwide, 1u);
-            if (c == kNodeSmall) sslot = atomicAdd(&nsmall, 1u);
+        }
+        if (!__syncthreads_or(!all)) continue;
+        const uint64_t in[3] = {__ballot(!all), __ballot(c == kNodeWide), __ballot(c == kNodeSmall)};
+#pragma unroll
+        for (int k = 0; k < 3; ++k)
+            if (lane == 0) part[wave][k] = (uint32_t)__popcll(in[k]);
+        __syncthreads();
+        if (lane == 0 && wave < (LISTS ? 3u : 1u)) {  // a wavefront's atomic each
+            uint32_t some = 0;
+            for (uint32_t w = 0; w < blockDim.x >> 6; ++w) some += part[w][wave];
+            constexpr int at[3] = {kFuseOpen, kFuseWide, kFuseSmall};
+            if (some) base[wave] = (uint32_t)atomicAdd(stats + at[wave], (unsigned long long)some);
         }
         __syncthreads();
-        if (threadIdx.x == 0 && nopen) base[0] = (uint32_t)atomicAdd(stats + kFuseOpen, (unsigned long long)nopen);
-        if (threadIdx.x == 64 && nwide) base[1] = (uint32_t)atomicAdd(stats + kFuseWide, (unsigned long long)nwide);
-        if (threadIdx.x == 128 && nsmall) base[2] = (uint32_t)atomicAdd(stats + kFuseSmall, (unsigned long long)nsmall);
-        __syncthreads();
-        if (slot != 0xffffffffu) open[base[0] + slot] = u;
-        if (wslot != 0xffffffffu) wide[base[1] + wslot] = u;
-        if (sslot != 0xffffffffu) wide[n - 1 - (base[2] + sslot)] = u;
-        __syncthreads();
-    }
-    if (entries) atomicAdd(&tot[0], entries);
-    if (bits) atomicAdd(&tot[1], bits);
-    if (inter) atomicAdd(&tot[2], inter);
+        uint32_t slot[3];
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off, 64);
-    if ((threadIdx.x & 63u) == 0) atomicAdd(&tot[3], sum);
+        for (int k = 0; k < 3; ++k) {
+            slot[k] = base[k] + (uint32_t)__popcll(in[k] & ((1ull << lane) - 1ull));
+            for (uint32_t w = 0; w < wave; ++w) slot[k] += part[w][k];
+        }
+        if (!all) open[slot[0]] = u;
+        if (c == kNodeWide) wide[slot[1]] = u;
+        if (c == kNodeSmall) wide[n - 1 - slot[2]] = u;
+    }
+    if (!LISTS) return;
+    __syncthreads();  // tot is clear
+    auto add = [&](int k, unsigned long long v) {
+        if (__ballot(v != 0) == 0) return;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        if (lane == 0) atomicAdd(&tot[k], v);
+    };
+    add(0, entries);
+    add(1, bits);
+    add(2, inter);
     __syncthreads();
-    if (threadIdx.x < 4 && tot[threadIdx.x])
-        atomicAdd(stats + kFuseEntries + threadIdx.x, tot[threadIdx.x]);
+    // (hundreds of workgroups' atomics on one word took as long as the rest)
+    if (threadIdx.x < 3 && tot[threadIdx.x])
+        atomicAdd(stats + kFuseStats + 8 * (blockIdx.x % kFuseParts) + threadIdx.x, tot[threadIdx.x]);
 }
 
-// The lists' entries and the bitmaps of a hash's rows that some node meets,
-// and the sum of bucket_mix over its counts, added to stats.  One workgroup
-// per hash.
-__global__ void __launch_bounds__(1024)
-k_list_totals(uint32_t n, uint32_t K, const int32_t *__restrict__ count,
-              const int32_t *__restrict__ rowsum, unsigned long long *__restrict__ stats) {
-    __shared__ unsigned long long tot[3];
+// The lists' entries and the bitmaps of a hash's rows that some node meets, and
+// the sums of bucket_mix over its nodes and over its counts, added to stats.
+// Workgroups over (part of a hash's rows and nodes, hash); nothing to do where
+// no node is open.
+__global__ void __launch_bounds__(256)
+k_list_totals(uint32_t n, uint32_t K, const uint32_t *__restrict__ bucket,
+              const int32_t *__restrict__ count, const int32_t *__restrict__ rowsum,
+              unsigned long long *__restrict__ stats) {
+    __shared__ unsigned long long tot[4];
     if (stats[kFuseOpen] == 0) return;
-    const uint32_t j = blockIdx.x;
-    if (threadIdx.x < 3) tot[threadIdx.x] = 0;
-    unsigned long long v[3] = {};  // entries, bitmaps, mix
-    for (uint32_t r = threadIdx.x; r < K; r += blockDim.x) {
+    const uint32_t j = blockIdx.y, t = blockIdx.x * blockDim.x + threadIdx.x;
+    const uint32_t step = gridDim.x * blockDim.x;
+    if (threadIdx.x < 4) tot[threadIdx.x] = 0;
+    unsigned long long v[4] = {};  // entries, bitmaps, mixes of nodes and of counts
+    for (uint32_t r = t; r < K; r += step) {
         const int32_t c = count[(size_t)j * K + r];
-        v[2] += bucket_mix(j, r) * (unsigned long long)(uint32_t)c;
+        v[3] += bucket_mix(j, r) * (unsigned long long)(uint32_t)c;
         uint32_t len = 0;
         if (c && row_list(n, rowsum[(size_t)j * K + r], len) == kRowBits) ++v[1];
         v[0] += c ? len : 0u;
     }
+    const uint32_t *nj = bucket + (size_t)j * n;
+    for (uint32_t u0 = t; u0 < n; u0 += 8 * step) {
+        uint32_t b[8];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q) b[q] = nj[min(u0 + q * step, n - 1)];
+#pragma unroll
+        for (uint32_t q = 0; q < 8; ++q)
+            if (u0 + (uint64_t)q * step < n) v[2] += bucket_mix(j, b[q]);
+    }
     __syncthreads();
 #pragma unroll
-    for (int k = 0; k < 3; ++k) {
+    for (int k = 0; k < 4; ++k) {
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
         if ((threadIdx.x & 63u) == 0) atomicAdd(&tot[k], v[k]);
     }
     __syncthreads();
-    if (threadIdx.x < 2) stats[kFuseRows + 16 * threadIdx.x + j] = tot[threadIdx.x];
-    if (threadIdx.x == 2) atomicAdd(stats + kFuseCountMix, tot[2]);
+    if (threadIdx.x < 2 && tot[threadIdx.x])
+        atomicAdd(stats + kFuseRows + 16 * threadIdx.x + j, tot[threadIdx.x]);
+    if (threadIdx.x == 2 || threadIdx.x == 3)
+        atomicAdd(stats + kFuseStats + 8 * ((16 * blockIdx.y + blockIdx.x) % kFuseParts) + 1 + threadIdx.x,
+                  tot[threadIdx.x]);
 }
 
 // The nodes of each hash sorted by bucket, in three kernels over (range of
@@ -1326,7 +1358,7 @@ hipError_t launch_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *
 static size_t fuse_wide_lds(uint32_t n) { return ((size_t)n + 63) / 64 * 8; }
 
 bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K) {
-    return n >= 8192 && H <= kListHashes && K <= kListMaxK && fuse_wide_lds(n) + 64 <= kRecombineLds;
+    return n >= kListMinN && H <= kListHashes && K <= kListMaxK && fuse_wide_lds(n) + 64 <= kRecombineLds;
 }
 
 size_t fuse_hist_words(uint32_t H, uint32_t K) { return (size_t)H * kListSplit * K; }
@@ -1337,14 +1369,18 @@ hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *b
                            uint32_t *open, uint32_t *wide, unsigned long long *stats,
                            hipStream_t st) {
     hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(64), 0, st, (int32_t *)stats,
-                       (size_t)2 * kFuseStats);
+                       (size_t)2 * (lists ? kFuseWords : 1));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_classify, dim3(grid_for(n, 256, 512)), dim3(256), 0, st, n, H, K, bucket,
+    // (a wavefront a workgroup spreads the fewer nodes of calls without lists)
+    const uint32_t threads = lists ? 256 : 64;
+    auto k = H <= 8 ? (lists ? k_classify<true, 8> : k_classify<false, 8>)
+                    : (lists ? k_classify<true, 16> : k_classify<false, 16>);
+    hipLaunchKernelGGL(k, dim3(grid_for(n, threads, 512)), dim3(threads), 0, st, n, H, K, bucket,
                        rowsum, full, lifted, cls, est, open, wide, stats);
     e = hipGetLastError();
     if (e != hipSuccess || !lists) return e;
-    hipLaunchKernelGGL(k_list_totals, dim3(H), dim3(1024), 0, st, n, K, count, rowsum, stats);
+    hipLaunchKernelGGL(k_list_totals, dim3(16, H), dim3(256), 0, st, n, K, bucket, count, rowsum, stats);
     return hipGetLastError();
 }
 

@@ -400,6 +400,8 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
         if (e == hipSuccess) {
             ProfScope ps(ctx, TN_K_ROWOR);
             uint32_t zl = 0;
+            // (without saturation a chunk leaves no state: what it wrote is unknown)
+            if (!ctx->saturation) s.zero_open = false;
             if (s.zero_open) {
                 zl = zero_phase_levels(ch.hs, (int64_t)s.n - s.zero_ops);
                 if (zl < ch.hs.Lops) s.zero_open = false;

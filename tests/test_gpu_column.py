@@ -160,3 +160,25 @@ def test_batches_of_word_columns_match_single_plans(last, flags):
     finally:
         ctx.saturation(True)
         b.close()
+
+
+@pytest.mark.parametrize("n", [500, 9000, 20_407, 21_000])
+def test_saturation_switched_within_a_stream(n):
+    # batches with saturation off leave no slice state; those after it must not
+    # take the rows for the identity's
+    s, d, t = T.uniform_pairs(n, 900, 90, seed=9600 + n)
+    cut = np.searchsorted(t, [30, 60])
+    ctx = tn.get_context()
+    live = tn.Online(n, flags=tn.FORWARD)
+    try:
+        for k, on in enumerate((False, True, True)):
+            part = slice(*([0, *cut, len(t)][k:k + 2]))
+            ctx.saturation(on)
+            live.insert(s[part], d[part], t[part])
+        got = host(live.C)
+    finally:
+        ctx.saturation(True)
+        live.close()
+    p = tn.Plan(n, s, d, t, tn.FORWARD)
+    assert (got == host(p.execute(slice_words=1))).all()
+    p.close()

@@ -54,7 +54,7 @@ KINDS = {
 
 
 @pytest.mark.parametrize("kind", sorted(KINDS))
-# the lists start at 8192 nodes and take up to 16 hashes
+# (tables, and lists where they fit: up to 16 hashes, from 24,576 nodes on)
 @pytest.mark.parametrize("n,H,K", [(1, 1, 1), (1029, 16, 65), (5003, 2, 900), (8191, 3, 64), (8192, 3, 64),
                                    (8200, 16, 63), (9001, 5, 130), (10_000, 2, 1100), (9000, 17, 70)])
 def test_every_kind_of_row(kind, n, H, K):
@@ -130,11 +130,12 @@ def test_rows_at_the_bounds_of_the_lists():
     assert est[:8].tolist() == [n - 128, n - 129, 1024, 1025, n - 1, 1, 0, n]
 
 
-# about the last n whose nodes mark a bitmap of n bits, below it the last few
+# from the first n that takes lists on; about the last n whose nodes mark a bitmap of n bits, below it the last few
 # sizes of a bitmap in 16-byte steps; lists of none, one to several chunks of 64
 # entries, nodes of up to 16 chunks, more, and past 2560 entries
 @pytest.mark.parametrize("n,K,H,density", [
-    (8192, 300, 16, [0.995, 1.0]), (8193, 300, 16, [0.97, 1.0]), (12_289, 192, 3, [0.994]),
+    (24_575, 300, 16, [0.995, 1.0]), (24_576, 300, 16, [0.97, 1.0]), (24_577, 192, 3, [0.994]),
+    (24_700, 300, 16, [0.02, 0.98, 1.0]), (30_001, 130, 5, [0.01]), (26_000, 260, 4, [0.4, 1.0]),
     (65_537, 1024, 9, [0.9992, 1.0]), (65_600, 512, 16, [0.994, 0.999]),
     (327_680, 1024, 4, [0.998]), (327_680, 1024, 4, [0.9997, 1.0]), (327_681, 1024, 4, [0.9997]),
 ])
@@ -146,7 +147,7 @@ def test_marked_and_hashed_nodes(n, K, H, density):
 
 def test_lists_of_whole_chunks():
     # every bucket holds 64 nodes, so a list ends where a chunk does
-    n, H, K = 16_384, 8, 256
+    n, H, K = 32_768, 8, 512
     _, _, P = _proxies(n, H, K, [0.98, 1.0], seed=11)
     bucket = np.stack([np.random.default_rng(j).permutation(n) % K for j in range(H)]).astype(np.uint32)
     count = np.full((H, K), 64, np.int32)
