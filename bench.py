@@ -486,7 +486,8 @@ def run_hashed(args):
     lds_bound = 2 * lds_tiles >= tiles
     pmc_key = f"{workload}_K{K}"
     r["roofline"] = counter_roofline(load_traffic("batch", pmc_key), proxy_ms,
-                                     "k_batch_persistent", dense, achieved,
+                                     "k_rowor_column_tiles" if lds_tiles == tiles
+                                     else "k_batch_persistent", dense, achieved,
                                      "lds" if lds_bound else "global")
     r["hashed"] = {"H_times_m_events_per_s": H * m / (proxy_ms * 1e-3),
                    "recombine_ms": rec_ms,
@@ -719,7 +720,8 @@ def run_batched(args):
     # global-memory tiles whose rows stream through L2 and HBM
     lds_bound = 2 * lds_tiles >= tiles
     r["roofline"] = counter_roofline(load_traffic("batch", config["workload"]), batch_ms,
-                                     "k_batch_persistent", dense, achieved,
+                                     "k_rowor_column_tiles" if lds_tiles == tiles
+                                     else "k_batch_persistent", dense, achieved,
                                      "lds" if lds_bound else "global")
     r["batched"] = {"graph_launch_ms": batch_ms, "plain_network_by_network_ms": plain_ms,
                     "speedup_vs_plain": plain_ms / batch_ms, "tiles": tiles,

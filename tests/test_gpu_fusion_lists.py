@@ -152,3 +152,17 @@ def test_lists_of_whole_chunks():
     bucket = np.stack([np.random.default_rng(j).permutation(n) % K for j in range(H)]).astype(np.uint32)
     count = np.full((H, K), 64, np.int32)
     _check(n, bucket, count, P, us=np.arange(0, n, 37))
+
+
+@pytest.mark.parametrize("n,K,H", [(60_000, 1024, 16), (24_576, 400, 9), (100_003, 1500, 12)])
+def test_lists_with_some_intersections_and_bitmaps(n, K, H):
+    # mostly nearly full rows, so that lists are the cheaper way, with a few rows
+    # that keep little and a few in between: nodes of every kind
+    bucket, count, P = _proxies(n, H, K, [0.01] * 2 + [0.5] * 5 + [1.0] * 600 + [0.999] * 393, seed=n)
+    kept = np.bitwise_count(P).sum(axis=2)
+    of = np.stack([kept[j][bucket[j]] for j in range(H)])  # by node
+    pick = np.random.default_rng(n)
+    us = np.unique(np.concatenate([
+        pick.choice(np.flatnonzero(m), min(int(m.sum()), 120), replace=False)
+        for m in ((of < 0.05 * K).any(0), ((of > 0.3 * K) & (of < 0.7 * K)).any(0), (of > 0.9 * K).all(0))]))
+    _check(n, bucket, count, P, us=us)
