@@ -170,8 +170,9 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     tn::HostSchedule hs;
     std::string err;
     const bool hll = flags & TN_HLL;
-    tn_status st = tn::plan_events(n, m, src, dst, t, flags & ~(uint32_t)TN_HLL, hs, err, nullptr,
-                                   0, hll ? tn::kFormGather : tn::kFormOps | tn::kFormColumn);
+    tn_status st = tn::plan_events(
+        n, m, src, dst, t, flags & ~(uint32_t)TN_HLL, hs, err, nullptr, 0,
+        hll ? tn::kFormGather : tn::kFormOps | tn::kFormColumn | tn::kFormHalf);
     if (st != TN_OK) return fail(st, err);
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
@@ -179,7 +180,7 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     if (!p) return fail(TN_E_NOMEM, "plan allocation failed");
     p->device = ctx->device;
     p->hll = hll;
-    // a network whose word columns fit in LDS also keeps its ops in that form
+    // a network whose columns fit in LDS also keeps its ops in that form
     const bool column = !hll && hs.in_columns;
     const size_t column_off = tn::ops_device_bytes(hs);
     // a TN_HLL plan whose register columns fit in LDS also keeps its pairs in
@@ -470,7 +471,7 @@ tn_status plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld
     if (ld < nwords) return fail(TN_E_ARG, "ld must be >= ceil(n/64)");
     if (plan->device != ctx->device) return fail(TN_E_ARG, "plan lives on another device");
     if (plan->hll) return fail(TN_E_ARG, "a TN_HLL plan runs only tn_hll_execute");
-    // a network whose word columns fit in LDS, with the slice width left to
+    // a network whose columns fit in LDS, with the slice width left to
     // the library, runs on one workgroup per column
     const bool column = slice_words == 0 && plan->column;
     if (slice_words == 0) slice_words = tn::default_slice_words(n, ld);
@@ -486,11 +487,13 @@ tn_status plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld
         // room for the popcounts, made by any execution (without it the sizes
         // come from the matrix)
         const uint32_t stride = (n + 3u) & ~3u;
-        if (tn::ensure_scratch(ctx, (size_t)stride * (size_t)nwords) != TN_OK) {
+        const uint32_t columns = tn::rowor_column_count(n, plan->scratch_used);
+        if (tn::ensure_scratch(ctx, (size_t)stride * columns) != TN_OK) {
             (void)hipGetLastError();
         } else if (sizes) {
             sizes->pop = (uint8_t *)ctx->scratch;
             sizes->stride = stride;
+            sizes->columns = columns;
         }
         // the identity is part of the launch
         { tn::ProfScope ps(ctx, TN_K_IDENTITY); }

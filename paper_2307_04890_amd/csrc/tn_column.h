@@ -28,6 +28,15 @@ struct ColumnNet {
 inline bool rowor_column_fits(uint32_t n, uint32_t scratch_rows) {
     return (uint64_t)n + scratch_rows < kColumnRows;
 }
+// ... in a column of half words: ids of 15 bits, and 127 rows a lane of 256 (the
+// counters of the sizes).
+inline bool rowor_half_column_fits(uint32_t n, uint32_t scratch_rows) {
+    return n <= 127 * 256 && (uint64_t)n + scratch_rows <= kColumnRow;
+}
+// The columns that a launch from the identity runs.
+inline uint32_t rowor_column_count(uint32_t n, uint32_t scratch_rows) {
+    return rowor_column_fits(n, scratch_rows) ? (n + 63) / 64 : (n + 31) / 32;
+}
 // The column form of s (s.column not empty, or no ops): blocks and levels set.
 inline ColumnNet column_net(const HostSchedule &s) {
     ColumnNet net{};
@@ -42,13 +51,14 @@ inline ColumnNet column_net(const HostSchedule &s) {
 struct ColumnSizes {
     uint8_t *pop = nullptr;
     uint32_t stride = 0;
+    uint32_t columns = 0;  // rowor_column_count
     int32_t *in = nullptr;
 };
 // One network.  It loads and stores C once, keeps persist when given, and
 // counts those loads and stores in traffic (nullable); with saturation a
 // column stops once every real row of it is all ones.  fresh: C starts as the
 // identity, written here with its row padding, and the traffic counters are
-// set, not added to.  scratch_rows: those in use.  sizes (pop not null): with fresh.
+// set, not added to, and half columns will do.  scratch_rows: those in use.  sizes (pop not null): with fresh.
 hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratch_rows,
                                unsigned long long *traffic, bool saturation, bool fresh,
                                unsigned int *done_count, hipStream_t st,

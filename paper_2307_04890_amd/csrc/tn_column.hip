@@ -15,15 +15,20 @@ namespace tn {
 namespace {
 
 // Stores the column as rowor_column does, each row's popcount, and the column
-// popcounts of its 64 nodes (their in-sizes): a lane's rows enter bit-sliced
-// counters (7 planes: at most 80 rows a lane), which six exchanges between
+// popcounts of its nodes (their in-sizes): a lane's rows enter bit-sliced
+// counters (7 planes: at most 127 rows a lane), which six exchanges between
 // lanes turn into one count a lane.  The column is given up.  It adds about 2 us
 // to the launch and leaves an eighth of the matrix to read for the out-sizes:
 // execution and sizes of 1,000 nodes take 13.4 us, with a pass over the matrix
 // after it 22.1; of 10,007 nodes 166 and 171; of 20,000 660 and 713.
+template <typename T>
 __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, uint32_t n,
                                              const ColumnSizes &sizes) {
-    extern __shared__ uint64_t rows[];
+    constexpr uint32_t kBits = 8 * sizeof(T);
+    extern __shared__ uint64_t column[];
+    const T *const rows = reinterpret_cast<const T *>(column);
+    T *const C = reinterpret_cast<T *>(net.C);
+    const size_t ld = (size_t)net.ld * (64 / kBits);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, W = blockDim.x;
     uint8_t *const pop = sizes.pop + (size_t)w * sizes.stride;
     uint64_t c[7] = {};
@@ -34,7 +39,7 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
             const uint32_t r = r0 + k * W;
             x[k] = r < n ? rows[r] : 0ull;
             if (r < n) {
-                net.C[(size_t)r * net.ld + w] = x[k];
+                C[(size_t)r * ld + w] = (T)x[k];
                 pop[r] = (uint8_t)__popcll(x[k]);
             }
         }
@@ -83,13 +88,13 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
 #pragma unroll
     for (int i = 0; i < 13; ++i) v |= (int32_t)(p[i] & 1u) << i;
     // the wavefronts' counts add up where the first rows were
-    int32_t *const count = reinterpret_cast<int32_t *>(rows);
+    int32_t *const count = reinterpret_cast<int32_t *>(column);
     __syncthreads();
     if (tid < 64) count[tid] = 0;
     __syncthreads();
     atomicAdd(&count[lane], v);
     __syncthreads();
-    if (sizes.in && tid < 64 && 64 * w + tid < n) sizes.in[64 * w + tid] = count[tid];
+    if (sizes.in && tid < kBits && kBits * w + tid < n) sizes.in[kBits * w + tid] = count[tid];
 }
 
 // Word column w of one network (n real rows, then the scratch rows and the
@@ -107,42 +112,51 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
 // wavefront with an LDS ring of 16-byte ops), 10^4, 55: 275 (3270 on slices of C
 // in memory); random, 16,000, 699: 391 (6140 so); uniform, 1,000, 119: 16.  16
 // hashed proxies of 4096 nodes in one launch: 218 us, 1032 on wavefronts.
-template <bool FRESH, bool SIZES = false>
+//
+// T: a word, or half a word, where a column of words does not fit (from the
+// identity only, and no state is kept).  Twice the columns, of half the LDS
+// traffic each: where both fit, words are as fast or faster (us, words and
+// halves: activity-driven, 20,000 nodes, 682 and 1015; random, 10,007, 256 and
+// 326), and past that halves save the slices in memory (activity-driven, 10
+// events a node, 25,000 nodes: 2017 and 1446; uniform, 5, 31,000: 1139 and 428).
+template <bool FRESH, bool SIZES = false, typename T = uint64_t>
 __device__ __forceinline__ void
 rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool sat,
              unsigned int *__restrict__ done_count, const ColumnSizes &sizes = {}) {
-    extern __shared__ uint64_t rows[];
+    constexpr uint32_t kBits = 8 * sizeof(T);
+    extern __shared__ uint64_t column[];
+    T *const rows = reinterpret_cast<T *>(column);
     __shared__ uint32_t open, total;
-    uint64_t *const C = net.C;
-    const int64_t ld = net.ld;
+    T *const C = reinterpret_cast<T *>(net.C);
+    const int64_t ld = net.ld * (64 / kBits);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, W = blockDim.x;
-    const uint32_t rwords = (n + 31) / 32, tail = n & 63u;
-    const uint64_t fullw = (w + 1 < nwords || tail == 0) ? ~0ull : (1ull << tail) - 1ull;
+    const uint32_t rwords = (n + 31) / 32, tail = n % kBits;
+    const T fullw = (w + 1 < nwords || tail == 0) ? (T)~(T)0 : (T)(((T)1 << tail) - 1);
     uint32_t *pst = net.persist ? net.persist + (size_t)w * (2 * (size_t)rwords + 2) : nullptr;
     if (!FRESH && net.blocks == 0) return;  // C is left as it is
     if (pst && pst[0]) return;              // all ones already (uniform)
     if (tid == 0) open = total = 0;
     for (uint32_t r = tid; r < n; r += W)
-        rows[r] = FRESH ? ((r >> 6) == w ? 1ull << (r & 63u) : 0ull) : C[(size_t)r * ld + w];
+        rows[r] = FRESH ? (r / kBits == w ? (T)1 << (r % kBits) : (T)0) : C[(size_t)r * ld + w];
     if (net.blocks) {
-        run_levels<uint64_t>(
+        run_levels<T>(
             rows, net.ops, net.blocks, net.levels, W / 64, n, sat, &open,
             [](const uint2 &o) {
                 return LevelOps{o.x & kColumnRow, (o.x >> 16) & kColumnRow, o.y & kColumnRow,
                                 (o.y >> 16) & kColumnRow, __ballot((int32_t)o.x < 0),
                                 (uint32_t)__ballot((int32_t)o.y < 0)};
             },
-            [](uint64_t x, uint64_t y) { return x | y; },
-            [=](uint64_t v) { return v == fullw; });
+            [](T x, T y) { return x | y; },
+            [=](T v) { return v == fullw; });
     }
     __syncthreads();
-    if constexpr (SIZES) column_sizes(net, w, n, sizes);
+    if constexpr (SIZES) column_sizes<T>(net, w, n, sizes);
     else
         for (uint32_t r = tid; r < n; r += W) C[(size_t)r * ld + w] = rows[r];
     if (FRESH)
         for (int64_t p = (int64_t)nwords + w; p < ld; p += nwords)
-            for (uint32_t r = tid; r < n; r += W) C[(size_t)r * ld + p] = 0ull;
-    if (!pst) return;
+            for (uint32_t r = tid; r < n; r += W) C[(size_t)r * ld + p] = (T)0;
+    if (kBits != 64 || !pst) return;
     // the slice state, as the other kernels of the stream keep it
     uint32_t nfull = 0;
     for (uint32_t k = tid & ~63u; k < n; k += W) {
@@ -167,7 +181,7 @@ rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool
 
 // One network, one workgroup per word column.  traffic (nullable): the row
 // words loaded and stored, written here where FRESH, else added.
-template <bool FRESH, bool SIZES>
+template <bool FRESH, bool SIZES, typename T>
 __global__ void __launch_bounds__(1024)
 k_rowor_column(ColumnNet net, uint32_t n, uint32_t nwords, bool sat,
                unsigned int *__restrict__ done_count, unsigned long long *__restrict__ traffic,
@@ -175,13 +189,13 @@ k_rowor_column(ColumnNet net, uint32_t n, uint32_t nwords, bool sat,
     if (traffic && threadIdx.x < 2) {
         if (FRESH) {
             if (blockIdx.x == 0)
-                traffic[threadIdx.x] = net.blocks ? (unsigned long long)n * nwords : 0ull;
+                traffic[threadIdx.x] = net.blocks ? (unsigned long long)n * ((n + 63) / 64) : 0ull;
         } else {
             atomicAdd(traffic + threadIdx.x, (unsigned long long)n);
         }
     }
-    rowor_column<FRESH, SIZES>(net, xcd_slice(blockIdx.x, gridDim.x), n, nwords, sat, done_count,
-                               sizes);
+    rowor_column<FRESH, SIZES, T>(net, xcd_slice(blockIdx.x, gridDim.x), n, nwords, sat,
+                                  done_count, sizes);
 }
 
 // Many networks of n nodes (the hashed proxies): workgroup b runs word column
@@ -212,7 +226,7 @@ k_column_out_sizes(const uint8_t *__restrict__ pop, uint32_t stride, uint32_t n,
     __shared__ uint32_t part[8][4][64];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t r = (blockIdx.x * 64 + lane) * 4;
-    uint32_t even = 0, odd = 0;  // two rows each (at most 319 * 64 a row)
+    uint32_t even = 0, odd = 0;  // two rows each (at most n a row)
     if (r < n)
         for (uint32_t w = wave; w < nwords; w += 8) {
             const uint32_t x = *(const uint32_t *)(pop + (size_t)w * stride + r);
@@ -233,9 +247,9 @@ k_column_out_sizes(const uint8_t *__restrict__ pop, uint32_t stride, uint32_t n,
     }
 }
 
-// (32 rows at least: column_sizes' counts)
-size_t column_lds(uint32_t n, uint32_t scratch_rows) {
-    return std::max<size_t>((size_t)n + scratch_rows + 1, 32) * 8;
+// (256 bytes at least: column_sizes' counts)
+size_t column_lds(uint32_t n, uint32_t scratch_rows, size_t row_bytes = 8) {
+    return std::max<size_t>(((size_t)n + scratch_rows + 1) * row_bytes, 256);
 }
 
 // Threads of a workgroup, from the ops of a level on average: enough
@@ -252,16 +266,20 @@ hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratc
                                unsigned long long *traffic, bool saturation, bool fresh,
                                unsigned int *done_count, hipStream_t st, const ColumnSizes &sizes) {
     if (!fresh && net.blocks == 0) return hipSuccess;
-    if (!rowor_column_fits(n, scratch_rows)) return hipErrorInvalidValue;
-    const size_t lds = column_lds(n, scratch_rows);
+    const bool half = !rowor_column_fits(n, scratch_rows);
+    if (half && (!fresh || net.persist || !rowor_half_column_fits(n, scratch_rows)))
+        return hipErrorInvalidValue;
+    const size_t lds = column_lds(n, scratch_rows, half ? 4 : 8);
     const uint32_t threads = column_threads(64 * (int64_t)net.blocks, net.levels);
-    auto k = sizes.pop ? k_rowor_column<true, true>
-             : fresh   ? k_rowor_column<true, false>
-                       : k_rowor_column<false, false>;
+    auto k = half        ? (sizes.pop ? k_rowor_column<true, true, uint32_t>
+                                      : k_rowor_column<true, false, uint32_t>)
+             : sizes.pop ? k_rowor_column<true, true, uint64_t>
+             : fresh     ? k_rowor_column<true, false, uint64_t>
+                         : k_rowor_column<false, false, uint64_t>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
                                        (int)lds);
     if (e != hipSuccess) return e;
-    const uint32_t nwords = (n + 63) / 64;
+    const uint32_t nwords = half ? (n + 31) / 32 : (n + 63) / 64;
     hipLaunchKernelGGL(k, dim3(nwords), dim3(threads), lds, st, net, n, nwords, saturation,
                        done_count, traffic, sizes);
     return hipGetLastError();
@@ -270,7 +288,7 @@ hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratc
 hipError_t launch_column_out_sizes(const ColumnSizes &sizes, uint32_t n, int32_t *out,
                                    hipStream_t st) {
     hipLaunchKernelGGL(k_column_out_sizes, dim3((n + 255) / 256), dim3(512), 0, st, sizes.pop,
-                       sizes.stride, n, (n + 63) / 64, out);
+                       sizes.stride, n, sizes.columns, out);
     return hipGetLastError();
 }
 

@@ -34,8 +34,9 @@ constexpr uint32_t ops_scratch_rows(uint32_t n) {
     return n + kOpsScratchRows >= kColumnRows && n + 64 < kColumnRows ? kColumnRows - 1 - n
                                                                      : kOpsScratchRows;
 }
-// kFormColumn: the column form (tn_column.h) where the rows fit, else kFormOps
-enum : int { kFormGather = 1, kFormOps = 2, kFormColumn = 4 };
+// kFormColumn: the column form (tn_column.h) where the rows fit, else kFormOps;
+// with kFormHalf also where they fit half columns
+enum : int { kFormGather = 1, kFormOps = 2, kFormColumn = 4, kFormHalf = 8 };
 
 // A single network's schedule on the host.  Items are sorted by level;
 // level l owns pairs [lvl_pair[l], lvl_pair[l+1]) and gathers

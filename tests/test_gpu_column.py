@@ -67,6 +67,46 @@ def test_word_columns_in_lds_match_slices_in_memory(n, kind, per_node, flags):
         assert (host(want)[:, w0:w0 + 1] == got).all(), w0
 
 
+# half columns: their tail bits, the row ids (32,767 with the scratch rows) and
+# the counters (32,512 nodes), and too few ops for them
+@pytest.mark.parametrize("sat", [True, False])
+@pytest.mark.parametrize("n,kind,per_node", [
+    (20_416, "random", 3), (20_449, "uniform", 3), (25_001, "stars", 2), (31_743, "activity", 3),
+    (31_744, "activity", 3), (32_511, "uniform", 2), (32_512, "random", 2), (32_513, "random", 2),
+    (25_000, "uniform", 0.5)])
+def test_half_columns_match_slices_in_memory(n, kind, per_node, sat):
+    s, d, t = case(kind, n, per_node, 9700 + n)
+    p = tn.Plan(n, s, d, t)
+    ctx = tn.get_context()
+    want = host(p.execute(slice_words=1))
+    wout, winn = tn.component_sizes(p.execute(slice_words=1), n)
+    C = torch.full((n, oracle.words(n) + 3), -1, dtype=torch.int64, device="cuda")
+    try:
+        ctx.saturation(sat)
+        p.execute(C=C)
+        assert (host(C) == want).all()
+        C.fill_(-1)
+        E, out, inn = p.execute_sizes(C)
+        assert (host(E) == want).all()
+        assert torch.equal(out, wout) and torch.equal(inn, winn)
+    finally:
+        ctx.saturation(True)
+        p.close()
+
+
+def test_full_half_columns_reach_every_counter_plane():
+    # one op a level takes the fewest threads, so a lane counts 127 rows
+    n = 32_512
+    spokes = np.random.default_rng(9800).permutation(np.arange(1, n, dtype=np.uint32))
+    d = np.concatenate([spokes, spokes])
+    s, t = np.zeros_like(d), np.arange(len(d), dtype=np.int64)
+    p = tn.Plan(n, s, d, t)
+    C, out, inn = p.execute_sizes()
+    assert (host(C) == np.uint64(2**64 - 1)).all()  # 32,512 = 508 words
+    assert (out == n).all() and (inn == n).all()
+    p.close()
+
+
 @pytest.mark.parametrize("n", [1000, 9000])
 def test_full_columns_stop_and_are_counted(n):
     # every row fills up long before the earliest events: plans give the full
