@@ -573,14 +573,16 @@ def fusion_timing(args):
             "nodes_not_full": nlist, "estimates_below_n": float((e < n).mean()),
             "mean_estimate": float(e.mean()),
             "call_ms": 1e3 * elapsed / 3, "recombine_est_ms": est_ms, "other_kernels_ms": aux_ms,
-            "and_bytes": and_bytes, "bound": "lds",
-            "achieved_GBs": and_bytes / (est_ms * 1e-3) / 1e9,
-            "frac": and_bytes / (est_ms * 1e-3) / 1e9 / LDS_PEAK_GBS,
+            "dense_equivalent_bytes": and_bytes,
+            "dense_equivalent_frac": and_bytes / (est_ms * 1e-3) / 1e9 / LDS_PEAK_GBS,
+            "dense_equivalent_note": "the AND words that lifted tables in LDS would read (LDS peak "
+                                     "256 CU x 128 B/clk x 2.4 GHz); the estimates come from the "
+                                     "nodes of each row's smallest buckets instead, so not a "
+                                     "bandwidth",
             "traffic": traffic,
             "traffic_frac": (traffic / (est_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if traffic else None),
-            "note": "k_recombine_est: the AND words come from lifted tables staged in LDS "
-                    "(LDS peak 256 CU x 128 B/clk x 2.4 GHz); traffic = rocprofv3 FETCH_SIZE + "
-                    "WRITE_SIZE of its dispatches, against HBM"}
+            "note": "traffic = rocprofv3 FETCH_SIZE + WRITE_SIZE of the estimates' dispatches, "
+                    "against HBM"}
 
 
 def hashed_block(args):
@@ -664,10 +666,9 @@ def run_fusion(args):
               "K": f["K"], "generator": "activity", "parallelism": "single-gpu"}
     r = base_result(args, f["n"] / (f["call_ms"] * 1e-3), "nodes/s", 3, f["call_ms"], config)
     r["value_note"] = "fusion estimates of every node per second (one tn_recombine call)"
-    r["roofline"] = {"bound": "lds", "achieved": f["achieved_GBs"], "peak": LDS_PEAK_GBS,
-                     "unit": "GB/s", "frac": f["frac"], "traffic": f["traffic"],
-                     "kernel": "k_recombine_est", "algorithmic_bytes": f["and_bytes"],
-                     "avg_launch_ms": f["recombine_est_ms"]}
+    r["roofline"] = {"bound": "latency", "achieved": None, "peak": None, "unit": "GB/s",
+                     "frac": None, "traffic": f["traffic"], "kernel": "k_fuse_marked",
+                     "algorithmic_bytes": None, "avg_launch_ms": f["recombine_est_ms"]}
     r["fusion"] = f
     return r
 
