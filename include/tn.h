@@ -114,14 +114,16 @@ void tn_destroy(tn_ctx *ctx);
  * id, milliseconds) in launch order to HOST arrays ids / ms, clears all
  * records and returns how many it wrote (or a negative tn_status). */
 enum {
-    TN_K_IDENTITY = 1,     /* C <- I                                        */
+    TN_K_IDENTITY = 1,     /* C <- I (on word columns part of TN_K_ROWOR:
+                              an empty record)                              */
     TN_K_ROWOR = 2,        /* the level-by-level row-OR stream              */
     TN_K_OUT_SIZES = 3,    /* row popcounts; asked for with the column ones:
                               the start of both arrays                      */
     TN_K_IN_SIZES = 4,     /* column popcounts; asked for with the row ones:
-                              the one pass that counts both (part of
-                              TN_K_ROWOR where tn_plan_execute_sizes runs on
-                              word columns)                                 */
+                              the one pass that counts both.  Where
+                              tn_plan_execute_sizes runs on word columns
+                              TN_K_OUT_SIZES is a fill and TN_K_ROWOR the
+                              counts                                        */
     TN_K_BATCH = 5,        /* persistent multi-network row-OR               */
     TN_K_HASH = 6,         /* bucket map and bucket counts                  */
     TN_K_RECOMBINE = 7,    /* fusion of the hashed proxies                  */
@@ -348,8 +350,9 @@ tn_status tn_hll_build(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src,
  * (Sec. 3.4: rows only gain bits); its columns then count in every row's
  * out-size and have in-size n without a read of the matrix, so a saturated
  * network's sizes cost no second pass over C.  Other slices, and executions
- * that keep no state (saturation off, networks whose word columns fit
- * in LDS), are counted from C.  Arguments and errors as
+ * that keep no state (saturation off), are counted from C.  Where the
+ * network's word columns fit in LDS the sizes come with the launch that builds
+ * the matrix.  Arguments and errors as
  * tn_plan_execute and tn_component_sizes; out_sizes, in_sizes: DEVICE
  * int32[n], either may be NULL. */
 tn_status tn_plan_execute_sizes(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld,

@@ -460,10 +460,10 @@ tn_status ensure_traffic(tn_ctx *ctx) {
 }  // namespace
 
 namespace {
-// tn_plan_execute.  sizes (nullable): left with pop set where the launch on word
-// columns gave the in-sizes and the rows' popcounts too.
+// tn_plan_execute.  out_sizes, in_sizes (nullable): *sized is set where the launch
+// on word columns gave them too.
 tn_status plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld,
-                       uint32_t slice_words, tn::ColumnSizes *sizes) {
+                       uint32_t slice_words, int32_t *out_sizes, int32_t *in_sizes, bool *sized) {
     if (!ctx || !plan) return fail(TN_E_ARG, "ctx or plan is NULL");
     if (!C) return fail(TN_E_ARG, "C is NULL");
     const uint32_t n = plan->stats.n;
@@ -484,24 +484,23 @@ tn_status plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld
         ctx->state_sw = 0;
         tn_status st = ensure_traffic(ctx);
         if (st != TN_OK) return st;
-        // room for the popcounts, made by any execution (without it the sizes
-        // come from the matrix)
-        const uint32_t stride = (n + 3u) & ~3u;
-        const uint32_t columns = tn::rowor_column_count(n, plan->scratch_used);
-        if (tn::ensure_scratch(ctx, (size_t)stride * columns) != TN_OK) {
-            (void)hipGetLastError();
-        } else if (sizes) {
-            sizes->pop = (uint8_t *)ctx->scratch;
-            sizes->stride = stride;
-            sizes->columns = columns;
+        // the launch uses no scratch of the context, so that executions on
+        // several streams, and captured ones, are independent of each other
+        hipError_t e = hipSuccess;
+        if (out_sizes) {
+            tn::ProfScope ps(ctx, TN_K_OUT_SIZES);
+            e = tn::launch_fill_u32((uint32_t *)out_sizes, n, 0u, ctx->stream);
         }
         // the identity is part of the launch
         { tn::ProfScope ps(ctx, TN_K_IDENTITY); }
-        tn::ProfScope ps(ctx, TN_K_ROWOR);
-        hipError_t e = tn::launch_rowor_column(
-            {plan->column, plan->column_blocks, plan->column_levels, C, ld, nullptr}, n,
-            plan->scratch_used, ctx->traffic, ctx->saturation, true, nullptr, ctx->stream,
-            sizes ? *sizes : tn::ColumnSizes{});
+        if (e == hipSuccess) {
+            tn::ProfScope ps(ctx, TN_K_ROWOR);
+            e = tn::launch_rowor_column(
+                {plan->column, plan->column_blocks, plan->column_levels, C, ld, nullptr}, n,
+                plan->scratch_used, ctx->traffic, ctx->saturation, true, nullptr, ctx->stream,
+                {out_sizes, in_sizes});
+        }
+        *sized = true;
         return e == hipSuccess ? TN_OK : hip_fail(e, "row-OR kernel launch");
     }
     // per-workgroup sink words (for the widest grid of the launches below,
@@ -611,7 +610,8 @@ tn_status plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld
 
 tn_status tn_plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld,
                           uint32_t slice_words) {
-    return plan_execute(ctx, plan, C, ld, slice_words, nullptr);
+    bool sized = false;
+    return plan_execute(ctx, plan, C, ld, slice_words, nullptr, nullptr, &sized);
 }
 
 tn_status tn_set_saturation(tn_ctx *ctx, int enable) {
@@ -853,23 +853,9 @@ tn_status tn_component_sizes(tn_ctx *ctx, uint32_t n, const uint64_t *C, int64_t
 
 tn_status tn_plan_execute_sizes(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld,
                                 uint32_t slice_words, int32_t *out_sizes, int32_t *in_sizes) {
-    tn::ColumnSizes sizes;
-    sizes.in = in_sizes;
-    tn_status st = plan_execute(ctx, plan, C, ld, slice_words,
-                                out_sizes || in_sizes ? &sizes : nullptr);
-    if (st != TN_OK) return st;
-    if (sizes.pop) {
-        DeviceGuard g(ctx->device);
-        if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
-        hipError_t e = hipSuccess;
-        if (out_sizes) {
-            tn::ProfScope ps(ctx, TN_K_OUT_SIZES);
-            e = tn::launch_column_out_sizes(sizes, plan->stats.n, out_sizes, ctx->stream);
-        }
-        // the in-sizes are part of the row-OR launch
-        if (in_sizes) tn::ProfScope ps(ctx, TN_K_IN_SIZES);
-        return e == hipSuccess ? TN_OK : hip_fail(e, "size kernel launch");
-    }
+    bool sized = false;
+    tn_status st = plan_execute(ctx, plan, C, ld, slice_words, out_sizes, in_sizes, &sized);
+    if (st != TN_OK || sized) return st;
     // the state the execution just left describes exactly this matrix
     return component_sizes(ctx, plan->stats.n, C, ld, out_sizes, in_sizes, ctx->state,
                            ctx->state_sw);

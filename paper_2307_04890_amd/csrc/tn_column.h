@@ -33,10 +33,6 @@ inline bool rowor_column_fits(uint32_t n, uint32_t scratch_rows) {
 inline bool rowor_half_column_fits(uint32_t n, uint32_t scratch_rows) {
     return n <= 127 * 256 && (uint64_t)n + scratch_rows <= kColumnRow;
 }
-// The columns that a launch from the identity runs.
-inline uint32_t rowor_column_count(uint32_t n, uint32_t scratch_rows) {
-    return rowor_column_fits(n, scratch_rows) ? (n + 63) / 64 : (n + 31) / 32;
-}
 // The column form of s (s.column not empty, or no ops): blocks and levels set.
 inline ColumnNet column_net(const HostSchedule &s) {
     ColumnNet net{};
@@ -44,27 +40,22 @@ inline ColumnNet column_net(const HostSchedule &s) {
     net.levels = s.Lops;
     return net;
 }
-// Component sizes with a launch from the identity: the popcounts of word column
-// w's n rows go to bytes at pop + w * stride (stride a multiple of 4, at least
-// n rounded up to one), the in-sizes to in (nullable); launch_column_out_sizes
-// then sums the popcounts.
+// Component sizes with a launch from the identity (either nullable): out-sizes
+// are added to out, which is 0 before, in-sizes written to in.
 struct ColumnSizes {
-    uint8_t *pop = nullptr;
-    uint32_t stride = 0;
-    uint32_t columns = 0;  // rowor_column_count
+    int32_t *out = nullptr;
     int32_t *in = nullptr;
 };
 // One network.  It loads and stores C once, keeps persist when given, and
 // counts those loads and stores in traffic (nullable); with saturation a
 // column stops once every real row of it is all ones.  fresh: C starts as the
 // identity, written here with its row padding, and the traffic counters are
-// set, not added to, and half columns will do.  scratch_rows: those in use.  sizes (pop not null): with fresh.
+// set, not added to, and half columns will do.  scratch_rows: those in use.
+// sizes: with fresh.
 hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratch_rows,
                                unsigned long long *traffic, bool saturation, bool fresh,
                                unsigned int *done_count, hipStream_t st,
                                const ColumnSizes &sizes = {});
-hipError_t launch_column_out_sizes(const ColumnSizes &sizes, uint32_t n, int32_t *out,
-                                   hipStream_t st);
 // Many networks of n nodes (nets: DEVICE array), scratch rows in use up to
 // max_scratch_rows in every one; blocks, levels: theirs together.  fresh: every
 // matrix starts as the identity.

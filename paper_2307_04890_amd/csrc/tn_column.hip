@@ -14,13 +14,15 @@ namespace tn {
 
 namespace {
 
-// Stores the column as rowor_column does, each row's popcount, and the column
-// popcounts of its nodes (their in-sizes): a lane's rows enter bit-sliced
-// counters (7 planes: at most 127 rows a lane), which six exchanges between
-// lanes turn into one count a lane.  The column is given up.  It adds about 2 us
-// to the launch and leaves an eighth of the matrix to read for the out-sizes:
-// execution and sizes of 1,000 nodes take 13.4 us, with a pass over the matrix
-// after it 22.1; of 10,007 nodes 166 and 171; of 20,000 660 and 713.
+// Stores the column as rowor_column does, adds each row's popcount to the row's
+// out-size, and writes the column popcounts of its nodes (their in-sizes): a
+// lane's rows enter bit-sliced counters (7 planes: at most 127 rows a lane),
+// which six exchanges between lanes turn into one count a lane.  The column is
+// given up.  Execution and sizes take 13.9 us at 1,000 nodes (10.3 without the
+// sizes), 163 at 10,007 (153), 713 at 20,000 (679).  (A byte of popcount a row and
+// word column, summed by a second kernel, took 705 at 20,000, but n^2 / 64 bytes of
+// the context's, which executions on several streams and captured ones would
+// share.)
 template <typename T>
 __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, uint32_t n,
                                              const ColumnSizes &sizes) {
@@ -30,7 +32,6 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
     T *const C = reinterpret_cast<T *>(net.C);
     const size_t ld = (size_t)net.ld * (64 / kBits);
     const uint32_t tid = threadIdx.x, lane = tid & 63u, W = blockDim.x;
-    uint8_t *const pop = sizes.pop + (size_t)w * sizes.stride;
     uint64_t c[7] = {};
     for (uint32_t r0 = tid; r0 < n; r0 += 4 * W) {
         uint64_t x[4], t[2], u;
@@ -40,7 +41,7 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
             x[k] = r < n ? rows[r] : 0ull;
             if (r < n) {
                 C[(size_t)r * ld + w] = (T)x[k];
-                pop[r] = (uint8_t)__popcll(x[k]);
+                if (sizes.out && x[k]) atomicAdd(sizes.out + r, (int32_t)__popcll(x[k]));
             }
         }
         full_add(c[0], x[0], x[1], c[0], t[0]);
@@ -53,6 +54,7 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
             u = v;
         }
     }
+    if (!sizes.in) return;
     // halves of the bits go to halves of the lanes, planes added: bit `lane`
     // stays (bits past it are other lanes' and of no account)
     uint32_t p[13] = {};
@@ -94,7 +96,7 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
     __syncthreads();
     atomicAdd(&count[lane], v);
     __syncthreads();
-    if (sizes.in && tid < kBits && kBits * w + tid < n) sizes.in[kBits * w + tid] = count[tid];
+    if (tid < kBits && kBits * w + tid < n) sizes.in[kBits * w + tid] = count[tid];
 }
 
 // Word column w of one network (n real rows, then the scratch rows and the
@@ -217,36 +219,6 @@ k_rowor_column_tiles(const ColumnTileNet *__restrict__ nets, const uint2 *__rest
     rowor_column<true>(t.net, tile.y, t.n, t.nwords, sat, nullptr);
 }
 
-// out[r] = the sum of row r's popcounts over the word columns (bytes, stride
-// apart, a multiple of 4): a lane takes four rows, a workgroup's wavefronts the
-// columns in turn.
-__global__ void __launch_bounds__(512)
-k_column_out_sizes(const uint8_t *__restrict__ pop, uint32_t stride, uint32_t n, uint32_t nwords,
-                   int32_t *__restrict__ out) {
-    __shared__ uint32_t part[8][4][64];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t r = (blockIdx.x * 64 + lane) * 4;
-    uint32_t even = 0, odd = 0;  // two rows each (at most n a row)
-    if (r < n)
-        for (uint32_t w = wave; w < nwords; w += 8) {
-            const uint32_t x = *(const uint32_t *)(pop + (size_t)w * stride + r);
-            even += x & 0x00ff00ffu;
-            odd += (x >> 8) & 0x00ff00ffu;
-        }
-    part[wave][0][lane] = even & 0xffffu;
-    part[wave][1][lane] = odd & 0xffffu;
-    part[wave][2][lane] = even >> 16;
-    part[wave][3][lane] = odd >> 16;
-    __syncthreads();
-    if (threadIdx.x < 256) {
-        const uint32_t row = blockIdx.x * 256 + threadIdx.x;
-        uint32_t sum = 0;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) sum += part[k][threadIdx.x & 3u][threadIdx.x >> 2];
-        if (row < n) out[row] = (int32_t)sum;
-    }
-}
-
 // (256 bytes at least: column_sizes' counts)
 size_t column_lds(uint32_t n, uint32_t scratch_rows, size_t row_bytes = 8) {
     return std::max<size_t>(((size_t)n + scratch_rows + 1) * row_bytes, 256);
@@ -271,9 +243,10 @@ hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratc
         return hipErrorInvalidValue;
     const size_t lds = column_lds(n, scratch_rows, half ? 4 : 8);
     const uint32_t threads = column_threads(64 * (int64_t)net.blocks, net.levels);
-    auto k = half        ? (sizes.pop ? k_rowor_column<true, true, uint32_t>
-                                      : k_rowor_column<true, false, uint32_t>)
-             : sizes.pop ? k_rowor_column<true, true, uint64_t>
+    const bool sized = sizes.out || sizes.in;
+    auto k = half        ? (sized ? k_rowor_column<true, true, uint32_t>
+                                  : k_rowor_column<true, false, uint32_t>)
+             : sized     ? k_rowor_column<true, true, uint64_t>
              : fresh     ? k_rowor_column<true, false, uint64_t>
                          : k_rowor_column<false, false, uint64_t>;
     hipError_t e = hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -282,13 +255,6 @@ hipError_t launch_rowor_column(const ColumnNet &net, uint32_t n, uint32_t scratc
     const uint32_t nwords = half ? (n + 31) / 32 : (n + 63) / 64;
     hipLaunchKernelGGL(k, dim3(nwords), dim3(threads), lds, st, net, n, nwords, saturation,
                        done_count, traffic, sizes);
-    return hipGetLastError();
-}
-
-hipError_t launch_column_out_sizes(const ColumnSizes &sizes, uint32_t n, int32_t *out,
-                                   hipStream_t st) {
-    hipLaunchKernelGGL(k_column_out_sizes, dim3((n + 255) / 256), dim3(512), 0, st, sizes.pop,
-                       sizes.stride, n, sizes.columns, out);
     return hipGetLastError();
 }
 

@@ -222,3 +222,53 @@ def test_saturation_switched_within_a_stream(n):
     p = tn.Plan(n, s, d, t, tn.FORWARD)
     assert (got == host(p.execute(slice_words=1))).all()
     p.close()
+
+
+def test_sizes_of_plans_on_two_streams_of_one_context():
+    # a long execution on one stream while short ones run on another: nothing of
+    # the context's may pass between them
+    made = []
+    for n, per_node in ((16_000, 6), (1000, 3)):
+        p = tn.Plan(n, *case("uniform", n, per_node, 9900 + n))
+        C, out, inn = p.execute_sizes(slice_words=2)
+        # a set of outputs for each of several executions
+        outs = [(torch.empty_like(C), torch.empty_like(out), torch.empty_like(inn)) for _ in range(6)]
+        made.append((p, C, out, inn, outs, torch.cuda.Stream()))
+    for _, _, _, _, _, st in made:
+        st.wait_stream(torch.cuda.current_stream())
+    for i in range(6):
+        for p, _, _, _, outs, st in made:
+            with torch.cuda.stream(st):
+                for _ in range(1 if p.n > 1000 else 20):
+                    E, o, x = outs[i]
+                    p.execute_sizes(E, out=o, inn=x)
+    torch.cuda.synchronize()
+    for p, C, out, inn, outs, _ in made:
+        for E, o, x in outs:
+            assert torch.equal(E, C) and torch.equal(o, out) and torch.equal(x, inn), p.n
+        p.close()
+
+
+@pytest.mark.parametrize("n", [700, 12_000, 25_000])
+def test_captured_sizes_replay_after_other_calls(n):
+    # a graph holds the launches of a plan and nothing of the context's scratch,
+    # which later calls replace
+    p = tn.Plan(n, *case("uniform", n, 3, 9950 + n))
+    other = tn.Plan(40_000, *T.uniform_pairs(40_000, 40_000, 400, seed=9960))
+    wC, wout, winn = (a.clone() for a in p.execute_sizes(slice_words=1))
+    C, out, inn = p.execute_sizes()
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g, stream=st):
+        p.execute_sizes(C, out=out, inn=inn)
+    for sw in (1, 4, 16):  # larger scratch each time
+        other.execute_sizes(slice_words=sw)
+        for a in (C, out, inn):
+            a.fill_(-1)
+        g.replay()
+        torch.cuda.synchronize()
+        assert (host(C) == host(wC)).all()
+        assert torch.equal(out, wout) and torch.equal(inn, winn)
+    p.close()
+    other.close()
