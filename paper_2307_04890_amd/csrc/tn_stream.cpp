@@ -338,7 +338,7 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
 
     int64_t launched = 0, run_events = 0, levels = 0;
     tn_status st = TN_OK;
-    hipError_t e;
+    hipError_t e = hipSuccess;  // a chunk without ops uploads nothing
     for (int64_t c = 0; c < nch && !s.all_done; ++c) {
         Chunk &ch = *chunks[c];
         {

@@ -272,3 +272,19 @@ def test_captured_sizes_replay_after_other_calls(n):
         assert torch.equal(out, wout) and torch.equal(inn, winn)
     p.close()
     other.close()
+
+
+@pytest.mark.parametrize("n", [64, 9000, 21_000])
+def test_chunks_without_ops(n):
+    # self-loops leave nothing to run or to upload, in every chunk or in some
+    a = np.arange(60, dtype=np.uint32) % n
+    s, d, t = a, a.copy(), np.arange(60, dtype=np.int64)
+    for moved in (0, 25):  # events that join two nodes, at the end of the list
+        d[60 - moved:] = (a[60 - moved:] + 7) % n
+        C, st = tn.build_component_matrix_streamed(n, s, d, t, chunk_events=5)
+        assert (host(C) == oracle.reverse_matrix(n, s, d, t)).all() and st["chunks_run"] == 12
+        live = tn.Online(n, flags=tn.FORWARD)
+        for k in range(0, 60, 20):
+            live.insert(s[k:k + 20], d[k:k + 20], t[k:k + 20])
+        assert (host(live.C) == oracle.forward_matrix(n, s, d, t)).all()
+        live.close()
