@@ -33,6 +33,26 @@ inline bool rowor_column_fits(uint32_t n, uint32_t scratch_rows) {
 inline bool rowor_half_column_fits(uint32_t n, uint32_t scratch_rows) {
     return n <= 127 * 256 && (uint64_t)n + scratch_rows <= kColumnRow;
 }
+// Rounds of word columns, one a compute unit, that cover n nodes: a launch takes
+// about as long for each whatever its ops, as it reads or writes all of C.
+inline uint32_t rowor_column_rounds(uint32_t n) { return ((n + 63) / 64 + 255) / 256; }
+// Whether a stream whose first batch's largest chunk has so many events takes
+// one-word slices, so that chunks may run on word columns.  A second round of
+// columns only pays for larger chunks, and small ones take less on slices of two
+// words, a round of them (us an insert, activity-driven, 19,000 nodes, two-word
+// slices, one-word slices and columns: 1 event 37, 30, 113; 600 83, 135, 110;
+// 1,500 110, 182, 110; 2,000 126, 196, 118; 4,000 154, 254, 127).
+inline bool rowor_column_stream(uint32_t n, int64_t events) {
+    return rowor_column_rounds(n) == 1 || 12 * events >= (int64_t)n;
+}
+// Whether a chunk of so many events of such a stream runs on word columns: fewer
+// touch so few rows that slices in memory take less (us on two-word slices,
+// one-word slices and columns: 10,000 nodes, 1 event 49, 56, 57, 100 53, 68, 54;
+// 12,000 nodes, 100 events 39, 41, 53, 200 58, 69, 54; 16,000 nodes 48, 44, 66 and
+// 59, 66, 66; 20,400 nodes 54, 51, 121, 300 69, 97, 120, 600 85, 138, 115).
+inline bool rowor_column_chunk(uint32_t n, int64_t events) {
+    return n <= 10240 || (rowor_column_rounds(n) == 1 ? 80 : 48) * events >= (int64_t)n;
+}
 // The column form of s (s.column not empty, or no ops): blocks and levels set.
 inline ColumnNet column_net(const HostSchedule &s) {
     ColumnNet net{};

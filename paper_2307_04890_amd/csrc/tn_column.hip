@@ -138,8 +138,18 @@ rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool
     if (!FRESH && net.blocks == 0) return;  // C is left as it is
     if (pst && pst[0]) return;              // all ones already (uniform)
     if (tid == 0) open = total = 0;
-    for (uint32_t r = tid; r < n; r += W)
-        rows[r] = FRESH ? (r / kBits == w ? (T)1 << (r % kBits) : (T)0) : C[(size_t)r * ld + w];
+    if (FRESH) {
+        for (uint32_t r = tid; r < n; r += W) rows[r] = r / kBits == w ? (T)1 << (r % kBits) : (T)0;
+    } else {
+        for (uint32_t r0 = tid; r0 < n; r0 += 8 * W) {  // eight loads in flight
+            T x[8];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k) x[k] = C[(size_t)min(r0 + k * W, n - 1) * ld + w];
+#pragma unroll
+            for (uint32_t k = 0; k < 8; ++k)
+                if (r0 + k * W < n) rows[r0 + k * W] = x[k];
+        }
+    }
     if (net.blocks) {
         run_levels<T>(
             rows, net.ops, net.blocks, net.levels, W / 64, n, sat, &open,

@@ -219,6 +219,8 @@ void state_release(tn_ctx *ctx, StreamState &s) {
     s.persist = nullptr;
 }
 
+bool state_columns(uint32_t n) { return rowor_column_fits(n, ops_scratch_rows(n)); }
+
 // Allocates the state of an n-row matrix C and writes C <- I.
 tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, uint64_t *C,
                      int64_t ld) {
@@ -226,9 +228,6 @@ tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, ui
     s.flags = flags;
     s.C = C;
     s.ld = ld;
-    // one-word slices where chunks run on whole word columns in LDS
-    s.sw = rowor_column_fits(n, ops_scratch_rows(n)) ? 1u : default_slice_words(n, ld);
-    s.slices = rowor_workgroups(n, s.sw);
     hipError_t e;
     if (!ctx->traffic) {
         e = hipMalloc((void **)&ctx->traffic, 2 * sizeof(unsigned long long));
@@ -237,7 +236,8 @@ tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, ui
             return fail(TN_E_NOMEM, "traffic counter allocation failed");
         }
     }
-    const size_t pwords = rowor_persist_words(n, s.sw);
+    // room for either slice width (state_slices)
+    const size_t pwords = rowor_persist_words(n, state_columns(n) ? 1u : default_slice_words(n, ld));
     const tn_status st = stream_buffers_take(ctx, pwords + 1, &s.buf);
     if (st != TN_OK) return st;
     s.persist = s.buf->persist;
@@ -253,6 +253,15 @@ tn_status state_init(tn_ctx *ctx, StreamState &s, uint32_t n, uint32_t flags, ui
         return hip_fail(e, "identity kernel launch");
     }
     return TN_OK;
+}
+
+// The slices of a state that no chunk was applied to yet (all zero), from the
+// largest chunk of its first batch: one-word ones where chunks may run on whole
+// word columns in LDS.
+void state_slices(StreamState &s, int64_t events) {
+    s.sw = state_columns(s.n) && rowor_column_stream(s.n, events) ? 1u
+                                                                  : default_slice_words(s.n, s.ld);
+    s.slices = rowor_workgroups(s.n, s.sw);
 }
 
 // Applies events [0, m) (already validated) to the state in its direction:
@@ -286,6 +295,7 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
     // is freed only after the stream, as hipFree would wait for the device.
     int64_t max_events = 0;
     for (const auto &c : chunks) max_events = std::max(max_events, c->b - c->a);
+    if (s.launches == 0) state_slices(s, max_events);
     const size_t reserve_ops = (size_t)max_events + (size_t)max_events / 4 + 4;
     const size_t image_guess = s.sw == 1 ? align256(8 * reserve_ops)
                                          : align256(4 * (reserve_ops + 1)) + align256(16 * reserve_ops);
@@ -319,7 +329,9 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
             if (!stop.load()) {
                 ch.st = plan_events(s.n, ch.b - ch.a, src + ch.a, dst + ch.a, t + ch.a, s.flags,
                                     ch.hs, ch.err, nullptr, 0,
-                                    s.sw == 1 ? kFormColumn : kFormOps, &stop);
+                                    s.sw == 1 && rowor_column_chunk(s.n, ch.b - ch.a) ? kFormColumn
+                                                                                      : kFormOps,
+                                    &stop);
                 if (ch.st == TN_OK && !stop.load()) {
                     ch.column = ch.hs.in_columns;
                     if (!ch.column) ops_pack(ch.hs, ch.image);

@@ -288,3 +288,32 @@ def test_chunks_without_ops(n):
             live.insert(s[k:k + 20], d[k:k + 20], t[k:k + 20])
         assert (host(live.C) == oracle.forward_matrix(n, s, d, t)).all()
         live.close()
+
+
+@pytest.mark.parametrize("first", ["small", "large"])
+@pytest.mark.parametrize("off", [None, 1, 4])
+@pytest.mark.parametrize("n", [8192, 10_240, 10_241, 16_384, 16_385, 20_407])
+def test_streams_of_small_and_large_chunks(n, off, first):
+    # batches of few events run on slices in memory, larger ones on word columns,
+    # about the number of events that decides, one of them without saturation; the
+    # first batch of a network of more than 16,384 nodes decides on the slices
+    edge = -(-n // (80 if n <= 16_384 else 48))
+    sizes = [1 if first == "small" else -(-n // 12), edge, 3, edge - 1, 4 * n, 2, edge, 7]
+    s, d, t = T.uniform_pairs(n, sum(sizes), 3 * sum(sizes), seed=10_000 + n)
+    t = np.arange(len(t), dtype=np.int64)
+    ctx = tn.get_context()
+    live = tn.Online(n, flags=tn.FORWARD)
+    try:
+        at = 0
+        for k, m in enumerate(sizes):
+            ctx.saturation(k != off)
+            st = live.insert(s[at:at + m], d[at:at + m], t[at:at + m])
+            assert st["slice_words"] == (1 if n <= 16_384 or first == "large" else 2)
+            at += m
+        got = host(live.C)
+    finally:
+        ctx.saturation(True)
+        live.close()
+    p = tn.Plan(n, s, d, t, tn.FORWARD)
+    assert (got == host(p.execute(slice_words=1))).all()
+    p.close()
