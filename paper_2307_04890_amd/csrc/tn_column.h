@@ -53,6 +53,16 @@ inline bool rowor_column_stream(uint32_t n, int64_t events) {
 inline bool rowor_column_chunk(uint32_t n, int64_t events) {
     return n <= 10240 || (rowor_column_rounds(n) == 1 ? 80 : 48) * events >= (int64_t)n;
 }
+// Whether a plan of so many ops runs on word columns where only its matrix is asked
+// for: of fewer, slices in memory after an identity written by whole lines take
+// less (us on slices and columns, activity-driven: 3,000 nodes, no ops 7 and 7,
+// 30 ops 24 and 7; 8,000, none 7 and 14, 80 ops 20 and 15; 12,000, none 8 and 25,
+// 120 ops 26 and 26; 16,000, 160 ops 29 and 32, 800 64 and 34; 20,000, none 10 and
+// 48, 200 ops 31 and 50, 1,000 64 and 49).  With the sizes, which come with the
+// columns, columns are always faster or as fast (20,000 nodes, 200 ops 73 and 67).
+inline bool rowor_column_plan(uint32_t n, int64_t ops) {
+    return n <= 10240 ? ops > 0 || n <= 4096 : 64 * ops >= (int64_t)n * rowor_column_rounds(n);
+}
 // The column form of s (s.column not empty, or no ops): blocks and levels set.
 inline ColumnNet column_net(const HostSchedule &s) {
     ColumnNet net{};

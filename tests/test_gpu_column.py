@@ -317,3 +317,24 @@ def test_streams_of_small_and_large_chunks(n, off, first):
     p = tn.Plan(n, s, d, t, tn.FORWARD)
     assert (got == host(p.execute(slice_words=1))).all()
     p.close()
+
+
+@pytest.mark.parametrize("n", [4096, 4097, 10_240, 10_241, 16_384, 16_385, 20_407])
+def test_plans_of_few_ops(n):
+    # about the number of ops from which on a matrix alone is built on word columns;
+    # its sizes always come with them
+    edge = -(-n * (1 if n <= 16_384 else 2) // 64)
+    for m in (0, 1, edge - 1, edge):
+        s, d, t = T.uniform_pairs(n, m, max(1, m), seed=10_100 + n + m) if m else \
+            (np.zeros(0, np.uint32), np.zeros(0, np.uint32), np.zeros(0, np.int64))
+        t = np.arange(m, dtype=np.int64)
+        p = tn.Plan(n, s, d, t)
+        want = host(p.execute(slice_words=1))
+        C = torch.full((n, oracle.words(n) + 3), -1, dtype=torch.int64, device="cuda")
+        p.execute(C)
+        assert (host(C) == want).all(), m
+        wout, winn = tn.component_sizes(C, n)
+        C.fill_(-1)
+        _, out, inn = p.execute_sizes(C)
+        assert (host(C) == want).all() and torch.equal(out, wout) and torch.equal(inn, winn), m
+        p.close()
