@@ -376,13 +376,14 @@ tn_status tn_batch_create(tn_ctx *ctx, int32_t B, const uint32_t *n,
                           uint32_t flags, tn_batch **out);
 
 /* Builds all B component matrices in one graph launch.  Networks whose word
- * columns fit in LDS (n and the scratch rows in use under 20,472) run one
- * workgroup per column; of larger ones, workgroups of a persistent kernel
- * take (network, column slice) tiles from a device work queue, largest first.
- * The first call tunes the tile shape on the device, where there are tiles,
- * and captures the launches in a HIP graph; later calls with the same C / ld
- * replay it.  C: HOST array of B
- * DEVICE pointers, ld: HOST array of B leading dimensions. */
+ * columns fit in LDS (n and the scratch rows in use under 20,472) and that have
+ * an event per two nodes or more (or, where every network fits and none of more
+ * than 4,096 nodes has fewer, any events) run one workgroup per column; of the
+ * others, workgroups of a persistent kernel take (network, column slice) tiles
+ * from a device work queue, largest first.  The first call tunes the tile shape
+ * on the device, where there are tiles, and captures the launches in a HIP
+ * graph; later calls with the same C / ld replay it.  C: HOST array of B DEVICE
+ * pointers, ld: HOST array of B leading dimensions. */
 tn_status tn_batch_execute(tn_ctx *ctx, tn_batch *batch, uint64_t *const *C,
                            const int64_t *ld);
 

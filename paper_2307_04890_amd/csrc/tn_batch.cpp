@@ -152,7 +152,17 @@ void group_columns(tn_batch *b, std::vector<uint2> &tiles) {
         }
         tn_batch::ColumnGroup &g = b->groups.back();
         g.rows = std::max(g.rows, b->col_rows[t.net]);
-        for (uint32_t w = 0; w < b->nwords[t.net]; ++w) tiles.push_back(make_uint2(t.net, w));
+        // Workgroups go round the 8 XCDs: neighbouring columns, which share the
+        // matrix's lines, to one of them, whose L2 brings their words together (48
+        // networks of 500 to 20,000 nodes, us: no events 592, so 320; two a node
+        // 992, 882).
+        const uint32_t nw = b->nwords[t.net], at = g.count;
+        uint32_t next[8], w = 0;
+        for (uint32_t x = 0; x < 8; ++x) {
+            next[x] = w;
+            w += (nw + 7 - ((x - at) & 7u)) / 8;
+        }
+        for (uint32_t i = 0; i < nw; ++i) tiles.push_back(make_uint2(t.net, next[(at + i) & 7u]++));
         g.count = (uint32_t)tiles.size() - g.first;
     }
     b->col_tiles = (uint32_t)tiles.size();
@@ -462,15 +472,26 @@ tn_status plan_batch(int32_t B, const uint32_t *n, const int64_t *m, const uint3
     std::atomic<int32_t> next{0};
     const unsigned hw = std::max(1u, std::thread::hardware_concurrency());
     const unsigned nth = std::min<unsigned>(threads ? threads : hw, (unsigned)B);
+    const bool choose = (forms & kFormColumn) && (forms & kFormGather);
+    auto fits = [&](int32_t i) { return (forms & kFormColumn) && rowor_column_fits(n[i], 64); };
+    auto many = [&](int32_t i) { return 2 * m[i] >= (int64_t)n[i]; };
+    bool any_tiles = false;
+    for (int32_t i = 0; choose && i < B; ++i) any_tiles |= !fits(i) || (n[i] > 4096 && !many(i));
     auto worker = [&]() {
         for (;;) {
             const int32_t i = next.fetch_add(1);
             if (i >= B) return;
-            // the column form where it fits (batches on word columns and on
-            // LDS tiles of several words a row, us: 48 networks of 500 to
-            // 20,000 nodes 1881 and 6972, 100 of 200 to 2,000 417 and 2809, 16
-            // of 3,000 to 9,000 498 and 3732)
-            const bool column = forms == kFormColumn && rowor_column_fits(n[i], 64);
+            // the column form where it fits, and with a choice of forms where it
+            // pays: columns write a matrix by words, LDS tiles by several words a
+            // row, which takes less where few events come to a node (us on columns
+            // and tiles, 16 networks of 9,000 nodes, activity-driven, 0.1, 0.3 and 1
+            // event a node 126 and 107, 142 and 191, 220 and 449, uniform, 0.5 and 1
+            // 132 and 114, 140 and 163; 32 of 4,096, no events 57 and 60, one a node
+            // 93 and 369; 48 of 500 to 20,000, 20 a node and more 1690 and 5620).
+            // Small networks of few events go with the others (48 of 500 to 20,000,
+            // no events: 194 with those of 4,096 and fewer on columns beside the
+            // tiles, 167 all as tiles).
+            const bool column = fits(i) && (!choose || many(i) || (n[i] <= 4096 && !any_tiles));
             sts[i] = plan_events(n[i], m[i], src[i], dst[i], t[i], flags, hs[i], errs[i],
                                  maps ? maps[i] : nullptr, n_src, column ? kFormColumn : kFormGather);
             if (column && sts[i] == TN_OK && !hs[i].in_columns) {
@@ -500,7 +521,8 @@ tn_status batch_create(tn_ctx *ctx, int32_t B, const uint32_t *n, const int64_t 
     *out = nullptr;
     std::vector<HostSchedule> hs;
     std::string err;
-    tn_status st = plan_batch(B, n, m, src, dst, t, flags, hs, err, maps, n_src, 0, kFormColumn);
+    tn_status st = plan_batch(B, n, m, src, dst, t, flags, hs, err, maps, n_src, 0,
+                              kFormColumn | kFormGather);
     if (st != TN_OK) return fail(st, err);
     return batch_from_plans(ctx, B, n, flags, hs, out, stream);
 }

@@ -338,3 +338,38 @@ def test_plans_of_few_ops(n):
         _, out, inn = p.execute_sizes(C)
         assert (host(C) == want).all() and torch.equal(out, wout) and torch.equal(inn, winn), m
         p.close()
+
+
+@pytest.mark.parametrize("which", [
+    [(4096, 0), (4096, 100), (4097, 0), (4097, 2048), (4097, 2049), (9000, 4499), (9000, 4500), (20_407, 10),
+     (20_407, 10_204), (60, 3), (60, 40)],
+    [(4096, 0), (4097, 2049), (60, 3), (9000, 4500)], [(4096, 5), (60, 0)], [(60, 3), (4097, 2048)]])
+def test_batches_of_few_events(which):
+    # about the size and the number of events from which on a network runs on word
+    # columns, others as tiles beside them in one launch
+    nets = []
+    for k, (n, m) in enumerate(which):
+        ev = T.uniform_pairs(n, m, max(2, m // 40), seed=10_200 + k) if m else \
+            (np.zeros(0, np.uint32), np.zeros(0, np.uint32), np.zeros(0, np.int64))
+        nets.append((n, *ev))
+    want = []
+    for net in nets:
+        p = tn.Plan(*net)
+        want.append(host(p.execute(slice_words=1)))
+        p.close()
+    b = tn.Batch(nets)
+    ctx = tn.get_context()
+    try:
+        for sat in (True, False, True):
+            ctx.saturation(sat)
+            for lead in (0, 5):
+                Cs = [torch.full((n, oracle.words(n) + lead), -1, dtype=torch.int64, device="cuda")
+                      for n, *_ in nets]
+                for _ in range(3):
+                    b.execute(Cs)
+                    for k, (C, w) in enumerate(zip(Cs, want)):
+                        assert (host(C) == w).all(), (k, sat, lead)
+                        C.fill_(-1)
+    finally:
+        ctx.saturation(True)
+        b.close()
