@@ -35,6 +35,22 @@ tn_status not_built(const char *what) {
     return fail(TN_E_UNSUPPORTED, std::string(what) + " is not built in this library version");
 }
 
+// hipMalloc; where memory is short the stream buffers that the context keeps
+// between calls are given back first.
+hipError_t device_alloc(tn_ctx *ctx, void **p, size_t bytes) {
+    hipError_t e = hipMalloc(p, bytes);
+    if (e != hipSuccess && ctx->stream_kept) {
+        stream_buffers_free(ctx->stream_kept);
+        ctx->stream_kept = nullptr;
+        e = hipMalloc(p, bytes);
+    }
+    if (e != hipSuccess) {
+        *p = nullptr;
+        (void)hipGetLastError();  // reported here, not by a later launch
+    }
+    return e;
+}
+
 // Grows the context scratch to at least `bytes` (waits for the stream first,
 // since queued kernels may still use the old buffer).
 tn_status ensure_scratch(tn_ctx *ctx, size_t bytes) {
@@ -45,9 +61,8 @@ tn_status ensure_scratch(tn_ctx *ctx, size_t bytes) {
     ctx->scratch = nullptr;
     ctx->scratch_bytes = 0;
     size_t want = bytes < (1u << 20) ? (1u << 20) : bytes;
-    e = hipMalloc(&ctx->scratch, want);
+    e = device_alloc(ctx, &ctx->scratch, want);
     if (e != hipSuccess) {
-        ctx->scratch = nullptr;
         return fail(TN_E_NOMEM, "scratch allocation of " + std::to_string(want) + " bytes failed");
     }
     ctx->scratch_bytes = want;
@@ -209,7 +224,7 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     p->dev_bytes = columns ? lq_off + 4 * lvl_quad.size()
                    : hll   ? src_off
                            : column_off + 4 * hs.column.size();
-    hipError_t e = hipMalloc(&p->dev, p->dev_bytes);
+    hipError_t e = tn::device_alloc(ctx, &p->dev, p->dev_bytes);
     if (e != hipSuccess) {
         delete p;
         return fail(TN_E_NOMEM, "device schedule allocation failed");
@@ -427,7 +442,7 @@ tn_status plan_fwd(tn_ctx *ctx, const tn_plan *plan, uint32_t l0, uint32_t l1, v
     const size_t lb = (4 * flvl.size() + 255) & ~(size_t)255;
     const size_t bytes = lb + 4 * std::max<size_t>(fops.size(), 4);
     void *d = nullptr;
-    hipError_t e = hipMalloc(&d, bytes);
+    hipError_t e = tn::device_alloc(ctx, &d, bytes);
     if (e != hipSuccess) return fail(TN_E_NOMEM, "forwarded schedule allocation failed");
     e = hipMemcpyAsync(d, flvl.data(), 4 * flvl.size(), hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess && !fops.empty())

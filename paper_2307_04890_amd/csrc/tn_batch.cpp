@@ -262,7 +262,7 @@ tn_status apply_shape(tn_ctx *ctx, tn_batch *b, const BatchShape &shape) {
     const size_t o_scr = off; off = align256(off + sizeof(uint64_t) * std::max<size_t>(gscr_words, 1));
     const size_t o_cols = off; off = align256(off + sizeof(ColumnTileNet) * B);
     const size_t o_ctiles = off; off = align256(off + sizeof(uint2) * std::max<size_t>(col_tiles.size(), 1));
-    e = hipMalloc(&b->dev_meta, off);
+    e = device_alloc(ctx, &b->dev_meta, off);
     if (e != hipSuccess) {
         b->dev_meta = nullptr;
         return fail(TN_E_NOMEM, "batch metadata allocation failed");
@@ -547,7 +547,7 @@ tn_status batch_from_plans(tn_ctx *ctx, int32_t B, const uint32_t *n, uint32_t f
         total += align256(hs[i].in_columns ? std::max<size_t>(4 * hs[i].column.size(), 4)
                                            : schedule_device_bytes(hs[i]));
     }
-    hipError_t e = hipMalloc(&b->dev_sched, total);
+    hipError_t e = device_alloc(ctx, &b->dev_sched, total);
     if (e != hipSuccess) {
         delete b;
         return fail(TN_E_NOMEM, "batch schedule allocation failed");

@@ -330,6 +330,7 @@ void schedule_pieces(const HostSchedule &s, std::vector<SchedPiece> &out);
 
 // Grows the context scratch to at least `bytes`.
 tn_status ensure_scratch(tn_ctx *ctx, size_t bytes);
+hipError_t device_alloc(tn_ctx *ctx, void **p, size_t bytes);
 // Grows the context's pinned host staging buffer to at least `bytes`
 // (waits for the context's stream first; the buffer serves one call at a
 // time, like the device scratch).

@@ -1,0 +1,54 @@
+"""GPU memory that calls need: with little of it left they take the way that
+needs less, and the context gives back what it keeps between calls."""
+import contextlib
+import gc
+
+import numpy as np
+import pytest
+import torch
+
+import tn_inputs as T
+from gpu_util import host
+
+pytestmark = pytest.mark.gpu
+
+tn = pytest.importorskip("paper_2307_04890_amd")
+
+MB = 1 << 20
+
+
+def free_bytes():
+    torch.cuda.synchronize()
+    gc.collect()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+@contextlib.contextmanager
+def only(left):
+    """All but about `left` bytes of the device's free memory taken."""
+    hold = torch.empty(free_bytes() - left, dtype=torch.uint8, device="cuda")
+    try:
+        yield
+    finally:
+        del hold
+        torch.cuda.empty_cache()
+
+
+def test_kept_stream_buffers_are_given_back():
+    # a stream of large chunks leaves its ring (4 slots of 12 MB and more) with the
+    # context; a plan that does not fit beside it takes that memory
+    n, m = 40_000, 2_400_000
+    s, d, t = T.uniform_pairs(4000, m, m // 8, seed=1)  # 36,000 rows never fill
+    few = tuple(a[:2_000_000] for a in (s, d, t))
+    ctx = tn.Context()
+    p = tn.Plan(n, *few, ctx=ctx)
+    want = host(p.execute())
+    p.close()
+    st = tn.build_component_matrix_streamed(n, s, d, t, chunk_events=600_000, ctx=ctx)[1]
+    assert st["chunks_run"] >= 4
+    with only(16 * len(few[0]) - 16 * MB):
+        p = tn.Plan(n, *few, ctx=ctx)
+    assert (host(p.execute()) == want).all()
+    p.close()
+    ctx.close()
