@@ -39,14 +39,16 @@ tn_status not_built(const char *what) {
 // between calls are given back first.
 hipError_t device_alloc(tn_ctx *ctx, void **p, size_t bytes) {
     hipError_t e = hipMalloc(p, bytes);
-    if (e != hipSuccess && ctx->stream_kept) {
-        stream_buffers_free(ctx->stream_kept);
-        ctx->stream_kept = nullptr;
-        e = hipMalloc(p, bytes);
-    }
+    if (e == hipSuccess) return e;
+    (void)hipGetLastError();  // reported here, not by a later call
+    *p = nullptr;
+    if (!ctx->stream_kept) return e;
+    stream_buffers_free(ctx->stream_kept);
+    ctx->stream_kept = nullptr;
+    e = hipMalloc(p, bytes);
     if (e != hipSuccess) {
+        (void)hipGetLastError();
         *p = nullptr;
-        (void)hipGetLastError();  // reported here, not by a later launch
     }
     return e;
 }

@@ -27,11 +27,17 @@ def free_bytes():
 @contextlib.contextmanager
 def only(left):
     """All but about `left` bytes of the device's free memory taken."""
-    hold = torch.empty(free_bytes() - left, dtype=torch.uint8, device="cuda")
+    hold, free = [], free_bytes()
     try:
+        # (a large allocation leaves more than was reported before it)
+        for _ in range(4):
+            if free > left + 4 * MB:
+                hold.append(torch.empty(free - left, dtype=torch.uint8, device="cuda"))
+            free = torch.cuda.mem_get_info()[0]
+        assert abs(free - left) < 8 * MB
         yield
     finally:
-        del hold
+        hold.clear()
         torch.cuda.empty_cache()
 
 
