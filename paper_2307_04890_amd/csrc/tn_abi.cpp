@@ -732,16 +732,19 @@ tn_status tn_hll_execute(tn_ctx *ctx, const tn_plan *plan, uint32_t log2s,
     // maxima; other plans: per-workgroup sink words, then the compound scratch
     // rows
     const size_t gat_words = (size_t)std::max<uint32_t>(plan->gview.max_gat, 1) * nwords;
+    // columns of one register take scratch as large as M; a launch per level
+    // where there is no room for it
     const bool columns = plan->hll && plan->columns.lvl_src &&
                          tn::hll_columns_pay(n, plan->gview.max_gat, log2s, plan->stats.levels,
-                                             plan->stats.pairs);
-    {
+                                             plan->stats.pairs) &&
+                         tn::ensure_scratch(ctx, tn::hll_columns_scratch(n, plan->gview.max_gat,
+                                                                         log2s)) == TN_OK;
+    if (!columns) {
         const size_t words =
-            columns     ? tn::hll_columns_scratch(n, plan->gview.max_gat, log2s) / 8
-            : plan->hll ? gat_words + nwords + 1 + ((size_t)1 << log2s) / 2
-                        : (size_t)tn::rowmax_workgroups(nwords) * tn::kRoworSinkWords +
-                              (size_t)plan->scratch_rows *
-                                  (size_t)tn::scratch_stride((uint32_t)nwords);
+            plan->hll ? gat_words + nwords + 1 + ((size_t)1 << log2s) / 2
+                      : (size_t)tn::rowmax_workgroups(nwords) * tn::kRoworSinkWords +
+                            (size_t)plan->scratch_rows *
+                                (size_t)tn::scratch_stride((uint32_t)nwords);
         tn_status st = tn::ensure_scratch(ctx, sizeof(uint64_t) * words);
         if (st != TN_OK) return st;
     }

@@ -58,3 +58,28 @@ def test_kept_stream_buffers_are_given_back():
     assert (host(p.execute()) == want).all()
     p.close()
     ctx.close()
+
+
+def test_hll_columns_without_room_for_their_scratch():
+    # register columns of 50,000 nodes, 2,048 registers, need 102 MB beside the
+    # registers; a launch per level needs a few rows
+    n, b = 50_000, 11
+    s, d, t = T.activity_driven(n, 60_000, 60_000, seed=3)
+    h = np.random.default_rng(4).integers(0, 2**64, size=n, dtype=np.uint64)
+    p = tn.Plan(n, s, d, t, tn.HLL)
+    ctx = p.ctx = tn.Context()
+    want = torch.empty((n, 1 << b), dtype=torch.uint8, device="cuda")
+    west = torch.empty(n, dtype=torch.float64, device="cuda")
+    M, est = torch.empty_like(want), torch.empty_like(west)
+    before = free_bytes()
+    p.hll(h, b, M=want, est=west)
+    assert before - free_bytes() > 90 * MB  # on columns
+    ctx.close()
+    ctx = p.ctx = tn.Context()
+    with only(60 * MB):
+        p.hll(h, b, M=M, est=est)
+        torch.cuda.synchronize()
+    assert torch.equal(M, want) and torch.equal(est, west)
+    p.ctx = tn.get_context()
+    p.close()
+    ctx.close()
