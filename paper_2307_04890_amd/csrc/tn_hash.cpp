@@ -599,9 +599,10 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
     const size_t per_q = (size_t)H * K * 8;
     uint32_t qr = (uint32_t)std::max<size_t>(4, std::min<size_t>(nq, kLiftedBudget / per_q));
     qr = (qr + 3) / 4 * 4;
-    const bool lists_fit = fuse_lists_fit(n, H, K);
-    // the totals first (8-byte entries), the lifted tables last: bitmaps and
-    // lists take their place in a call without tables
+    bool lists_fit = fuse_lists_fit(n, H, K);
+    // the totals first (8-byte entries), then what the tables need, the lifted
+    // ones last of it: bitmaps and lists take their place in a call without
+    // tables; then the lists' set-up, without which the tables serve too
     size_t need = 0;
     auto part = [&](size_t bytes) {
         const size_t at = need;
@@ -612,12 +613,14 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
     const size_t o_stats = part(kFuseWords * 8), o_pt = part(rows * ldK * 8), o_rs = part(rows * 4),
                  o_full = part(rows), o_cls = part(n), o_open = part((size_t)n * 4),
                  o_wide = part((size_t)n * 4), o_bs = part((size_t)H * ((K + 63) / 64) * 4),
-                 o_hist = part(lists_fit ? fuse_hist_words(H, K) * 4 : 0),
-                 o_start = part(lists_fit ? (rows + H) * 4 : 0),
-                 o_nodes = part(lists_fit ? (size_t)H * n * 4 : 0),
-                 o_rows = part(lists_fit ? rows * 8 : 0), o_brow = part(lists_fit ? rows * 4 : 0),
-                 o_lt = part(lt_bytes);
-    tn_status st = ensure_scratch(ctx, need);
+                 o_lt = part(lt_bytes), tables = need,
+                 o_hist = part(fuse_hist_words(H, K) * 4), o_start = part((rows + H) * 4),
+                 o_nodes = part((size_t)H * n * 4), o_rows = part(rows * 8), o_brow = part(rows * 4);
+    tn_status st = ensure_scratch(ctx, lists_fit ? need : tables);
+    if (st == TN_E_NOMEM && lists_fit) {
+        lists_fit = false;
+        st = ensure_scratch(ctx, tables);
+    }
     if (st != TN_OK) return st;
     unsigned char *base = (unsigned char *)ctx->scratch;
     unsigned long long *stats = (unsigned long long *)(base + o_stats);

@@ -7,6 +7,7 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 import tn_inputs as T
 from gpu_util import host
 
@@ -82,4 +83,36 @@ def test_hll_columns_without_room_for_their_scratch():
     assert torch.equal(M, want) and torch.equal(est, west)
     p.ctx = tn.get_context()
     p.close()
+    ctx.close()
+
+
+def test_fusion_without_room_for_lists():
+    # the lists' set-up takes 83 MB more than the tables' 1.1 GB; either gives the
+    # oracle's estimates
+    n, H, K = 1_000_000, 16, 8192
+    g = np.random.default_rng(5)
+    bucket = g.integers(0, K, (H, n)).astype(np.uint32)
+    count = np.stack([np.bincount(b, minlength=K) for b in bucket]).astype(np.int32)
+    P = np.full((H, K, K // 64), ~np.uint64(0))
+    for j in range(H):
+        for r in g.integers(0, K, 40):  # all but a few of the others
+            for c in g.integers(0, K, 5):
+                if c != r:
+                    P[j, r, c // 64] &= ~(np.uint64(1) << np.uint64(c % 64))
+    args = (torch.from_numpy(P.view(np.int64)).cuda(), torch.from_numpy(bucket.view(np.int32)).cuda(),
+            torch.from_numpy(count).cuda(), n)
+    ctx = tn.Context()
+    before = free_bytes()
+    want, _ = tn.recombine(*args, lifted=False, ctx=ctx)
+    need = before - free_bytes()
+    ctx.close()
+    full = (P == ~np.uint64(0)).all(axis=2)
+    us = np.flatnonzero(~np.stack([full[j][bucket[j]] for j in range(H)]).all(axis=0))[:300]
+    we, _ = oracle.recombine(n, P, bucket, us)
+    assert (want.cpu().numpy()[us] == we).all() and (we < n).any()
+    ctx = tn.Context()
+    with only(need - 40 * MB):
+        est, _ = tn.recombine(*args, lifted=False, ctx=ctx)
+        torch.cuda.synchronize()
+    assert torch.equal(est, want)
     ctx.close()
