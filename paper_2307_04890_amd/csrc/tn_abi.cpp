@@ -198,16 +198,11 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
     p->device = ctx->device;
     p->hll = hll;
     // a network whose columns fit in LDS also keeps its ops in that form
-    const bool column = !hll && hs.in_columns;
-    const size_t column_off = tn::ops_device_bytes(hs);
+    bool column = !hll && hs.in_columns;
     // a TN_HLL plan whose register columns fit in LDS also keeps its pairs in
     // blocks, the ends of each level's gather sources and each source's gather
     // within its level
-    const bool columns = hll && tn::hll_columns_fit(n, (uint32_t)hs.max_level_gathers);
-    const size_t src_off = hll ? tn::schedule_device_bytes(hs) : 0;
-    const size_t slot_off = src_off + ((4 * ((size_t)hs.L + 1) + 255) & ~(size_t)255);
-    const size_t pair_off =
-        (slot_off + 4 * std::max<size_t>(hs.gat_src.size(), 1) + 255) & ~(size_t)255;
+    bool columns = hll && tn::hll_columns_fit(n, (uint32_t)hs.max_level_gathers);
     std::vector<uint32_t> lvl_src, slot, pairs, quad, lvl_quad;
     if (columns) {
         tn::hll_column_quads(hs, quad, lvl_quad);
@@ -221,36 +216,53 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
             lvl_src[l + 1] = hs.gat_ptr.empty() ? 0u : hs.gat_ptr[hs.lvl_gat[l + 1]];
         }
     }
-    const size_t quad_off = (pair_off + 4 * pairs.size() + 255) & ~(size_t)255;
-    const size_t lq_off = quad_off + 4 * quad.size();
-    p->dev_bytes = columns ? lq_off + 4 * lvl_quad.size()
-                   : hll   ? src_off
-                           : column_off + 4 * hs.column.size();
-    hipError_t e = tn::device_alloc(ctx, &p->dev, p->dev_bytes);
+    // the device image: the schedule, then those
+    std::vector<tn::SchedPiece> pieces;
+    if (hll) {
+        tn::schedule_pieces(hs, pieces);
+    } else {
+        const tn::DevOps at = tn::ops_view(hs, nullptr);  // offsets
+        pieces.push_back({(size_t)at.lvl, hs.lvl_op.data(), 4 * hs.lvl_op.size()});
+        pieces.push_back({(size_t)at.ops, hs.ops.data(), 4 * hs.ops.size()});
+    }
+    const size_t base = hll ? tn::schedule_device_bytes(hs) : tn::ops_device_bytes(hs);
+    const size_t base_pieces = pieces.size();
+    size_t total = base;
+    auto add = [&](const std::vector<uint32_t> &v) {
+        const size_t at = total;
+        pieces.push_back({at, v.data(), 4 * v.size()});
+        total = (at + 4 * std::max<size_t>(v.size(), 1) + 255) & ~(size_t)255;
+        return at;
+    };
+    const size_t column_off = column ? add(hs.column) : 0;
+    const size_t src_off = columns ? add(lvl_src) : 0, slot_off = columns ? add(slot) : 0,
+                 pair_off = columns ? add(pairs) : 0, quad_off = columns ? add(quad) : 0,
+                 lq_off = columns ? add(lvl_quad) : 0;
+    hipError_t e = tn::device_alloc(ctx, &p->dev, total);
+    if (e != hipSuccess && total > base) {
+        // without the columns' forms, which the plan runs without as well
+        column = columns = false;
+        total = base;
+        pieces.resize(base_pieces);
+        e = tn::device_alloc(ctx, &p->dev, total);
+    }
     if (e != hipSuccess) {
         delete p;
         return fail(TN_E_NOMEM, "device schedule allocation failed");
     }
-    auto put = [&](size_t off, const void *from, size_t bytes) {
-        if (bytes && e == hipSuccess)
-            e = hipMemcpyAsync((unsigned char *)p->dev + off, from, bytes, hipMemcpyHostToDevice,
-                               ctx->stream);
-    };
-    if (hll) {
-        std::vector<tn::SchedPiece> pieces;
-        tn::schedule_pieces(hs, pieces);
-        for (const tn::SchedPiece &pc : pieces) put(pc.off, pc.src, pc.bytes);
-        put(src_off, lvl_src.data(), 4 * lvl_src.size());
-        put(slot_off, slot.data(), 4 * slot.size());
-        put(pair_off, pairs.data(), 4 * pairs.size());
-        put(quad_off, quad.data(), 4 * quad.size());
-        put(lq_off, lvl_quad.data(), 4 * lvl_quad.size());
-    } else {
-        const tn::DevOps at = tn::ops_view(hs, nullptr);  // offsets
-        put((size_t)at.lvl, hs.lvl_op.data(), 4 * hs.lvl_op.size());
-        put((size_t)at.ops, hs.ops.data(), 4 * hs.ops.size());
-        put(column_off, hs.column.data(), 4 * hs.column.size());
+    p->dev_bytes = total;
+    // small plans as one copy: each takes the host 8 us
+    std::vector<unsigned char> image;
+    if (total <= ((size_t)1 << 20)) {
+        image.resize(total);
+        for (const tn::SchedPiece &pc : pieces)
+            if (pc.bytes) std::memcpy(image.data() + pc.off, pc.src, pc.bytes);
+        pieces.assign(1, {0, image.data(), total});
     }
+    for (const tn::SchedPiece &pc : pieces)
+        if (pc.bytes && e == hipSuccess)
+            e = hipMemcpyAsync((unsigned char *)p->dev + pc.off, pc.src, pc.bytes,
+                               hipMemcpyHostToDevice, ctx->stream);
     if (e == hipSuccess) e = hipStreamSynchronize(ctx->stream);
     if (e != hipSuccess) {
         (void)hipFree(p->dev);
@@ -258,6 +270,7 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
         return hip_fail(e, "schedule upload");
     }
     tn::fill_stats(hs, p->stats);
+    p->stats.device_bytes = (int64_t)p->dev_bytes;
     if (hll) {
         p->gview = tn::schedule_view(hs, p->dev);
         if (columns) {

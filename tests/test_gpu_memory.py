@@ -116,3 +116,30 @@ def test_fusion_without_room_for_lists():
         torch.cuda.synchronize()
     assert torch.equal(est, want)
     ctx.close()
+
+
+@pytest.mark.parametrize("hll", [False, True])
+def test_plans_without_room_for_their_column_form(hll):
+    # the columns' forms of a plan take half as much again as its schedule; it runs
+    # without them too
+    n = 20_000
+    s, d, t = T.uniform_pairs(n, 3_000_000, 750_000, seed=6)
+    flags = tn.HLL if hll else 0
+    h = np.random.default_rng(7).integers(0, 2**64, size=n, dtype=np.uint64)
+    p = tn.Plan(n, s, d, t, flags)
+    size, base = p.stats["device_bytes"], (8 if hll else 16) * len(s)
+    assert size > 1.3 * base
+    want = p.hll(h, 6)[0].cpu() if hll else host(p.execute())
+    p.close()
+    ctx = tn.Context()
+    before = free_bytes()
+    p = tn.Plan(n, s, d, t, flags, ctx=ctx)
+    assert abs(before - free_bytes() - size) < 6 * MB
+    p.close()
+    with only((size + base) // 2):
+        p = tn.Plan(n, s, d, t, flags, ctx=ctx)
+    assert base <= p.stats["device_bytes"] < (size + base) // 2
+    got = p.hll(h, 6)[0].cpu() if hll else host(p.execute())
+    assert (got == want).all()
+    p.close()
+    ctx.close()
