@@ -239,7 +239,9 @@ tn_status tn_set_saturation(tn_ctx *ctx, int enable);
 
 /* Row traffic of the last tn_plan_execute on this context: words[0] = uint64
  * row words its row-OR kernel loaded, words[1] = row words it stored (words
- * of the padding columns past ceil(n/64) are not counted).  words: HOST
+ * of the padding columns past ceil(n/64) are not counted).  A plan that ran on
+ * word columns in LDS counts each word of C once loaded and once stored, as if
+ * the identity its columns start from were read (0 without ops).  words: HOST
  * uint64[2], zeros before the first execute.  Waits for the context's
  * stream.  Errors: TN_E_ARG, TN_E_HIP. */
 tn_status tn_plan_last_traffic(tn_ctx *ctx, uint64_t *words);

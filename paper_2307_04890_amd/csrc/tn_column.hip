@@ -124,7 +124,8 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
 template <bool FRESH, bool SIZES = false, typename T = uint64_t>
 __device__ __forceinline__ void
 rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool sat,
-             unsigned int *__restrict__ done_count, const ColumnSizes &sizes = {}) {
+             unsigned int *__restrict__ done_count, const ColumnSizes &sizes = {},
+             unsigned long long *__restrict__ traffic = nullptr) {
     constexpr uint32_t kBits = 8 * sizeof(T);
     extern __shared__ uint64_t column[];
     T *const rows = reinterpret_cast<T *>(column);
@@ -137,6 +138,7 @@ rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool
     uint32_t *pst = net.persist ? net.persist + (size_t)w * (2 * (size_t)rwords + 2) : nullptr;
     if (!FRESH && net.blocks == 0) return;  // C is left as it is
     if (pst && pst[0]) return;              // all ones already (uniform)
+    if (traffic && tid < 2) atomicAdd(traffic + tid, (unsigned long long)n);
     if (tid == 0) open = total = 0;
     if (FRESH) {
         for (uint32_t r = tid; r < n; r += W) rows[r] = r / kBits == w ? (T)1 << (r % kBits) : (T)0;
@@ -192,22 +194,17 @@ rowor_column(const ColumnNet &net, uint32_t w, uint32_t n, uint32_t nwords, bool
 }
 
 // One network, one workgroup per word column.  traffic (nullable): the row
-// words loaded and stored, written here where FRESH, else added.
+// words loaded and stored, written here where FRESH (each word once, as if the
+// identity were read), else those of the columns not done before added.
 template <bool FRESH, bool SIZES, typename T>
 __global__ void __launch_bounds__(1024)
 k_rowor_column(ColumnNet net, uint32_t n, uint32_t nwords, bool sat,
                unsigned int *__restrict__ done_count, unsigned long long *__restrict__ traffic,
                ColumnSizes sizes) {
-    if (traffic && threadIdx.x < 2) {
-        if (FRESH) {
-            if (blockIdx.x == 0)
-                traffic[threadIdx.x] = net.blocks ? (unsigned long long)n * ((n + 63) / 64) : 0ull;
-        } else {
-            atomicAdd(traffic + threadIdx.x, (unsigned long long)n);
-        }
-    }
+    if (FRESH && traffic && blockIdx.x == 0 && threadIdx.x < 2)
+        traffic[threadIdx.x] = net.blocks ? (unsigned long long)n * ((n + 63) / 64) : 0ull;
     rowor_column<FRESH, SIZES, T>(net, xcd_slice(blockIdx.x, gridDim.x), n, nwords, sat,
-                                  done_count, sizes);
+                                  done_count, sizes, FRESH ? nullptr : traffic);
 }
 
 // Many networks of n nodes (the hashed proxies): workgroup b runs word column

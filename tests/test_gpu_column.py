@@ -373,3 +373,21 @@ def test_batches_of_few_events(which):
     finally:
         ctx.saturation(True)
         b.close()
+
+
+def test_columns_full_before_a_chunk_move_nothing():
+    # node 0 collects nodes 1 to 63 and gives them to all: word column 0 is full,
+    # column 1 never; chunks before that in time move column 1 alone
+    n = 128
+    give = np.tile(np.arange(1, n), 3)
+    s = np.concatenate([give, np.arange(1, n), np.zeros(63, int)]).astype(np.uint32)
+    d = np.concatenate([np.zeros(4 * (n - 1), int), np.arange(1, 64)]).astype(np.uint32)
+    t = np.arange(len(s), dtype=np.int64)
+    live = tn.Online(n, flags=tn.DIRECTED)
+    ctx = tn.get_context()
+    cuts = [len(s), 3 * (n - 1), 2 * (n - 1), n - 1, 0]
+    for k, (hi, lo) in enumerate(zip(cuts, cuts[1:])):
+        live.insert(s[lo:hi], d[lo:hi], t[lo:hi])
+        assert ctx.last_traffic() == ((2 + k) * n,) * 2
+    assert (host(live.C) == oracle.reverse_matrix(n, s, d, t, directed=True)).all()
+    live.close()
