@@ -105,7 +105,8 @@ tn_status tn_set_stream(tn_ctx *ctx, void *stream);
 tn_status tn_sync(tn_ctx *ctx);
 
 /* Frees the context's scratch memory (device and pinned host).  Plans and
- * batches must be destroyed first.  NULL is ignored. */
+ * batches must be destroyed first; online states end with their context, and
+ * only their handles are left to destroy.  NULL is ignored. */
 void tn_destroy(tn_ctx *ctx);
 
 /* Kernel timing on the context's stream.  While enabled, every kernel the

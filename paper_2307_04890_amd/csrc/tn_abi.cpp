@@ -141,6 +141,7 @@ void tn_destroy(tn_ctx *ctx) {
     if (ctx->scratch) (void)hipFree(ctx->scratch);
     if (ctx->host_staging) (void)hipHostFree(ctx->host_staging);
     tn::ring_free(ctx);
+    tn::online_detach_all(ctx);
     tn::stream_buffers_free(ctx->stream_kept);
     if (ctx->traffic) (void)hipFree(ctx->traffic);
     for (auto &r : ctx->recs) {

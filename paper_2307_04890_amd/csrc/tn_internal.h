@@ -235,6 +235,7 @@ struct tn_ctx {
     bool ring_busy[kRingSlots] = {};
     int ring_next = 0;
     tn::StreamBuffers *stream_kept = nullptr;
+    std::vector<struct tn_online *> onlines;  // live, detached by tn_destroy
     bool saturation = true;
     int num_cus = 0;
     // kernel timing (tn_profile_enable)
@@ -493,6 +494,9 @@ hipError_t launch_hll_estimate(uint32_t n, uint32_t log2s, const uint8_t *M, dou
 tn_status stream_buffers_take(tn_ctx *ctx, size_t persist_words, StreamBuffers **out);
 void stream_buffers_give(tn_ctx *ctx, StreamBuffers *b);
 void stream_buffers_free(StreamBuffers *b);
+// Frees what the context's live online states hold; their handles then only
+// wait for tn_online_destroy.
+void online_detach_all(tn_ctx *ctx);
 // streamed one-shot build (tn_stream.cpp)
 tn_status build_streamed(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src,
                          const uint32_t *dst, const int64_t *t, uint32_t flags, uint64_t *C,

@@ -537,9 +537,17 @@ tn_status build_streamed(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
 }  // namespace tn
 
 struct tn_online {
-    tn_ctx *ctx = nullptr;
+    tn_ctx *ctx = nullptr;  // null once the context is destroyed
     tn::StreamState s;
 };
+
+void tn::online_detach_all(tn_ctx *ctx) {
+    for (tn_online *o : ctx->onlines) {
+        state_release(ctx, o->s);
+        o->ctx = nullptr;
+    }
+    ctx->onlines.clear();
+}
 
 extern "C" {
 
@@ -568,6 +576,7 @@ tn_status tn_online_create(tn_ctx *ctx, uint32_t n, uint32_t flags, uint64_t *C,
         delete o;
         return st;
     }
+    ctx->onlines.push_back(o);
     *out = o;
     return TN_OK;
 }
@@ -610,8 +619,12 @@ tn_status tn_online_insert(tn_ctx *ctx, tn_online *o, int64_t m, const uint32_t 
 
 void tn_online_destroy(tn_online *o) {
     if (!o) return;
-    tn::DeviceGuard g(o->ctx->device);
-    tn::state_release(o->ctx, o->s);
+    if (o->ctx) {
+        tn::DeviceGuard g(o->ctx->device);
+        tn::state_release(o->ctx, o->s);
+        auto &live = o->ctx->onlines;
+        live.erase(std::find(live.begin(), live.end(), o));
+    }
     delete o;
 }
 

@@ -40,3 +40,36 @@ def test_child_process_exits_cleanly():
                        text=True, timeout=300)
     assert "child done" in r.stdout, r.stdout + r.stderr
     assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
+
+
+ONLINE = r"""
+import numpy as np
+import torch
+import paper_2307_04890_amd as tn
+import tn_inputs as T
+live = [tn.Online(n) for n in (100, 3000, 12000)]
+for o in live[1:]:
+    o.insert(*T.uniform_pairs(o.n, 500, 100, seed=1))
+other = tn.Context()
+held = tn.Online(500, ctx=other)
+held.insert(*T.uniform_pairs(500, 500, 100, seed=2))
+other.close()
+try:
+    held.insert(*T.uniform_pairs(500, 5, 10, seed=3))
+except tn.TNError:
+    print("refused", flush=True)
+held.close()
+live[1].close()
+tn.build_component_matrix_streamed(3000, *T.uniform_pairs(3000, 5000, 100, seed=1), chunk_events=900)
+print("child done", flush=True)
+"""
+
+
+def test_live_online_states_at_exit():
+    # contexts are destroyed before the objects that module teardown destroys
+    env = dict(os.environ)
+    env["PYTHONPATH"] = ROOT + os.pathsep + env.get("PYTHONPATH", "")
+    r = subprocess.run([sys.executable, "-c", ONLINE], cwd=ROOT, env=env, capture_output=True,
+                       text=True, timeout=300)
+    assert "refused" in r.stdout and "child done" in r.stdout, r.stdout + r.stderr
+    assert r.returncode == 0, (r.returncode, r.stderr[-2000:])
