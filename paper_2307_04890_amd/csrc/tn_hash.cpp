@@ -31,8 +31,7 @@ inline size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 // nodes' entries and bitmaps (more where a node takes a hash table, past
 // kMarkBits nodes), and the random reads of intersections.  Below
 // kListMinN nodes the lists gain little (n = 10^4, H = 16, K = 512 0.106 against
-// 0.116 ms) or lose (n = 2*10^4, 0.43 against 0.33), and their totals cost each
-// call 10 us.
+// 0.116 ms) or lose (n = 2*10^4, 0.43 against 0.33).
 bool fuse_by_lists(uint32_t n, uint32_t H, uint32_t K, const unsigned long long *stats,
                    unsigned long long entries, unsigned long long nbitmaps, size_t room) {
     using namespace tn;
@@ -610,8 +609,8 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
         return at;
     };
     const size_t rows = (size_t)H * K, lt_bytes = (size_t)qr * per_q;
-    const size_t o_stats = part(kFuseWords * 8), o_pt = part(rows * ldK * 8), o_rs = part(rows * 4),
-                 o_full = part(rows), o_cls = part(n), o_open = part((size_t)n * 4),
+    const size_t o_stats = part(kFuseWords * 8), o_pt = part(rows * ldK * 8), o_rs = part(rows * 8),
+                 o_cls = part(n), o_open = part((size_t)n * 4),
                  o_wide = part((size_t)n * 4), o_bs = part((size_t)H * ((K + 63) / 64) * 4),
                  o_lt = part(lt_bytes), tables = need,
                  o_hist = part(fuse_hist_words(H, K) * 4), o_start = part((rows + H) * 4),
@@ -625,16 +624,17 @@ tn_status tn_recombine(tn_ctx *ctx, uint32_t n, uint32_t H, uint32_t K, const ui
     unsigned char *base = (unsigned char *)ctx->scratch;
     unsigned long long *stats = (unsigned long long *)(base + o_stats);
     uint64_t *PT = (uint64_t *)(base + o_pt), *Lt = (uint64_t *)(base + o_lt);
-    int32_t *rowsum = (int32_t *)(base + o_rs), *bsum = (int32_t *)(base + o_bs);
-    uint8_t *full = base + o_full, *cls = base + o_cls;
+    int2 *rowsum = (int2 *)(base + o_rs);
+    int32_t *bsum = (int32_t *)(base + o_bs);
+    uint8_t *cls = base + o_cls;
     uint32_t *open = (uint32_t *)(base + o_open), *wide = (uint32_t *)(base + o_wide);
     hipError_t e;
     unsigned long long host[kFuseWords] = {};
     {
         ProfScope ps(ctx, TN_K_AUX);
-        e = launch_row_sums(H, K, ldK, P, count, bsum, rowsum, full, ctx->stream);
+        e = launch_row_sums(H, K, ldK, P, count, bsum, rowsum, ctx->stream);
         if (e == hipSuccess)
-            e = launch_classify(n, H, K, bucket, count, rowsum, full, lifted, lists_fit, cls, est, open,
+            e = launch_classify(n, H, K, bucket, count, rowsum, lifted, lists_fit, cls, est, open,
                                 wide, stats, ctx->stream);
     }
     if (e == hipSuccess)

@@ -12,12 +12,11 @@ hipError_t launch_hash_buckets(uint32_t n, uint32_t H, const uint64_t *coeffs, i
                                uint32_t *bucket, int32_t *count, hipStream_t st);
 hipError_t launch_transpose_proxies(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
                                     uint64_t *PT, hipStream_t st);
-// full[j K + r] = 1 iff row r of P_j is full, and rowsum[j K + r] = the nodes
-// that it lifts to: the sum of count[j] over the super-nodes set in it (bsum:
-// scratch of H ceil(K/64) int32).
+// rowsum[j K + r] = {the nodes that row r of P_j lifts to: the sum of count[j] over
+// the super-nodes set in it, 1 iff the row is full} (bsum: scratch of H
+// ceil(K/64) int32).  One pair, so that a node's row takes one read.
 hipError_t launch_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
-                           const int32_t *count, int32_t *bsum, int32_t *rowsum, uint8_t *full,
-                           hipStream_t st);
+                           const int32_t *count, int32_t *bsum, int2 *rowsum, hipStream_t st);
 hipError_t launch_zero_i32(int32_t *p, size_t n, hipStream_t st);
 hipError_t launch_build_lifted(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *PT,
                                const uint32_t *bucket, uint32_t q0, uint32_t nq, uint64_t *Lt,
@@ -53,19 +52,19 @@ struct FuseScratch {
 // hashes, LDS for K counters and n bits)
 bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K);
 size_t fuse_hist_words(uint32_t H, uint32_t K);
-// cls[u] (the node's kind), lifted[j n + u] = rowsum[j K + h_j(u)] (nullable),
+// cls[u] (the node's kind), lifted[j n + u] = rowsum[j K + h_j(u)].x (nullable),
 // est[u] = n where every row is full, else 0 and u in open[0 ..
 // stats[kFuseOpen]); the wide nodes in wide[0 .. stats[kFuseWide]), the small
 // ones in the last stats[kFuseSmall] of wide's n; with lists also the rows'
 // totals.
 hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
-                           const int32_t *count, const int32_t *rowsum, const uint8_t *full,
+                           const int32_t *count, const int2 *rowsum,
                            int32_t *lifted, bool lists, uint8_t *cls, int32_t *est,
                            uint32_t *open, uint32_t *wide, unsigned long long *stats,
                            hipStream_t st);
 // The estimates of union and intersection nodes (stats_host: stats' values).
 hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
-                             const uint32_t *bucket, const int32_t *count, const int32_t *rowsum,
+                             const uint32_t *bucket, const int32_t *count, const int2 *rowsum,
                              const uint8_t *cls, const unsigned long long *stats, FuseScratch s,
                              uint32_t nbitmaps, const uint32_t *wide,
                              const unsigned long long *stats_host, int32_t *est, hipStream_t st);

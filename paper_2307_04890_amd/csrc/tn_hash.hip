@@ -150,14 +150,14 @@ k_block_sums(uint32_t H, uint32_t K, const int32_t *__restrict__ count, int32_t 
 }
 
 // One pass over every proxy row r of P_j, one wavefront per row, its lanes
-// on consecutive words: full[j][r] = 1 iff the row has all K bits set, and
-// rowsum[j][r] = sum of count[j][c] over the super-nodes c set in the row.
+// on consecutive words: rowsum[j][r] = {sum of count[j][c] over the super-nodes c
+// set in the row, 1 iff the row has all K bits set}.
 // A full word adds its block sum, an empty one nothing,
 // and each other word one count load per lane (lane l: super-node 64 wd + l).
 __global__ void __launch_bounds__(256)
 k_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
            const int32_t *__restrict__ count, const int32_t *__restrict__ bsum,
-           int32_t *__restrict__ rowsum, uint8_t *__restrict__ full) {
+           int2 *__restrict__ rowsum) {
     const uint32_t lane = threadIdx.x & 63u;
     const size_t rows = (size_t)H * K;
     const uint32_t kw = (K + 63) / 64;
@@ -190,10 +190,7 @@ k_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__restrict__ P,
 #pragma unroll
         for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off, 64);
         const bool row_full = __ballot(!all) == 0ull;
-        if (lane == 0) {
-            rowsum[row] = acc;
-            full[row] = row_full ? 1 : 0;
-        }
+        if (lane == 0) rowsum[row] = make_int2(acc, row_full ? 1 : 0);
     }
 }
 
@@ -509,33 +506,77 @@ __device__ __forceinline__ uint32_t row_list(uint32_t n, int32_t s, uint32_t &le
     return kRowBits;
 }
 
-// A 64-bit mix of (hash, super-node): the sums of it over the nodes' buckets
-// and over the counts agree when the counts are the buckets' own.
+// A 64-bit weight of (hash, super-node): the sums of it over the nodes' buckets
+// and over the counts agree when the counts are the buckets' own.  Two products
+// of one mixed word: 64-bit ones took every node and hash 7 multiplications, 3 us
+// a call of 2*10^5 nodes and 16 hashes.
 __device__ __forceinline__ unsigned long long bucket_mix(uint32_t j, uint32_t r) {
-    unsigned long long z = ((unsigned long long)j << 32 | r) * 0x9e3779b97f4a7c15ull;
-    z ^= z >> 29;
-    return z * 0xbf58476d1ce4e5b9ull;
+    uint32_t a = (r + j * 0x9e3779b9u) * 0x7f4a7c15u;
+    a ^= a >> 15;
+    uint32_t hi = a * 0xbf58476du, lo = a * 0x1ce4e5b9u;
+    hi ^= hi >> 16;
+    lo ^= lo >> 13;
+    return (unsigned long long)hi << 32 | lo;
+}
+
+// The lists' entries and the bitmaps of hash j's rows that some node meets, and
+// the sum of bucket_mix over its counts, added to stats; workgroup `part` of
+// kTotalParts.  tot: 3 words of LDS.
+constexpr uint32_t kTotalParts = 4;
+__device__ __forceinline__ void list_totals(uint32_t n, uint32_t K, uint32_t j, uint32_t part,
+                                            const int32_t *__restrict__ count,
+                                            const int2 *__restrict__ rowsum,
+                                            unsigned long long *tot,
+                                            unsigned long long *__restrict__ stats) {
+    unsigned long long v[3] = {};  // entries, bitmaps, mix
+    for (uint32_t r = part * blockDim.x + threadIdx.x; r < K; r += kTotalParts * blockDim.x) {
+        const int32_t c = count[(size_t)j * K + r];
+        v[2] += bucket_mix(j, r) * (unsigned long long)(uint32_t)c;
+        uint32_t len = 0;
+        if (c && row_list(n, rowsum[(size_t)j * K + r].x, len) == kRowBits) ++v[1];
+        v[0] += c ? len : 0u;
+    }
+    __syncthreads();  // tot is clear
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
+        if ((threadIdx.x & 63u) == 0) atomicAdd(&tot[k], v[k]);
+    }
+    __syncthreads();
+    if (threadIdx.x < 2 && tot[threadIdx.x])
+        atomicAdd(stats + kFuseRows + 16 * threadIdx.x + j, tot[threadIdx.x]);
+    if (threadIdx.x == 2)
+        atomicAdd(stats + kFuseStats + 8 * ((kTotalParts * j + part) % kFuseParts) + 4, tot[2]);
 }
 
 // Each node's kind (cls), its lifted sizes (lifted, nullable), est (n where
 // every row is full, else 0), the nodes some row of which is not full (open)
 // and of them the wide ones (wide, from its start) and the small ones (wide,
 // from its end); totals in stats.  Without LISTS only what the tables need: the
-// lifted sizes, est and the open nodes.
+// lifted sizes, est and the open nodes.  With LISTS the last kTotalParts workgroups
+// of each hash add up its rows (list_totals) beside the others: in a launch of
+// their own, with the sum of bucket_mix over the nodes, they took each call 10 us.
 template <bool LISTS, uint32_t B>  // B hashes at a time
 __global__ void __launch_bounds__(256)
 k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
-           const int32_t *__restrict__ rowsum, const uint8_t *__restrict__ full,
+           const int32_t *__restrict__ count, const int2 *__restrict__ rowsum,
            int32_t *__restrict__ lifted, uint8_t *__restrict__ cls, int32_t *__restrict__ est,
            uint32_t *__restrict__ open, uint32_t *__restrict__ wide,
            unsigned long long *__restrict__ stats) {
     __shared__ uint32_t part[4][3], base[3];  // open, wide and small nodes
-    __shared__ unsigned long long tot[3];
+    __shared__ unsigned long long tot[4];
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    if (threadIdx.x < 3) tot[threadIdx.x] = 0;
-    unsigned long long entries = 0, bits = 0, inter = 0;
+    if (threadIdx.x < 4) tot[threadIdx.x] = 0;
+    const uint32_t groups = gridDim.x - (LISTS ? kTotalParts * H : 0u);
+    if (LISTS && blockIdx.x >= groups) {
+        const uint32_t k = blockIdx.x - groups;
+        list_totals(n, K, k / kTotalParts, k % kTotalParts, count, rowsum, tot, stats);
+        return;
+    }
+    unsigned long long entries = 0, bits = 0, inter = 0, mix = 0;
     const uint32_t small = n <= kMarkBits ? kSmallMarked : kSmallHashed;
-    for (uint32_t t0 = blockIdx.x * blockDim.x; t0 < n; t0 += gridDim.x * blockDim.x) {
+    for (uint32_t t0 = blockIdx.x * blockDim.x; t0 < n; t0 += groups * blockDim.x) {
         const uint32_t u = t0 + threadIdx.x;
         bool all = true;
         uint8_t c = kNodeDone;
@@ -546,23 +587,21 @@ k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ buck
                 // past the last hash its loads again: none depends on a branch, so
                 // that all are in flight
                 uint32_t b[B];
-                int32_t s[B];
-                uint8_t f[B];
+                int2 s[B];
 #pragma unroll
                 for (uint32_t k = 0; k < B; ++k)
                     b[k] = bucket[(size_t)min(j0 + k, H - 1) * n + u];
 #pragma unroll
                 for (uint32_t k = 0; k < B; ++k) s[k] = rowsum[(size_t)min(j0 + k, H - 1) * K + b[k]];
 #pragma unroll
-                for (uint32_t k = 0; k < B; ++k) f[k] = full[(size_t)min(j0 + k, H - 1) * K + b[k]];
-#pragma unroll
                 for (uint32_t k = 0; k < B; ++k) {
                     if (j0 + k >= H) continue;
-                    if (lifted) lifted[(size_t)(j0 + k) * n + u] = s[k];
-                    all &= f[k] != 0;
+                    if (lifted) lifted[(size_t)(j0 + k) * n + u] = s[k].x;
+                    all &= s[k].y != 0;
                     if (!LISTS) continue;
+                    mix += bucket_mix(j0 + k, b[k]);
                     uint32_t len;
-                    const uint32_t kind = row_list(n, s[k], len);
+                    const uint32_t kind = row_list(n, s[k].x, len);
                     if (kind == kRowOut) out += len;
                     if (kind == kRowKept) smin = min(smin, len);
                     if (kind == kRowBits) ++nbits;
@@ -617,55 +656,11 @@ k_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ buck
     add(0, entries);
     add(1, bits);
     add(2, inter);
+    add(3, mix);
     __syncthreads();
     // (hundreds of workgroups' atomics on one word took as long as the rest)
-    if (threadIdx.x < 3 && tot[threadIdx.x])
+    if (threadIdx.x < 4 && tot[threadIdx.x])
         atomicAdd(stats + kFuseStats + 8 * (blockIdx.x % kFuseParts) + threadIdx.x, tot[threadIdx.x]);
-}
-
-// The lists' entries and the bitmaps of a hash's rows that some node meets, and
-// the sums of bucket_mix over its nodes and over its counts, added to stats.
-// Workgroups over (part of a hash's rows and nodes, hash); nothing to do where
-// no node is open.
-__global__ void __launch_bounds__(256)
-k_list_totals(uint32_t n, uint32_t K, const uint32_t *__restrict__ bucket,
-              const int32_t *__restrict__ count, const int32_t *__restrict__ rowsum,
-              unsigned long long *__restrict__ stats) {
-    __shared__ unsigned long long tot[4];
-    if (stats[kFuseOpen] == 0) return;
-    const uint32_t j = blockIdx.y, t = blockIdx.x * blockDim.x + threadIdx.x;
-    const uint32_t step = gridDim.x * blockDim.x;
-    if (threadIdx.x < 4) tot[threadIdx.x] = 0;
-    unsigned long long v[4] = {};  // entries, bitmaps, mixes of nodes and of counts
-    for (uint32_t r = t; r < K; r += step) {
-        const int32_t c = count[(size_t)j * K + r];
-        v[3] += bucket_mix(j, r) * (unsigned long long)(uint32_t)c;
-        uint32_t len = 0;
-        if (c && row_list(n, rowsum[(size_t)j * K + r], len) == kRowBits) ++v[1];
-        v[0] += c ? len : 0u;
-    }
-    const uint32_t *nj = bucket + (size_t)j * n;
-    for (uint32_t u0 = t; u0 < n; u0 += 8 * step) {
-        uint32_t b[8];
-#pragma unroll
-        for (uint32_t q = 0; q < 8; ++q) b[q] = nj[min(u0 + q * step, n - 1)];
-#pragma unroll
-        for (uint32_t q = 0; q < 8; ++q)
-            if (u0 + (uint64_t)q * step < n) v[2] += bucket_mix(j, b[q]);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) v[k] += __shfl_xor(v[k], off, 64);
-        if ((threadIdx.x & 63u) == 0) atomicAdd(&tot[k], v[k]);
-    }
-    __syncthreads();
-    if (threadIdx.x < 2 && tot[threadIdx.x])
-        atomicAdd(stats + kFuseRows + 16 * threadIdx.x + j, tot[threadIdx.x]);
-    if (threadIdx.x == 2 || threadIdx.x == 3)
-        atomicAdd(stats + kFuseStats + 8 * ((16 * blockIdx.y + blockIdx.x) % kFuseParts) + 1 + threadIdx.x,
-                  tot[threadIdx.x]);
 }
 
 // The nodes of each hash sorted by bucket, in three kernels over (range of
@@ -759,7 +754,7 @@ k_bucket_nodes(uint32_t n, uint32_t K, const uint32_t *__restrict__ bucket,
 // before it.
 __global__ void __launch_bounds__(1024)
 k_list_starts(uint32_t n, uint32_t K, const int32_t *__restrict__ count,
-              const int32_t *__restrict__ rowsum, const unsigned long long *__restrict__ stats,
+              const int2 *__restrict__ rowsum, const unsigned long long *__restrict__ stats,
               uint2 *__restrict__ rows, uint32_t *__restrict__ bitmap_row) {
     __shared__ uint32_t part[16];
     const uint32_t j = blockIdx.x;
@@ -771,7 +766,7 @@ k_list_starts(uint32_t n, uint32_t K, const int32_t *__restrict__ count,
     for (uint32_t r0 = 0; r0 < K; r0 += blockDim.x) {
         const uint32_t r = r0 + threadIdx.x;
         uint32_t kind = kRowOut, len = 0, all;
-        if (r < K && count[(size_t)j * K + r]) kind = row_list(n, rowsum[(size_t)j * K + r], len);
+        if (r < K && count[(size_t)j * K + r]) kind = row_list(n, rowsum[(size_t)j * K + r].x, len);
         const uint32_t e = entries + block_scan(len, part, all);
         entries += all;
         const uint32_t m = bitmaps + block_scan(kind == kRowBits ? 1u : 0u, part, all);
@@ -1343,15 +1338,14 @@ hipError_t launch_transpose_proxies(uint32_t H, uint32_t K, int64_t ldK, const u
 }
 
 hipError_t launch_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
-                           const int32_t *count, int32_t *bsum, int32_t *rowsum, uint8_t *full,
-                           hipStream_t st) {
+                           const int32_t *count, int32_t *bsum, int2 *rowsum, hipStream_t st) {
     const size_t kw = (K + 63) / 64;
     hipLaunchKernelGGL(k_block_sums, dim3(grid_for((size_t)H * kw * 64, 256)), dim3(256), 0, st, H, K,
                        count, bsum);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_row_sums, dim3(grid_for((size_t)H * K * 64, 256)), dim3(256), 0, st, H, K, ldK,
-                       P, count, bsum, rowsum, full);
+                       P, count, bsum, rowsum);
     return hipGetLastError();
 }
 
@@ -1364,7 +1358,7 @@ bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K) {
 size_t fuse_hist_words(uint32_t H, uint32_t K) { return (size_t)H * kListSplit * K; }
 
 hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *bucket,
-                           const int32_t *count, const int32_t *rowsum, const uint8_t *full,
+                           const int32_t *count, const int2 *rowsum,
                            int32_t *lifted, bool lists, uint8_t *cls, int32_t *est,
                            uint32_t *open, uint32_t *wide, unsigned long long *stats,
                            hipStream_t st) {
@@ -1376,16 +1370,14 @@ hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *b
     const uint32_t threads = lists ? 256 : 64;
     auto k = H <= 8 ? (lists ? k_classify<true, 8> : k_classify<false, 8>)
                     : (lists ? k_classify<true, 16> : k_classify<false, 16>);
-    hipLaunchKernelGGL(k, dim3(grid_for(n, threads, 512)), dim3(threads), 0, st, n, H, K, bucket,
-                       rowsum, full, lifted, cls, est, open, wide, stats);
-    e = hipGetLastError();
-    if (e != hipSuccess || !lists) return e;
-    hipLaunchKernelGGL(k_list_totals, dim3(16, H), dim3(256), 0, st, n, K, bucket, count, rowsum, stats);
+    const uint32_t groups = grid_for(n, threads, lists ? 1024 : 512) + (lists ? kTotalParts * H : 0u);
+    hipLaunchKernelGGL(k, dim3(groups), dim3(threads), 0, st, n, H, K, bucket, count, rowsum,
+                       lifted, cls, est, open, wide, stats);
     return hipGetLastError();
 }
 
 hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
-                             const uint32_t *bucket, const int32_t *count, const int32_t *rowsum,
+                             const uint32_t *bucket, const int32_t *count, const int2 *rowsum,
                              const uint8_t *cls, const unsigned long long *stats, FuseScratch s,
                              uint32_t nbitmaps, const uint32_t *wide,
                              const unsigned long long *stats_host, int32_t *est, hipStream_t st) {
