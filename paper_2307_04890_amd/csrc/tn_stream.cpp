@@ -345,8 +345,11 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
         }
     };
     std::vector<std::thread> pool;
-    if (!s.all_done)
-        for (int64_t k = 0; k < nth; ++k) pool.emplace_back(worker);
+    if (!s.all_done) {
+        if (nch == 1) worker();  // a thread would cost a small insert more than its planning
+        else
+            for (int64_t k = 0; k < nth; ++k) pool.emplace_back(worker);
+    }
 
     int64_t launched = 0, run_events = 0, levels = 0;
     tn_status st = TN_OK;
