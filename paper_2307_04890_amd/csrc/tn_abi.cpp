@@ -279,8 +279,6 @@ tn_status tn_plan_create(tn_ctx *ctx, uint32_t n, int64_t m, const uint32_t *src
             p->columns = {hs.L,
                           (uint32_t)(pairs.size() / 128),
                           (uint32_t)(quad.size() / 4),
-                          (uint32_t)hs.gat_tgt.size(),
-                          (uint32_t)hs.gat_src.size(),
                           p->gview.max_gat,
                           (const uint2 *)(d + pair_off),
                           (const uint4 *)(d + quad_off),

@@ -118,8 +118,9 @@ __device__ __forceinline__ void column_sizes(const ColumnNet &net, uint32_t w, u
 // T: a word, or half a word, where a column of words does not fit (from the
 // identity only, and no state is kept).  Twice the columns, of half the LDS
 // traffic each: where both fit, words are as fast or faster (us, words and
-// halves: activity-driven, 20,000 nodes, 682 and 1015; random, 10,007, 256 and
-// 326), and past that halves save the slices in memory (activity-driven, 10
+// halves: activity-driven, 20,000 nodes, 10 events a node, 698 and 699; uniform, 20
+// a node, 304 and 313; random, 10,007 nodes, 300,007 one-way events, 155 and 197),
+// and past that halves save the slices in memory (activity-driven, 10
 // events a node, 25,000 nodes: 2017 and 1446; uniform, 5, 31,000: 1139 and 428).
 template <bool FRESH, bool SIZES = false, typename T = uint64_t>
 __device__ __forceinline__ void

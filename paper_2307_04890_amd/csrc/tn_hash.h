@@ -17,7 +17,6 @@ hipError_t launch_transpose_proxies(uint32_t H, uint32_t K, int64_t ldK, const u
 // ceil(K/64) int32).  One pair, so that a node's row takes one read.
 hipError_t launch_row_sums(uint32_t H, uint32_t K, int64_t ldK, const uint64_t *P,
                            const int32_t *count, int32_t *bsum, int2 *rowsum, hipStream_t st);
-hipError_t launch_zero_i32(int32_t *p, size_t n, hipStream_t st);
 hipError_t launch_build_lifted(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *PT,
                                const uint32_t *bucket, uint32_t q0, uint32_t nq, uint64_t *Lt,
                                hipStream_t st);
@@ -48,7 +47,7 @@ struct FuseScratch {
     uint64_t *bitmaps;     // the sum of stats[kFuseRows + 16 ..], of ceil(n/64) words, then
                            // the lists' entries (uint32, the sum of stats[kFuseRows ..])
 };
-// whether the lists' kernels take this size (8192 nodes and more, up to 16
+// whether the lists' kernels take this size (kListMinN nodes and more, up to 16
 // hashes, LDS for K counters and n bits)
 bool fuse_lists_fit(uint32_t n, uint32_t H, uint32_t K);
 size_t fuse_hist_words(uint32_t H, uint32_t K);

@@ -470,8 +470,7 @@ k_recombine_est2(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict_
 // list: of the nodes it leaves out, or of those it keeps; any other row that
 // some node meets is a bitmap of n bits, built once for all its nodes.  A
 // node is then
-//  - done: every row is full, est = n, or lifts to all n nodes or one to
-//    none;
+//  - done: every row is full, est = n, or one lifts to none, est = 0;
 //  - an intersection node where some row has a list of kept nodes: est = the
 //    nodes of the shortest one that every other row keeps too;
 //  - else a union node: est = n - |union of the nodes its rows leave out|, a
@@ -479,7 +478,7 @@ k_recombine_est2(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict_
 //    one.
 // fuse_by_lists (tn_hash.cpp) says when this beats the tables: with 2*10^5
 // nodes and 4*10^4 events (H = 16, K = 4096), rows that leave out 39 nodes of
-// a hash on average, a call takes 1.01 ms against 5.79 ms.
+// a hash on average, a call takes 0.65 ms against 5.80 ms.
 constexpr uint32_t kListPart = 64;        // lists of left-out nodes hold at most n / 64
 constexpr uint32_t kInterMax = 1u << 10;  // lists of kept nodes
 constexpr uint32_t kListSplit = 16;       // node ranges of a hash in the bucket sort
@@ -1007,8 +1006,9 @@ k_fuse_inter(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, const uint64_t *__
 // and has a whole turn to arrive: its number; its buckets; its rows' descriptors;
 // the map of its lists' chunks of 64 entries (chunk t in lane t) and the loads of
 // the first kMarkSlots; the marks.  A lane past a chunk's end (entries of other
-// lists, or past the last list) marks no bit.  Four nodes are in hand, so the
-// turns are written out by fours, each node staying in its registers.
+// lists, or past the last list) marks no bit.  Four nodes are in hand, and the
+// number of a fifth, so the turns are written out by fours, each node staying in
+// its registers.
 //
 // Bound by vector instructions (300 a node; 1143 with a hash table of 8 KB by
 // compare-and-swap, whatever the wavefronts) and the latency that 6 wavefronts a
@@ -1226,7 +1226,6 @@ k_fuse_hashed(uint32_t n, uint32_t H, uint32_t K,
 // of a bucket share them) and the latency of the lists'; n bits of LDS limit
 // the nodes at work on a CU, so a workgroup has as many wavefronts as fill it
 // (launch_fuse_lists): 53,000 nodes of 1400 entries (n = 2*10^5) in 0.22 ms.
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 __global__ void __launch_bounds__(1024)
 k_fuse_wide(uint32_t n, uint32_t H, uint32_t K, const uint32_t *__restrict__ bucket,
             const uint2 *__restrict__ rows, const uint32_t *__restrict__ lists,
@@ -1445,11 +1444,6 @@ hipError_t launch_fuse_lists(uint32_t n, uint32_t H, uint32_t K, int64_t ldK, co
     const uint32_t resident = std::min(fit, 2048u / threads);
     hipLaunchKernelGGL(k_fuse_wide, dim3(grid_for(nwide, 1, 256 * resident)), dim3(threads), lds, st, n,
                        H, K, bucket, s.rows, lists, s.bitmaps, wide, nwide, est);
-    return hipGetLastError();
-}
-
-hipError_t launch_zero_i32(int32_t *p, size_t n, hipStream_t st) {
-    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(n, 256)), dim3(256), 0, st, p, n);
     return hipGetLastError();
 }
 

@@ -123,7 +123,7 @@ struct DevSchedule {
 constexpr uint32_t kHllEnd = 0x80000000u, kHllLevel = 0x40000000u, kHllNode = 0x3fffffffu;
 constexpr uint32_t kHllBig = 0x80u, kHllSource = 0x3ffffu;
 struct HllColumns {
-    uint32_t L, blocks, quads, gathers, sources, max_gat;
+    uint32_t L, blocks, quads, max_gat;
     const uint2 *pair;
     const uint4 *quad;
     const uint32_t *lvl_quad;  // first << 8 | count, or kHllBig

@@ -276,8 +276,9 @@ tn_status state_apply(tn_ctx *ctx, StreamState &s, int64_t m, const uint32_t *sr
     const bool forward = s.flags & TN_FORWARD;
     const int64_t nwords = (s.n + 63) / 64;
     int64_t first = 0;
-    // the device time of the matrix stream dominates and planning runs ahead
-    // of it, so its first chunk is only a quarter of the others
+    // the device waits for the first chunk's plan, so that is only a quarter of
+    // the others; after it planning runs ahead of slices in memory, while word
+    // columns wait for it again
     default_chunks(m, chunk_events, first, 4);
     std::vector<std::pair<int64_t, int64_t>> bounds;
     stream_chunks(m, t, chunk_events, first, seq, forward, bounds);
