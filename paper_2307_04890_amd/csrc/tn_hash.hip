@@ -1365,8 +1365,10 @@ hipError_t launch_classify(uint32_t n, uint32_t H, uint32_t K, const uint32_t *b
                        (size_t)2 * (lists ? kFuseWords : 1));
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // (a wavefront a workgroup spreads the fewer nodes of calls without lists)
-    const uint32_t threads = lists ? 256 : 64;
+    // a wavefront a workgroup spreads few nodes, more keep them in order for the
+    // estimates' reads (us a call without lists, 64 and 256 threads: 4,000 nodes,
+    // 16 hashes 113.4 and 115.3; 11,843 278.7 and 275.5; 20,009 308.9 and 306.9)
+    const uint32_t threads = lists || n >= 8192 ? 256 : 64;
     auto k = H <= 8 ? (lists ? k_classify<true, 8> : k_classify<false, 8>)
                     : (lists ? k_classify<true, 16> : k_classify<false, 16>);
     const uint32_t groups = grid_for(n, threads, lists ? 1024 : 512) + (lists ? kTotalParts * H : 0u);
