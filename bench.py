@@ -77,8 +77,9 @@ def kernel_source_hash(files) -> str:
 ROWOR_SAT_KERNELS = "k_rowor_global|k_rowor_fwd|k_slice_full_state|k_slice_order"
 KERNEL_SOURCES = {"rowor": ("tn_kernels.hip", "tn_internal.h", "tn_device.h", "tn_plan.cpp"),
                   "rowor_plain": ("tn_kernels.hip", "tn_internal.h", "tn_device.h", "tn_plan.cpp"),
-                  "batch": ("tn_batch.hip", "tn_batch.h", "tn_batch.cpp", "tn_internal.h"),
-                  "recombine": ("tn_hash.hip", "tn_hash.h")}
+                  "batch": ("tn_batch.hip", "tn_batch.h", "tn_batch.cpp", "tn_column.hip", "tn_column.h",
+                            "tn_levels.h", "tn_device.h", "tn_plan.cpp", "tn_internal.h"),
+                  "recombine": ("tn_hash.hip", "tn_hash.h", "tn_hash.cpp")}
 
 
 def load_traffic(kernel: str, workload: str):
@@ -539,11 +540,11 @@ FUSION_WORKLOAD = "fusion_activity_n200000_m40000_K4096"
 def fusion_timing(args):
     """Fusion (Sec. 4.2) timed where it intersects: 2*10^5 nodes, 4*10^4
     activity-driven events, H = 16 hashes to K = 4096 super-nodes, so that
-    proxy rows are mostly not full and every estimate is below n.  The
-    AND/popcount kernel reads one word per (node, chunk of 64 nodes, hash)
-    from the lifted tables it stages in LDS: its algorithmic bytes are
-    8 * nlist * ceil(n/64) * H for the nlist nodes whose rows are not full
-    in every hash."""
+    proxy rows are mostly not full and every estimate is below n.  On tables
+    the AND/popcount kernel reads one word per (node, chunk of 64 nodes, hash)
+    from the lifted tables it stages in LDS, 8 * nlist * ceil(n/64) * H bytes
+    for the nlist nodes whose rows are not full in every hash; on lists of the
+    nodes that rows leave out or keep these bytes are an equivalent only."""
     import numpy as np
     import torch
 
@@ -569,16 +570,19 @@ def fusion_timing(args):
     est_ms = float(np.sum(per.get("recombine", [0.0]))) / 3
     aux_ms = float(np.sum(per.get("aux", [0.0]))) / 3
     traffic = load_traffic("recombine", FUSION_WORKLOAD)
+    # tables are transposed and built in launches of their own
+    lists = len(per.get("aux", [])) == len(per.get("recombine", []))
     return {"workload": FUSION_WORKLOAD, "n": n, "m": m, "T": Tm, "H": H, "K": K,
             "nodes_not_full": nlist, "estimates_below_n": float((e < n).mean()),
             "mean_estimate": float(e.mean()),
             "call_ms": 1e3 * elapsed / 3, "recombine_est_ms": est_ms, "other_kernels_ms": aux_ms,
+            "route": "lists" if lists else "tables",
             "dense_equivalent_bytes": and_bytes,
             "dense_equivalent_frac": and_bytes / (est_ms * 1e-3) / 1e9 / LDS_PEAK_GBS,
             "dense_equivalent_note": "the AND words that lifted tables in LDS would read (LDS peak "
-                                     "256 CU x 128 B/clk x 2.4 GHz); the estimates come from the "
-                                     "nodes of each row's smallest buckets instead, so not a "
-                                     "bandwidth",
+                                     "256 CU x 128 B/clk x 2.4 GHz); on lists the estimates come "
+                                     "from the nodes that each row leaves out or keeps instead, "
+                                     "so not a bandwidth",
             "traffic": traffic,
             "traffic_frac": (traffic / (est_ms * 1e-3) / 1e9 / HBM_PEAK_GBS if traffic else None),
             "note": "traffic = rocprofv3 FETCH_SIZE + WRITE_SIZE of the estimates' dispatches, "
@@ -667,7 +671,8 @@ def run_fusion(args):
     r = base_result(args, f["n"] / (f["call_ms"] * 1e-3), "nodes/s", 3, f["call_ms"], config)
     r["value_note"] = "fusion estimates of every node per second (one tn_recombine call)"
     r["roofline"] = {"bound": "latency", "achieved": None, "peak": None, "unit": "GB/s",
-                     "frac": None, "traffic": f["traffic"], "kernel": "k_fuse_marked",
+                     "frac": None, "traffic": f["traffic"],
+                     "kernel": "k_fuse_marked" if f["route"] == "lists" else "k_recombine_est2",
                      "algorithmic_bytes": None, "avg_launch_ms": f["recombine_est_ms"]}
     r["fusion"] = f
     return r
@@ -1067,7 +1072,9 @@ def summarize_pmc(fetch_csv, write_csv, kernel, workload, command, calib_mib, la
     keeps only the kernel's last `last` dispatches (the timed ones, after
     autotuning); a launch is `per_launch` consecutive dispatches."""
     match = match or {"rowor": ROWOR_SAT_KERNELS, "rowor_plain": "k_rowor_fwd",
-                      "batch": "k_batch_persistent", "recombine": "k_recombine_est"}[kernel]
+                      "batch": "k_batch_persistent|k_rowor_column_tiles",
+                      "recombine": "k_recombine_est|k_bucket_hist|k_bucket_starts|k_bucket_nodes|"
+                                   "k_list_starts|k_fill_lists|k_fill_bitmaps|k_fuse_"}[kernel]
     alts = match.split("|")
     out = {"kernel": match, "workload": workload, "command": command,
            "kernel_source_sha": kernel_source_hash(KERNEL_SOURCES[kernel])}
