@@ -391,3 +391,21 @@ def test_columns_full_before_a_chunk_move_nothing():
         assert ctx.last_traffic() == ((2 + k) * n,) * 2
     assert (host(live.C) == oracle.reverse_matrix(n, s, d, t, directed=True)).all()
     live.close()
+
+
+@pytest.mark.parametrize("n,per_node", [(700, 4), (20_000, 0.01), (25_000, 2), (33_000, 1)])
+def test_either_sizes_alone(n, per_node):
+    # word columns, half columns and slices: out-sizes, in-sizes or none
+    p = tn.Plan(n, *case("uniform", n, per_node, 10_300 + n))
+    C, out, inn = p.execute_sizes()
+    want = host(C).copy()
+    ctx, dp = tn.get_context(), tn.api._dp
+    for o, i in ((True, False), (False, True), (False, False)):
+        C.fill_(-1)
+        a, b = torch.full_like(out, -7), torch.full_like(inn, -7)
+        rc = tn.lib.tn_plan_execute_sizes(ctx.bind_stream(), p.h, dp(C), C.stride(0), 0, dp(a if o else None),
+                                          dp(b if i else None))
+        assert rc == 0 and (host(C) == want).all()
+        assert torch.equal(a, out) if o else (a == -7).all()
+        assert torch.equal(b, inn) if i else (b == -7).all()
+    p.close()
