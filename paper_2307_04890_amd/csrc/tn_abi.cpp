@@ -862,17 +862,22 @@ tn_status component_sizes(tn_ctx *ctx, uint32_t n, const uint64_t *C, int64_t ld
     DeviceGuard g(ctx->device);
     if (!g.ok) return fail(TN_E_HIP, "cannot select the context's device");
     hipError_t e = hipSuccess;
-    {
+    if (!in_sizes) {
+        tn::ProfScope ps(ctx, TN_K_OUT_SIZES);
+        e = tn::launch_out_sizes(C, n, ld, out_sizes, ctx->stream, state, state_sw);
+    } else {
         // both arrays from one pass over the matrix: their start is recorded
-        // as out-sizes and the pass as in-sizes (one of them alone: as it)
-        tn::ProfScope ps(ctx, out_sizes ? TN_K_OUT_SIZES : TN_K_IN_SIZES);
-        e = tn::launch_sizes_base(n, out_sizes, in_sizes, ctx->stream, state, state_sw);
-        if (e == hipSuccess && !(out_sizes && in_sizes))
+        // as out-sizes and the pass as in-sizes (in-sizes alone: all as them)
+        {
+            tn::ProfScope ps(ctx, out_sizes ? TN_K_OUT_SIZES : TN_K_IN_SIZES);
+            e = tn::launch_sizes_base(n, out_sizes, in_sizes, ctx->stream, state, state_sw);
+            if (e == hipSuccess && !out_sizes)
+                e = tn::launch_sizes(C, n, ld, nullptr, in_sizes, ctx->stream, state, state_sw);
+        }
+        if (e == hipSuccess && out_sizes) {
+            tn::ProfScope ps(ctx, TN_K_IN_SIZES);
             e = tn::launch_sizes(C, n, ld, out_sizes, in_sizes, ctx->stream, state, state_sw);
-    }
-    if (e == hipSuccess && out_sizes && in_sizes) {
-        tn::ProfScope ps(ctx, TN_K_IN_SIZES);
-        e = tn::launch_sizes(C, n, ld, out_sizes, in_sizes, ctx->stream, state, state_sw);
+        }
     }
     if (e != hipSuccess) return hip_fail(e, "size kernel launch");
     return TN_OK;

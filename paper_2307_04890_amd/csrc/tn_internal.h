@@ -506,10 +506,12 @@ inline bool rowor_saturates(uint32_t n, uint32_t scratch_rows) {
     const uint64_t sbits = (((uint64_t)n + 31) & ~31ull) + scratch_rows + 1;
     return ((sbits + 31) / 32) * 4 <= kRoworSatLds;
 }
-// Row and column popcounts of C (out_sizes or in_sizes may be null, not
-// both): launch_sizes_base starts the arrays, launch_sizes adds one pass over
-// C.  With a slice state (persist of slices of state_sw words, nullable) the
-// words of slices left all ones are counted by the first without a read.
+// Row popcounts of C; row (unless out_sizes is null) and column popcounts:
+// launch_sizes_base starts the arrays, launch_sizes adds one pass over C.  With
+// a slice state (persist of slices of state_sw words, nullable) the words of
+// slices left all ones are counted without a read.
+hipError_t launch_out_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *out_sizes,
+                            hipStream_t st, const uint32_t *persist, uint32_t state_sw);
 hipError_t launch_sizes_base(uint32_t n, int32_t *out_sizes, int32_t *in_sizes, hipStream_t st,
                              const uint32_t *persist, uint32_t state_sw);
 hipError_t launch_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *out_sizes,

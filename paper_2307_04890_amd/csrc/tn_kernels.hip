@@ -1149,8 +1149,9 @@ __device__ __forceinline__ bool word_done(const uint32_t *persist, uint32_t psli
     return persist && persist[(size_t)(w / sw) * pslice] != 0u;
 }
 
-// Component sizes.  k_sizes_base starts the two arrays, k_sizes adds the
-// counts of one pass over the matrix.
+// Component sizes.  Out-sizes alone come from k_out_sizes.  For the others
+// k_sizes_base starts the arrays and k_sizes adds the counts of one pass over
+// the matrix.
 //
 // With a slice state (persist: pslice words per slice of sw words) a word of
 // a slice left all ones counts without a read: its valid columns in every
@@ -1174,9 +1175,55 @@ k_sizes_base(uint32_t n, uint32_t nwords, int32_t *__restrict__ out, int32_t *__
     }
 }
 
-// Out-sizes (row popcounts) and in-sizes (column popcounts) of open words,
-// added to out and in, in one pass: memory-bound, so both come from the same
-// read.  A wavefront takes 64 >> lw rows at a time, 1 << lw lanes on
+// out[u] = popcount of row u: one wavefront per row, lanes stride the words,
+// memory-bound.  A row ends in one store, so out needs no start and no atomics:
+// at n = 1000 9.8 us a call, where k_sizes_base and k_sizes<true> without its
+// columns took 14.1, at 20,000 13 and 16, at 50,000 69 and 97, at 10^5 250 and
+// 269 (5.0 TB/s).
+//
+// With a slice state (persist: pslice words per slice of sw words), a word
+// of a slice left all ones counts its valid columns without a read.
+__global__ void __launch_bounds__(256)
+k_out_sizes(const uint64_t *__restrict__ C, uint32_t n, int64_t ld, uint32_t nwords,
+            int32_t *__restrict__ out, const uint32_t *__restrict__ persist, uint32_t pslice,
+            uint32_t sw) {
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
+    const uint32_t nwave = (gridDim.x * blockDim.x) >> 6;
+    // this lane's done words: their columns once, a row read for the rest
+    int base = 0;
+    bool any_open = false;
+    for (uint32_t j = lane; j < nwords; j += 64) {
+        if (word_done(persist, pslice, sw, j))
+            base += (j + 1 < nwords || (n & 63u) == 0) ? 64 : (int)(n & 63u);
+        else
+            any_open = true;
+    }
+    if (__ballot(any_open) == 0) {
+        // every word of the row is done: the same count for every row,
+        // reduced once (a shuffle step is an LDS permute)
+        int total = base;
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) total += __shfl_xor(total, off, 64);
+        for (uint32_t r = wave * 64 + lane; r < n; r += nwave * 64) out[r] = total;
+        return;
+    }
+    for (uint32_t r = wave; r < n; r += nwave) {
+        const uint64_t *row = C + (size_t)r * (size_t)ld;
+        int c = base;
+        if (any_open) {
+            for (uint32_t j = lane; j < nwords; j += 64)
+                if (!word_done(persist, pslice, sw, j)) c += __popcll(row[j]);
+        }
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) c += __shfl_xor(c, off, 64);
+        if (lane == 0) out[r] = c;
+    }
+}
+
+// In-sizes (column popcounts) of open words, with OUT also out-sizes (row
+// popcounts), added to in and out, in one pass: memory-bound, so both come
+// from the same read.  A wavefront takes 64 >> lw rows at a time, 1 << lw lanes on
 // consecutive words of each (all 64 on one row where it has 64 words or
 // more), and 16 such steps per round, their loads all in flight.
 //  - Rows: the 16 popcounts of a lane are packed two to a register (a sum
@@ -1194,21 +1241,19 @@ k_sizes_base(uint32_t n, uint32_t nwords, int32_t *__restrict__ out, int32_t *__
 constexpr uint32_t kSizesWaves = 8;
 constexpr uint32_t kSizesSteps = 16;       // rows in flight per lane group
 constexpr uint32_t kSizesMaxSteps = 4080;  // per wavefront: 12 planes hold the counts
-template <bool OUT, bool IN>
+template <bool OUT>
 __global__ void __launch_bounds__(kSizesWaves * 64)
 k_sizes(const uint64_t *__restrict__ C, uint32_t n, int64_t ld, uint32_t nwords,
         int32_t *__restrict__ out, int32_t *__restrict__ in, const uint32_t *__restrict__ persist,
         uint32_t pslice, uint32_t sw, uint32_t lw, uint32_t rows_per_wave) {
-    __shared__ int32_t cnt[IN ? 64 * 64 : 1];  // [bit][column word]: a wave's lanes on distinct banks
+    __shared__ int32_t cnt[64 * 64];  // [bit][column word]: a wave's lanes on distinct banks
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
     const uint32_t W = 1u << lw, sub = lane & (W - 1u), g = lane >> lw, GR = 64u >> lw;
     const uint32_t j = blockIdx.x * W + sub;
     const bool open = j < nwords && !word_done(persist, pslice, sw, j);
     if (__ballot(open) == 0) return;  // the same words in every wave: the whole workgroup
-    if (IN) {
-        for (uint32_t i = threadIdx.x; i < 64 * 64; i += blockDim.x) cnt[i] = 0;
-        __syncthreads();
-    }
+    for (uint32_t i = threadIdx.x; i < 64 * 64; i += blockDim.x) cnt[i] = 0;
+    __syncthreads();
     const uint64_t first = ((uint64_t)blockIdx.y * kSizesWaves + wave) * rows_per_wave;
     const uint32_t r0 = (uint32_t)min((uint64_t)n, first);
     const uint32_t r1 = (uint32_t)min((uint64_t)n, first + rows_per_wave);
@@ -1246,24 +1291,21 @@ k_sizes(const uint64_t *__restrict__ C, uint32_t n, int64_t ld, uint32_t nwords,
                 if (r + GR < r1) atomicAdd(out + r + GR, (int32_t)(p[0] >> 16));
             }
         }
-        if (IN) {
-            uint64_t t2[8], t4[4], t8[2], carry;
+        uint64_t t2[8], t4[4], t8[2], carry;
 #pragma unroll
-            for (int i = 0; i < 8; ++i) full_add(c[0], x[2 * i], x[2 * i + 1], c[0], t2[i]);
+        for (int i = 0; i < 8; ++i) full_add(c[0], x[2 * i], x[2 * i + 1], c[0], t2[i]);
 #pragma unroll
-            for (int i = 0; i < 4; ++i) full_add(c[1], t2[2 * i], t2[2 * i + 1], c[1], t4[i]);
+        for (int i = 0; i < 4; ++i) full_add(c[1], t2[2 * i], t2[2 * i + 1], c[1], t4[i]);
 #pragma unroll
-            for (int i = 0; i < 2; ++i) full_add(c[2], t4[2 * i], t4[2 * i + 1], c[2], t8[i]);
-            full_add(c[3], t8[0], t8[1], c[3], carry);
+        for (int i = 0; i < 2; ++i) full_add(c[2], t4[2 * i], t4[2 * i + 1], c[2], t8[i]);
+        full_add(c[3], t8[0], t8[1], c[3], carry);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint64_t t = up[i] & carry;
-                up[i] ^= carry;
-                carry = t;
-            }
+        for (int i = 0; i < 8; ++i) {
+            const uint64_t t = up[i] & carry;
+            up[i] ^= carry;
+            carry = t;
         }
     }
-    if (!IN) return;
     if (open && r0 < r1) {
         // the counters leave their planes: six planes where the wavefront's
         // steps are at most 63
@@ -1573,6 +1615,17 @@ uint32_t state_slice_words(const uint32_t *persist, uint32_t n) {
 }
 }  // namespace
 
+hipError_t launch_out_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *out_sizes,
+                            hipStream_t st, const uint32_t *persist, uint32_t state_sw) {
+    const uint32_t nwords = (n + 63) / 64;
+    // with a state every wave first reads the done words of its lanes: fewer
+    // waves, each taking more rows
+    const uint32_t blocks = std::min<uint32_t>((n + 3) / 4, persist ? 2048u : 16384u);
+    hipLaunchKernelGGL(k_out_sizes, dim3(blocks), dim3(256), 0, st, C, n, ld, nwords, out_sizes,
+                       persist, state_slice_words(persist, n), state_sw ? state_sw : 1u);
+    return hipGetLastError();
+}
+
 hipError_t launch_sizes_base(uint32_t n, int32_t *out_sizes, int32_t *in_sizes, hipStream_t st,
                              const uint32_t *persist, uint32_t state_sw) {
     // with a state every wave first reads the done words: fewer waves
@@ -1597,9 +1650,7 @@ hipError_t launch_sizes(const uint64_t *C, uint32_t n, int64_t ld, int32_t *out_
     uint64_t rpw = (want + unit - 1) / unit * unit;
     rpw = std::min<uint64_t>(rpw, (uint64_t)kSizesMaxSteps * (64u >> lw));
     const uint32_t yb = (uint32_t)((n + kSizesWaves * rpw - 1) / (kSizesWaves * rpw));
-    auto k = out_sizes && in_sizes ? k_sizes<true, true>
-             : out_sizes           ? k_sizes<true, false>
-                                   : k_sizes<false, true>;
+    auto k = out_sizes ? k_sizes<true> : k_sizes<false>;
     hipLaunchKernelGGL(k, dim3(xb, yb), dim3(kSizesWaves * 64), 0, st, C, n, ld, nwords, out_sizes,
                        in_sizes, persist, state_slice_words(persist, n), state_sw ? state_sw : 1u,
                        lw, (uint32_t)rpw);

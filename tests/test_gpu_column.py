@@ -9,6 +9,7 @@ import torch
 import oracle
 import tn_inputs as T
 from gpu_util import host
+from test_gpu_exact import _partial_network
 
 pytestmark = pytest.mark.gpu
 
@@ -408,4 +409,35 @@ def test_either_sizes_alone(n, per_node):
         assert rc == 0 and (host(C) == want).all()
         assert torch.equal(a, out) if o else (a == -7).all()
         assert torch.equal(b, inn) if i else (b == -7).all()
+    p.close()
+
+
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 255, 4097, 10_000])
+def test_out_sizes_alone_of_any_words(n):
+    # lines that end in a part of a word, rows wider than the matrix, whatever was in
+    # the array before
+    rng = np.random.default_rng(10_400 + n)
+    nw = oracle.words(n)
+    C = rng.integers(0, 2**64, (n, nw + n % 3), dtype=np.uint64)
+    C[:: 3, :nw] = 2**64 - 1
+    if n % 64:
+        C[:, nw - 1] &= np.uint64(2 ** (n % 64) - 1)
+    want = np.bitwise_count(C[:, :nw]).sum(axis=1)
+    dev = torch.from_numpy(C.view(np.int64)).cuda()
+    for _ in range(2):
+        assert (tn.component_sizes(dev, n, inn=False)[0].cpu().numpy() == want).all()
+    assert (tn.component_sizes(dev, n)[0].cpu().numpy() == want).all()
+
+
+@pytest.mark.parametrize("n,m,steps,seed", [(8001, 400_000, 50, 8430), (16_385, 500_000, 100, 8420)])
+def test_out_sizes_alone_from_the_slice_state(n, m, steps, seed):
+    # slices left all ones beside one that is not, and a plan's own choice
+    n, s, d, t, flags = _partial_network(n, m, steps, seed)
+    p = tn.Plan(n, s, d, t, flags)
+    ctx, dp = tn.get_context(), tn.api._dp
+    for sw in (0, 1, 2, 4):
+        C, want, _ = p.execute_sizes(slice_words=sw)
+        out = torch.full_like(want, -7)
+        assert tn.lib.tn_plan_execute_sizes(ctx.bind_stream(), p.h, dp(C), C.stride(0), sw, dp(out), None) == 0
+        assert torch.equal(out, want)
     p.close()
