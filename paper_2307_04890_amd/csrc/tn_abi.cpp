@@ -503,7 +503,8 @@ tn_status plan_execute(tn_ctx *ctx, const tn_plan *plan, uint64_t *C, int64_t ld
     // a network whose columns fit in LDS, with the slice width left to
     // the library, runs on one workgroup per column
     const bool column = slice_words == 0 && plan->column &&
-                        (out_sizes || in_sizes || tn::rowor_column_plan(n, plan->stats.ops));
+                        (out_sizes || in_sizes ||
+                         tn::rowor_column_plan(n, plan->stats.ops, ctx->saturation));
     if (slice_words == 0) slice_words = tn::default_slice_words(n, ld);
     if (slice_words > 64 || (slice_words & (slice_words - 1)))
         return fail(TN_E_ARG, "slice_words must be a power of two <= 64");

@@ -56,12 +56,22 @@ inline bool rowor_column_chunk(uint32_t n, int64_t events) {
 // Whether a plan of so many ops runs on word columns where only its matrix is asked
 // for: of fewer, slices in memory after an identity written by whole lines take
 // less (us on slices and columns, activity-driven: 3,000 nodes, no ops 7 and 7,
-// 30 ops 24 and 7; 8,000, none 7 and 14, 80 ops 20 and 15; 12,000, none 8 and 25,
-// 120 ops 26 and 26; 16,000, 160 ops 29 and 32, 800 64 and 34; 20,000, none 10 and
-// 48, 200 ops 31 and 50, 1,000 64 and 49).  With the sizes, which come with the
+// 30 ops 24 and 7; 8,000, none 7 and 14, 80 ops 20 and 15; 9,500, 19 ops 18 and 21,
+// 95 ops 21 and 21; 12,000, none 8 and 25, 120 ops 26 and 26; 16,000, 160 ops 29
+// and 32, 800 64 and 34; 20,000, none 10 and 48, 200 ops 31 and 50, 1,000 64 and
+// 49).  Without saturation the slices forward rows from op to op and keep no
+// bitmaps, so the line lies higher (5,000 nodes, 10 ops 11 and 10; 6,000, 30 ops 11
+// and 12, 120 ops 13 and 13, 325 ops 22 and 13; 8,000, 80 ops 15 and 15, on slices
+// of two words from 8,065 nodes on 10,000, 20 ops 12 and 20, 310 ops 19 and 21,
+// 525 ops 29 and 22; 16,000, 330 ops 30 and 33, 485 ops 38 and 33; 20,000, 1,000
+// uniform ops 44 and 49, 2,045 ops 64 and 58).  With the sizes, which come with the
 // columns, columns are always faster or as fast (20,000 nodes, 200 ops 73 and 67).
-inline bool rowor_column_plan(uint32_t n, int64_t ops) {
-    return n <= 10240 ? ops > 0 || n <= 4096 : 64 * ops >= (int64_t)n * rowor_column_rounds(n);
+inline bool rowor_column_plan(uint32_t n, int64_t ops, bool saturation) {
+    if (n <= 4096) return true;
+    if (saturation && n <= 10240) return ops > 0 && (n <= 9216 || 128 * ops >= (int64_t)n);
+    if (n <= 5120) return ops > 0;
+    const int64_t line = (int64_t)n * rowor_column_rounds(n);
+    return (saturation || n <= 8064 ? 64 : 32) * ops >= line;
 }
 // The column form of s (s.column not empty, or no ops): blocks and levels set.
 inline ColumnNet column_net(const HostSchedule &s) {

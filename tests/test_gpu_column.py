@@ -441,3 +441,30 @@ def test_out_sizes_alone_from_the_slice_state(n, m, steps, seed):
         assert tn.lib.tn_plan_execute_sizes(ctx.bind_stream(), p.h, dp(C), C.stride(0), sw, dp(out), None) == 0
         assert torch.equal(out, want)
     p.close()
+
+
+@pytest.mark.parametrize("n,per_op", [(4096, 64), (4097, 64), (5120, 64), (5121, 64), (8064, 64), (8065, 32),
+                                      (9217, 128), (10_000, 32), (10_240, 128), (10_241, 32), (16_385, 16)])
+def test_plans_of_few_ops_without_saturation(n, per_op):
+    # about the number of ops from which on a matrix alone is built on word columns,
+    # with and without the saturation of full rows
+    ctx = tn.get_context()
+    edge = -(-n // per_op)
+    for m in (0, 1, edge - 1, edge):
+        s, d, _ = T.uniform_pairs(n, max(1, m), max(1, m), seed=10_500 + n + m)
+        p = tn.Plan(n, s[:m], d[:m], np.arange(m, dtype=np.int64))
+        want = host(p.execute(slice_words=1))
+        C = torch.empty((n, oracle.words(n) + 3), dtype=torch.int64, device="cuda")
+        try:
+            for saturation in (True, False):
+                ctx.saturation(saturation)
+                C.fill_(-1)
+                p.execute(C)
+                assert (host(C) == want).all(), (m, saturation)
+                C.fill_(-1)
+                _, out, inn = p.execute_sizes(C)
+                assert (host(C) == want).all(), (m, saturation)
+                assert torch.equal(out, tn.component_sizes(C, n, inn=False)[0]), (m, saturation)
+        finally:
+            ctx.saturation(True)
+            p.close()
